@@ -383,7 +383,9 @@ int moe_rs(agg_ctx* ctx, int Ttok, int topk, int E, int N, int Klocal,
  * (0 = 256x224, 1 = 128x128, 2 = 256x256, 3 = 128x256), bit 2 = MFMA form of the main loop (0: 32x32x16, 4: 16x16x32,
  * what the automatic choice takes).  A tuning knob (Section 3.8).  All shapes of one MFMA form give the same bits
  * (the sum over K runs in the same order in all of them); the two forms group the sum over K differently (16 or 32
- * terms per instruction) and may differ in the last bits, both within the tolerance. */
+ * terms per instruction) and may differ in the last bits, both within the tolerance.  The automatic choice also has smaller
+ * tiles for problems that would leave most of the chip idle with these; they cannot be selected by number, and they add up
+ * K in a few partial sums (fp32, fixed order), so their last bits may differ as well. */
 int agg_set_tile_config(agg_ctx* ctx, int tile_config);
 
 /*

@@ -31,38 +31,63 @@ inline long long wait_ticks(const agg_ctx* c)
     return (long long)((double)c->wall_khz * (double)c->wait_limit_us / 1000.0);
 }
 
-// Pick the tile shape with the smallest estimated time: waves of tiles over the CUs times the cost of a
-// tile (its area over a rough efficiency of the shape).
-int choose_tile(const agg_ctx* c, int M, int N)
+// Estimated time of one tile in a full round, in microseconds: what a tile takes whatever its K, and what it takes per 64
+// of K.  From sweeps of M, N, K with every shape: what a tile costs follows the bytes it pulls through its compute unit's
+// load path, (BM + BN) x 128 per 64 of K at about 70 KB/us, up to 128 x 128; the large tiles are bound by the matrix pipes
+// at the clock the chip holds with all of them busy.  Over 60 shapes drawn from M 16..8192, N 96..7168, K 256..8192 (over
+// their logarithms) the choice costs 1.7 % more than the best shape of each.  Where the line lies, both sides measured in
+// us: 16x3584x4096 16x16 8.7, 128x128 24.9; 64x8192x3584 64x32 19.1, 64x64 22, 128x128 33; 128x7168x8192 64x64 42,
+// 128x128 75; 999x1999x1984 64x128 17.2, 128x128 21; 1024x3584x4096 128x128 34, 64x128 51.
+struct TileCost { int cfg; double fixed_us, us_per_k64; };
+const TileCost kTileCosts[] = {
+    {TILE_256x224 | TILE_K32, 4.0, 1.25}, {TILE_256x256 | TILE_K32, 4.0, 1.42}, {TILE_128x256 | TILE_K32, 4.0, 0.83},
+    {TILE_128x128 | TILE_K32, 4.0, 0.46},
+    {KS_64x128, 3.5, 0.37}, {KS_64x64, 3.0, 0.24}, {KS_64x32, 4.0, 0.20}, {KS_32x32, 3.0, 0.125}, {KS_16x32, 3.0, 0.09},
+    {KS_16x16, 3.0, 0.07},
+};
+// the K-split kernels divide row and tile numbers with 32-bit multipliers, exact while rows x divisor < 2^32
+constexpr int kKsMaxRows = 65535;
+
+// Pick the tile shape with the smallest estimated time: rounds of tiles over the CUs times the cost of a tile.  The
+// 16x16x32 form of the main loop everywhere: the same work at a lower power per flop, so the chip holds a higher clock
+// (measured 5 to 8 % faster on every shape); the 32x32x16 form stays selectable (configurations 0 to 3).
+int choose_tile(const agg_ctx* c, int M, int N, int K)
 {
     if (c->tile_config >= 0) return c->tile_config;
-    // measured rates per flop relative to the large shapes (70B shape, GEMM alone): 128x256 0.86, 128x128 0.78
-    const int cand[4] = {TILE_256x224, TILE_256x256, TILE_128x256, TILE_128x128};
-    const double eff[4] = {1.0, 1.0, 0.86, 0.75};
-    int best = cand[0];
+    int best = kTileCosts[0].cfg;
     double best_cost = 1e300;
-    for (int i = 0; i < 4; ++i) {
-        const TileShape t = tile_shape(cand[i]);
+    for (const TileCost& k : kTileCosts) {
+        if (k.cfg >= TILE_CONFIGS && M > kKsMaxRows) continue;
+        const TileShape t = tile_shape(k.cfg);
         const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-        const long long waves = (tiles + c->num_cus - 1) / c->num_cus;
-        const double cost = (double)waves * t.bm * t.bn / eff[i];
+        const long long rounds = (tiles + c->num_cus - 1) / c->num_cus;
+        const double cost = (double)rounds * (k.fixed_us + k.us_per_k64 * (K / 64));
         if (cost < best_cost) {
             best_cost = cost;
-            best = cand[i];
+            best = k.cfg;
         }
     }
-    // the 16x16x32 form of the main loop: the same work at a lower power per flop, so the chip holds a higher clock
-    // (measured 5 to 8 % faster on every shape); the 32x32x16 form stays selectable (configurations 0 to 3)
-    return best | TILE_K32;
+    return best;
+}
+
+// Workgroups of a launch of `tiles` tiles: one per tile up to one per CU (a multiple of 8, so that neighbouring tiles can be
+// given to one XCD; a workgroup without a tile ends at once).
+int gemm_grid(const agg_ctx* c, int cfg, long long tiles)
+{
+    if (cfg >= TILE_CONFIGS) tiles = (tiles + 7) & ~7ll;
+    return (int)(tiles < c->num_cus ? tiles : c->num_cus);
 }
 
 // Fill the schedule fields: panels of `rows_per_shard` rows starting at the panel of `first_row`.
-void fill_schedule(GemmParams& p, int cfg, int rows_per_shard, int first_row)
+void fill_schedule(const agg_ctx* c, GemmParams& p, int cfg, int rows_per_shard, int first_row)
 {
     const TileShape t = tile_shape(cfg);
     p.tiles_m = (p.M + t.bm - 1) / t.bm;
     p.tiles_n = (p.N + t.bn - 1) / t.bn;
     int pm = rows_per_shard / t.bm;
+    // A single round of tiles: they all start at once, so their order follows the L2s alone.  All m-tiles of a column
+    // block then go to one XCD, and B is read from memory once instead of once per panel
+    if ((long long)p.tiles_m * p.tiles_n <= c->num_cus) pm = p.tiles_m;
     if (pm < 1) pm = 1;
     if (pm > 32) pm = 32;
     p.panel_m = pm;
@@ -526,8 +551,8 @@ int ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb, int b_layou
     p.K = K;
     p.c_is_f32 = c_dtype == AGG_F32;
     p.c_vec_ok = aligned16(C) && ((long long)ldc * (p.c_is_f32 ? 4 : 2)) % 16 == 0;
-    const int cfg = choose_tile(c, M, N);
-    fill_schedule(p, cfg, Ms, c->rank * Ms);
+    const int cfg = choose_tile(c, M, N, K);
+    fill_schedule(c, p, cfg, Ms, c->rank * Ms);
     {
         // sub-chunk order (Section 3.7, full mesh): possible when shards and chunks are whole numbers of tiles
         const TileShape t = tile_shape(cfg);
@@ -548,7 +573,7 @@ int ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb, int b_layou
     p.wait_ticks = wait_ticks(c);
     p.err = c->err;
     const long long tiles = (long long)p.tiles_m * p.tiles_n;
-    const int grid = (int)(tiles < c->num_cus ? tiles : c->num_cus);
+    const int grid = gemm_grid(c, cfg, tiles);
     if ((rc = hip_fail(launch_gemm(p, cfg, grid, (hipStream_t)consumer_stream))) != AGG_OK) return rc;
     return b_kn_launched(c, b_layout, (hipStream_t)consumer_stream);
 }
@@ -738,10 +763,10 @@ int gemm_rs_scatter(agg_ctx* c, int M, int N, int Kl, const void* A_local, int l
         p.slice_dst[w] = slice_dst[w];
         p.slice_flag[w] = slice_signal ? slice_signal[w] : nullptr;
     }
-    const int cfg = choose_tile(c, M, N);
-    fill_schedule(p, cfg, Ms, first_slice * Ms);
+    const int cfg = choose_tile(c, M, N, Kl);
+    fill_schedule(c, p, cfg, Ms, first_slice * Ms);
     const long long tiles = (long long)p.tiles_m * p.tiles_n;
-    const int grid = (int)(tiles < c->num_cus ? tiles : c->num_cus);
+    const int grid = gemm_grid(c, cfg, tiles);
     if ((rc = hip_fail(launch_gemm(p, cfg, grid, (hipStream_t)gemm_stream))) != AGG_OK) return rc;
     return b_kn_launched(c, b_layout, (hipStream_t)gemm_stream);
 }
@@ -802,10 +827,10 @@ int gemm_rs(agg_ctx* c, int M, int N, int Kl, const void* A_local, int lda, cons
         p.ldc_slice = N;
         p.slice_ctr = c->counters + c->n_signals;
         p.slice_flag[0] = own_flag;
-        const int cfg = choose_tile(c, Ms, N);
-        fill_schedule(p, cfg, Ms, 0);
+        const int cfg = choose_tile(c, Ms, N, Kl);
+        fill_schedule(c, p, cfg, Ms, 0);
         const long long tiles = (long long)p.tiles_m * p.tiles_n;
-        const int grid = (int)(tiles < c->num_cus ? tiles : c->num_cus);
+        const int grid = gemm_grid(c, cfg, tiles);
         rc = hip_fail(launch_gemm(p, cfg, grid, (hipStream_t)gemm_stream));
         if (rc == AGG_OK) rc = b_kn_launched(c, b_layout, (hipStream_t)gemm_stream);
     }
@@ -927,7 +952,7 @@ static int grouped_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, con
     p.n_tiles_dev = r.n_tiles_dev;
     p.b_group_stride = (long long)N * K;
     p.a_bytes = (unsigned)a_bytes;
-    const int grid = (int)(cap < c->num_cus ? cap : c->num_cus);
+    const int grid = gemm_grid(c, cfg, cap);
     return hip_fail(launch_gemm_grouped(p, cfg, grid, stream));
 }
 

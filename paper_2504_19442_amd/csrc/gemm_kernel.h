@@ -31,45 +31,11 @@
 // wave of a small kernel (the producer's copy waves, the reducer) run beside a consumer wave on every
 // SIMD: communication and computation share all CUs instead of splitting them (Section 3.8).
 #pragma once
-#include "agg_internal.h"
-
-#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
-#error "this kernel names gfx950 instructions and registers (MFMA forms, accumulator registers, global->LDS loads)"
-#endif
+#include "gemm_tile.h"
 
 #include <numeric>
-#include <type_traits>
-#include <utility>
 
 namespace agg {
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-
-#define LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
-
-// Raw buffer descriptor over `bytes` bytes at p: loads whose per-lane offset is >= bytes return zero, which
-// is how rows past the edge of A or B are masked.  0x00020000 = 32-bit data format, no swizzle (gfx9 family).
-__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
-}
-
-// s_waitcnt immediate that waits only for vmcnt <= n (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt_hi[15:14]).
-__host__ __device__ constexpr int vmcnt_imm(int n) { return (n & 0xF) | (0x7 << 4) | (0xF << 8) | ((n >> 4) << 14); }
-
-// compile-time loop: f(std::integral_constant<int, I>) for I in [0, N)
-template <class F, int... Is>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>)
-{
-    (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f)
-{
-    static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
 
 // ---- accumulator registers, touched only here.  Block b is a[16b : 16b+15].
 template <int BLK>
@@ -96,9 +62,6 @@ __device__ __forceinline__ float acc_read()
     return x;
 }
 
-constexpr int BK = 64;                 // bf16 per stage
-constexpr int ROW_BYTES = BK * 2;      // 128-byte rows in LDS: one cache line per row and stage
-constexpr int UNIT_ROWS = 8;           // one wave-wide 16-byte-per-lane load covers 8 rows
 [[maybe_unused]] constexpr int QS = 4;   // quarter-steps (K = 16 each) per stage
 
 template <int BM, int BN>
@@ -259,86 +222,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
         int t;
         if ((G & 7) == 0) t = base + (g & 7) * xcd_slots + (g >> 3); else t = base + g;
         if (t >= total_tiles) continue;
-        int m0, n0, m_lim, f_lo = 0, f_hi = -1, expert = 0;
-        int st_lo = 0, st_hi;                 // rows of the output that are stored: [st_lo, st_hi)
-        bool from_local = false;
-        if constexpr (GROUPED) {
-            const MoeTile mt = p.tile_tab[t];
-            expert = __builtin_amdgcn_readfirstlane(mt.expert);
-            m0 = __builtin_amdgcn_readfirstlane(mt.m0);
-            m_lim = __builtin_amdgcn_readfirstlane(mt.m_end);
-            st_lo = __builtin_amdgcn_readfirstlane(mt.st_lo);
-            st_hi = __builtin_amdgcn_readfirstlane(mt.st_hi);
-            if (st_hi <= st_lo) continue;     // no row of this tile is wanted (MoE + ReduceScatter without Z_other)
-            n0 = __builtin_amdgcn_readfirstlane(mt.n_tile) * BN;
-            f_lo = __builtin_amdgcn_readfirstlane(mt.f_lo);
-            f_hi = __builtin_amdgcn_readfirstlane(mt.f_hi);
-        } else {
-            int m_tile, n_tile;
-            const int per_panel = p.panel_m * p.tiles_n;
-            const int panel = t / per_panel;
-            const int pm = min(p.panel_m, p.tiles_m - panel * p.panel_m);
-            const int q = t - panel * per_panel;
-            const int blk = q / (pm * p.group_n);
-            const int r = q - blk * pm * p.group_n;
-            const int gn = min(p.group_n, p.tiles_n - blk * p.group_n);
-            const int mi = r / gn;
-            n_tile = blk * p.group_n + (r - mi * gn);
-            const int v = panel * p.panel_m + mi;            // place in the order of m-tiles
-            if (p.order == AGG_ORDER_SUBCHUNK) {
-                // the local shard, then sub-chunk 0 of every peer (in pull order), sub-chunk 1 of every peer, ...
-                if (v < p.tiles_per_shard) {
-                    m_tile = p.rank * p.tiles_per_shard + v;
-                } else {
-                    const int v2 = v - p.tiles_per_shard;
-                    const int per_c = (p.world - 1) * p.tiles_per_chunk;
-                    const int c = v2 / per_c, rem = v2 - c * per_c;
-                    const int jj = rem / p.tiles_per_chunk, k = rem - jj * p.tiles_per_chunk;
-                    const int shard = (p.rank + 1 + jj) % p.world;
-                    m_tile = shard * p.tiles_per_shard + c * p.tiles_per_chunk + k;
-                }
-            } else {
-                m_tile = (p.m_tile_start + v) % p.tiles_m;
-            }
-            m0 = m_tile * BM;
-            n0 = n_tile * BN;
-            m_lim = p.M;
-            st_hi = p.M;
-            // a tile that lies inside this rank's own shard reads it where the caller keeps it: nothing to wait for
-            from_local = p.A_local && m0 >= p.local_lo && m0 + BM <= p.local_hi;
-            if (p.flags && !from_local) {
-                f_lo = m0 / p.rows_per_flag;
-                f_hi = min((min(m0 + BM, p.M) - 1) / p.rows_per_flag, p.n_flags - 1);
-            }
-        }
-
-        // ---- wait for the signals covering rows [m0, min(m0+BM, M))  (wait + consume_token, Section 2.2)
-        if (p.flags && f_hi >= f_lo) {
-            // Wave 0 polls (lane l takes signals f_lo + l, f_lo + l + 64, ...) and, once it has seen them all, executes
-            // the acquire: the wave that observed the signals is the wave that orders the loads of A after them.  The
-            // acquire invalidates this CU's L1 and this XCD's L2 lines of remotely written memory, so that no load of
-            // A below is served from a line cached before the data arrived; one wave does it for the workgroup
-            // (invalidates from all waves of all CUs queue up behind each other at the L2), and the barrier holds the
-            // other waves back until it is done.
-            int gave_up = 0;
-            if (wave == 0) {
-                for (int f = f_lo + lane; f <= f_hi; f += 64) {
-                    const int* fp = p.flags + (long long)f * kSignalStride;
-                    const long long t0 = wall_clock64();
-                    while (__hip_atomic_load(fp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch) {
-                        if (__hip_atomic_load(p.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-                            wall_clock64() - t0 > p.wait_ticks) {
-                            gave_up = 1;
-                            break;
-                        }
-                        __builtin_amdgcn_s_sleep(1);
-                    }
-                }
-                if (gave_up) __hip_atomic_store(p.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            }
-            if (__syncthreads_or(gave_up)) return;   // the launch drains; agg_status reports the time-out
-        }
+        TileWork w;
+        if (!tile_work<BM, BN, GROUPED>(p, t, w)) continue;
+        const int m0 = w.m0, n0 = w.n0, m_lim = w.m_lim, expert = w.expert;
+        const int st_lo = w.st_lo, st_hi = w.st_hi;      // rows of the output that are stored: [st_lo, st_hi)
+        const bool from_local = w.from_local;
+        if (p.flags && w.f_hi >= w.f_lo && tile_wait_gave_up(p, w.f_lo, w.f_hi, epoch, wave, lane)) return;
 
         // ---- per-tile buffer descriptors and per-lane load offsets (bytes from the tile's A / B origin);
         // rows past the edge of the matrix fall outside the descriptor and load as zero
@@ -600,16 +489,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
             asm volatile("" : "+v"(lane_e));     // keeps the address arithmetic below inside the tile loop
             const int row_w = m0 + wave * TM;    // first output row of this wave
             const int n_valid = min(BN, p.N - n0);      // columns of this tile inside the matrix
-            // where a row of the output goes: C, or (GEMM-RS) the destination of its slice; nullptr = not stored
-            auto row_ptr = [&](int row, int esz) -> char* {
-                if (row < st_lo || row >= st_hi) return nullptr;
-                if (!GROUPED && p.n_slices) {
-                    const int w = row / p.slice_rows;
-                    if (p.slice_dst[w])
-                        return (char*)p.slice_dst[w] + ((long long)(row - w * p.slice_rows) * p.ldc_slice + n0) * esz;
-                }
-                return p.C ? (char*)p.C + ((long long)row * p.ldc + n0) * esz : nullptr;
-            };
+            auto row_ptr = [&](int row, int esz) { return out_row(p, GROUPED, row, st_lo, st_hi, n0, esz); };
             auto epilogue = [&](auto tag) {
                 using T = decltype(tag);                              // float or __bf16
                 constexpr int esz = sizeof(T);
@@ -785,40 +665,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
             if (p.c_is_f32) epilogue(float{}); else epilogue(__bf16{});
         }
 
-        // GEMM-RS: count this tile for every chunk of every slice it touches; the last tile of a chunk raises the
-        // chunk's signal (the notify of Algorithm 3: those rows are complete where their reducer will read them)
-        if (!GROUPED && p.n_slices && p.slice_ctr) {
-            const int w_lo = m0 / p.slice_rows, w_hi = (min(m0 + BM, p.M) - 1) / p.slice_rows;
-            bool any = false;
-            for (int w = w_lo; w <= w_hi; ++w) any = any || p.slice_flag[w] != nullptr;
-            if (any) {
-                __builtin_amdgcn_s_waitcnt(0);   // this wave's stores of the tile have reached L2 ...
-                __syncthreads();                 // ... and so have every other wave's, before thread 0 publishes them
-                if (tid == 0) {
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-                    const int m_end = min(m0 + BM, p.M);
-                    for (int w = w_lo; w <= w_hi; ++w) {
-                        if (!p.slice_flag[w]) continue;
-                        const int s0 = w * p.slice_rows;                       // first row of slice w
-                        const int c_lo = (max(m0, s0) - s0) / p.chunk_rows;
-                        const int c_hi = (min(m_end, s0 + p.slice_rows) - 1 - s0) / p.chunk_rows;
-                        for (int c = c_lo; c <= c_hi; ++c) {
-                            // tiles that touch these rows: their m-tiles times all n-tiles
-                            const int r0 = s0 + c * p.chunk_rows;
-                            const int mt_lo = r0 / BM, mt_hi = (r0 + p.chunk_rows - 1) / BM;
-                            const int target = (mt_hi - mt_lo + 1) * p.tiles_n;
-                            int* ctr = p.slice_ctr + w * p.slice_chunks + c;
-                            const int prev = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-                            if (prev == target - 1) {
-                                __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                                __hip_atomic_store(p.slice_flag[w] + c * kSignalStride, epoch, __ATOMIC_RELEASE,
-                                                   __HIP_MEMORY_SCOPE_AGENT);
-                            }
-                        }
-                    }
-                }
-            }
-        }
+        if (!GROUPED && p.n_slices && p.slice_ctr) tile_publish<BM>(p, m0, epoch, tid);
 
         // the stage buffers are reused by the next tile: every wave must be done with its staging reads first.
         // The C stores need not be waited for: the next tile's waits count them as well, which only makes

@@ -1,0 +1,83 @@
+"""The K-split GEMM kernels that the automatic tile choice takes for small problems, at the sizes where they can go wrong:
+one row, one short of and one past a tile, a single piece of K, fewer pieces than waves, a ragged last column block with
+aligned and unaligned rows, more tiles than one round, slices smaller and larger than a tile.  Integer inputs: exact."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2504_19442_amd as agg
+import workloads as wl
+from harness import AgGemmRun, dev_bf16, host_bits
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("W,Ms,K,N,chunks", [
+    (1, 1, 64, 16, 1),          # one row, one piece of K (seven of eight waves have none)
+    (3, 1, 576, 40, 1),         # 16-row tiles, nine pieces over eight waves
+    (2, 17, 192, 99, 1),        # three tiles of 16 rows, odd columns: the element-wise store
+    (4, 16, 4096, 200, 2),      # 16 x 16 tiles, deep K
+    (2, 35, 448, 1500, 1),      # 16 x 32
+    (5, 26, 640, 1302, 2),      # 32 x 32, columns not a multiple of four
+    (3, 11, 128, 4100, 1),      # 64 x 32, rows of one tile, two pieces of K
+    (2, 260, 448, 1200, 4),     # 64 x 64 over several signals
+    (3, 333, 512, 1999, 1),     # 64 x 128, odd columns
+    (3, 333, 64, 2001, 3),      # one piece of K
+    (2, 33, 64, 6148, 1),       # more tiles than compute units
+])
+def test_ag_gemm_small_shapes_exact(W, Ms, K, N, chunks):
+    sh = wl.AgGemmShape(f"ag_small_{W}_{Ms}_{K}_{N}", 21, W, Ms, K, N)
+    inp = wl.make_ag_gemm(sh, a_dist=("int", 2), b_dist=("int", 2))
+    rank = W - 1
+    want = oracle.ag_gemm(inp.shards, inp.B_kn, rank)
+    run = AgGemmRun(inp, rank, chunks_per_shard=chunks)
+    try:
+        for local in (False, True):                       # own shard from T, and in place
+            run.ctx.set_local_shard(run.remote[rank] if local else None)
+            for consumer_first in (True, False):
+                C = run.run(consumer_first=consumer_first).cpu().numpy()
+                assert np.array_equal(C.astype(np.float64), want), (local, consumer_first)
+        C16 = host_bits(run.run(out_dtype=agg.BF16))
+        assert np.array_equal(C16, wl.f32_to_bf16_bits(want.astype(np.float32)))
+    finally:
+        run.close()
+
+
+@pytest.mark.parametrize("W,Ms,K,N,chunks", [
+    (4, 1, 64, 16, 1), (8, 8, 576, 260, 4), (2, 40, 192, 1500, 2), (3, 100, 320, 2000, 5), (2, 300, 128, 900, 3),
+])
+def test_gemm_rs_small_shapes_exact(W, Ms, K, N, chunks):
+    sh = wl.GemmRsShape(f"rs_small_{W}_{Ms}_{K}_{N}", 22, W, W * Ms, K, N)
+    rank = 1
+    inp = wl.make_gemm_rs(sh, rank=rank, a_dist=("int", 2), b_dist=("int", 2), slot_dist=("int", 5))
+    A = wl.bf16_bits_to_f32(inp.A_loc).astype(np.float64)
+    prod = A @ wl.bf16_bits_to_f32(inp.B_kn).astype(np.float64)
+    want = prod[rank * Ms:(rank + 1) * Ms] + sum(s.astype(np.float64) for s in inp.peer_slots.values())
+    A_d, B_d = dev_bf16(inp.A_loc), dev_bf16(np.ascontiguousarray(inp.B_kn.T))
+    ctx = agg.symm_alloc(W, rank, 16, W * chunks)
+    try:
+        ctx.set_rs_chunks(chunks)
+        ps, cs = ctx.streams()
+        slots = [torch.from_numpy(inp.peer_slots[w]).cuda() if w != rank else torch.empty((Ms, N), device="cuda") for w in range(W)]
+        for other, two_streams in ((True, True), (True, False), (False, True)):
+            slots[rank].fill_(float("nan"))
+            P = torch.full((W * Ms, N), float("nan"), device="cuda") if other else None
+            R = torch.full((Ms, N), float("nan"), device="cuda")
+            agg.signal_reset(ctx)
+            torch.cuda.synchronize()
+            for w in range(W):
+                for c in range(chunks):
+                    if w != rank:
+                        agg.signal_set(ctx, w * chunks + c, cs)
+            agg.gemm_rs(ctx, W * Ms, N, K, A_d, K, B_d, K, agg.B_NK, slots, P, R, N, agg.F32, ps if two_streams else cs, cs)
+            torch.cuda.synchronize()
+            assert agg.agg_status(ctx) == agg.OK
+            assert np.array_equal(R.cpu().numpy().astype(np.float64), want)
+            if other:
+                got = P.cpu().numpy()
+                assert np.isnan(got[rank * Ms:(rank + 1) * Ms]).all()            # the own rows went to the slot
+                keep = [r for r in range(W * Ms) if not rank * Ms <= r < (rank + 1) * Ms]
+                assert np.array_equal(got[keep].astype(np.float64), prod[keep])
+    finally:
+        ctx.free()
