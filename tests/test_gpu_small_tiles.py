@@ -81,3 +81,34 @@ def test_gemm_rs_small_shapes_exact(W, Ms, K, N, chunks):
                 assert np.array_equal(got[keep].astype(np.float64), prod[keep])
     finally:
         ctx.free()
+
+
+@pytest.mark.parametrize("K,N,ldb,offset", [
+    (64, 8, 8, 0),              # one 16-byte piece per row
+    (128, 63, 64, 0),           # a ragged last piece, a wave's tile not full
+    (192, 130, 136, 0),         # second column tile almost empty, padded rows
+    (320, 257, 264, 8),         # base moved by 16 bytes
+    (128, 100, 104, 1),         # base not 16-byte aligned: two bytes at a time
+    (64, 65, 65, 0),            # odd leading dimension: two bytes at a time
+])
+def test_b_given_as_k_by_n_any_alignment_exact(K, N, ldb, offset):
+    sh = wl.AgGemmShape(f"ag_kn_{K}_{N}", 23, 2, 24, K, N)
+    inp = wl.make_ag_gemm(sh, a_dist=("int", 2), b_dist=("int", 2))
+    want = oracle.ag_gemm(inp.shards, inp.B_kn, 0)
+    # rows of ldb elements from `offset` on, and not one element more behind the last row's N
+    flat = np.full(offset + (K - 1) * ldb + N, 0x7FC0, dtype=np.uint16)           # NaN wherever no element of B is
+    for k in range(K):
+        flat[offset + k * ldb: offset + k * ldb + N] = inp.B_kn[k]
+    B = dev_bf16(flat)
+    run = AgGemmRun(inp, 0)
+    try:
+        agg.agg_reserve_b_kn(run.ctx, N, K)
+        C = torch.full((sh.M, N), float("nan"), device="cuda")
+        agg.signal_reset(run.ctx)
+        agg.ag_producer_emulate(run.ctx, run.remote, None, agg.PRODUCER_KERNEL, 0, run.prod)
+        agg.ag_gemm(run.ctx, sh.M, N, K, B.data_ptr() + 2 * offset, ldb, agg.B_KN, C, N, agg.F32, run.prod)
+        torch.cuda.synchronize()
+        assert agg.agg_status(run.ctx) == agg.OK
+        assert np.array_equal(C.cpu().numpy().astype(np.float64), want)
+    finally:
+        run.close()
