@@ -3,6 +3,11 @@
 // across arrival orders.  Each workgroup waits (acquire) for slot w's signal before its first read of
 // slot w.  The kernel is bandwidth bound: W reads and one write per element, 16 bytes per lane per
 // access; ordinary loads (streaming-hinted loads measured 10 % slower here), streaming stores.
+// What is left beside the bytes is the start: the signals are looked at by the lanes of one wave side by side (one after
+// the other by one thread, each a trip to memory, cost 4 us per workgroup), and where all slots are there the first
+// block is loaded like every other.  Eight slots of 1024 x 8192 (302 MB, in no cache) 64.7 -> 59.6 us, of 8 x 8192 5.2 -> 3.6;
+// six slots of 512 x 4096 20.6 -> 15.6 and sixteen of 256 x 4096 29.8 -> 18.1 (four slots' loads in flight together
+// where no kernel is unrolled for the world size).
 #include "agg_internal.h"
 
 namespace agg {
@@ -12,17 +17,25 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 
 
-__device__ inline bool wait_signal(const int* fp, int epoch, long long ticks, int* err)
+// Wave 0 of a workgroup waits for the n signals f(0) .. f(n - 1), one lane each (64 at a time): they are looked at side by
+// side, each look is a trip to memory.  False in the lanes that gave up.
+template <class F>
+__device__ inline bool wait_signals(const ReduceArgs& a, int n, int epoch, int lane, F&& f)
 {
-    const long long t0 = wall_clock64();
-    while (__hip_atomic_load(fp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch) {
-        if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || wall_clock64() - t0 > ticks) {
-            __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return false;
+    bool ok = true;
+    for (int k = lane; k < n; k += 64) {
+        const int* fp = a.flags + f(k) * kSignalStride;
+        const long long t0 = wall_clock64();
+        while (__hip_atomic_load(fp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch) {
+            if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || wall_clock64() - t0 > a.wait_ticks) {
+                __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                ok = false;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
         }
-        __builtin_amdgcn_s_sleep(1);
     }
-    return true;
+    return ok;
 }
 
 __device__ inline void store_out(const ReduceArgs& a, long long i, f32x4 v)
@@ -53,7 +66,36 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a)
     const int W = WT > 0 ? WT : a.W;
     const int epoch = a.epoch_ptr ? __hip_atomic_load(a.epoch_ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : a.epoch;
     const long long stride = (long long)gridDim.x * 256;
+    __shared__ int s_upto;
     int seen = 0;                      // slots 0..seen-1 are known to have arrived (uniform over the workgroup)
+    // Wave 0 looks at all slots' signals at once (lane w at slot w's) until slots 0 .. want - 1 have arrived; one acquire (an
+    // L2 invalidate) covers all that have.  False: the wait was given up.
+    auto look = [&](int want) {
+        bool ok = true;
+        if (tid < 64) {
+            const int* fp = a.flags + (long long)(tid < W ? tid : 0) * a.flag_step * kSignalStride;
+            const long long t0 = wall_clock64();
+            int upto;
+            for (;;) {
+                const bool here = tid >= W || __hip_atomic_load(fp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= epoch;
+                const unsigned long long missing = ~__ballot(here);
+                upto = missing ? (int)__builtin_ctzll(missing) : W;
+                if (upto >= want) break;
+                if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || wall_clock64() - t0 > a.wait_ticks) {
+                    ok = false;
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+            if (!ok && tid == 0) __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0) s_upto = upto;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        if (__syncthreads_or(!ok)) return false;
+        seen = s_upto;
+        __syncthreads();
+        return true;
+    };
     int chunks_seen = 0;               // chunked slots: row chunks 0..chunks_seen-1 of EVERY slot have arrived
     for (long long base = (long long)blockIdx.x * 256 + tid; base - tid < a.n_vec4; base += stride * RU) {
         f32x4 acc[RU];
@@ -67,39 +109,22 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a)
             if (last >= a.n_vec4) last = a.n_vec4 - 1;
             const int need = (int)(last / a.chunk_vec4);
             if (need >= chunks_seen) {
-                int ok = 1;
-                if (tid == 0) {
-                    for (int c = chunks_seen; ok && c <= need; ++c)
-                        for (int w = 0; ok && w < W; ++w)
-                            ok = wait_signal(a.flags + ((long long)w * a.flag_step + c) * kSignalStride, epoch,
-                                             a.wait_ticks, a.err);
+                bool ok = true;
+                if (tid < 64) {
+                    const int c0 = chunks_seen;
+                    ok = wait_signals(a, (need - c0 + 1) * W, epoch, tid, [&](int k) { return (long long)(k % W) * a.flag_step + c0 + k / W; });
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 }
                 if (__syncthreads_or(!ok)) return;
                 chunks_seen = need + 1;
             }
+        } else if (seen < W) {
+            look(0);                   // when all have arrived, the block is loaded whole below
         }
         if (a.chunks <= 1 && seen < W) {
-            // slots still to arrive: take them one by one in the order of Algorithm 3.  A wait that ends also
-            // looks at the signals after it, so that one acquire (an L2 invalidate) covers all that are set.
+            // slots still to arrive: take them one by one in the order of Algorithm 3
             for (int w = 0; w < W; ++w) {
-                if (w >= seen) {
-                    int ok = 1, upto = w + 1;
-                    if (tid == 0) {
-                        ok = wait_signal(a.flags + (long long)w * a.flag_step * kSignalStride, epoch, a.wait_ticks, a.err);
-                        while (ok && upto < W &&
-                               __hip_atomic_load(a.flags + (long long)upto * a.flag_step * kSignalStride, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT) >= epoch)
-                            ++upto;
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                    }
-                    upto = __builtin_amdgcn_readfirstlane(upto);      // thread 0 is lane 0 of wave 0
-                    __shared__ int s_upto;
-                    if (tid == 0) s_upto = upto;
-                    if (__syncthreads_or(!ok)) return;
-                    seen = s_upto;
-                    __syncthreads();
-                }
+                if (w >= seen && !look(w + 1)) return;
                 const f32x4* s = (const f32x4*)a.slot[w];
 #pragma unroll
                 for (int u = 0; u < RU; ++u) {
@@ -125,13 +150,23 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a)
 #pragma unroll
                     for (int u = 0; u < RU; ++u) acc[u] = acc[u] + v[w][u];
             } else {
-                for (int w = 0; w < W; ++w) {
-                    const f32x4* s = (const f32x4*)a.slot[w];
+                for (int w0 = 0; w0 < W; w0 += 4) {          // four slots at a time
+                    f32x4 v[4][RU];
 #pragma unroll
-                    for (int u = 0; u < RU; ++u) {
-                        const long long i = base + u * stride;
-                        const f32x4 v = (i < a.n_vec4) ? s[i] : f32x4{0.f, 0.f, 0.f, 0.f};
-                        acc[u] = acc[u] + v;
+                    for (int k = 0; k < 4; ++k) {
+                        if (w0 + k >= W) break;
+                        const f32x4* s = (const f32x4*)a.slot[w0 + k];
+#pragma unroll
+                        for (int u = 0; u < RU; ++u) {
+                            const long long i = base + u * stride;
+                            v[k][u] = (i < a.n_vec4) ? s[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        if (w0 + k >= W) break;
+#pragma unroll
+                        for (int u = 0; u < RU; ++u) acc[u] = acc[u] + v[k][u];
                     }
                 }
             }
@@ -155,6 +190,7 @@ hipError_t launch_reduce(const ReduceArgs& a, int n_workgroups, hipStream_t stre
     }
     switch (a.W) {
         case 8: hipLaunchKernelGGL((reduce_kernel<8, 2>), dim3(n_workgroups), dim3(256), 0, stream, a); break;
+        case 3: hipLaunchKernelGGL((reduce_kernel<3, 2>), dim3(n_workgroups), dim3(256), 0, stream, a); break;
         case 4: hipLaunchKernelGGL((reduce_kernel<4, 2>), dim3(n_workgroups), dim3(256), 0, stream, a); break;
         case 2: hipLaunchKernelGGL((reduce_kernel<2, 4>), dim3(n_workgroups), dim3(256), 0, stream, a); break;
         default: hipLaunchKernelGGL((reduce_kernel<0, 2>), dim3(n_workgroups), dim3(256), 0, stream, a); break;
