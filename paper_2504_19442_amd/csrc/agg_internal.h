@@ -205,7 +205,8 @@ struct agg_ctx {
     // grouped GEMM workspace (sized by agg_reserve_moe; no other call allocates it)
     int* moe_ws;          // the MoE routing's control block (kMoeCtrlBytes; its first word is the tile count of the launch under way)
     agg::MoeTile* moe_tab;
-    int moe_tab_cap;
+    int moe_tab_cap;      // entries the table holds ...
+    int moe_tab_base;     // ... and how many agg_reserve_moe was asked for (at least kStaticTabEntries are there)
     uint16_t* b_nk;       // [N][K] copy of a B that was given as [K][N] (sized by agg_reserve_b_kn)
     size_t b_nk_elems;
     hipEvent_t b_nk_free;     // recorded behind the last GEMM that read b_nk, on b_nk_stream

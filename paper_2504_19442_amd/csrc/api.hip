@@ -3,6 +3,7 @@
 #include "agg_internal.h"
 
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 #include <new>
@@ -149,9 +150,66 @@ constexpr size_t kStaticTabEntries = 32760;
 constexpr size_t kStaticScratchBytes = kStaticTabOffset + kStaticTabEntries * sizeof(MoeTile);   // 1088 KiB
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
-// Upper bound of the grouped GEMM's tile table over all tile configurations: sum over experts of
-// ceil(rows / bm) <= P / bm + E, times the n-tiles, for the smallest tile (128 x 128).
-long long moe_table_bound(long long P, int E, int N) { return (P / 128 + E) * ((N + 127) / 128); }
+// Upper bound of the grouped GEMM's tile table for one tile shape: sum over experts of ceil(rows / bm) <= P / bm + E, times
+// the n-tiles.
+long long moe_table_entries(long long P, int E, int N, TileShape t) { return (P / t.bm + E) * ((N + t.bn - 1) / t.bn); }
+// ... and over the shapes that can be selected by number (128 x 128 is the smallest)
+long long moe_table_bound(long long P, int E, int N) { return moe_table_entries(P, E, N, {128, 128}); }
+
+// The shape, among those that can be selected by number, that decides whether a reserved table is large enough for a call:
+// rounds of tiles over the CUs times the cost of a tile (the small tile is bound by the global->LDS path: about 0.6 of the
+// large tile's rate per flop), with segments 15 % above the mean.
+int table_tile_grouped(const agg_ctx* c, long long wanted_rows, int E, int N)
+{
+    const int cand[3] = {TILE_256x224, TILE_256x256, TILE_128x128};
+    const double eff[3] = {1.0, 1.0, 0.6};
+    const double rows = 1.15 * (double)wanted_rows / E;
+    double best = 1e300;
+    int cfg = cand[0];
+    for (int i = 0; i < 3; ++i) {
+        const TileShape ts = tile_shape(cand[i]);
+        const long long mt = (long long)((rows + ts.bm - 1) / ts.bm);
+        const long long tiles = (long long)E * mt * ((N + ts.bn - 1) / ts.bn);
+        const long long waves = (tiles + c->num_cus - 1) / c->num_cus;
+        const double cost = (double)waves * ts.bm * ts.bn / eff[i];
+        if (cost < best) { best = cost; cfg = cand[i]; }
+    }
+    return cfg | TILE_K32;
+}
+
+// Tile shape of a grouped GEMM: `rows` rows of A spread over E experts, [N][K] weights per expert.  Segments are ragged:
+// 15 % above the mean is allowed for.  Beside the rounds of tiles (choose_tile) there are the weights of the experts that
+// have rows, from HBM at 5.9 TB/s; where they bound it, a last round that fills only part of the chip costs its share of
+// that time, and the smaller tile wins.  Measured, us per call with routing: 64 tokens of Table 4 (two rows per expert)
+// 128x128 203, 64x64 179, 16x32 164; 512 tokens 128x128 230, 32x32 208; 8192 tokens 256x256 356, 128x256 332, 128x128 452.
+// Left out are shapes whose table (P pairs) would have more than `tab_base` entries, and of the small ones those beyond the
+// static table's size, whatever table is used: the choice depends on the problem alone.  -1 if that is all of them.
+int choose_tile_grouped(const agg_ctx* c, long long rows, int E, int N, int K, long long P, long long tab_base)
+{
+    static const TileCost cand[] = {
+        {KS_16x32, 3.0, 0.09}, {KS_16x64, 3.0, 0.12}, {KS_32x32, 3.0, 0.125}, {KS_64x64, 3.0, 0.24}, {KS_64x128, 3.5, 0.37},
+        {TILE_128x128 | TILE_K32, 4.0, 0.46}, {TILE_128x256 | TILE_K32, 4.0, 0.83}, {TILE_256x224 | TILE_K32, 4.0, 1.25},
+        {TILE_256x256 | TILE_K32, 4.0, 1.42},
+    };
+    const double active = E * (1.0 - std::pow(1.0 - 1.0 / E, (double)rows));       // experts with at least one row
+    const double hbm_us = active * N * K * 2.0 / 5.9e6;
+    int best = -1;
+    double best_cost = 1e300;
+    for (const TileCost& k : cand) {
+        const TileShape t = tile_shape(k.cfg);
+        if (moe_table_entries(P, E, N, t) > (k.cfg >= TILE_CONFIGS ? (long long)kStaticTabEntries : tab_base)) continue;
+        const double mt = std::ceil(1.15 * (double)rows / active / t.bm);
+        const double tiles = std::max(1.0, active * mt * ((N + t.bn - 1) / t.bn));
+        const double rounds = std::ceil(tiles / c->num_cus);
+        const double cost = std::max(rounds * (k.fixed_us + k.us_per_k64 * (K / 64)),
+                                     hbm_us * rounds * c->num_cus / std::max(tiles, (double)c->num_cus));
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = k.cfg;
+        }
+    }
+    return best;
+}
 
 // The producer stream must run side by side with the consumer stream: streams that the runtime has put on one
 // hardware queue run their kernels one after the other.  Which queue a new stream gets cannot be asked for, so it
@@ -394,8 +452,11 @@ int agg_reserve_b_kn(agg_ctx* c, int N, int K)
 int agg_reserve_moe(agg_ctx* c, int Ttok, int topk, int E, int N)
 {
     if (!c || Ttok < 0 || topk < 1 || E < 1 || E > 4096 || N < 0) return AGG_ERR_INVALID_ARG;
-    const long long cap = moe_table_bound((long long)Ttok * topk, E, N);
-    if (cap > (1ll << 28)) return AGG_ERR_UNSUPPORTED_SHAPE;
+    const long long P = (long long)Ttok * topk;
+    if (moe_table_bound(P, E, N) > (1ll << 28)) return AGG_ERR_UNSUPPORTED_SHAPE;
+    // the table holds any shape that can be selected by number, and the small tiles of the automatic choice up to the size
+    // of the static table (with which the two entry points choose alike)
+    const long long base = moe_table_bound(P, E, N), cap = std::max(base, (long long)kStaticTabEntries);
     if (!c->moe_ws) {
         HIP_TRY(hipDeviceSynchronize());
         HIP_TRY(hipMalloc((void**)&c->moe_ws, kMoeCtrlBytes));
@@ -409,6 +470,7 @@ int agg_reserve_moe(agg_ctx* c, int Ttok, int topk, int E, int N)
         HIP_TRY(hipMalloc((void**)&c->moe_tab, (size_t)cap * sizeof(MoeTile)));
         c->moe_tab_cap = (int)cap;
     }
+    c->moe_tab_base = std::max(c->moe_tab_base, (int)base);
     return AGG_OK;
 }
 
@@ -868,7 +930,7 @@ int gemm_rs(agg_ctx* c, int M, int N, int Kl, const void* A_local, int lda, cons
 // (one run of rows per expert, since tokens rise inside a segment).
 static int grouped_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, const int32_t* topk_ids, const void* A,
                         bool gathered, const void* weights, int32_t* sorted_token, int32_t* seg_off, int32_t* pair_pos,
-                        void* Y, int ldy, int y_dtype, hipStream_t stream, int* n_tiles_word, MoeTile* tab, long long tab_cap,
+                        void* Y, int ldy, int y_dtype, hipStream_t stream, int* n_tiles_word, MoeTile* tab, long long tab_base,
                         int keep_lo = 0, int keep_hi = 0)
 {
     const long long P = (long long)Ttok * topk;
@@ -879,31 +941,21 @@ static int grouped_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, con
     if (reinterpret_cast<uintptr_t>(Y) % (y_dtype == AGG_F32 ? 4 : 2) != 0) return AGG_ERR_MISALIGNED;
     const int tpr = Ttok / c->W, cps = c->n_signals / c->W;
 
-    // Tile shape: segments are ragged (about P / E rows each, a binomial spread around it).  Estimate the tiles
-    // each shape would need with segments 15 % above the mean, in waves over the CUs, times the cost of a tile
-    // (the small tile is bound by the global->LDS path: about 0.6 of the large tile's rate per flop).
-    int cfg = c->tile_config;
-    if (cfg < 0) {
-        const int cand[3] = {TILE_256x224, TILE_256x256, TILE_128x128};
-        const double eff[3] = {1.0, 1.0, 0.6};
-        // (with a token range to keep, only the rows of those tokens get tiles)
-        const double rows = 1.15 * (keep_lo < keep_hi ? (double)(keep_hi - keep_lo) * topk : (double)P) / E;
-        double best = 1e300;
-        for (int i = 0; i < 3; ++i) {
-            const TileShape ts = tile_shape(cand[i]);
-            const long long mt = (long long)((rows + ts.bm - 1) / ts.bm);
-            const long long tiles = (long long)E * mt * ((N + ts.bn - 1) / ts.bn);
-            const long long waves = (tiles + c->num_cus - 1) / c->num_cus;
-            const double cost = (double)waves * ts.bm * ts.bn / eff[i];
-            if (cost < best) { best = cost; cfg = cand[i]; }
-        }
-        cfg |= TILE_K32;
+    // (with a token range to keep, only the rows of those tokens get tiles)
+    const long long rows = keep_lo < keep_hi ? (long long)(keep_hi - keep_lo) * topk : P;
+    int cfg = c->tile_config >= 0 ? c->tile_config : table_tile_grouped(c, rows, E, N);
+    {
+        const long long cap = moe_table_entries(P, E, N, tile_shape(cfg));
+        if (cap > (1ll << 28)) return AGG_ERR_UNSUPPORTED_SHAPE;
+        if (!n_tiles_word || !tab || tab_base < cap) return AGG_ERR_NOT_RESERVED;
+    }
+    if (c->tile_config < 0) {
+        const int better = choose_tile_grouped(c, rows, E, N, K, P, tab_base);
+        if (better >= 0) cfg = better;
     }
     const TileShape t = tile_shape(cfg);
     const int tiles_n = (N + t.bn - 1) / t.bn;
-    const long long cap = (P / t.bm + E) * tiles_n;              // sum over experts of ceil(rows / bm) <= P / bm + E
-    if (cap > (1ll << 28)) return AGG_ERR_UNSUPPORTED_SHAPE;
-    if (!n_tiles_word || !tab || tab_cap < cap) return AGG_ERR_NOT_RESERVED;
+    const long long cap = moe_table_entries(P, E, N, t);
     MoeRouteArgs r{};
     r.topk_ids = topk_ids;
     r.P = (int)P;
@@ -958,7 +1010,7 @@ static int grouped_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, con
 
 static int ag_moe_gemm_impl(agg_ctx* c, int Ttok, int topk, int E, int N, int K, const int32_t* topk_ids, const void* weights,
                             int32_t* sorted_token, int32_t* sorted_expert_offsets, void* Y, int ldy, int y_dtype, void* stream,
-                            int* n_tiles_word, MoeTile* tab, long long tab_cap)
+                            int* n_tiles_word, MoeTile* tab, long long tab_base)
 {
     if (!c || Ttok < 0 || topk < 1 || E < 1 || E > 4096 || N < 0 || K < 0) return AGG_ERR_INVALID_ARG;
     if (y_dtype != AGG_BF16 && y_dtype != AGG_F32) return AGG_ERR_INVALID_ARG;
@@ -972,7 +1024,7 @@ static int ag_moe_gemm_impl(agg_ctx* c, int Ttok, int topk, int E, int N, int K,
     const int cps = c->n_signals / c->W;
     if (tpr % cps != 0) return AGG_ERR_UNSUPPORTED_SHAPE;
     return grouped_gemm(c, Ttok, topk, E, N, K, topk_ids, c->staging, true, weights, sorted_token, sorted_expert_offsets,
-                        nullptr, Y, ldy, y_dtype, (hipStream_t)stream, n_tiles_word, tab, tab_cap);
+                        nullptr, Y, ldy, y_dtype, (hipStream_t)stream, n_tiles_word, tab, tab_base);
 }
 
 int ag_moe_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, const int32_t* topk_ids, const void* weights,
@@ -980,7 +1032,7 @@ int ag_moe_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, const int32
 {
     if (!c) return AGG_ERR_INVALID_ARG;
     return ag_moe_gemm_impl(c, Ttok, topk, E, N, K, topk_ids, weights, sorted_token, sorted_expert_offsets, Y, ldy, y_dtype,
-                            stream, c->moe_ws, c->moe_tab, c->moe_tab_cap);
+                            stream, c->moe_ws, c->moe_tab, c->moe_tab_base);
 }
 
 int ag_moe_gemm_static(agg_ctx* c, int Ttok, int topk, int E, int N, int K, const int32_t* topk_ids, const void* weights,
@@ -1022,7 +1074,7 @@ int moe_rs(agg_ctx* c, int Ttok, int topk, int E, int N, int Kl, const void* H, 
     // that hold none of them (inside an expert's segment the tokens rise, so the rows of one rank are one run)
     const int keep_lo = Z_other ? 0 : c->rank * Tr, keep_hi = Z_other ? 0 : keep_lo + Tr;
     int rc = grouped_gemm(c, Ttok, topk, E, N, Kl, topk_ids, H, false, weights2, sorted_token, sorted_expert_offsets,
-                          pair_pos, Y, N, AGG_F32, (hipStream_t)gemm_stream, c->moe_ws, c->moe_tab, c->moe_tab_cap,
+                          pair_pos, Y, N, AGG_F32, (hipStream_t)gemm_stream, c->moe_ws, c->moe_tab, c->moe_tab_base,
                           keep_lo, keep_hi);
     if (rc != AGG_OK) return rc;
     // 2. top-k reduction: this rank's tokens into its own slot (first), the others' into Z_other

@@ -112,3 +112,47 @@ def test_b_given_as_k_by_n_any_alignment_exact(K, N, ldb, offset):
         assert np.array_equal(C.cpu().numpy().astype(np.float64), want)
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("W,tpr,K,N,E,topk", [
+    (4, 1, 64, 32, 4, 1),           # one piece of K, a token or none per expert
+    (2, 3, 192, 100, 7, 2),         # rows of a tile beyond the segment, ragged columns
+    (8, 8, 1024, 130, 16, 2),       # eight rows per expert
+    (2, 96, 320, 66, 6, 2),         # segments of 64 rows: some need two tiles of 64
+    (3, 111, 128, 1999, 5, 3),      # odd columns, 64 x 128 tiles
+    (8, 128, 64, 260, 8, 2),        # 256 rows per expert
+])
+def test_moe_small_shapes_exact(W, tpr, K, N, E, topk):
+    sh = wl.MoeShape(f"moe_small_{tpr}_{K}_{N}", 24, W, tpr, K, N, E, topk)
+    inp = wl.make_moe(sh, x_dist=("int", 2), w_dist=("int", 2))
+    tok_ref, _, seg_ref = oracle.moe_route(inp.topk_ids, E)
+    X = wl.bf16_bits_to_f32(np.concatenate(inp.shards)).astype(np.float64)
+    want = np.empty((sh.T * topk, N))
+    for e in range(E):
+        rows = slice(int(seg_ref[e]), int(seg_ref[e + 1]))
+        want[rows] = X[tok_ref[rows]] @ wl.bf16_bits_to_f32(inp.W_ekn[e]).astype(np.float64)
+    shards = [dev_bf16(s) for s in inp.shards]
+    B = dev_bf16(np.ascontiguousarray(np.transpose(inp.W_ekn, (0, 2, 1))))
+    ids = torch.from_numpy(inp.topk_ids).cuda()
+    tok = torch.empty(sh.T * topk, device="cuda", dtype=torch.int32)
+    seg = torch.empty(E + 1, device="cuda", dtype=torch.int32)
+    ctx = agg.symm_alloc(W, 0, tpr * K * 2, W)
+    try:
+        agg.agg_reserve_moe(ctx, sh.T, topk, E, N)
+        ps, cs = ctx.streams()
+        for call in (agg.ag_moe_gemm, agg.ag_moe_gemm_static):
+            for dtype, tdt in ((agg.F32, torch.float32), (agg.BF16, torch.bfloat16)):
+                Y = torch.full((sh.T * topk, N), float("nan"), device="cuda", dtype=tdt)
+                agg.signal_reset(ctx)
+                torch.cuda.synchronize()
+                agg.ag_producer_emulate(ctx, shards, None, agg.PRODUCER_KERNEL, 0, ps)
+                call(ctx, sh.T, topk, E, N, K, ids, B, tok, seg, Y, N, dtype, cs)
+                torch.cuda.synchronize()
+                assert agg.agg_status(ctx) == agg.OK
+                assert np.array_equal(tok.cpu().numpy(), tok_ref) and np.array_equal(seg.cpu().numpy().astype(np.int64), seg_ref)
+                if dtype == agg.F32:
+                    assert np.array_equal(Y.cpu().numpy().astype(np.float64), want)
+                else:
+                    assert np.array_equal(host_bits(Y), wl.f32_to_bf16_bits(want.astype(np.float32)))
+    finally:
+        ctx.free()
