@@ -204,7 +204,8 @@ struct agg_ctx {
     hipStream_t producer_stream, consumer_stream;
     // grouped GEMM workspace (sized by agg_reserve_moe; no other call allocates it)
     int* moe_ws;          // the MoE routing's control block (kMoeCtrlBytes; its first word is the tile count of the launch under way)
-    agg::MoeTile* moe_tab;
+    agg::MoeTile* moe_tab;        // the table in use: behind the control block, or moe_tab_large
+    agg::MoeTile* moe_tab_large;  // a table larger than that
     int moe_tab_cap;      // entries the table holds ...
     int moe_tab_base;     // ... and how many agg_reserve_moe was asked for (at least kStaticTabEntries are there)
     uint16_t* b_nk;       // [N][K] copy of a B that was given as [K][N] (sized by agg_reserve_b_kn)

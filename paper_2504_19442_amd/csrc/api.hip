@@ -52,13 +52,14 @@ constexpr int kKsMaxRows = 65535;
 // Pick the tile shape with the smallest estimated time: rounds of tiles over the CUs times the cost of a tile.  The
 // 16x16x32 form of the main loop everywhere: the same work at a lower power per flop, so the chip holds a higher clock
 // (measured 5 to 8 % faster on every shape); the 32x32x16 form stays selectable (configurations 0 to 3).
-int choose_tile(const agg_ctx* c, int M, int N, int K)
+// large_only: without the K-split tiles.
+int choose_tile(const agg_ctx* c, int M, int N, int K, bool large_only = false)
 {
     if (c->tile_config >= 0) return c->tile_config;
     int best = kTileCosts[0].cfg;
     double best_cost = 1e300;
     for (const TileCost& k : kTileCosts) {
-        if (k.cfg >= TILE_CONFIGS && M > kKsMaxRows) continue;
+        if (k.cfg >= TILE_CONFIGS && (large_only || M > kKsMaxRows)) continue;
         const TileShape t = tile_shape(k.cfg);
         const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
         const long long rounds = (tiles + c->num_cus - 1) / c->num_cus;
@@ -177,19 +178,34 @@ int table_tile_grouped(const agg_ctx* c, long long wanted_rows, int E, int N)
     return cfg | TILE_K32;
 }
 
-// Tile shape of a grouped GEMM: `rows` rows of A spread over E experts, [N][K] weights per expert.  Segments are ragged:
-// 15 % above the mean is allowed for.  Beside the rounds of tiles (choose_tile) there are the weights of the experts that
-// have rows, from HBM at 5.9 TB/s; where they bound it, a last round that fills only part of the chip costs its share of
-// that time, and the smaller tile wins.  Measured, us per call with routing: 64 tokens of Table 4 (two rows per expert)
-// 128x128 203, 64x64 179, 16x32 164; 512 tokens 128x128 230, 32x32 208; 8192 tokens 256x256 356, 128x256 332, 128x128 452.
+// Expected number of tiles of `bm` rows of a segment of `mean` rows on average, its length spread around that like that of a
+// random routing (standard deviation sqrt(mean)): sum over k of P(length > k * bm).
+double expected_m_tiles(double mean, int bm)
+{
+    const double sd = std::sqrt(mean);
+    double n = 1.0;
+    for (int k = 1; k * (double)bm < mean + 3.0 * sd; ++k) n += 0.5 * std::erfc((k * (double)bm - mean) / (sd * std::sqrt(2.0)));
+    return n;
+}
+
+// Tile shape of a grouped GEMM: `rows` rows of A spread over E experts, [N][K] weights per expert.  Rounds of tiles times
+// the cost of a tile, as in choose_tile (the large tiles cost a fifth more here, where every tile has a weight matrix of its
+// own to pull from HBM; fp32 rows are stored at about 19 KB/us per compute unit), but not less than the weights of the
+// experts that have rows take from HBM at 5.9 TB/s; where they bound it, a last round that fills only part of the chip
+// costs its share of that time, and the smaller tile wins.  Measured, us per call with routing, bf16 out: 64 tokens of
+// Table 4 (two rows per expert) 128x128 203, 64x64 179, 16x32 164; 512 tokens 128x128 230, 32x32 208.  Rows in place with
+// K = 192 and fp32 out (the GEMM of Table 5, kernel alone): 256x256 70, 128x256 63, 128x128 71.  Gathered rows never take
+// 128x256: the whole call at 8192 tokens is 1 % faster in bf16 (374 against 376) but its first pass on new weights 5 %
+// slower (457 against 435), and in fp32 it is 5 % slower throughout (392 against 371).
 // Left out are shapes whose table (P pairs) would have more than `tab_base` entries, and of the small ones those beyond the
 // static table's size, whatever table is used: the choice depends on the problem alone.  -1 if that is all of them.
-int choose_tile_grouped(const agg_ctx* c, long long rows, int E, int N, int K, long long P, long long tab_base)
+int choose_tile_grouped(const agg_ctx* c, long long rows, int E, int N, int K, bool gathered, bool f32, long long P, long long tab_base,
+                        bool large_only = false)
 {
     static const TileCost cand[] = {
-        {KS_16x32, 3.0, 0.09}, {KS_16x64, 3.0, 0.12}, {KS_32x32, 3.0, 0.125}, {KS_64x64, 3.0, 0.24}, {KS_64x128, 3.5, 0.37},
-        {TILE_128x128 | TILE_K32, 4.0, 0.46}, {TILE_128x256 | TILE_K32, 4.0, 0.83}, {TILE_256x224 | TILE_K32, 4.0, 1.25},
-        {TILE_256x256 | TILE_K32, 4.0, 1.42},
+        {KS_16x32, 3.0, 0.09}, {KS_16x64, 3.0, 0.12}, {KS_32x32, 3.0, 0.125}, {KS_64x64, 3.0, 0.24}, {KS_64x128, 3.5, 0.38},
+        {TILE_128x128 | TILE_K32, 4.0, 0.60}, {TILE_128x256 | TILE_K32, 4.0, 0.94}, {TILE_256x224 | TILE_K32, 4.0, 1.50},
+        {TILE_256x256 | TILE_K32, 4.0, 1.73},
     };
     const double active = E * (1.0 - std::pow(1.0 - 1.0 / E, (double)rows));       // experts with at least one row
     const double hbm_us = active * N * K * 2.0 / 5.9e6;
@@ -198,11 +214,11 @@ int choose_tile_grouped(const agg_ctx* c, long long rows, int E, int N, int K, l
     for (const TileCost& k : cand) {
         const TileShape t = tile_shape(k.cfg);
         if (moe_table_entries(P, E, N, t) > (k.cfg >= TILE_CONFIGS ? (long long)kStaticTabEntries : tab_base)) continue;
-        const double mt = std::ceil(1.15 * (double)rows / active / t.bm);
-        const double tiles = std::max(1.0, active * mt * ((N + t.bn - 1) / t.bn));
+        if ((large_only && k.cfg >= TILE_CONFIGS) || (gathered && t.bm == 128 && t.bn == 256)) continue;
+        const double tiles = active * expected_m_tiles((double)rows / active, t.bm) * ((N + t.bn - 1) / t.bn);
         const double rounds = std::ceil(tiles / c->num_cus);
-        const double cost = std::max(rounds * (k.fixed_us + k.us_per_k64 * (K / 64)),
-                                     hbm_us * rounds * c->num_cus / std::max(tiles, (double)c->num_cus));
+        const double tile_us = k.fixed_us + k.us_per_k64 * (K / 64) + (f32 ? t.bm * t.bn * 4 / 19e3 : 0.0);
+        const double cost = std::max(rounds * tile_us, hbm_us * rounds * c->num_cus / std::max(tiles, (double)c->num_cus));
         if (cost < best_cost) {
             best_cost = cost;
             best = k.cfg;
@@ -311,7 +327,7 @@ int symm_free(agg_ctx* c)
     if (c->b_nk_free) (void)hipEventDestroy(c->b_nk_free);
     if (c->b_nk) (void)hipFree(c->b_nk);
     if (c->moe_ws) (void)hipFree(c->moe_ws);
-    if (c->moe_tab) (void)hipFree(c->moe_tab);
+    if (c->moe_tab_large) (void)hipFree(c->moe_tab_large);
     if (c->staging) (void)hipFree(c->staging);
     if (c->signals) (void)hipFree(c->signals);
     if (c->counters) (void)hipFree(c->counters);
@@ -456,19 +472,23 @@ int agg_reserve_moe(agg_ctx* c, int Ttok, int topk, int E, int N)
     if (moe_table_bound(P, E, N) > (1ll << 28)) return AGG_ERR_UNSUPPORTED_SHAPE;
     // the table holds any shape that can be selected by number, and the small tiles of the automatic choice up to the size
     // of the static table (with which the two entry points choose alike)
-    const long long base = moe_table_bound(P, E, N), cap = std::max(base, (long long)kStaticTabEntries);
+    const long long base = moe_table_bound(P, E, N);
     if (!c->moe_ws) {
+        // the control block and a table of that size behind it, in one allocation
         HIP_TRY(hipDeviceSynchronize());
-        HIP_TRY(hipMalloc((void**)&c->moe_ws, kMoeCtrlBytes));
+        HIP_TRY(hipMalloc((void**)&c->moe_ws, kStaticScratchBytes));
         HIP_TRY(hipMemset(c->moe_ws, 0, kMoeCtrlBytes));         // the routing's counters start at zero
+        c->moe_tab = (MoeTile*)((char*)c->moe_ws + kStaticTabOffset);
+        c->moe_tab_cap = (int)kStaticTabEntries;
     }
-    if (c->moe_tab_cap < cap) {
+    if (c->moe_tab_cap < base) {
         HIP_TRY(hipDeviceSynchronize());
-        if (c->moe_tab) (void)hipFree(c->moe_tab);
-        c->moe_tab = nullptr;
+        if (c->moe_tab_large) (void)hipFree(c->moe_tab_large);
+        c->moe_tab = c->moe_tab_large = nullptr;
         c->moe_tab_cap = 0;
-        HIP_TRY(hipMalloc((void**)&c->moe_tab, (size_t)cap * sizeof(MoeTile)));
-        c->moe_tab_cap = (int)cap;
+        HIP_TRY(hipMalloc((void**)&c->moe_tab_large, (size_t)base * sizeof(MoeTile)));
+        c->moe_tab = c->moe_tab_large;
+        c->moe_tab_cap = (int)base;
     }
     c->moe_tab_base = std::max(c->moe_tab_base, (int)base);
     return AGG_OK;
@@ -889,7 +909,10 @@ int gemm_rs(agg_ctx* c, int M, int N, int Kl, const void* A_local, int lda, cons
         p.ldc_slice = N;
         p.slice_ctr = c->counters + c->n_signals;
         p.slice_flag[0] = own_flag;
-        const int cfg = choose_tile(c, Ms, N, Kl);
+        // the sum over K in the same order as with P_other, so that the slice is the same bit for bit: a K-split tile if
+        // the whole product takes one, and then that one
+        int cfg = choose_tile(c, M, N, Kl);
+        if (cfg < TILE_CONFIGS) cfg = choose_tile(c, Ms, N, Kl, true);
         fill_schedule(c, p, cfg, Ms, 0);
         const long long tiles = (long long)p.tiles_m * p.tiles_n;
         const int grid = gemm_grid(c, cfg, tiles);
@@ -950,7 +973,11 @@ static int grouped_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, con
         if (!n_tiles_word || !tab || tab_base < cap) return AGG_ERR_NOT_RESERVED;
     }
     if (c->tile_config < 0) {
-        const int better = choose_tile_grouped(c, rows, E, N, K, P, tab_base);
+        // with a token range to keep, the sum over K in the same order as without: a K-split tile if all rows would take one,
+        // and then that one
+        int better = choose_tile_grouped(c, P, E, N, K, gathered, y_dtype == AGG_F32, P, tab_base);
+        if (rows != P && better >= 0 && better < TILE_CONFIGS)
+            better = choose_tile_grouped(c, rows, E, N, K, gathered, y_dtype == AGG_F32, P, tab_base, true);
         if (better >= 0) cfg = better;
     }
     const TileShape t = tile_shape(cfg);

@@ -511,14 +511,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
                             char* dst = row_ptr(row_w + i * 16 + (lane_e & 15), esz);
                             if (dst) {
                                 T* q = (T*)dst + colq;
-                                static_for<C_::NB16>([&](auto j_c) {
-                                    constexpr int j = decltype(j_c)::value;
-                                    constexpr int r0 = (i * C_::NB16 + j) * 4;
-                                    const float x0 = acc_read<r0>(), x1 = acc_read<r0 + 1>(), x2 = acc_read<r0 + 2>(),
-                                                x3 = acc_read<r0 + 3>();
-                                    if (n_valid == BN || colq + j * 16 < n_valid)
-                                        __builtin_nontemporal_store(Tx4{(T)x0, (T)x1, (T)x2, (T)x3}, (Tx4*)(q + j * 16));
-                                });
+                                auto store_row = [&](auto put) {
+                                    static_for<C_::NB16>([&](auto j_c) {
+                                        constexpr int j = decltype(j_c)::value;
+                                        constexpr int r0 = (i * C_::NB16 + j) * 4;
+                                        const float x0 = acc_read<r0>(), x1 = acc_read<r0 + 1>(), x2 = acc_read<r0 + 2>(),
+                                                    x3 = acc_read<r0 + 3>();
+                                        if (n_valid == BN || colq + j * 16 < n_valid)
+                                            put(Tx4{(T)x0, (T)x1, (T)x2, (T)x3}, (Tx4*)(q + j * 16));
+                                    });
+                                };
+                                // rows in place (MoE + ReduceScatter): the next kernel reads them, they may stay in the caches
+                                // (256x256 tiles at K = 192: 80 us with streaming stores, 70 without)
+                                if (GROUPED && !p.row_index) store_row([](Tx4 v, Tx4* at) { *at = v; });
+                                else store_row([](Tx4 v, Tx4* at) { __builtin_nontemporal_store(v, at); });
                             }
                         });
                         return;

@@ -156,3 +156,67 @@ def test_moe_small_shapes_exact(W, tpr, K, N, E, topk):
                     assert np.array_equal(host_bits(Y), wl.f32_to_bf16_bits(want.astype(np.float32)))
     finally:
         ctx.free()
+
+
+@pytest.mark.parametrize("W,tpr,K,N,E,topk", [(4, 4, 192, 64, 8, 2), (8, 16, 640, 260, 16, 2), (2, 300, 64, 512, 4, 1)])
+def test_moe_rs_own_tokens_alone_are_the_same_bits_as_with_all(W, tpr, K, N, E, topk):
+    sh = wl.MoeRsShape(f"moers_small_{tpr}_{K}", 25, W, tpr, K, N, E, topk)
+    rank = W - 1
+    inp = wl.make_moe_rs(sh, rank=rank)
+    want = oracle.moe_rs(inp.H, inp.W2_ekn, inp.topk_ids, inp.gate, inp.peer_slots, W, rank)
+    P = sh.T * topk
+    H, B = dev_bf16(inp.H), dev_bf16(np.ascontiguousarray(np.transpose(inp.W2_ekn, (0, 2, 1))))
+    ids, gate = torch.from_numpy(inp.topk_ids).cuda(), torch.from_numpy(inp.gate).cuda()
+    tok, pos = (torch.empty(P, device="cuda", dtype=torch.int32) for _ in range(2))
+    seg = torch.empty(E + 1, device="cuda", dtype=torch.int32)
+    slots = [torch.from_numpy(inp.peer_slots[w]).cuda() if w != rank else torch.empty((tpr, N), device="cuda") for w in range(W)]
+    ctx = agg.symm_alloc(W, rank, 16, W)
+    try:
+        agg.agg_reserve_moe(ctx, sh.T, topk, E, N)
+        ps, cs = ctx.streams()
+        got = []
+        for other, two_streams in ((True, True), (False, True), (True, False)):
+            slots[rank].fill_(float("nan"))
+            Y = torch.full((P, N), float("nan"), device="cuda")
+            Z = torch.full((sh.T, N), float("nan"), device="cuda") if other else None
+            R = torch.full((tpr, N), float("nan"), device="cuda")
+            agg.signal_reset(ctx)
+            torch.cuda.synchronize()
+            for w in range(W):
+                if w != rank:
+                    agg.signal_set(ctx, w, cs)
+            agg.moe_rs(ctx, sh.T, topk, E, N, K, H, B, ids, gate, Y, tok, seg, pos, slots, Z, R, N, agg.F32, ps if two_streams else cs, cs)
+            torch.cuda.synchronize()
+            assert agg.agg_status(ctx) == agg.OK
+            got.append(R.cpu().numpy())
+        rel = np.linalg.norm(got[0] - want) / np.linalg.norm(want)
+        assert rel <= 1e-6, rel           # fp32 sums of K = 64 .. 640 products
+        for g in got[1:]:
+            assert np.array_equal(g.view(np.uint32), got[0].view(np.uint32))
+    finally:
+        ctx.free()
+
+
+def test_gemm_rs_own_slice_alone_is_the_same_bits_as_with_all():
+    for W, Ms, K, N in ((8, 8, 640, 512), (4, 40, 448, 1500), (2, 300, 320, 900)):
+        sh = wl.GemmRsShape(f"rs_bits_{Ms}", 26, W, W * Ms, K, N)
+        inp = wl.make_gemm_rs(sh, rank=0)
+        A, B = dev_bf16(inp.A_loc), dev_bf16(np.ascontiguousarray(inp.B_kn.T))
+        ctx = agg.symm_alloc(W, 0, 16, W)
+        try:
+            _, cs = ctx.streams()
+            slots = [torch.zeros((Ms, N), device="cuda") for _ in range(W)]
+            got = []
+            for other in (True, False):
+                P = torch.zeros((W * Ms, N), device="cuda") if other else None
+                R = torch.zeros((Ms, N), device="cuda")
+                agg.signal_reset(ctx)
+                for w in range(1, W):
+                    agg.signal_set(ctx, w, cs)
+                agg.gemm_rs(ctx, W * Ms, N, K, A, K, B, K, agg.B_NK, slots, P, R, N, agg.F32, cs, cs)
+                torch.cuda.synchronize()
+                assert agg.agg_status(ctx) == agg.OK
+                got.append(R.cpu().numpy().view(np.uint32))
+            assert np.array_equal(got[0], got[1]), (W, Ms)
+        finally:
+            ctx.free()
