@@ -119,24 +119,38 @@ def _check(rc: int, what: str) -> int:
     return rc
 
 
-def _ptr(x) -> C.c_void_p:
+# Pointers and streams go to ctypes as plain integers (the functions' argtypes convert them): no wrapper object per argument.
+# A small GEMM takes about as long on the GPU as its call takes here.
+def _ptr(x):
     if x is None:
-        return C.c_void_p(None)
-    if hasattr(x, "data_ptr"):
-        return C.c_void_p(x.data_ptr())
-    return C.c_void_p(int(x))
+        return None
+    try:
+        return x.data_ptr()
+    except AttributeError:
+        return int(x)
 
 
-def _stream(s) -> C.c_void_p:
+def _stream(s):
     if s is None:
-        return C.c_void_p(None)
-    if hasattr(s, "cuda_stream"):
-        return C.c_void_p(s.cuda_stream)
-    return C.c_void_p(int(s))
+        return None
+    try:
+        return s.cuda_stream
+    except AttributeError:
+        return int(s)
+
+
+_ARRAYS: dict[int, type] = {}           # ctypes array type of n pointers
 
 
 def _ptr_array(items):
-    return (C.c_void_p * len(items))(*[_ptr(i).value for i in items])
+    n = len(items)
+    t = _ARRAYS.get(n)
+    if t is None:
+        t = _ARRAYS[n] = C.c_void_p * n
+    try:
+        return t(*[i.data_ptr() for i in items])
+    except AttributeError:              # an address or None among them
+        return t(*[_ptr(i) for i in items])
 
 
 class Ctx:
