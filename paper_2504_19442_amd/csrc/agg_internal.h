@@ -23,7 +23,6 @@ struct GemmParams {
     long long lda, ldb, ldc;
     int M, N, K;
     int c_is_f32;
-    int c_vec_ok;         // C, the slice destinations and their leading dimensions allow 16-byte row-chunk stores
     // tile schedule (Section 3.7: rank-rotated order, local shard first)
     int tiles_m, tiles_n;
     int panel_m;          // m-tiles per panel (a panel = the tiles of one shard step)

@@ -632,7 +632,6 @@ int ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb, int b_layou
     p.N = N;
     p.K = K;
     p.c_is_f32 = c_dtype == AGG_F32;
-    p.c_vec_ok = aligned16(C) && ((long long)ldc * (p.c_is_f32 ? 4 : 2)) % 16 == 0;
     const int cfg = choose_tile(c, M, N, K);
     fill_schedule(c, p, cfg, Ms, c->rank * Ms);
     {
@@ -830,7 +829,6 @@ int gemm_rs_scatter(agg_ctx* c, int M, int N, int Kl, const void* A_local, int l
     p.N = N;
     p.K = Kl;
     p.c_is_f32 = 1;
-    p.c_vec_ok = N % 4 == 0;              // every destination is 16-byte aligned (checked above)
     p.epoch = c->epoch;
     p.epoch_ptr = c->device_epoch ? c->epoch_word : nullptr;
     p.err = c->err;
@@ -897,8 +895,7 @@ int gemm_rs(agg_ctx* c, int M, int N, int Kl, const void* A_local, int lda, cons
         p.N = N;
         p.K = Kl;
         p.c_is_f32 = 1;
-        p.c_vec_ok = N % 4 == 0;
-        p.epoch = c->epoch;
+            p.epoch = c->epoch;
         p.epoch_ptr = c->device_epoch ? c->epoch_word : nullptr;
         p.err = c->err;
         p.wait_ticks = wait_ticks(c);
@@ -1017,7 +1014,6 @@ static int grouped_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, con
     p.N = N;
     p.K = K;
     p.c_is_f32 = y_dtype == AGG_F32;
-    p.c_vec_ok = aligned16(Y) && ((long long)ldy * (p.c_is_f32 ? 4 : 2)) % 16 == 0;
     p.tiles_n = tiles_n;
     p.flags = gathered ? c->signals : nullptr;
     p.epoch = c->epoch;

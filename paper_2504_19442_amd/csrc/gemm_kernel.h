@@ -495,178 +495,155 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
                 constexpr int esz = sizeof(T);
                 typedef __attribute__((__vector_size__(4 * sizeof(T)))) T Tx4;
                 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
-                // whole 16-byte chunks of rows can be stored when the pointers allow it and the tile's valid width is
-                // a whole number of chunks (always so for a full tile)
-                const bool fast = p.c_vec_ok && (n_valid * esz) % 16 == 0;
-                const int cpr_valid = n_valid * esz / 16;
+                typedef unaligned_t<u32x4> u32x4_any;
+                const int cpr_valid = n_valid * esz / 16;                  // whole 16-byte chunks of a row, and what is left
+                const int tail = n_valid - cpr_valid * (16 / esz);
                 if constexpr (MF == 16 && esz == 4) {
-                    if (fast) {
-                        // fp32 output from 16x16 blocks: the four values a lane holds of a block are 16 consecutive
-                        // bytes of an output row, and the four lanes that share a row cover 64 consecutive bytes --
-                        // whole 64-byte sectors per store, so the values go from the registers straight to memory
-                        // (neighbouring column blocks, stored back to back, complete the 128-byte lines in L2)
-                        const int colq = 4 * (lane_e >> 4);
-                        static_for<C_::MB16>([&](auto i_c) {
-                            constexpr int i = decltype(i_c)::value;
-                            char* dst = row_ptr(row_w + i * 16 + (lane_e & 15), esz);
-                            if (dst) {
-                                T* q = (T*)dst + colq;
-                                auto store_row = [&](auto put) {
-                                    static_for<C_::NB16>([&](auto j_c) {
-                                        constexpr int j = decltype(j_c)::value;
-                                        constexpr int r0 = (i * C_::NB16 + j) * 4;
-                                        const float x0 = acc_read<r0>(), x1 = acc_read<r0 + 1>(), x2 = acc_read<r0 + 2>(),
-                                                    x3 = acc_read<r0 + 3>();
-                                        if (n_valid == BN || colq + j * 16 < n_valid)
-                                            put(Tx4{(T)x0, (T)x1, (T)x2, (T)x3}, (Tx4*)(q + j * 16));
-                                    });
-                                };
-                                // rows in place (MoE + ReduceScatter): the next kernel reads them, they may stay in the caches
-                                // (256x256 tiles at K = 192: 80 us with streaming stores, 70 without)
-                                if (GROUPED && !p.row_index) store_row([](Tx4 v, Tx4* at) { *at = v; });
-                                else store_row([](Tx4 v, Tx4* at) { __builtin_nontemporal_store(v, at); });
-                            }
-                        });
-                        return;
-                    }
-                }
-                if (fast) {
-                    // stage 32 rows x BN columns per pass in this wave's own part of LDS, then move whole
-                    // 16-byte chunks of rows to C: full cache lines per store instruction
-                    constexpr int pitch = BN * esz + 16;
-                    constexpr int cpr = BN * esz / 16;                // 16-byte chunks per row
-                    constexpr int iters = (32 * cpr + 63) / 64;       // chunk c = lane + 64*it: row c / cpr, chunk c % cpr
-                    unsigned char* stage = lds + wave * 32 * pitch;
-                    unsigned char* wr = MF == 16 ? stage + (lane_e & 15) * pitch + 4 * (lane_e >> 4) * esz
-                                                 : stage + (lane_e & 31) * pitch + 4 * (lane_e >> 5) * esz;
-                    const int r_lane = lane_e / cpr, cc_lane = lane_e - r_lane * cpr;
-                    static_for<MB>([&](auto i_c) {
+                    // fp32 output from 16x16 blocks: the four values a lane holds of a block are 16 consecutive
+                    // bytes of an output row, and the four lanes that share a row cover 64 consecutive bytes --
+                    // whole 64-byte sectors per store, so the values go from the registers straight to memory
+                    // (neighbouring column blocks, stored back to back, complete the 128-byte lines in L2)
+                    const int colq = 4 * (lane_e >> 4);
+                    static_for<C_::MB16>([&](auto i_c) {
                         constexpr int i = decltype(i_c)::value;
-                        if constexpr (MF == 16) {
-                            // 16x16 block (ib, j) of the pass: lane l holds row 16 ib + l%16, columns 16 j + 4 (l/16) + 0..3
-                            static_for<2 * C_::NB16>([&](auto bj_c) {
-                                constexpr int ib = decltype(bj_c)::value / C_::NB16, j = decltype(bj_c)::value % C_::NB16;
-                                constexpr int r0 = ((2 * i + ib) * C_::NB16 + j) * 4;
-                                const float x0 = acc_read<r0>(), x1 = acc_read<r0 + 1>(), x2 = acc_read<r0 + 2>(),
-                                            x3 = acc_read<r0 + 3>();
-                                *(Tx4*)(wr + ib * 16 * pitch + j * 16 * esz) = Tx4{(T)x0, (T)x1, (T)x2, (T)x3};
-                            });
-                        } else {
-                            static_for<NB * 4>([&](auto jq_c) {
-                                constexpr int j = decltype(jq_c)::value / 4, qd = decltype(jq_c)::value % 4;
-                                constexpr int r0 = (i * NB + j) * 16 + qd * 4;
-                                const float x0 = acc_read<r0>(), x1 = acc_read<r0 + 1>(), x2 = acc_read<r0 + 2>(),
-                                            x3 = acc_read<r0 + 3>();
-                                *(Tx4*)(wr + (j * 32 + qd * 8) * esz) = Tx4{(T)x0, (T)x1, (T)x2, (T)x3};
-                            });
-                        }
-                        // the same wave wrote and reads: LDS keeps a wave's operations in order.  GRP chunks at a
-                        // time: their LDS reads first (independent registers), then their stores.
-                        const int row0 = row_w + i * 32;
-                        // the 32 rows go to C, or (GEMM-RS) to the destination of their slice; a block that
-                        // straddles a slice boundary takes the per-row route
-                        const int rows_ok = min(32, st_hi - row0);
-                        const int rows_lo = max(0, st_lo - row0);          // rows of the block before the first stored one
-                        bool one_dst = true;          // all rows of the block have one destination matrix
-                        char* base = p.C ? (char*)p.C + ((long long)row0 * p.ldc + n0) * esz : nullptr;
-                        unsigned ld_bytes = (unsigned)(p.ldc * esz);
-                        if (!GROUPED && p.n_slices && rows_ok > 0) {
-                            const int w0 = row0 / p.slice_rows, w1 = (row0 + rows_ok - 1) / p.slice_rows;
-                            one_dst = w0 == w1;
-                            if (one_dst && p.slice_dst[w0]) {
-                                base = (char*)p.slice_dst[w0] + ((long long)(row0 - w0 * p.slice_rows) * p.ldc_slice + n0) * esz;
-                                ld_bytes = (unsigned)(p.ldc_slice * esz);
-                            }
-                        }
-                        constexpr int GRP = 7;
-                        int r = r_lane, cc = cc_lane;
-                        if constexpr ((32 * cpr) % 64 == 0) {
-                            // the common case -- all 32 rows inside the matrix (or segment) and bound for one
-                            // destination -- has no per-lane conditions at all: every lane moves `iters` chunks
-                            if (base && rows_ok >= 32 && rows_lo == 0 && n_valid == BN && one_dst) {
-                                static_for<(iters + GRP - 1) / GRP>([&](auto g_c) {
-                                    constexpr int it0 = decltype(g_c)::value * GRP;
-                                    constexpr int n = (iters - it0 < GRP) ? iters - it0 : GRP;
-                                    u32x4 val[n];
-                                    unsigned off[n];
-                                    static_for<n>([&](auto k_c) {
-                                        constexpr int k = decltype(k_c)::value;
-                                        off[k] = (unsigned)r * ld_bytes + (unsigned)cc * 16u;
-                                        val[k] = *(const u32x4*)(stage + r * pitch + cc * 16);
-                                        cc += 64 % cpr;
-                                        r += 64 / cpr;
-                                        const bool wrap = cc >= cpr;
-                                        cc = wrap ? cc - cpr : cc;
-                                        r = wrap ? r + 1 : r;
-                                    });
-                                    static_for<n>([&](auto k_c) {
-                                        constexpr int k = decltype(k_c)::value;
-                                        __builtin_nontemporal_store(val[k], (u32x4*)(base + off[k]));
-                                    });
-                                });
-                                return;     // next row block
-                            }
-                        }
-                        static_for<(iters + GRP - 1) / GRP>([&](auto g_c) {
-                            constexpr int it0 = decltype(g_c)::value * GRP;
-                            constexpr int n = (iters - it0 < GRP) ? iters - it0 : GRP;
-                            u32x4 val[n];
-                            int rs[n], ccs[n];
-                            static_for<n>([&](auto k_c) {
-                                constexpr int k = decltype(k_c)::value;
-                                rs[k] = r;
-                                ccs[k] = cc;
-                                if (r < 32) val[k] = *(const u32x4*)(stage + r * pitch + cc * 16);
-                                // next chunk of this lane: 64 chunks further on
-                                cc += 64 % cpr;
-                                r += 64 / cpr;
-                                if (cc >= cpr) { cc -= cpr; r += 1; }
-                            });
-                            static_for<n>([&](auto k_c) {
-                                constexpr int k = decltype(k_c)::value;
-                                if (one_dst) {
-                                    if (base && rs[k] < rows_ok && rs[k] >= rows_lo && ccs[k] < cpr_valid) {
-                                        // C is not read again by this kernel: streaming stores keep it from
-                                        // displacing the A and B lines that are
-                                        __builtin_nontemporal_store(val[k], (u32x4*)(base + (unsigned)rs[k] * ld_bytes + (unsigned)ccs[k] * 16u));
+                        char* dst = row_ptr(row_w + i * 16 + (lane_e & 15), esz);
+                        if (dst) {
+                            T* q = (T*)dst + colq;
+                            auto store_row = [&](auto put) {
+                                static_for<C_::NB16>([&](auto j_c) {
+                                    constexpr int j = decltype(j_c)::value;
+                                    constexpr int r0 = (i * C_::NB16 + j) * 4;
+                                    const float x0 = acc_read<r0>(), x1 = acc_read<r0 + 1>(), x2 = acc_read<r0 + 2>(),
+                                                x3 = acc_read<r0 + 3>();
+                                    if (n_valid == BN || colq + j * 16 + 4 <= n_valid) {
+                                        put(Tx4{(T)x0, (T)x1, (T)x2, (T)x3}, (unaligned_t<Tx4>*)(q + j * 16));
+                                    } else {                       // the ragged end of the row
+                                        if (colq + j * 16 < n_valid) q[j * 16] = (T)x0;
+                                        if (colq + j * 16 + 1 < n_valid) q[j * 16 + 1] = (T)x1;
+                                        if (colq + j * 16 + 2 < n_valid) q[j * 16 + 2] = (T)x2;
                                     }
-                                } else {
-                                    char* dst = (rs[k] < 32 && ccs[k] < cpr_valid) ? row_ptr(row0 + rs[k], esz) : nullptr;
-                                    if (dst) *(u32x4*)(dst + ccs[k] * 16) = val[k];
-                                }
-                            });
-                        });
+                                });
+                            };
+                            // rows in place (MoE + ReduceScatter): the next kernel reads them, they may stay in the caches
+                            // (256x256 tiles at K = 192: 80 us with streaming stores, 70 without)
+                            if (GROUPED && !p.row_index) store_row([](Tx4 v, unaligned_t<Tx4>* at) { *at = v; });
+                            else store_row([](Tx4 v, unaligned_t<Tx4>* at) { __builtin_nontemporal_store(v, at); });
+                        }
                     });
-                } else {
-                    // edge tiles and unaligned outputs: one element at a time, constant offsets from one row pointer
+                    return;
+                }
+                // stage 32 rows x BN columns per pass in this wave's own part of LDS, then move whole
+                // 16-byte chunks of rows to C: full cache lines per store instruction
+                constexpr int pitch = BN * esz + 16;
+                constexpr int cpr = BN * esz / 16;                // 16-byte chunks per row
+                constexpr int iters = (32 * cpr + 63) / 64;       // chunk c = lane + 64*it: row c / cpr, chunk c % cpr
+                unsigned char* stage = lds + wave * 32 * pitch;
+                unsigned char* wr = MF == 16 ? stage + (lane_e & 15) * pitch + 4 * (lane_e >> 4) * esz
+                                             : stage + (lane_e & 31) * pitch + 4 * (lane_e >> 5) * esz;
+                const int r_lane = lane_e / cpr, cc_lane = lane_e - r_lane * cpr;
+                static_for<MB>([&](auto i_c) {
+                    constexpr int i = decltype(i_c)::value;
                     if constexpr (MF == 16) {
-                        static_for<C_::MB16>([&](auto i_c) {
-                            constexpr int i = decltype(i_c)::value;
-                            char* dst = row_ptr(row_w + i * 16 + (lane_e & 15), esz);
-                            const int col0 = n0 + 4 * (lane_e >> 4);
-                            T* q = (T*)dst + 4 * (lane_e >> 4);
-                            static_for<C_::NB16 * 4>([&](auto jv_c) {
-                                constexpr int j = decltype(jv_c)::value / 4, v = decltype(jv_c)::value % 4;
-                                constexpr int off = j * 16 + v;
-                                const float x = acc_read<(i * C_::NB16 + j) * 4 + v>();
-                                if (dst && col0 + off < p.N) q[off] = (T)x;
-                            });
+                        // 16x16 block (ib, j) of the pass: lane l holds row 16 ib + l%16, columns 16 j + 4 (l/16) + 0..3
+                        static_for<2 * C_::NB16>([&](auto bj_c) {
+                            constexpr int ib = decltype(bj_c)::value / C_::NB16, j = decltype(bj_c)::value % C_::NB16;
+                            constexpr int r0 = ((2 * i + ib) * C_::NB16 + j) * 4;
+                            const float x0 = acc_read<r0>(), x1 = acc_read<r0 + 1>(), x2 = acc_read<r0 + 2>(),
+                                        x3 = acc_read<r0 + 3>();
+                            *(Tx4*)(wr + ib * 16 * pitch + j * 16 * esz) = Tx4{(T)x0, (T)x1, (T)x2, (T)x3};
                         });
                     } else {
-                    static_for<MB>([&](auto i_c) {
-                        constexpr int i = decltype(i_c)::value;
-                        char* dst = row_ptr(row_w + i * 32 + (lane_e & 31), esz);
-                        const int col0 = n0 + 4 * (lane_e >> 5);
-                        T* q = (T*)dst + 4 * (lane_e >> 5);
-                        static_for<NB * 16>([&](auto jv_c) {
-                            constexpr int j = decltype(jv_c)::value / 16, v = decltype(jv_c)::value % 16;
-                            constexpr int off = j * 32 + 8 * (v >> 2) + (v & 3);
-                            const float x = acc_read<(i * NB + j) * 16 + v>();
-                            if (dst && col0 + off < p.N) q[off] = (T)x;
+                        static_for<NB * 4>([&](auto jq_c) {
+                            constexpr int j = decltype(jq_c)::value / 4, qd = decltype(jq_c)::value % 4;
+                            constexpr int r0 = (i * NB + j) * 16 + qd * 4;
+                            const float x0 = acc_read<r0>(), x1 = acc_read<r0 + 1>(), x2 = acc_read<r0 + 2>(),
+                                        x3 = acc_read<r0 + 3>();
+                            *(Tx4*)(wr + (j * 32 + qd * 8) * esz) = Tx4{(T)x0, (T)x1, (T)x2, (T)x3};
+                        });
+                    }
+                    // the same wave wrote and reads: LDS keeps a wave's operations in order.  GRP chunks at a
+                    // time: their LDS reads first (independent registers), then their stores.
+                    const int row0 = row_w + i * 32;
+                    // the 32 rows go to C, or (GEMM-RS) to the destination of their slice; a block that
+                    // straddles a slice boundary takes the per-row route
+                    const int rows_ok = min(32, st_hi - row0);
+                    const int rows_lo = max(0, st_lo - row0);          // rows of the block before the first stored one
+                    bool one_dst = true;          // all rows of the block have one destination matrix
+                    char* base = p.C ? (char*)p.C + ((long long)row0 * p.ldc + n0) * esz : nullptr;
+                    unsigned ld_bytes = (unsigned)(p.ldc * esz);
+                    if (!GROUPED && p.n_slices && rows_ok > 0) {
+                        const int w0 = row0 / p.slice_rows, w1 = (row0 + rows_ok - 1) / p.slice_rows;
+                        one_dst = w0 == w1;
+                        if (one_dst && p.slice_dst[w0]) {
+                            base = (char*)p.slice_dst[w0] + ((long long)(row0 - w0 * p.slice_rows) * p.ldc_slice + n0) * esz;
+                            ld_bytes = (unsigned)(p.ldc_slice * esz);
+                        }
+                    }
+                    constexpr int GRP = 7;
+                    int r = r_lane, cc = cc_lane;
+                    if constexpr ((32 * cpr) % 64 == 0) {
+                        // the common case -- all 32 rows inside the matrix (or segment) and bound for one
+                        // destination -- has no per-lane conditions at all: every lane moves `iters` chunks
+                        if (base && rows_ok >= 32 && rows_lo == 0 && n_valid == BN && one_dst) {
+                            static_for<(iters + GRP - 1) / GRP>([&](auto g_c) {
+                                constexpr int it0 = decltype(g_c)::value * GRP;
+                                constexpr int n = (iters - it0 < GRP) ? iters - it0 : GRP;
+                                u32x4 val[n];
+                                unsigned off[n];
+                                static_for<n>([&](auto k_c) {
+                                    constexpr int k = decltype(k_c)::value;
+                                    off[k] = (unsigned)r * ld_bytes + (unsigned)cc * 16u;
+                                    val[k] = *(const u32x4*)(stage + r * pitch + cc * 16);
+                                    cc += 64 % cpr;
+                                    r += 64 / cpr;
+                                    const bool wrap = cc >= cpr;
+                                    cc = wrap ? cc - cpr : cc;
+                                    r = wrap ? r + 1 : r;
+                                });
+                                static_for<n>([&](auto k_c) {
+                                    constexpr int k = decltype(k_c)::value;
+                                    __builtin_nontemporal_store(val[k], (u32x4_any*)(base + off[k]));
+                                });
+                            });
+                            return;     // next row block
+                        }
+                    }
+                    static_for<(iters + GRP - 1) / GRP>([&](auto g_c) {
+                        constexpr int it0 = decltype(g_c)::value * GRP;
+                        constexpr int n = (iters - it0 < GRP) ? iters - it0 : GRP;
+                        u32x4 val[n];
+                        int rs[n], ccs[n];
+                        static_for<n>([&](auto k_c) {
+                            constexpr int k = decltype(k_c)::value;
+                            rs[k] = r;
+                            ccs[k] = cc;
+                            if (r < 32) val[k] = *(const u32x4*)(stage + r * pitch + cc * 16);
+                            // next chunk of this lane: 64 chunks further on
+                            cc += 64 % cpr;
+                            r += 64 / cpr;
+                            if (cc >= cpr) { cc -= cpr; r += 1; }
+                        });
+                        static_for<n>([&](auto k_c) {
+                            constexpr int k = decltype(k_c)::value;
+                            if (one_dst) {
+                                if (base && rs[k] < rows_ok && rs[k] >= rows_lo && ccs[k] < cpr_valid) {
+                                    // C is not read again by this kernel: streaming stores keep it from
+                                    // displacing the A and B lines that are
+                                    __builtin_nontemporal_store(val[k], (u32x4_any*)(base + (unsigned)rs[k] * ld_bytes + (unsigned)ccs[k] * 16u));
+                                }
+                            } else {
+                                char* dst = (rs[k] < 32 && ccs[k] < cpr_valid) ? row_ptr(row0 + rs[k], esz) : nullptr;
+                                if (dst) *(u32x4_any*)(dst + ccs[k] * 16) = val[k];
+                            }
                         });
                     });
+                    // the elements behind the last whole chunk of a row (a ragged last column block)
+                    for (int k = lane_e; k < 32 * tail; k += 64) {
+                        const int tr = k / tail, e = cpr_valid * (16 / esz) + k - tr * tail;
+                        char* dst = row_ptr(row0 + tr, esz);
+                        if (dst) ((T*)dst)[e] = *(const T*)(stage + tr * pitch + e * esz);
                     }
-                }
+                });
             };
             if (p.c_is_f32) epilogue(float{}); else epilogue(__bf16{});
         }

@@ -45,7 +45,7 @@ struct KsParams {
     const int* epoch_ptr;
     int* err;
     long long wait_ticks;
-    int epoch, n_flags, c_is_f32, c_vec_ok;
+    int epoch, n_flags, c_is_f32;
     // KS_GROUPED
     const int* row_index;
     const MoeTile* tile_tab;
@@ -148,26 +148,19 @@ __device__ __forceinline__ void ks_store(const KsParams& p, const SL& sl, const 
             }
             return (T*)p.C + (long long)row * p.ldc + w.n0;
         };
-        if (p.c_vec_ok && n_valid % 4 == 0) {
-            for (int idx = tid; idx < BM * BN / 4; idx += THREADS) {
-                const int r = idx / (BN / 4), c = idx % (BN / 4) * 4;
-                T* dst = row_at(r);
-                if (!dst || c >= n_valid) continue;
-                f32x4_ v = *(const f32x4_*)(red + r * PITCH + c);
+        for (int idx = tid; idx < BM * BN / 4; idx += THREADS) {
+            const int r = idx / (BN / 4), c = idx % (BN / 4) * 4;
+            T* dst = row_at(r);
+            if (!dst || c >= n_valid) continue;
+            f32x4_ v = *(const f32x4_*)(red + r * PITCH + c);
 #pragma unroll
-                for (int k = 1; k < NP; ++k) v = v + *(const f32x4_*)(red + (k * BM + r) * PITCH + c);
-                *(Tx4*)(dst + c) = Tx4{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
-            }
-        } else {
-            // unaligned rows or a ragged last column block: one element per lane, neighbours side by side
-            for (int idx = tid; idx < BM * BN; idx += THREADS) {
-                const int r = idx / BN, c = idx % BN;
-                T* dst = row_at(r);
-                if (!dst || c >= n_valid) continue;
-                float v = red[r * PITCH + c];
-#pragma unroll
-                for (int k = 1; k < NP; ++k) v += red[(k * BM + r) * PITCH + c];
-                dst[c] = (T)v;
+            for (int k = 1; k < NP; ++k) v = v + *(const f32x4_*)(red + (k * BM + r) * PITCH + c);
+            if (c + 4 <= n_valid) {
+                *(unaligned_t<Tx4>*)(dst + c) = Tx4{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
+            } else {                           // the ragged end of the row
+                dst[c] = (T)v[0];
+                if (c + 1 < n_valid) dst[c + 1] = (T)v[1];
+                if (c + 2 < n_valid) dst[c + 2] = (T)v[2];
             }
         }
     };
@@ -522,7 +515,7 @@ static hipError_t launch_ks(const GemmParams& g, bool grouped, int grid, hipStre
     p.flag_mul = div_mul(g.rows_per_flag);
     p.local_lo = g.local_lo; p.local_hi = g.local_hi;
     p.flags = g.flags; p.epoch_ptr = g.epoch_ptr; p.err = g.err; p.wait_ticks = g.wait_ticks;
-    p.epoch = g.epoch; p.n_flags = g.n_flags; p.c_is_f32 = g.c_is_f32; p.c_vec_ok = g.c_vec_ok;
+    p.epoch = g.epoch; p.n_flags = g.n_flags; p.c_is_f32 = g.c_is_f32;
     if (grouped) {
         p.row_index = g.row_index; p.tile_tab = g.tile_tab; p.n_tiles_dev = g.n_tiles_dev;
         p.b_group_stride = g.b_group_stride; p.a_bytes = g.a_bytes;

@@ -25,6 +25,12 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned bytes
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
 
+// The vector type V at any even address.  Rows of C start wherever its leading dimension puts them; a store through this
+// type is one instruction all the same (the hardware allows its address to be unaligned), and rows of any width are
+// stored 16 bytes at a time (one element at a time, 4000 x 3267 x 1024 in bf16 took 51 us; 32 like this, 3264 columns 29).
+template <class V> struct Unaligned { typedef V type __attribute__((aligned(2))); };
+template <class V> using unaligned_t = typename Unaligned<V>::type;
+
 // s_waitcnt immediate that waits only for vmcnt <= n (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt_hi[15:14]).
 __host__ __device__ constexpr int vmcnt_imm(int n) { return (n & 0xF) | (0x7 << 4) | (0xF << 8) | ((n >> 4) << 14); }
 

@@ -220,3 +220,46 @@ def test_gemm_rs_own_slice_alone_is_the_same_bits_as_with_all():
             assert np.array_equal(got[0], got[1]), (W, Ms)
         finally:
             ctx.free()
+
+
+@pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3, 4, 5, 6, 7])
+def test_odd_row_widths_every_tile(tile):
+    """Rows of C that start at any element: widths that leave 1, 3 and 6 columns behind the last 16 bytes, padded rows whose padding
+    stays untouched, and slices whose borders lie inside a block of 32 rows."""
+    for W, Ms, K, N, pad in ((2, 150, 128, 331, 0), (1, 270, 64, 517, 1), (3, 45, 192, 262, 3)):
+        sh = wl.AgGemmShape(f"ag_odd_{N}", 27, W, Ms, K, N)
+        inp = wl.make_ag_gemm(sh, a_dist=("int", 2), b_dist=("int", 2))
+        want = oracle.ag_gemm(inp.shards, inp.B_kn, 0)
+        run = AgGemmRun(inp, 0)
+        try:
+            run.ctx.set_tile_config(tile)
+            agg.signal_reset(run.ctx)
+            agg.ag_producer_emulate(run.ctx, run.remote, None, agg.PRODUCER_KERNEL, 0, run.cons)
+            for dtype, tdt in ((agg.F32, torch.float32), (agg.BF16, torch.bfloat16)):
+                C = torch.full((sh.M, N + pad), 7.0, device="cuda", dtype=tdt)
+                torch.cuda.synchronize()
+                agg.ag_gemm(run.ctx, sh.M, N, K, run.B_nk, K, agg.B_NK, C, N + pad, dtype, run.cons)
+                torch.cuda.synchronize()
+                got = C.float().cpu().numpy()
+                ref = want if dtype == agg.F32 else wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(want.astype(np.float32)))
+                assert np.array_equal(got[:, :N], ref.astype(np.float32)), (W, Ms, N, dtype)
+                assert (got[:, N:] == 7.0).all()
+        finally:
+            run.close()
+    # the product cut into slices of 44 rows, odd width, every slice at a destination of its own
+    W, Ms, K, N = 4, 44, 128, 331
+    inp = wl.make_gemm_rs(wl.GemmRsShape("rs_odd", 28, W, W * Ms, K, N), a_dist=("int", 2), b_dist=("int", 2))
+    prod = wl.bf16_bits_to_f32(inp.A_loc).astype(np.float64) @ wl.bf16_bits_to_f32(inp.B_kn).astype(np.float64)
+    A, B = dev_bf16(inp.A_loc), dev_bf16(np.ascontiguousarray(inp.B_kn.T))
+    ctx = agg.symm_alloc(W, 0, 16, W)
+    try:
+        ctx.set_tile_config(tile)
+        _, cs = ctx.streams()
+        dst = [torch.full((Ms, N), float("nan"), device="cuda") for _ in range(W)]
+        torch.cuda.synchronize()
+        agg.gemm_rs_scatter(ctx, W * Ms, N, K, A, K, B, K, agg.B_NK, dst, None, None, 1, cs)
+        torch.cuda.synchronize()
+        got = torch.cat(dst).cpu().numpy().astype(np.float64)
+        assert np.array_equal(got, prod)
+    finally:
+        ctx.free()
