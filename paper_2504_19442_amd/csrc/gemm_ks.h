@@ -167,6 +167,14 @@ __device__ __forceinline__ void ks_store(const KsParams& p, const SL& sl, const 
     if (p.c_is_f32) store(float{}); else store(__bf16{});
 }
 
+// Asks for all of the launch's arguments at once: fetched where they are used they are two trips to memory in a row (0.2 us of
+// 4.5 to 19 us kernels).
+__device__ __forceinline__ void ks_fetch_params(const KsParams& p)
+{
+    asm volatile("" ::"s"(p.A), "s"(p.A_local), "s"(p.B), "s"(p.C), "s"(p.lda), "s"(p.KC), "s"(p.tiles_m), "s"(p.tiles_m_mul), "s"(p.flags),
+                 "s"(p.err), "s"(p.n_flags), "s"(p.wait_ticks), "s"(p.local_lo));
+}
+
 // Private rings.
 template <int BM, int BN, int S, int NST, KsKind KIND>
 __global__ __launch_bounds__(S * 64)
@@ -178,6 +186,7 @@ void gemm_ks_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
     constexpr bool GROUPED = KIND == KS_GROUPED;
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     __shared__ int s_gave_up;
+    ks_fetch_params(p);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the LDS layout of a stage is that of the large kernel: rows of 128 bytes, 16-byte chunk c of row r in slot c ^ ((r >> 1) & 7)
@@ -345,6 +354,7 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
     constexpr bool GROUPED = KIND == KS_GROUPED;
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     __shared__ int s_gave_up;
+    ks_fetch_params(p);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kh = wave & 1, nw = wave >> 1;
