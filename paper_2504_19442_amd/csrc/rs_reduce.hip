@@ -2,7 +2,7 @@
 // that order starting from +0 whatever order the slots arrive in, so the result is bit-identical
 // across arrival orders.  Each workgroup waits (acquire) for slot w's signal before its first read of
 // slot w.  The kernel is bandwidth bound: W reads and one write per element, 16 bytes per lane per
-// access; ordinary loads (streaming-hinted loads measured 10 % slower here), streaming stores.
+// access; streaming stores.
 // What is left beside the bytes is the start: the signals are looked at by the lanes of one wave side by side (one after
 // the other by one thread, each a trip to memory, cost 4 us per workgroup), and where all slots are there the first
 // block is loaded like every other.  Eight slots of 1024 x 8192 (302 MB, in no cache) 64.7 -> 59.6 us, of 8 x 8192 5.2 -> 3.6;
@@ -59,13 +59,15 @@ __device__ inline void store_out(const ReduceArgs& a, long long i, f32x4 v)
 
 // WT > 0: the world size is the compile-time constant WT (loops over slots unroll, all loads of a block are in
 // flight together); WT == 0: any world size.
-template <int WT, int RU>   // RU = float4 per lane per slot and block
+// NT: the slots are read past the caches (launch_reduce).
+template <int WT, int RU, bool NT>   // RU = float4 per lane per slot and block
 __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a)
 {
     const int tid = threadIdx.x;
     const int W = WT > 0 ? WT : a.W;
     const int epoch = a.epoch_ptr ? __hip_atomic_load(a.epoch_ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : a.epoch;
     const long long stride = (long long)gridDim.x * 256;
+    auto load = [](const f32x4* p) { return NT ? __builtin_nontemporal_load(p) : *p; };
     __shared__ int s_upto;
     int seen = 0;                      // slots 0..seen-1 are known to have arrived (uniform over the workgroup)
     // Wave 0 looks at all slots' signals at once (lane w at slot w's) until slots 0 .. want - 1 have arrived; one acquire (an
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a)
 #pragma unroll
                     for (int u = 0; u < RU; ++u) {
                         const long long i = base + u * stride;
-                        v[w][u] = (i < a.n_vec4) ? ((const f32x4*)a.slot[w])[i]
+                        v[w][u] = (i < a.n_vec4) ? load((const f32x4*)a.slot[w] + i)
                                                  : f32x4{0.f, 0.f, 0.f, 0.f};
                     }
 #pragma unroll
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a)
 #pragma unroll
                         for (int u = 0; u < RU; ++u) {
                             const long long i = base + u * stride;
-                            v[k][u] = (i < a.n_vec4) ? s[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+                            v[k][u] = (i < a.n_vec4) ? load(s + i) : f32x4{0.f, 0.f, 0.f, 0.f};
                         }
                     }
 #pragma unroll
@@ -181,20 +183,31 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a)
 
 // beside_gemm: the launch is meant to run on the same compute units as the GEMM kernel, whose waves leave 64 vector
 // registers per SIMD lane free: only kernels of at most 64 registers per lane fit there (a bigger one starts only where
-// a GEMM workgroup has finished).  All variants but <8, 2> are that small.
+// a GEMM workgroup has finished).  All variants but <8, 2, ..> are that small.
+template <bool NT>
+static void launch_reduce_nt(const ReduceArgs& a, int n_workgroups, hipStream_t stream, bool beside_gemm)
+{
+    const dim3 grid(n_workgroups), wg(256);
+    switch (a.W) {
+        case 8:
+            if (beside_gemm) hipLaunchKernelGGL((reduce_kernel<8, 1, NT>), grid, wg, 0, stream, a);
+            else hipLaunchKernelGGL((reduce_kernel<8, 2, NT>), grid, wg, 0, stream, a);
+            break;
+        case 4: hipLaunchKernelGGL((reduce_kernel<4, 2, NT>), grid, wg, 0, stream, a); break;
+        case 3: hipLaunchKernelGGL((reduce_kernel<3, 2, NT>), grid, wg, 0, stream, a); break;
+        case 2: hipLaunchKernelGGL((reduce_kernel<2, 4, NT>), grid, wg, 0, stream, a); break;
+        default: hipLaunchKernelGGL((reduce_kernel<0, 2, NT>), grid, wg, 0, stream, a); break;
+    }
+}
+
+// Slots that together exceed the memory-side cache (256 MB) come from HBM whatever the loads ask for, and loads with the
+// streaming hint run faster then: eight slots of 1024 x 8192 (268 MB) that were not read before 59.7 us, with the hint 54.6
+// (in a loop over one and the same slots, a part of which the cache then keeps, it is the other way round: 49 and 53).
+// Below, ordinary loads: 67 MB in two slots 25.1 and 24.4, 134 MB in four 34.6 and 34.5, 33 MB in four 12.0 and 12.8.
 hipError_t launch_reduce(const ReduceArgs& a, int n_workgroups, hipStream_t stream, bool beside_gemm)
 {
-    if (a.W == 8 && beside_gemm) {
-        hipLaunchKernelGGL((reduce_kernel<8, 1>), dim3(n_workgroups), dim3(256), 0, stream, a);
-        return hipGetLastError();
-    }
-    switch (a.W) {
-        case 8: hipLaunchKernelGGL((reduce_kernel<8, 2>), dim3(n_workgroups), dim3(256), 0, stream, a); break;
-        case 3: hipLaunchKernelGGL((reduce_kernel<3, 2>), dim3(n_workgroups), dim3(256), 0, stream, a); break;
-        case 4: hipLaunchKernelGGL((reduce_kernel<4, 2>), dim3(n_workgroups), dim3(256), 0, stream, a); break;
-        case 2: hipLaunchKernelGGL((reduce_kernel<2, 4>), dim3(n_workgroups), dim3(256), 0, stream, a); break;
-        default: hipLaunchKernelGGL((reduce_kernel<0, 2>), dim3(n_workgroups), dim3(256), 0, stream, a); break;
-    }
+    if (a.n_vec4 * 16 * a.W > (256ll << 20) - 1) launch_reduce_nt<true>(a, n_workgroups, stream, beside_gemm);
+    else launch_reduce_nt<false>(a, n_workgroups, stream, beside_gemm);
     return hipGetLastError();
 }
 

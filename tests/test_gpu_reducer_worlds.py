@@ -43,3 +43,28 @@ def test_reducer_world_sizes_bit_exact(W, Ms, N):
             assert np.array_equal(R.cpu().numpy().view(np.uint32), want.view(np.uint32)), order
     finally:
         ctx.free()
+
+
+@pytest.mark.parametrize("W,Ms,N,ldr", [(8, 1024, 8192, 8192), (16, 1024, 4100, 4104), (3, 2048, 11000, 11000), (2, 4096, 8188, 8188)])
+def test_reducer_slots_beyond_the_memory_side_cache_bit_exact(W, Ms, N, ldr):
+    # 256 MB of slots and more (the last: just below); the reference adds the slots in order, one fp32 rounding each
+    g = torch.Generator(device="cuda").manual_seed(7400 + W)
+    slots = [torch.randn((Ms, N), device="cuda", generator=g) for _ in range(W)]
+    want = torch.zeros((Ms, N), device="cuda")
+    for s in slots:
+        want = want + s
+    ctx = agg.symm_alloc(W, 0, 16, W)
+    try:
+        _, cs = ctx.streams()
+        agg.signal_reset(ctx)
+        for w in range(W):
+            agg.signal_set(ctx, w, cs)
+        R = torch.full((Ms, ldr), 3.0, device="cuda")
+        torch.cuda.synchronize()
+        agg.rs_reduce(ctx, Ms, N, slots, R, ldr, agg.F32, 0, cs)
+        torch.cuda.synchronize()
+        assert agg.agg_status(ctx) == agg.OK
+        assert torch.equal(R[:, :N].contiguous().view(torch.int32), want.view(torch.int32))
+        assert bool((R[:, N:] == 3.0).all())
+    finally:
+        ctx.free()
