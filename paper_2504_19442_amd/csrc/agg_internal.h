@@ -21,6 +21,7 @@ struct GemmParams {
     const uint16_t* B;
     void* C;              // every row whose slice has no destination of its own
     long long lda, ldb, ldc;
+    long long b_total_bytes;   // all of B (all groups' matrices)
     int M, N, K;
     int c_is_f32;
     // tile schedule (Section 3.7: rank-rotated order, local shard first)

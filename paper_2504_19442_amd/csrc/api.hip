@@ -625,6 +625,7 @@ int ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb, int b_layou
     p.local_lo = c->rank * Ms;
     p.local_hi = p.local_lo + Ms;
     if ((rc = resolve_b(c, B, ldb, b_layout, N, K, (hipStream_t)consumer_stream, &p.B, &p.ldb)) != AGG_OK) return rc;
+    p.b_total_bytes = p.ldb * N * 2;
     p.C = C;
     p.lda = K;
     p.ldc = ldc;
@@ -822,6 +823,7 @@ int gemm_rs_scatter(agg_ctx* c, int M, int N, int Kl, const void* A_local, int l
     GemmParams p{};
     p.A = (const uint16_t*)A_local;
     if ((rc = resolve_b(c, B_local, ldb, b_layout, N, Kl, (hipStream_t)gemm_stream, &p.B, &p.ldb)) != AGG_OK) return rc;
+    p.b_total_bytes = p.ldb * N * 2;
     p.C = P_other;
     p.lda = lda;
     p.ldc = N;
@@ -888,6 +890,7 @@ int gemm_rs(agg_ctx* c, int M, int N, int Kl, const void* A_local, int lda, cons
         GemmParams p{};
         p.A = (const uint16_t*)A_local + (long long)c->rank * Ms * lda;
         if ((rc = resolve_b(c, B_local, ldb, b_layout, N, Kl, (hipStream_t)gemm_stream, &p.B, &p.ldb)) != AGG_OK) return rc;
+        p.b_total_bytes = p.ldb * N * 2;
         p.C = (void*)slots[c->rank];
         p.lda = lda;
         p.ldc = N;
@@ -1026,6 +1029,7 @@ static int grouped_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, con
     p.tile_tab = tab;
     p.n_tiles_dev = r.n_tiles_dev;
     p.b_group_stride = (long long)N * K;
+    p.b_total_bytes = (long long)E * N * K * 2;
     p.a_bytes = (unsigned)a_bytes;
     const int grid = gemm_grid(c, cfg, cap);
     return hip_fail(launch_gemm_grouped(p, cfg, grid, stream));

@@ -263,3 +263,37 @@ def test_odd_row_widths_every_tile(tile):
         assert np.array_equal(got, prod)
     finally:
         ctx.free()
+
+
+@pytest.mark.parametrize("W,tpr,K,N,E,topk", [(2, 8, 2048, 1024, 64, 2), (8, 256, 4096, 1028, 32, 1)])
+def test_moe_weights_beyond_the_memory_side_cache_exact(W, tpr, K, N, E, topk):
+    # 268 MB of weights, a row or two and 64 rows per expert; small integers, so that fp32 sums are exact in any order
+    T = W * tpr
+    g = torch.Generator(device="cuda").manual_seed(29)
+    shards = [torch.randint(-2, 3, (tpr, K), device="cuda", generator=g).to(torch.bfloat16) for _ in range(W)]
+    B = torch.randint(-2, 3, (E, N, K), device="cuda", generator=g, dtype=torch.int8).to(torch.bfloat16)
+    ids = torch.rand((T, E), device="cuda", generator=g).argsort(dim=1)[:, :topk].to(torch.int32).contiguous()
+    flat = ids.reshape(-1).long()
+    order = torch.argsort(flat, stable=True)
+    X = torch.cat(shards)[order // topk].float()
+    want = torch.empty((T * topk, N), device="cuda")
+    for e in range(E):
+        rows = (flat[order] == e).nonzero().reshape(-1)
+        if rows.numel():
+            want[rows] = X[rows] @ B[e].float().t()
+    tok, seg = torch.empty(T * topk, device="cuda", dtype=torch.int32), torch.empty(E + 1, device="cuda", dtype=torch.int32)
+    ctx = agg.symm_alloc(W, 0, tpr * K * 2, W)
+    try:
+        agg.agg_reserve_moe(ctx, T, topk, E, N)
+        ps, cs = ctx.streams()
+        Y = torch.full((T * topk, N), float("nan"), device="cuda")
+        agg.signal_reset(ctx)
+        torch.cuda.synchronize()
+        agg.ag_producer_emulate(ctx, shards, None, agg.PRODUCER_KERNEL, 0, ps)
+        agg.ag_moe_gemm(ctx, T, topk, E, N, K, ids, B, tok, seg, Y, N, agg.F32, cs)
+        torch.cuda.synchronize()
+        assert agg.agg_status(ctx) == agg.OK
+        assert torch.equal(tok.long(), order // topk)
+        assert torch.equal(Y, want)
+    finally:
+        ctx.free()
