@@ -699,8 +699,8 @@ static int reduce_impl(agg_ctx* c, int Ms, int N, const float* const* slots, voi
     int nwg = n_workgroups;
     if (nwg == 0) {
         // persistent: two workgroups per CU, each walking many blocks (one acquire per workgroup, not per block).  Measured
-        // with slots that are in no cache (us at 1 / 1.25 / 1.5 / 2 / 3 / 4 per CU): eight slots of 1024 x 8192 59.7 /
-        // 64.7 / 61.0 / 59.6 / 62.9 / 67.1 (5.1 TB/s at two), two slots 32.8 / 30.0 / 27.6 / 25.2 / 25.0 / 27.2.
+        // with slots that are in no cache (us at 1 / 1.25 / 1.5 / 2 / 3 / 4 per CU): eight slots of 1024 x 8192 59.4 /
+        // 62.0 / 57.9 / 54.6 / 59.0 / 64.1 (5.5 TB/s at two), two slots 32.8 / 30.0 / 27.6 / 25.2 / 25.0 / 27.2.
         const long long need = (a.n_vec4 + 255) / 256;
         // Beside the GEMM a CU has room for one reducer workgroup only (one 64-register wave per SIMD).
         const long long want = beside_gemm ? (long long)c->num_cus : (long long)c->num_cus * 2;

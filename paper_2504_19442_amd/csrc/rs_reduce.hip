@@ -5,7 +5,8 @@
 // access; streaming stores.
 // What is left beside the bytes is the start: the signals are looked at by the lanes of one wave side by side (one after
 // the other by one thread, each a trip to memory, cost 4 us per workgroup), and where all slots are there the first
-// block is loaded like every other.  Eight slots of 1024 x 8192 (302 MB, in no cache) 64.7 -> 59.6 us, of 8 x 8192 5.2 -> 3.6;
+// block is loaded like every other.  Eight slots of 1024 x 8192 (302 MB, in no cache) 64.7 -> 59.6 us (54.6 with the loads
+// launch_reduce picks), of 8 x 8192 5.2 -> 3.6;
 // six slots of 512 x 4096 20.6 -> 15.6 and sixteen of 256 x 4096 29.8 -> 18.1 (four slots' loads in flight together
 // where no kernel is unrolled for the world size).
 #include "agg_internal.h"
