@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/agg.h"
+#include "moe_table.h"
 
 namespace agg {
 
@@ -62,6 +63,7 @@ struct GemmParams {
 struct MoeTile {
     int expert, m0, m_end, n_tile, f_lo, f_hi, st_lo, st_hi;
 };
+static_assert(sizeof(MoeTile) == kMoeTileBytes, "tables are sized in entries of this many bytes");
 
 struct MoeRouteArgs {
     const int* topk_ids;          // [P] = [Ttok * topk]
@@ -79,12 +81,6 @@ struct MoeRouteArgs {
     long long wait_ticks;         // bound of the wait for the other experts' counts, in wall-clock ticks
     int* err;                     // device word: set to 1 when that wait is given up
 };
-// Control block of the MoE routing: the tile count (int, read by the grouped GEMM), the number of finished routing
-// calls, the ticket counter, and two tagged counts per expert (its pairs; those of them that get tiles).
-constexpr int kMoeMaxExperts = 4096;
-constexpr size_t kMoeCtrlCall = 8, kMoeCtrlTicket = 16, kMoeCtrlCounts = 256;
-constexpr size_t kMoeCtrlKept = kMoeCtrlCounts + (size_t)kMoeMaxExperts * 8;
-constexpr size_t kMoeCtrlBytes = kMoeCtrlKept + (size_t)kMoeMaxExperts * 8;
 hipError_t launch_moe_route(const MoeRouteArgs& a, hipStream_t stream);
 
 // Top-k reduction of MoE + ReduceScatter: Z[t, :] = sum_s gate[t, s] * Y[pair_pos[t * topk + s], :]
@@ -203,11 +199,7 @@ struct agg_ctx {
     double link_GBps;    // pace of a link of the full-mesh producer (0 = not paced)
     hipStream_t producer_stream, consumer_stream;
     // grouped GEMM workspace (sized by agg_reserve_moe; no other call allocates it)
-    int* moe_ws;          // the MoE routing's control block (kMoeCtrlBytes; its first word is the tile count of the launch under way)
-    agg::MoeTile* moe_tab;        // the table in use: behind the control block, or moe_tab_large
-    agg::MoeTile* moe_tab_large;  // a table larger than that
-    int moe_tab_cap;      // entries the table holds ...
-    int moe_tab_base;     // ... and how many agg_reserve_moe was asked for (at least kStaticTabEntries are there)
+    agg::MoeWorkspace moe;
     uint16_t* b_nk;       // [N][K] copy of a B that was given as [K][N] (sized by agg_reserve_b_kn)
     size_t b_nk_elems;
     hipEvent_t b_nk_free;     // recorded behind the last GEMM that read b_nk, on b_nk_stream

@@ -146,9 +146,6 @@ int b_kn_launched(agg_ctx* c, int b_layout, hipStream_t stream)
 // ---- device memory that no call allocates: a fixed array in the library's image, one copy per GPU, used by
 // ag_moe_gemm_static for the MoE routing's control block and the grouped GEMM's tile table.  Host code never uses the array's name as an
 // address: the device address is looked up once per context (symm_alloc, with the context's device current).
-constexpr size_t kStaticTabOffset = kMoeCtrlBytes;         // the routing's control block first, the table after it
-constexpr size_t kStaticTabEntries = 32760;
-constexpr size_t kStaticScratchBytes = kStaticTabOffset + kStaticTabEntries * sizeof(MoeTile);   // 1088 KiB
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 // Upper bound of the grouped GEMM's tile table for one tile shape: sum over experts of ceil(rows / bm) <= P / bm + E, times
@@ -213,7 +210,7 @@ int choose_tile_grouped(const agg_ctx* c, long long rows, int E, int N, int K, b
     double best_cost = 1e300;
     for (const TileCost& k : cand) {
         const TileShape t = tile_shape(k.cfg);
-        if (moe_table_entries(P, E, N, t) > (k.cfg >= TILE_CONFIGS ? (long long)kStaticTabEntries : tab_base)) continue;
+        if (moe_table_entries(P, E, N, t) > (k.cfg >= TILE_CONFIGS ? kStaticTabEntries : tab_base)) continue;
         if ((large_only && k.cfg >= TILE_CONFIGS) || (gathered && t.bm == 128 && t.bn == 256)) continue;
         const double tiles = active * expected_m_tiles((double)rows / active, t.bm) * ((N + t.bn - 1) / t.bn);
         const double rounds = std::ceil(tiles / c->num_cus);
@@ -326,8 +323,8 @@ int symm_free(agg_ctx* c)
     if (c->gemm_done) (void)hipEventDestroy(c->gemm_done);
     if (c->b_nk_free) (void)hipEventDestroy(c->b_nk_free);
     if (c->b_nk) (void)hipFree(c->b_nk);
-    if (c->moe_ws) (void)hipFree(c->moe_ws);
-    if (c->moe_tab_large) (void)hipFree(c->moe_tab_large);
+    if (c->moe.ctrl) (void)hipFree(c->moe.ctrl);
+    if (c->moe.tab_large) (void)hipFree(c->moe.tab_large);
     if (c->staging) (void)hipFree(c->staging);
     if (c->signals) (void)hipFree(c->signals);
     if (c->counters) (void)hipFree(c->counters);
@@ -469,29 +466,22 @@ int agg_reserve_moe(agg_ctx* c, int Ttok, int topk, int E, int N)
 {
     if (!c || Ttok < 0 || topk < 1 || E < 1 || E > 4096 || N < 0) return AGG_ERR_INVALID_ARG;
     const long long P = (long long)Ttok * topk;
-    if (moe_table_bound(P, E, N) > (1ll << 28)) return AGG_ERR_UNSUPPORTED_SHAPE;
     // the table holds any shape that can be selected by number, and the small tiles of the automatic choice up to the size
     // of the static table (with which the two entry points choose alike)
-    const long long base = moe_table_bound(P, E, N);
-    if (!c->moe_ws) {
-        // the control block and a table of that size behind it, in one allocation
-        HIP_TRY(hipDeviceSynchronize());
-        HIP_TRY(hipMalloc((void**)&c->moe_ws, kStaticScratchBytes));
-        HIP_TRY(hipMemset(c->moe_ws, 0, kMoeCtrlBytes));         // the routing's counters start at zero
-        c->moe_tab = (MoeTile*)((char*)c->moe_ws + kStaticTabOffset);
-        c->moe_tab_cap = (int)kStaticTabEntries;
+    const long long entries = moe_table_bound(P, E, N);
+    if (entries > (1ll << 28)) return AGG_ERR_UNSUPPORTED_SHAPE;
+    const auto alloc = [](void** p, size_t bytes) { return hip_fail(hipMalloc(p, bytes)); };
+    const auto alloc_ctrl = [&](void** p, size_t bytes) {
+        int rc = alloc(p, bytes);
+        if (rc == AGG_OK && (rc = hip_fail(hipMemset(*p, 0, kMoeCtrlBytes))) != AGG_OK) (void)hipFree(*p);   // the routing's counters start at zero
+        return rc;
+    };
+    if (c->moe.ctrl && c->moe.cap >= entries) {
+        c->moe.base = std::max(c->moe.base, entries);
+        return AGG_OK;
     }
-    if (c->moe_tab_cap < base) {
-        HIP_TRY(hipDeviceSynchronize());
-        if (c->moe_tab_large) (void)hipFree(c->moe_tab_large);
-        c->moe_tab = c->moe_tab_large = nullptr;
-        c->moe_tab_cap = 0;
-        HIP_TRY(hipMalloc((void**)&c->moe_tab_large, (size_t)base * sizeof(MoeTile)));
-        c->moe_tab = c->moe_tab_large;
-        c->moe_tab_cap = (int)base;
-    }
-    c->moe_tab_base = std::max(c->moe_tab_base, (int)base);
-    return AGG_OK;
+    HIP_TRY(hipDeviceSynchronize());
+    return moe_workspace_reserve(c->moe, entries, alloc_ctrl, alloc, [](void* p) { (void)hipFree(p); });
 }
 
 int ag_producer_emulate(agg_ctx* c, const void* const* remote_shards, const int* arrival_order, int n_arrivals,
@@ -948,13 +938,14 @@ int gemm_rs(agg_ctx* c, int M, int N, int Kl, const void* A_local, int lda, cons
 // Routing + grouped GEMM, shared by ag_moe_gemm (A = T, rows gathered by token, tiles gated by the signals) and moe_rs
 // (A = the routed rows themselves, nothing to wait for).
 // The routing's control block (its first word is the tile count) and the tile table come from the caller of this
-// function: the context's reserved buffers, or the library's static scratch.
+// function: the context's reserved buffers, or the library's static scratch.  tab_base: what the table was reserved for, which
+// decides whether the call is accepted; tab_cap: the entries it holds.
 // keep_lo < keep_hi: only the rows of tokens in [keep_lo, keep_hi) are wanted: the routing lists tiles for those rows only
 // (one run of rows per expert, since tokens rise inside a segment).
 static int grouped_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, const int32_t* topk_ids, const void* A,
                         bool gathered, const void* weights, int32_t* sorted_token, int32_t* seg_off, int32_t* pair_pos,
                         void* Y, int ldy, int y_dtype, hipStream_t stream, int* n_tiles_word, MoeTile* tab, long long tab_base,
-                        int keep_lo = 0, int keep_hi = 0)
+                        long long tab_cap, int keep_lo = 0, int keep_hi = 0)
 {
     const long long P = (long long)Ttok * topk;
     const unsigned long long a_bytes = (unsigned long long)(gathered ? Ttok : P) * K * 2;
@@ -983,6 +974,7 @@ static int grouped_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, con
     const TileShape t = tile_shape(cfg);
     const int tiles_n = (N + t.bn - 1) / t.bn;
     const long long cap = moe_table_entries(P, E, N, t);
+    if (cap > tab_cap) return AGG_ERR_NOT_RESERVED;
     MoeRouteArgs r{};
     r.topk_ids = topk_ids;
     r.P = (int)P;
@@ -1037,7 +1029,7 @@ static int grouped_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, con
 
 static int ag_moe_gemm_impl(agg_ctx* c, int Ttok, int topk, int E, int N, int K, const int32_t* topk_ids, const void* weights,
                             int32_t* sorted_token, int32_t* sorted_expert_offsets, void* Y, int ldy, int y_dtype, void* stream,
-                            int* n_tiles_word, MoeTile* tab, long long tab_base)
+                            int* n_tiles_word, MoeTile* tab, long long tab_base, long long tab_cap)
 {
     if (!c || Ttok < 0 || topk < 1 || E < 1 || E > 4096 || N < 0 || K < 0) return AGG_ERR_INVALID_ARG;
     if (y_dtype != AGG_BF16 && y_dtype != AGG_F32) return AGG_ERR_INVALID_ARG;
@@ -1051,7 +1043,7 @@ static int ag_moe_gemm_impl(agg_ctx* c, int Ttok, int topk, int E, int N, int K,
     const int cps = c->n_signals / c->W;
     if (tpr % cps != 0) return AGG_ERR_UNSUPPORTED_SHAPE;
     return grouped_gemm(c, Ttok, topk, E, N, K, topk_ids, c->staging, true, weights, sorted_token, sorted_expert_offsets,
-                        nullptr, Y, ldy, y_dtype, (hipStream_t)stream, n_tiles_word, tab, tab_base);
+                        nullptr, Y, ldy, y_dtype, (hipStream_t)stream, n_tiles_word, tab, tab_base, tab_cap);
 }
 
 int ag_moe_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, const int32_t* topk_ids, const void* weights,
@@ -1059,7 +1051,7 @@ int ag_moe_gemm(agg_ctx* c, int Ttok, int topk, int E, int N, int K, const int32
 {
     if (!c) return AGG_ERR_INVALID_ARG;
     return ag_moe_gemm_impl(c, Ttok, topk, E, N, K, topk_ids, weights, sorted_token, sorted_expert_offsets, Y, ldy, y_dtype,
-                            stream, c->moe_ws, c->moe_tab, c->moe_tab_base);
+                            stream, c->moe.ctrl, c->moe.tab, c->moe.base, c->moe.cap);
 }
 
 int ag_moe_gemm_static(agg_ctx* c, int Ttok, int topk, int E, int N, int K, const int32_t* topk_ids, const void* weights,
@@ -1067,11 +1059,11 @@ int ag_moe_gemm_static(agg_ctx* c, int Ttok, int topk, int E, int N, int K, cons
 {
     if (!c || !c->static_scratch) return AGG_ERR_INVALID_ARG;
     // the table lives in the library's static device array: a problem whose table could exceed it is refused
-    const long long room = (long long)((kStaticScratchBytes - kStaticTabOffset) / sizeof(MoeTile));
-    if (Ttok > 0 && topk > 0 && E > 0 && N > 0 && moe_table_bound((long long)Ttok * topk, E, N) > room)
+    if (Ttok > 0 && topk > 0 && E > 0 && N > 0 && moe_table_bound((long long)Ttok * topk, E, N) > kStaticTabEntries)
         return AGG_ERR_UNSUPPORTED_SHAPE;
     return ag_moe_gemm_impl(c, Ttok, topk, E, N, K, topk_ids, weights, sorted_token, sorted_expert_offsets, Y, ldy, y_dtype,
-                            stream, (int*)c->static_scratch, (MoeTile*)(c->static_scratch + kStaticTabOffset), room);
+                            stream, (int*)c->static_scratch, (MoeTile*)(c->static_scratch + kStaticTabOffset), kStaticTabEntries,
+                            kStaticTabEntries);
 }
 
 int moe_rs(agg_ctx* c, int Ttok, int topk, int E, int N, int Kl, const void* H, const void* weights2,
@@ -1101,7 +1093,7 @@ int moe_rs(agg_ctx* c, int Ttok, int topk, int E, int N, int Kl, const void* H, 
     // that hold none of them (inside an expert's segment the tokens rise, so the rows of one rank are one run)
     const int keep_lo = Z_other ? 0 : c->rank * Tr, keep_hi = Z_other ? 0 : keep_lo + Tr;
     int rc = grouped_gemm(c, Ttok, topk, E, N, Kl, topk_ids, H, false, weights2, sorted_token, sorted_expert_offsets,
-                          pair_pos, Y, N, AGG_F32, (hipStream_t)gemm_stream, c->moe_ws, c->moe_tab, c->moe_tab_base,
+                          pair_pos, Y, N, AGG_F32, (hipStream_t)gemm_stream, c->moe.ctrl, c->moe.tab, c->moe.base, c->moe.cap,
                           keep_lo, keep_hi);
     if (rc != AGG_OK) return rc;
     // 2. top-k reduction: this rank's tokens into its own slot (first), the others' into Z_other

@@ -1,0 +1,43 @@
+// The host-side rules of the library behind plain C functions, for the tests that check them without a GPU.
+#include "moe_table.h"
+
+#include <cstdlib>
+#include <map>
+
+using namespace agg;
+
+extern "C" {
+
+// Plays agg_reserve_moe(entries[0]), ..(entries[n - 1]) on one context; allocation number k fails where fails[k] is set.  For
+// each call: its return code, whether there is a table, the entries that can really be stored in it, and what the calls
+// may assume of it (the reservation, and the fixed size that the small tiles go by).
+void moe_reserve_play(int n, const long long* entries, int n_allocs, const int* fails, int* rc, int* has_table, long long* room,
+                      long long* base, int* leaked)
+{
+    MoeWorkspace w{};
+    std::map<char*, size_t> live;
+    int k = 0;
+    auto take = [&](void** p, size_t bytes) {
+        if (k < n_allocs && fails[k++]) return -6;
+        *p = std::malloc(64);                     // an address of its own; nothing is stored there
+        live[(char*)*p] = bytes;
+        return 0;
+    };
+    for (int i = 0; i < n; ++i) {
+        rc[i] = moe_workspace_reserve(w, entries[i], take, take, [&](void* p) { live.erase((char*)p); std::free(p); });
+        has_table[i] = w.tab != nullptr;
+        base[i] = w.base;
+        room[i] = 0;
+        for (const auto& a : live)
+            if ((char*)w.tab == a.first) room[i] = (long long)(a.second / kMoeTileBytes);
+            else if (w.ctrl && (char*)w.ctrl == a.first && (char*)w.tab == a.first + kStaticTabOffset)
+                room[i] = (long long)((a.second - kStaticTabOffset) / kMoeTileBytes);
+    }
+    const size_t held = (w.ctrl ? 1u : 0u) + (w.tab_large ? 1u : 0u);
+    *leaked = (int)(live.size() - held);
+    for (const auto& a : live) std::free(a.first);
+}
+
+long long static_table_entries() { return kStaticTabEntries; }
+
+}

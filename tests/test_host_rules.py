@@ -1,0 +1,39 @@
+"""No GPU: the rules by which the host sizes workspaces and picks tiles and grids."""
+import ctypes as C
+import itertools
+
+import pytest
+
+from host_rules import lib
+
+
+def _play(entries, fails):
+    n = len(entries)
+    rc, has, leaked = (C.c_int * n)(), (C.c_int * n)(), C.c_int()
+    room, base = (C.c_longlong * n)(), (C.c_longlong * n)()
+    lib().moe_reserve_play(n, (C.c_longlong * n)(*entries), len(fails), (C.c_int * len(fails))(*fails), rc, has, room, base, C.byref(leaked))
+    return list(rc), list(has), list(room), list(base), leaked.value
+
+
+@pytest.mark.parametrize("entries", [(1040,), (70000, 1040), (40000, 90000, 1040, 50000), (1040, 70000, 32760, 32761)])
+def test_a_table_holds_what_its_users_assume_whichever_allocation_fails(entries):
+    """A MoE call checks the reserved size, and lists up to the fixed number of small tiles whatever was reserved: both have to
+    fit into the table that is there, also behind a reservation that failed, which changes nothing."""
+    fixed = lib().static_table_entries()
+    for fails in itertools.product((0, 1), repeat=len(entries) + 1):
+        rc, has, room, base, leaked = _play(entries, fails)
+        asked = 0
+        had = 0
+        for i, e in enumerate(entries):
+            if rc[i] == 0:
+                asked = max(asked, e)
+            assert base[i] == asked, (entries, fails, i)
+            assert has[i] or not had                       # a table that was there is still there
+            had = has[i]
+            if has[i]:
+                assert room[i] >= max(base[i], fixed), (entries, fails, i)
+            else:
+                assert base[i] == 0
+        assert leaked == 0
+        if not any(fails):
+            assert all(r == 0 for r in rc)
