@@ -21,6 +21,7 @@
 // tiles), 64 x 8192 x 3584 33.3 -> 18.5 (64x32), 128 x 7168 x 8192 74.6 -> 42 (64x64), 999 x 1999 x 1984 21 -> 15.6 (64x128).
 #pragma once
 #include "gemm_tile.h"
+#include "ks_stage.h"
 
 namespace agg {
 
@@ -240,14 +241,13 @@ void gemm_ks_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
             constexpr bool is_a = decltype(is_a_c)::value;
             constexpr int u0 = is_a ? 0 : C_::A_UNITS, n = is_a ? C_::A_UNITS : C_::B_UNITS;
             const int c = wave + s * S;
-            const bool in = c < KC;
-            const __amdgpu_buffer_rsrc_t rs = make_rsrc(is_a ? a_base : b_base, in ? (is_a ? a_bytes : b_bytes) : 0u);
-            const int k_off = in ? c * ROW_BYTES : 0;
+            const KsStage st = ks_stage(c, KC, ROW_BYTES, is_a ? a_bytes : b_bytes);
+            const __amdgpu_buffer_rsrc_t rs = make_rsrc(is_a ? a_base : b_base, st.bytes);
             auto load = [&](auto aux_c) {
                 static_for<n>([&](auto u_c) {
                     constexpr int u = u0 + decltype(u_c)::value;
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_byte*)(unsigned long)(lds_wave + slot * C_::STAGE + u * 1024), 16,
-                                                             ld_off[u], k_off, 0, decltype(aux_c)::value);
+                                                             ld_off[u], st.k_off, 0, decltype(aux_c)::value);
                 });
             };
             if (!is_a && p.b_streams) load(std::integral_constant<int, 2>{});      // 2 = nt
@@ -399,12 +399,13 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
         for (int i = 0; i < LB; ++i) off_b[i] = (unsigned)((wave + S * i) * UNIT_ROWS + ld_row) * ldb2 + (unsigned)(ld_chunk * 16);
         auto issue_b = [&](int s, auto slot_c) {
             constexpr int slot = decltype(slot_c)::value;
-            const __amdgpu_buffer_rsrc_t rs = make_rsrc(b_base, s < KC ? b_bytes : 0u);
+            const KsStage st = ks_stage(s, KC, ROW_BYTES, b_bytes);
+            const __amdgpu_buffer_rsrc_t rs = make_rsrc(b_base, st.bytes);
             auto load = [&](auto aux_c) {
                 static_for<LB>([&](auto i_c) {
                     constexpr int i = decltype(i_c)::value;
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_byte*)(unsigned long)(lds_ld + slot * C_::STAGE + (C_::A_UNITS + S * i) * 1024),
-                                                             16, off_b[i], s * ROW_BYTES, 0, decltype(aux_c)::value);
+                                                             16, off_b[i], st.k_off, 0, decltype(aux_c)::value);
                 });
             };
             if (p.b_streams) load(std::integral_constant<int, 2>{});               // 2 = nt
@@ -412,11 +413,12 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
         };
         auto issue_a = [&](int s, auto slot_c) {
             constexpr int slot = decltype(slot_c)::value;
-            const __amdgpu_buffer_rsrc_t rs = make_rsrc(a_base, s < KC ? a_bytes : 0u);
+            const KsStage st = ks_stage(s, KC, ROW_BYTES, a_bytes);
+            const __amdgpu_buffer_rsrc_t rs = make_rsrc(a_base, st.bytes);
             static_for<LA>([&](auto i_c) {
                 constexpr int i = decltype(i_c)::value;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_byte*)(unsigned long)(lds_ld + slot * C_::STAGE + S * i * 1024), 16,
-                                                         off_a[i], s * ROW_BYTES, 0, 0);
+                                                         off_a[i], st.k_off, 0, 0);
             });
         };
         auto issue_all_b = [&] { static_for<NST - 1>([&](auto j_c) { issue_b(decltype(j_c)::value, j_c); }); };

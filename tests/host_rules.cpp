@@ -1,4 +1,5 @@
 // The host-side rules of the library behind plain C functions, for the tests that check them without a GPU.
+#include "ks_stage.h"
 #include "moe_table.h"
 
 #include <cstdlib>
@@ -36,6 +37,27 @@ void moe_reserve_play(int n, const long long* entries, int n_allocs, const int* 
     const size_t held = (w.ctrl ? 1u : 0u) + (w.tab_large ? 1u : 0u);
     *leaked = (int)(live.size() - held);
     for (const auto& a : live) std::free(a.first);
+}
+
+// Every 16-byte access of stages 0 .. KC + past - 1 of a tile of `tile_rows` rows, of which `rows` exist, each `ld` bytes apart and
+// 64 KC elements long: the number of accesses that a bounds check lets through outside the rows, for both ways in which it
+// may treat the scalar offset (added to the lane's, or taken from the size, modulo 2^32), plus those it holds back inside.
+int ks_stage_bad_accesses(int KC, int past, int rows, int tile_rows, unsigned ld)
+{
+    int bad = 0;
+    const unsigned bytes = (unsigned)rows * ld;
+    for (int s = 0; s < KC + past; ++s) {
+        const KsStage st = ks_stage(s, KC, 128, bytes);
+        for (int row = 0; row < tile_rows; ++row)
+            for (unsigned chunk = 0; chunk < 8; ++chunk) {
+                const unsigned lane = (unsigned)row * ld + chunk * 16;
+                const bool wanted = s < KC && row < rows;
+                const bool added = (unsigned long long)lane + (unsigned)st.k_off < st.bytes;
+                const bool taken = lane < (unsigned)(st.bytes - (unsigned)st.k_off);
+                bad += (added != wanted) + (taken != wanted);
+            }
+    }
+    return bad;
 }
 
 long long static_table_entries() { return kStaticTabEntries; }

@@ -37,3 +37,10 @@ def test_a_table_holds_what_its_users_assume_whichever_allocation_fails(entries)
         assert leaked == 0
         if not any(fails):
             assert all(r == 0 for r in rc)
+
+
+@pytest.mark.parametrize("KC,rows,tile_rows,ld", [(1, 1, 64, 128), (1, 64, 64, 128), (5, 63, 64, 640), (7, 3, 64, 1024), (12, 128, 128, 1536), (31, 7, 128, 4000)])
+def test_stages_past_the_end_of_k_load_nothing(KC, rows, tile_rows, ld):
+    """The rings ask for up to eight stages past the last one (gemm_ks.h): none of those loads may reach memory, however the bounds
+    check treats the scalar offset, and those of the real stages read the rows that are there."""
+    assert lib().ks_stage_bad_accesses(KC, 64, rows, tile_rows, C.c_uint(ld)) == 0
