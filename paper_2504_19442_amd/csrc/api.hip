@@ -1,6 +1,7 @@
 // C ABI of libagg.so: argument checks, context bookkeeping and launches.  No arithmetic of the
 // method happens on the host; every step runs in the HIP kernels of this library.
 #include "agg_internal.h"
+#include "launch_rules.h"
 
 #include <algorithm>
 #include <cmath>
@@ -686,17 +687,7 @@ static int reduce_impl(agg_ctx* c, int Ms, int N, const float* const* slots, voi
     a.epoch_ptr = c->device_epoch ? c->epoch_word : nullptr;
     a.wait_ticks = wait_ticks(c);
     a.err = c->err;
-    int nwg = n_workgroups;
-    if (nwg == 0) {
-        // persistent: two workgroups per CU, each walking many blocks (one acquire per workgroup, not per block).  Measured
-        // with slots that are in no cache (us at 1 / 1.25 / 1.5 / 2 / 3 / 4 per CU): eight slots of 1024 x 8192 59.4 /
-        // 62.0 / 57.9 / 54.6 / 59.0 / 64.1 (5.5 TB/s at two), two slots 32.8 / 30.0 / 27.6 / 25.2 / 25.0 / 27.2.
-        const long long need = (a.n_vec4 + 255) / 256;
-        // Beside the GEMM a CU has room for one reducer workgroup only (one 64-register wave per SIMD).
-        const long long want = beside_gemm ? (long long)c->num_cus : (long long)c->num_cus * 2;
-        nwg = (int)(need < want ? need : want);
-        if (nwg < 1) nwg = 1;
-    }
+    const int nwg = n_workgroups > 0 ? n_workgroups : reduce_workgroups(c->W, c->num_cus, a.n_vec4, beside_gemm);
     return hip_fail(launch_reduce(a, nwg, (hipStream_t)stream, beside_gemm));
 }
 

@@ -1,5 +1,6 @@
 // The host-side rules of the library behind plain C functions, for the tests that check them without a GPU.
 #include "ks_stage.h"
+#include "launch_rules.h"
 #include "moe_table.h"
 
 #include <cstdlib>
@@ -59,6 +60,8 @@ int ks_stage_bad_accesses(int KC, int past, int rows, int tile_rows, unsigned ld
     }
     return bad;
 }
+
+int reduce_grid(int W, int num_cus, long long n_vec4, int beside_gemm) { return reduce_workgroups(W, num_cus, n_vec4, beside_gemm != 0); }
 
 long long static_table_entries() { return kStaticTabEntries; }
 

@@ -68,3 +68,35 @@ def test_reducer_slots_beyond_the_memory_side_cache_bit_exact(W, Ms, N, ldr):
         assert bool((R[:, N:] == 3.0).all())
     finally:
         ctx.free()
+
+
+@pytest.mark.parametrize("tile,W", [(6, 2), (6, 3), (6, 4), (4, 6)])
+def test_a_gemm_launched_behind_a_waiting_reducer_feeds_it(tile, W):
+    """The reducer is launched first, with the library's own grid, and waits for all slots; the GEMM that produces them comes
+    afterwards on another stream, on large tiles, and has to find room."""
+    Ms, N, K = 64 * (12 // W), 8192, 64              # 3072 to 1024 blocks of the reducer: more than two for every CU
+    g = torch.Generator(device="cuda").manual_seed(7500 + W)
+    A = torch.randint(-2, 3, (W * Ms, K), device="cuda", generator=g).to(torch.bfloat16)
+    B = torch.randint(-2, 3, (N, K), device="cuda", generator=g).to(torch.bfloat16)
+    P = A.float() @ B.float().t()
+    want = P.reshape(W, Ms, N).sum(dim=0)             # small integers: exact in any order
+    ctx = agg.symm_alloc(W, 0, 16, W)
+    try:
+        ctx.set_tile_config(tile)
+        ps, cs = ctx.streams()
+        slots = [torch.full((Ms, N), float("nan"), device="cuda") for _ in range(W)]
+        R = torch.full((Ms, N), float("nan"), device="cuda")
+        signals = [ctx.signals + w * agg.SIGNAL_STRIDE * 4 for w in range(W)]
+        for reducer_first in (False, True):            # (the first run also gets the kernels loaded)
+            agg.signal_reset(ctx)
+            torch.cuda.synchronize()
+            if reducer_first:
+                agg.rs_reduce(ctx, Ms, N, slots, R, N, agg.F32, 0, cs)
+            agg.gemm_rs_scatter(ctx, W * Ms, N, K, A, K, B, K, agg.B_NK, slots, None, signals, 0, ps)
+            if not reducer_first:
+                agg.rs_reduce(ctx, Ms, N, slots, R, N, agg.F32, 0, cs)
+            torch.cuda.synchronize()
+            assert agg.agg_status(ctx) == agg.OK
+            assert torch.equal(R, want)
+    finally:
+        ctx.free()
