@@ -210,8 +210,12 @@ int gemm_rs(agg_ctx* ctx, int M, int N, int Klocal,
  * signal_reset, ag_producer_emulate (rotated arrival order) on the context's producer stream, ag_gemm on its consumer
  * stream, join -- with the signals reset before every run, never a kernel repeated on its own.  Candidates: the four
  * tile shapes x both tile orders x three producer sizes (half, one and two workgroups per compute unit; one candidate
- * when the copy engines are used).  Each candidate runs once to warm up (the very first thirty times, so that the
- * chip's clocks have settled) and runs_per_config more times; the median run counts.  The best configuration is stored in the context (tile shape, tile order, producer
+ * when the copy engines are used).  Each candidate runs once to warm up (before the very first one there are twenty-nine runs
+ * more, so that the chip's clocks have settled) and runs_per_config more times; the median run counts.  For problems on which
+ * the automatic choice takes one of its small tiles (see agg_set_tile_config) those first runs use that choice and the last
+ * fifteen are timed: where no candidate comes within a microsecond of it the result is tile_config = -1 (automatic) in the
+ * rotated order.  The GPU is held back for 0.1 ms before every run, so that the time is the GPU's and not that of the host's
+ * calls.  The best configuration is stored in the context (tile shape, tile order, producer
  * size used when ag_producer_emulate is called with n_workgroups = 0) and returned.  Synchronous.  On one GPU
  * there is no agreement between ranks to reach; on a node the ranks would exchange *out and take the slowest
  * rank's best.  C is overwritten.  Any error leaves the context's settings as they were.
@@ -232,7 +236,8 @@ int agg_autotune_ag_gemm(agg_ctx* ctx, int M, int N, int K, const void* B, int l
  * header line, then "W M N K tile_config tile_order producer_workgroups configs_tried best_ms" per entry; lines
  * starting with # are comments); load merges such a file into the table (entries of the file win) and returns the
  * number of entries read, AGG_ERR_IO if the file cannot be read, or AGG_ERR_INVALID_ARG for a file with a wrong
- * header, a malformed line or a value out of range -- the table is then left exactly as it was.  None of these calls
+ * header, a malformed line or a value out of range -- the table is then left exactly as it was.  tile_config = -1 (automatic) is
+ * in range with the rotated order only.  None of these calls
  * touches the GPU.
  */
 int agg_tune_table_size(void);

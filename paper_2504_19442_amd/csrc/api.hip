@@ -719,6 +719,43 @@ int agg_autotune_ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb
         (void)hipEventDestroy(e0); (void)hipEventDestroy(e1); return rc;
     }
     const bool sdma = (producer_mode & 0xff) == AGG_PRODUCER_SDMA;
+    // one run of the function
+    auto run = [&](float* ms) {
+        int rc_;
+        if ((rc_ = signal_reset(c, c->consumer_stream)) != AGG_OK) return rc_;   // ahead of the fork below
+        // the GPU is kept from starting (0.1 ms, by a wait for a word that nobody sets) until all of the run is enqueued: of a
+        // small problem the events would otherwise time the gaps between the host's calls (35 to 55 us of them)
+        if ((rc_ = hip_fail(launch_signal_probe(c->err + 32, 1, c->wall_khz / 10, c->err + 33, c->consumer_stream))) != AGG_OK) return rc_;
+        // fork: both streams start from the same point
+        if ((rc_ = hip_fail(hipEventRecord(e0, c->consumer_stream))) != AGG_OK) return rc_;
+        if ((rc_ = hip_fail(hipStreamWaitEvent(c->producer_stream, e0, 0))) != AGG_OK) return rc_;
+        if ((rc_ = ag_producer_emulate(c, remote_shards, nullptr, 0, producer_mode, 0, c->producer_stream)) != AGG_OK) return rc_;
+        if ((rc_ = ag_gemm(c, M, N, K, B, ldb, b_layout, C, ldc, c_dtype, c->consumer_stream)) != AGG_OK) return rc_;
+        // join: the function is over when both parts are
+        if ((rc_ = hip_fail(hipEventRecord(join, c->producer_stream))) != AGG_OK) return rc_;
+        if ((rc_ = hip_fail(hipStreamWaitEvent(c->consumer_stream, join, 0))) != AGG_OK) return rc_;
+        if ((rc_ = hip_fail(hipEventRecord(e1, c->consumer_stream))) != AGG_OK) return rc_;
+        if ((rc_ = hip_fail(hipEventSynchronize(e1))) != AGG_OK) return rc_;
+        return hip_fail(hipEventElapsedTime(ms, e0, e1));
+    };
+    auto median = [](std::vector<float>& t) {
+        std::sort(t.begin(), t.end());
+        return t.empty() ? 1e30f : t[t.size() / 2];
+    };
+    // Untimed runs first: one per candidate, and a longer series before the very first candidate, so that the chip's clocks
+    // have settled under load before anything is compared.  Where the automatic choice takes a tile that is not among the
+    // candidates, that series runs with it, and its second half is timed: the time a candidate has to come near to.
+    constexpr int kWarm = 30, kSettled = 15;
+    c->tile_config = -1;
+    const bool automatic = choose_tile(c, M, N, K) >= TILE_CONFIGS;
+    std::vector<float> auto_times;
+    for (int it = 0; it < kWarm - 1 && rc == AGG_OK; ++it) {
+        c->tile_config = automatic ? -1 : tiles[0];
+        c->tile_order = orders[0];
+        c->producer_wgs = wgs[1];
+        float ms = 0.f;
+        if ((rc = run(&ms)) == AGG_OK && automatic && it >= kWarm - 1 - kSettled) auto_times.push_back(ms);
+    }
     for (int ti = 0; ti < 4 && rc == AGG_OK; ++ti)
         for (int oi = 0; oi < 2 && rc == AGG_OK; ++oi)
             for (int wi = 0; wi < (sdma ? 1 : 3) && rc == AGG_OK; ++wi) {
@@ -726,30 +763,11 @@ int agg_autotune_ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb
                 c->tile_order = orders[oi];
                 c->producer_wgs = wgs[wi];
                 std::vector<float> times;
-                // untimed runs first: one per candidate, and a longer series before the very first candidate, so
-                // that the chip's clocks have settled under load before anything is compared
-                const int warm = res.configs_tried == 0 ? 30 : 1;
-                for (int it = 0; it < runs_per_config + warm && rc == AGG_OK; ++it) {
-                    if ((rc = signal_reset(c, c->consumer_stream)) != AGG_OK) break;   // ahead of the fork below
-                    // fork: both streams start from the same point
-                    if ((rc = hip_fail(hipEventRecord(e0, c->consumer_stream))) != AGG_OK) break;
-                    if ((rc = hip_fail(hipStreamWaitEvent(c->producer_stream, e0, 0))) != AGG_OK) break;
-                    if ((rc = ag_producer_emulate(c, remote_shards, nullptr, 0, producer_mode, 0, c->producer_stream)) != AGG_OK) break;
-                    if ((rc = ag_gemm(c, M, N, K, B, ldb, b_layout, C, ldc, c_dtype, c->consumer_stream)) != AGG_OK) break;
-                    // join: the function is over when both parts are
-                    if ((rc = hip_fail(hipEventRecord(join, c->producer_stream))) != AGG_OK) break;
-                    if ((rc = hip_fail(hipStreamWaitEvent(c->consumer_stream, join, 0))) != AGG_OK) break;
-                    if ((rc = hip_fail(hipEventRecord(e1, c->consumer_stream))) != AGG_OK) break;
-                    if ((rc = hip_fail(hipEventSynchronize(e1))) != AGG_OK) break;
+                for (int it = 0; it < runs_per_config + 1 && rc == AGG_OK; ++it) {
                     float ms = 0.f;
-                    if ((rc = hip_fail(hipEventElapsedTime(&ms, e0, e1))) != AGG_OK) break;
-                    if (it >= warm) times.push_back(ms);
+                    if ((rc = run(&ms)) == AGG_OK && it >= 1) times.push_back(ms);
                 }
-                float best_here = 1e30f;
-                if (!times.empty()) {
-                    std::sort(times.begin(), times.end());
-                    best_here = times[times.size() / 2];       // the median run
-                }
+                const float best_here = median(times);
                 if (rc == AGG_OK) rc = agg_status(c);          // a candidate whose waits time out is an error, not a result
                 ++res.configs_tried;
                 if (rc == AGG_OK && best_here < best) {
@@ -760,6 +778,17 @@ int agg_autotune_ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb
                     res.best_ms = best_here;
                 }
             }
+    // A candidate is the result (they all add up K in one order) unless the automatic choice is faster by more than the
+    // medians of repeated tunings differ.  Measured, ms, automatic choice and best candidate: 16 x 3584 x 4096 0.0226 and 0.038,
+    // 128 x 7168 x 8192 0.0475 and 0.0617, 999 x 1999 x 1984 0.0351 and 0.037, 1024 x 256 x 128 0.023 and 0.0213.
+    constexpr float kResolutionMs = 0.001f;
+    const float auto_ms = median(auto_times);
+    if (rc == AGG_OK && auto_ms + kResolutionMs < best) {
+        res.tile_config = -1;
+        res.tile_order = orders[0];
+        res.producer_workgroups = sdma ? 0 : wgs[1];
+        res.best_ms = auto_ms;
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     (void)hipEventDestroy(join);

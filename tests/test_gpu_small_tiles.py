@@ -297,3 +297,35 @@ def test_moe_weights_beyond_the_memory_side_cache_exact(W, tpr, K, N, E, topk):
         assert torch.equal(Y, want)
     finally:
         ctx.free()
+
+
+def test_tuning_a_small_problem_does_not_end_on_a_slower_tile():
+    # 16 rows: with the best of the numbered tiles the function takes twice as long as untuned
+    W, Ms, K, N = 8, 2, 8192, 3584
+    g = torch.Generator(device="cuda").manual_seed(30)
+    shards = [torch.randint(-2, 3, (Ms, K), device="cuda", generator=g).to(torch.bfloat16) for _ in range(W)]
+    B = torch.randint(-2, 3, (N, K), device="cuda", generator=g).to(torch.bfloat16)
+    want = torch.cat(shards).float() @ B.float().t()
+    C = torch.full((W * Ms, N), float("nan"), device="cuda")
+    ctx, other = agg.symm_alloc(W, 0, Ms * K * 2, W), agg.symm_alloc(W, 0, Ms * K * 2, W)
+    try:
+        torch.cuda.synchronize()
+        res = agg.agg_autotune_ag_gemm(ctx, W * Ms, N, K, B, K, agg.B_NK, C, N, agg.F32, shards, agg.PRODUCER_KERNEL, 3)
+        assert res.configs_tried == 24 and (res.tile_config, res.tile_order) == (-1, agg.ORDER_ROTATED)
+        assert res.producer_workgroups > 0 and 0.0 < res.best_ms < 1000.0
+        assert agg.agg_tune_table_get(W, W * Ms, N, K).tile_config == -1
+        assert agg.agg_tune_table_apply(other, W * Ms, N, K)
+        for c in (ctx, other):
+            ps, cs = c.streams()
+            C.fill_(float("nan"))
+            agg.signal_reset(c)
+            torch.cuda.synchronize()
+            agg.ag_producer_emulate(c, shards, None, agg.PRODUCER_KERNEL, 0, ps)
+            agg.ag_gemm(c, W * Ms, N, K, B, K, agg.B_NK, C, N, agg.F32, cs)
+            torch.cuda.synchronize()
+            assert agg.agg_status(c) == agg.OK
+            assert torch.equal(C, want)
+    finally:
+        ctx.free()
+        other.free()
+        agg.agg_tune_table_clear()

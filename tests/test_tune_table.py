@@ -95,3 +95,20 @@ def test_comments_blank_lines_and_missing_files(tmp_path):
         agg.agg_tune_table_save(str(tmp_path / "no_such_dir" / "t.txt"))
     assert e.value.code == agg.ERR_IO
     assert agg.agg_strerror(agg.ERR_NOT_FOUND) == "no such entry"
+
+
+def test_the_automatic_choice_can_be_kept_in_the_rotated_order_only(tmp_path):
+    p = str(tmp_path / "auto.txt")
+    agg.agg_tune_table_put(8, 16, 3584, 4096, _entry(tile=-1, order=0))
+    agg.agg_tune_table_save(p)
+    assert "8 16 3584 4096 -1 0 256 18 0.7125" in open(p).read().splitlines()
+    agg.agg_tune_table_clear()
+    assert agg.agg_tune_table_load(p) == 1
+    got = agg.agg_tune_table_get(8, 16, 3584, 4096)
+    assert (got.tile_config, got.tile_order, got.producer_workgroups) == (-1, 0, 256)
+    for bad in ("-1 1", "-2 0"):
+        open(p, "w").write(f"agg-tune-table 1\n8 64 64 64 {bad} 256 1 0.5\n")
+        with pytest.raises(agg.AggError) as e:
+            agg.agg_tune_table_load(p)
+        assert e.value.code == agg.ERR_INVALID_ARG
+    assert agg.agg_tune_table_size() == 1
