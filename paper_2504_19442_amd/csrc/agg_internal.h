@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/agg.h"
+#include "launch_rules.h"
 #include "moe_table.h"
 
 namespace agg {
@@ -95,35 +96,6 @@ struct TopkReduceArgs {
 };
 hipError_t launch_topk_reduce(const TopkReduceArgs& a, int n_workgroups, hipStream_t stream);
 hipError_t launch_gemm_grouped(const GemmParams& p, int cfg, int grid, hipStream_t stream);
-
-// A tile configuration = a tile shape (bits 0-1) and the MFMA form of the main loop (bit 2): v_mfma_f32_32x32x16_bf16,
-// or, with TILE_K32, v_mfma_f32_16x16x32_bf16 (half the accumulator traffic per flop: the chip holds a higher clock).
-enum TileConfig { TILE_256x224 = 0, TILE_128x128 = 1, TILE_256x256 = 2, TILE_128x256 = 3, TILE_K32 = 4, TILE_CONFIGS = 8 };
-
-// Tile configurations of the K-split kernels (gemm_ks.h): what the automatic choice takes where the tiles above would leave
-// most of the chip idle; not selectable by number.
-enum KsTileConfig { KS_16x16 = 8, KS_16x32, KS_16x64, KS_32x32, KS_64x32, KS_64x64, KS_64x128, KS_CONFIGS_END };
-
-struct TileShape { int bm, bn; };
-inline TileShape tile_shape(int cfg)
-{
-    switch (cfg) {
-        case KS_16x16: return {16, 16};
-        case KS_16x32: return {16, 32};
-        case KS_16x64: return {16, 64};
-        case KS_32x32: return {32, 32};
-        case KS_64x32: return {64, 32};
-        case KS_64x64: return {64, 64};
-        case KS_64x128: return {64, 128};
-        default: break;
-    }
-    switch (cfg & 3) {
-        case TILE_256x224: return {256, 224};
-        case TILE_256x256: return {256, 256};
-        case TILE_128x256: return {128, 256};
-        default: return {128, 128};
-    }
-}
 
 hipError_t launch_gemm(const GemmParams& p, int cfg, int grid, hipStream_t stream);
 

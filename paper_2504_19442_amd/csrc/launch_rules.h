@@ -1,7 +1,158 @@
-// Rules by which the host picks grids.  Plain C++, so that they can be checked without a GPU.
+// Rules by which the host picks tiles and grids.  Plain C++, so that they can be checked without a GPU.
 #pragma once
+#include "moe_table.h"
+
+#include <algorithm>
+#include <cmath>
 
 namespace agg {
+
+// A tile configuration = a tile shape (bits 0-1) and the MFMA form of the main loop (bit 2): v_mfma_f32_32x32x16_bf16,
+// or, with TILE_K32, v_mfma_f32_16x16x32_bf16 (half the accumulator traffic per flop: the chip holds a higher clock).
+enum TileConfig { TILE_256x224 = 0, TILE_128x128 = 1, TILE_256x256 = 2, TILE_128x256 = 3, TILE_K32 = 4, TILE_CONFIGS = 8 };
+
+// Tile configurations of the K-split kernels (gemm_ks.h): what the automatic choice takes where the tiles above would leave
+// most of the chip idle; not selectable by number.
+enum KsTileConfig { KS_16x16 = 8, KS_16x32, KS_16x64, KS_32x32, KS_64x32, KS_64x64, KS_64x128, KS_CONFIGS_END };
+
+struct TileShape { int bm, bn; };
+inline TileShape tile_shape(int cfg)
+{
+    switch (cfg) {
+        case KS_16x16: return {16, 16};
+        case KS_16x32: return {16, 32};
+        case KS_16x64: return {16, 64};
+        case KS_32x32: return {32, 32};
+        case KS_64x32: return {64, 32};
+        case KS_64x64: return {64, 64};
+        case KS_64x128: return {64, 128};
+        default: break;
+    }
+    switch (cfg & 3) {
+        case TILE_256x224: return {256, 224};
+        case TILE_256x256: return {256, 256};
+        case TILE_128x256: return {128, 256};
+        default: return {128, 128};
+    }
+}
+
+// Estimated time of one tile in a full round, in microseconds: what a tile takes whatever its K, and what it takes per 64
+// of K.  From sweeps of M, N, K with every shape: what a tile costs follows the bytes it pulls through its compute unit's
+// load path, (BM + BN) x 128 per 64 of K at about 70 KB/us, up to 128 x 128; the large tiles are bound by the matrix pipes
+// at the clock the chip holds with all of them busy.  Over 60 shapes drawn from M 16..8192, N 96..7168, K 256..8192 (over
+// their logarithms) the choice costs 1.7 % more than the best shape of each.  Where the line lies, both sides measured in
+// us: 16x3584x4096 16x16 8.7, 128x128 24.9; 64x8192x3584 64x32 19.1, 64x64 22, 128x128 33; 128x7168x8192 64x64 42,
+// 128x128 75; 999x1999x1984 64x128 17.2, 128x128 21; 1024x3584x4096 128x128 34, 64x128 51.
+struct TileCost { int cfg; double fixed_us, us_per_k64; };
+constexpr TileCost kTileCosts[] = {
+    {TILE_256x224 | TILE_K32, 4.0, 1.25}, {TILE_256x256 | TILE_K32, 4.0, 1.42}, {TILE_128x256 | TILE_K32, 4.0, 0.83},
+    {TILE_128x128 | TILE_K32, 4.0, 0.46},
+    {KS_64x128, 3.5, 0.37}, {KS_64x64, 3.0, 0.24}, {KS_64x32, 4.0, 0.20}, {KS_32x32, 3.0, 0.125}, {KS_16x32, 3.0, 0.09},
+    {KS_16x16, 3.0, 0.07},
+};
+// the K-split kernels divide row and tile numbers with 32-bit multipliers, exact while rows x divisor < 2^32
+constexpr int kKsMaxRows = 65535;
+
+// Pick the tile shape with the smallest estimated time: rounds of tiles over the CUs times the cost of a tile.  The
+// 16x16x32 form of the main loop everywhere: the same work at a lower power per flop, so the chip holds a higher clock
+// (measured 5 to 8 % faster on every shape); the 32x32x16 form stays selectable (configurations 0 to 3).
+// large_only: without the K-split tiles.
+inline int best_tile(int num_cus, int M, int N, int K, bool large_only = false)
+{
+    int best = kTileCosts[0].cfg;
+    double best_cost = 1e300;
+    for (const TileCost& k : kTileCosts) {
+        if (k.cfg >= TILE_CONFIGS && (large_only || M > kKsMaxRows)) continue;
+        const TileShape t = tile_shape(k.cfg);
+        const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        const long long rounds = (tiles + num_cus - 1) / num_cus;
+        const double cost = (double)rounds * (k.fixed_us + k.us_per_k64 * (K / 64));
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = k.cfg;
+        }
+    }
+    return best;
+}
+
+// Upper bound of the grouped GEMM's tile table for one tile shape: sum over experts of ceil(rows / bm) <= P / bm + E, times
+// the n-tiles.
+inline long long moe_table_entries(long long P, int E, int N, TileShape t) { return (P / t.bm + E) * ((N + t.bn - 1) / t.bn); }
+// ... and over the shapes that can be selected by number (128 x 128 is the smallest)
+inline long long moe_table_bound(long long P, int E, int N) { return moe_table_entries(P, E, N, {128, 128}); }
+
+// The shape, among those that can be selected by number, that decides whether a reserved table is large enough for a call:
+// rounds of tiles over the CUs times the cost of a tile (the small tile is bound by the global->LDS path: about 0.6 of the
+// large tile's rate per flop), with segments 15 % above the mean.
+inline int table_tile_grouped(int num_cus, long long wanted_rows, int E, int N)
+{
+    const int cand[3] = {TILE_256x224, TILE_256x256, TILE_128x128};
+    const double eff[3] = {1.0, 1.0, 0.6};
+    const double rows = 1.15 * (double)wanted_rows / E;
+    double best = 1e300;
+    int cfg = cand[0];
+    for (int i = 0; i < 3; ++i) {
+        const TileShape ts = tile_shape(cand[i]);
+        const long long mt = (long long)((rows + ts.bm - 1) / ts.bm);
+        const long long tiles = (long long)E * mt * ((N + ts.bn - 1) / ts.bn);
+        const long long waves = (tiles + num_cus - 1) / num_cus;
+        const double cost = (double)waves * ts.bm * ts.bn / eff[i];
+        if (cost < best) { best = cost; cfg = cand[i]; }
+    }
+    return cfg | TILE_K32;
+}
+
+// Expected number of tiles of `bm` rows of a segment of `mean` rows on average, its length spread around that like that of a
+// random routing (standard deviation sqrt(mean)): sum over k of P(length > k * bm).
+inline double expected_m_tiles(double mean, int bm)
+{
+    const double sd = std::sqrt(mean);
+    // up to nine standard deviations below the mean a term is 1 (to the last bit): those are counted, not computed -- of a
+    // segment of 4 M rows the sum took 0.3 ms of host time per call
+    const long long whole = std::max(0ll, (long long)((mean - 9.0 * sd) / bm));
+    double n = 1.0 + (double)whole;
+    for (long long k = whole + 1; k * (double)bm < mean + 3.0 * sd; ++k) n += 0.5 * std::erfc((k * (double)bm - mean) / (sd * std::sqrt(2.0)));
+    return n;
+}
+
+// Tile shape of a grouped GEMM: `rows` rows of A spread over E experts, [N][K] weights per expert.  Rounds of tiles times
+// the cost of a tile, as in best_tile (the large tiles cost a fifth more here, where every tile has a weight matrix of its
+// own to pull from HBM; fp32 rows are stored at about 19 KB/us per compute unit), but not less than the weights of the
+// experts that have rows take from HBM at 5.9 TB/s; where they bound it, a last round that fills only part of the chip
+// costs its share of that time, and the smaller tile wins.  Measured, us per call with routing, bf16 out: 64 tokens of
+// Table 4 (two rows per expert) 128x128 203, 64x64 179, 16x32 164; 512 tokens 128x128 230, 32x32 208.  Rows in place with
+// K = 192 and fp32 out (the GEMM of Table 5, kernel alone): 256x256 70, 128x256 63, 128x128 71.  Gathered rows never take
+// 128x256: the whole call at 8192 tokens is 1 % faster in bf16 (374 against 376) but its first pass on new weights 5 %
+// slower (457 against 435), and in fp32 it is 5 % slower throughout (392 against 371).
+// Left out are shapes whose table (P pairs) would have more than `tab_base` entries, and of the small ones those beyond the
+// static table's size, whatever table is used: the choice depends on the problem alone.  -1 if that is all of them.
+inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, bool gathered, bool f32, long long P, long long tab_base,
+                        bool large_only = false)
+{
+    static const TileCost cand[] = {
+        {KS_16x32, 3.0, 0.09}, {KS_16x64, 3.0, 0.12}, {KS_32x32, 3.0, 0.125}, {KS_64x64, 3.0, 0.24}, {KS_64x128, 3.5, 0.38},
+        {TILE_128x128 | TILE_K32, 4.0, 0.60}, {TILE_128x256 | TILE_K32, 4.0, 0.94}, {TILE_256x224 | TILE_K32, 4.0, 1.50},
+        {TILE_256x256 | TILE_K32, 4.0, 1.73},
+    };
+    const double active = E * (1.0 - std::pow(1.0 - 1.0 / E, (double)rows));       // experts with at least one row
+    const double hbm_us = active * N * K * 2.0 / 5.9e6;
+    int best = -1;
+    double best_cost = 1e300;
+    for (const TileCost& k : cand) {
+        const TileShape t = tile_shape(k.cfg);
+        if (moe_table_entries(P, E, N, t) > (k.cfg >= TILE_CONFIGS ? kStaticTabEntries : tab_base)) continue;
+        if ((large_only && k.cfg >= TILE_CONFIGS) || (gathered && t.bm == 128 && t.bn == 256)) continue;
+        const double tiles = active * expected_m_tiles((double)rows / active, t.bm) * ((N + t.bn - 1) / t.bn);
+        const double rounds = std::ceil(tiles / num_cus);
+        const double tile_us = k.fixed_us + k.us_per_k64 * (K / 64) + (f32 ? t.bm * t.bn * 4 / 19e3 : 0.0);
+        const double cost = std::max(rounds * tile_us, hbm_us * rounds * num_cus / std::max(tiles, (double)num_cus));
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = k.cfg;
+        }
+    }
+    return best;
+}
 
 // Workgroups of a reducer launch over n_vec4 float4 whose caller leaves the size to the library.  Persistent, each walking
 // many blocks of 256 (one acquire per workgroup, not per block).

@@ -63,6 +63,22 @@ int ks_stage_bad_accesses(int KC, int past, int rows, int tile_rows, unsigned ld
 
 int reduce_grid(int W, int num_cus, long long n_vec4, int beside_gemm) { return reduce_workgroups(W, num_cus, n_vec4, beside_gemm != 0); }
 
+double m_tiles(double mean, int bm) { return expected_m_tiles(mean, bm); }
+
+// The same sum term by term, as it is defined.
+double m_tiles_plain(double mean, int bm)
+{
+    const double sd = std::sqrt(mean);
+    double n = 1.0;
+    for (long long k = 1; k * (double)bm < mean + 3.0 * sd; ++k) n += 0.5 * std::erfc((k * (double)bm - mean) / (sd * std::sqrt(2.0)));
+    return n;
+}
+
+int tile_grouped(int num_cus, long long rows, int E, int N, int K, int gathered, int f32, long long P, long long tab_base, int large_only)
+{
+    return best_tile_grouped(num_cus, rows, E, N, K, gathered != 0, f32 != 0, P, tab_base, large_only != 0);
+}
+
 long long static_table_entries() { return kStaticTabEntries; }
 
 }

@@ -17,4 +17,8 @@ def lib() -> C.CDLL:
                         os.path.join(HERE, "host_rules.cpp"), "-o", out], check=True)
         L = C.CDLL(out)
     L.static_table_entries.restype = C.c_longlong
+    L.m_tiles.restype = L.m_tiles_plain.restype = C.c_double
+    L.m_tiles.argtypes = L.m_tiles_plain.argtypes = [C.c_double, C.c_int]
+    i, q = C.c_int, C.c_longlong
+    L.tile_grouped.argtypes = [i, q, i, i, i, i, i, q, q, i]
     return L

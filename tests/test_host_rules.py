@@ -1,6 +1,8 @@
 """No GPU: the rules by which the host sizes workspaces and picks tiles and grids."""
 import ctypes as C
 import itertools
+import random
+import time
 
 import pytest
 
@@ -60,3 +62,15 @@ def test_a_waiting_reducer_leaves_room_for_a_gemm_that_comes_later(W):
         spread = [3 * grid // cus + (i < 3 * grid % cus) for i in range(cus)]
         assert all(512 - 56 * k >= 208 for k in spread), (W, n_vec4, grid)
         assert lib().reduce_grid(W, cus, C.c_longlong(n_vec4), 1) <= cus
+
+
+def test_expected_number_of_tiles_is_the_sum_and_costs_no_more_for_long_segments():
+    rng = random.Random(31)
+    for bm in (16, 32, 64, 128, 256):
+        for mean in [0.01, 0.5, 1.0, 15.9, 16.0, 256.0, 1e5, 1e6] + [10.0 ** rng.uniform(-2, 6) for _ in range(200)]:
+            assert lib().m_tiles(mean, bm) == lib().m_tiles_plain(mean, bm), (mean, bm)
+    # a MoE call makes this choice on the host: 16 Mi rows of one expert, 1000 calls (1.4 s if every tile is a term of the sum)
+    t0 = time.monotonic()
+    for _ in range(1000):
+        assert 0 <= lib().tile_grouped(256, 1 << 24, 1, 128, 64, 0, 1, 1 << 24, 1 << 28, 0) < 8
+    assert time.monotonic() - t0 < 0.8
