@@ -124,10 +124,11 @@ inline double expected_m_tiles(double mean, int bm)
 // K = 192 and fp32 out (the GEMM of Table 5, kernel alone): 256x256 70, 128x256 63, 128x128 71.  Gathered rows never take
 // 128x256: the whole call at 8192 tokens is 1 % faster in bf16 (374 against 376) but its first pass on new weights 5 %
 // slower (457 against 435), and in fp32 it is 5 % slower throughout (392 against 371).
-// Left out are shapes whose table (P pairs) would have more than `tab_base` entries, and of the small ones those beyond the
-// static table's size, whatever table is used: the choice depends on the problem alone.  -1 if that is all of them.
-inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, bool gathered, bool f32, long long P, long long tab_base,
-                        bool large_only = false)
+// Which K-split tile is taken, or that a numbered one is, follows from the problem alone: the small tiles are left out where their
+// table (P pairs) would have more entries than the static one, whatever table is used.  Among the numbered ones, which all give
+// the same bits, those are left out whose table would have more than `tab_base` entries; -1 if that is all of them.
+inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, bool gathered, bool f32, long long P,
+                             long long tab_base, bool large_only = false)
 {
     static const TileCost cand[] = {
         {KS_16x32, 3.0, 0.09}, {KS_16x64, 3.0, 0.12}, {KS_32x32, 3.0, 0.125}, {KS_64x64, 3.0, 0.24}, {KS_64x128, 3.5, 0.38},
@@ -136,12 +137,13 @@ inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, b
     };
     const double active = E * (1.0 - std::pow(1.0 - 1.0 / E, (double)rows));       // experts with at least one row
     const double hbm_us = active * N * K * 2.0 / 5.9e6;
-    int best = -1;
-    double best_cost = 1e300;
+    int best = -1, best_that_fits = -1;
+    double best_cost = 1e300, fits_cost = 1e300;
     for (const TileCost& k : cand) {
         const TileShape t = tile_shape(k.cfg);
-        if (moe_table_entries(P, E, N, t) > (k.cfg >= TILE_CONFIGS ? kStaticTabEntries : tab_base)) continue;
-        if ((large_only && k.cfg >= TILE_CONFIGS) || (gathered && t.bm == 128 && t.bn == 256)) continue;
+        const bool small = k.cfg >= TILE_CONFIGS;
+        const long long entries = moe_table_entries(P, E, N, t);
+        if ((small && (large_only || entries > kStaticTabEntries)) || (gathered && t.bm == 128 && t.bn == 256)) continue;
         const double tiles = active * expected_m_tiles((double)rows / active, t.bm) * ((N + t.bn - 1) / t.bn);
         const double rounds = std::ceil(tiles / num_cus);
         const double tile_us = k.fixed_us + k.us_per_k64 * (K / 64) + (f32 ? t.bm * t.bn * 4 / 19e3 : 0.0);
@@ -150,8 +152,12 @@ inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, b
             best_cost = cost;
             best = k.cfg;
         }
+        if (!small && entries <= tab_base && cost < fits_cost) {
+            fits_cost = cost;
+            best_that_fits = k.cfg;
+        }
     }
-    return best;
+    return best >= TILE_CONFIGS ? best : best_that_fits;
 }
 
 // Workgroups of a reducer launch over n_vec4 float4 whose caller leaves the size to the library.  Persistent, each walking

@@ -74,3 +74,18 @@ def test_expected_number_of_tiles_is_the_sum_and_costs_no_more_for_long_segments
     for _ in range(1000):
         assert 0 <= lib().tile_grouped(256, 1 << 24, 1, 128, 64, 0, 1, 1 << 24, 1 << 28, 0) < 8
     assert time.monotonic() - t0 < 0.8
+
+
+@pytest.mark.parametrize("gathered,f32", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_the_order_of_the_sums_does_not_depend_on_what_was_reserved(gathered, f32):
+    """All numbered tiles give the same bits and so does each K-split tile: whichever of them a call takes may depend on the problem
+    only, not on whether its context was reserved for a larger one."""
+    rng = random.Random(32)
+    for _ in range(4000):
+        P, E = int(10.0 ** rng.uniform(0, 5)), rng.randint(1, 128)
+        N, K = rng.randint(1, 4096), 64 * rng.randint(1, 64)
+        taken = set()
+        for room in (0, 1, 500, 5000, 32760, 1 << 28):
+            tile = lib().tile_grouped(256, P, E, N, K, gathered, f32, P, room, 0)
+            taken.add(tile if tile >= 8 else "numbered")
+        assert len(taken) == 1, (P, E, N, K, taken)
