@@ -115,6 +115,12 @@ inline double expected_m_tiles(double mean, int bm)
     return n;
 }
 
+constexpr TileCost kTileCostsGrouped[] = {
+    {KS_16x32, 3.0, 0.09}, {KS_16x64, 3.0, 0.12}, {KS_32x32, 3.0, 0.125}, {KS_64x64, 3.0, 0.24}, {KS_64x128, 3.5, 0.38},
+    {TILE_128x128 | TILE_K32, 4.0, 0.60}, {TILE_128x256 | TILE_K32, 4.0, 0.94}, {TILE_256x224 | TILE_K32, 4.0, 1.50},
+    {TILE_256x256 | TILE_K32, 4.0, 1.73},
+};
+
 // Tile shape of a grouped GEMM: `rows` rows of A spread over E experts, [N][K] weights per expert.  Rounds of tiles times
 // the cost of a tile, as in best_tile (the large tiles cost a fifth more here, where every tile has a weight matrix of its
 // own to pull from HBM; fp32 rows are stored at about 19 KB/us per compute unit), but not less than the weights of the
@@ -130,16 +136,11 @@ inline double expected_m_tiles(double mean, int bm)
 inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, bool gathered, bool f32, long long P,
                              long long tab_base, bool large_only = false)
 {
-    static const TileCost cand[] = {
-        {KS_16x32, 3.0, 0.09}, {KS_16x64, 3.0, 0.12}, {KS_32x32, 3.0, 0.125}, {KS_64x64, 3.0, 0.24}, {KS_64x128, 3.5, 0.38},
-        {TILE_128x128 | TILE_K32, 4.0, 0.60}, {TILE_128x256 | TILE_K32, 4.0, 0.94}, {TILE_256x224 | TILE_K32, 4.0, 1.50},
-        {TILE_256x256 | TILE_K32, 4.0, 1.73},
-    };
     const double active = E * (1.0 - std::pow(1.0 - 1.0 / E, (double)rows));       // experts with at least one row
     const double hbm_us = active * N * K * 2.0 / 5.9e6;
     int best = -1, best_that_fits = -1;
     double best_cost = 1e300, fits_cost = 1e300;
-    for (const TileCost& k : cand) {
+    for (const TileCost& k : kTileCostsGrouped) {
         const TileShape t = tile_shape(k.cfg);
         const bool small = k.cfg >= TILE_CONFIGS;
         const long long entries = moe_table_entries(P, E, N, t);

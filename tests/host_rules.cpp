@@ -74,6 +74,22 @@ double m_tiles_plain(double mean, int bm)
     return n;
 }
 
+int tile_plain(int num_cus, int M, int N, int K) { return best_tile(num_cus, M, N, K); }
+
+int tile_rows_and_columns(int tile) { return tile_shape(tile).bm << 16 | tile_shape(tile).bn; }
+
+// The K-split tiles that the automatic choice can take; returns how many.
+int ks_tiles(int grouped, int* out)
+{
+    int n = 0;
+    auto add = [&](const TileCost& k) {
+        if (k.cfg >= TILE_CONFIGS) out[n++] = k.cfg;
+    };
+    if (grouped) for (const TileCost& k : kTileCostsGrouped) add(k);
+    else for (const TileCost& k : kTileCosts) add(k);
+    return n;
+}
+
 int tile_grouped(int num_cus, long long rows, int E, int N, int K, int gathered, int f32, long long P, long long tab_base, int large_only)
 {
     return best_tile_grouped(num_cus, rows, E, N, K, gathered != 0, f32 != 0, P, tab_base, large_only != 0);

@@ -22,3 +22,36 @@ def lib() -> C.CDLL:
     i, q = C.c_int, C.c_longlong
     L.tile_grouped.argtypes = [i, q, i, i, i, i, i, q, q, i]
     return L
+
+
+def tile_name(tile: int) -> str:
+    """"16x32" for a K-split tile, "numbered" for those of agg_set_tile_config."""
+    if tile < 8:
+        return "numbered"
+    rc = lib().tile_rows_and_columns(tile)
+    return f"{rc >> 16}x{rc & 0xffff}"
+
+
+def gemm_tile(num_cus: int, M: int, N: int, K: int):
+    """The automatic choice for ag_gemm, gemm_rs and gemm_rs_scatter, and how many of those tiles the problem has."""
+    tile = lib().tile_plain(num_cus, M, N, K)
+    rc = lib().tile_rows_and_columns(tile)
+    return tile_name(tile), -(-M // (rc >> 16)) * -(-N // (rc & 0xffff))
+
+
+def moe_tile(num_cus: int, tokens: int, topk: int, E: int, N: int, K: int, gathered: bool, f32: bool) -> str:
+    """The automatic choice for ag_moe_gemm (gathered) and moe_rs on a context reserved for the problem."""
+    return tile_name(lib().tile_grouped(num_cus, tokens * topk, E, N, K, int(gathered), int(f32), tokens * topk, 1 << 28, 0))
+
+
+def _ks_tiles(grouped: int):
+    out = (C.c_int * 16)()
+    return list(out[:lib().ks_tiles(grouped, out)])
+
+
+def dense_ks_tiles():
+    return _ks_tiles(0)
+
+
+def moe_ks_tiles():
+    return _ks_tiles(1)

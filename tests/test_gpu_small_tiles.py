@@ -1,6 +1,7 @@
 """The K-split GEMM kernels that the automatic tile choice takes for small problems, at the sizes where they can go wrong:
 one row, one short of and one past a tile, a single piece of K, fewer pieces than waves, a ragged last column block with
-aligned and unaligned rows, more tiles than one round, slices smaller and larger than a tile.  Integer inputs: exact."""
+aligned and unaligned rows, slices smaller and larger than a tile.  Integer inputs: exact.  (Every tile in every form, with K longer
+than its ring and more tiles than workgroups: test_gpu_ks_tiles.py.)"""
 import numpy as np
 import pytest
 import torch
@@ -16,15 +17,15 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("W,Ms,K,N,chunks", [
     (1, 1, 64, 16, 1),          # one row, one piece of K (seven of eight waves have none)
     (3, 1, 576, 40, 1),         # 16-row tiles, nine pieces over eight waves
-    (2, 17, 192, 99, 1),        # three tiles of 16 rows, odd columns: the element-wise store
+    (2, 17, 192, 99, 1),        # three tiles of 16 rows, odd columns
     (4, 16, 4096, 200, 2),      # 16 x 16 tiles, deep K
     (2, 35, 448, 1500, 1),      # 16 x 32
     (5, 26, 640, 1302, 2),      # 32 x 32, columns not a multiple of four
-    (3, 11, 128, 4100, 1),      # 64 x 32, rows of one tile, two pieces of K
+    (3, 11, 128, 4100, 1),      # 64 x 64, half a tile of rows, two pieces of K
     (2, 260, 448, 1200, 4),     # 64 x 64 over several signals
     (3, 333, 512, 1999, 1),     # 64 x 128, odd columns
     (3, 333, 64, 2001, 3),      # one piece of K
-    (2, 33, 64, 6148, 1),       # more tiles than compute units
+    (2, 33, 64, 6148, 1),       # 64 x 64, the second tile of rows almost empty, a single piece of K
 ])
 def test_ag_gemm_small_shapes_exact(W, Ms, K, N, chunks):
     sh = wl.AgGemmShape(f"ag_small_{W}_{Ms}_{K}_{N}", 21, W, Ms, K, N)
@@ -88,8 +89,8 @@ def test_gemm_rs_small_shapes_exact(W, Ms, K, N, chunks):
     (128, 63, 64, 0),           # a ragged last piece, a wave's tile not full
     (192, 130, 136, 0),         # second column tile almost empty, padded rows
     (320, 257, 264, 8),         # base moved by 16 bytes
-    (128, 100, 104, 1),         # base not 16-byte aligned: two bytes at a time
-    (64, 65, 65, 0),            # odd leading dimension: two bytes at a time
+    (128, 100, 104, 1),         # base not 16-byte aligned
+    (64, 65, 65, 0),            # odd leading dimension: every row at another alignment
 ])
 def test_b_given_as_k_by_n_any_alignment_exact(K, N, ldb, offset):
     sh = wl.AgGemmShape(f"ag_kn_{K}_{N}", 23, 2, 24, K, N)
@@ -118,9 +119,9 @@ def test_b_given_as_k_by_n_any_alignment_exact(K, N, ldb, offset):
     (4, 1, 64, 32, 4, 1),           # one piece of K, a token or none per expert
     (2, 3, 192, 100, 7, 2),         # rows of a tile beyond the segment, ragged columns
     (8, 8, 1024, 130, 16, 2),       # eight rows per expert
-    (2, 96, 320, 66, 6, 2),         # segments of 64 rows: some need two tiles of 64
-    (3, 111, 128, 1999, 5, 3),      # odd columns, 64 x 128 tiles
-    (8, 128, 64, 260, 8, 2),        # 256 rows per expert
+    (2, 96, 320, 66, 6, 2),         # segments of 64 rows: some end inside a fifth tile of 16
+    (3, 111, 128, 1999, 5, 3),      # odd columns, the smallest numbered tile
+    (8, 128, 64, 260, 8, 2),        # 256 rows per expert, 64 x 64 tiles
 ])
 def test_moe_small_shapes_exact(W, tpr, K, N, E, topk):
     sh = wl.MoeShape(f"moe_small_{tpr}_{K}_{N}", 24, W, tpr, K, N, E, topk)
