@@ -796,7 +796,7 @@ int gemm_rs(agg_ctx* c, int M, int N, int Kl, const void* A_local, int lda, cons
         p.N = N;
         p.K = Kl;
         p.c_is_f32 = 1;
-            p.epoch = c->epoch;
+        p.epoch = c->epoch;
         p.epoch_ptr = c->device_epoch ? c->epoch_word : nullptr;
         p.err = c->err;
         p.wait_ticks = wait_ticks(c);

@@ -520,8 +520,11 @@ static hipError_t launch_ks_kind(const KsParams& p, const std::conditional_t<KIN
     return hipGetLastError();
 }
 
+// The forms of a tile that the automatic choice takes (launch_rules.h): KS_PLAIN and KS_SLICED, KS_GROUPED.
+enum KsForms { KS_DENSE = 1, KS_MOE = 2 };
+
 // The launch of `g` (a GemmParams whose tile fields are those of this tile shape) on this kernel.
-template <bool SHARED, int BM, int BN, int X, int NST>
+template <bool SHARED, int BM, int BN, int X, int NST, int FORMS>
 static hipError_t launch_ks(const GemmParams& g, bool grouped, int grid, hipStream_t stream)
 {
     KsParams p{};
@@ -541,27 +544,33 @@ static hipError_t launch_ks(const GemmParams& g, bool grouped, int grid, hipStre
     // faster with the streaming hint: 64 tokens of Table 4 (1 GB of weights) 165 -> 155 us per call, 512 tokens 209 -> 199.
     // Weights that it may hold do not take the hint: 16 x 3584 x 4096 (29 MB) 8.5 without, 9.8 with it.
     p.b_streams = g.b_total_bytes >= (256ll << 20);
-    if (grouped) {
-        p.row_index = g.row_index; p.tile_tab = g.tile_tab; p.n_tiles_dev = g.n_tiles_dev;
-        p.b_group_stride = g.b_group_stride; p.a_bytes = g.a_bytes;
-        return launch_ks_kind<SHARED, BM, BN, X, NST, KS_GROUPED>(p, KsNoSlices{}, stream);
+    if (grouped ? !(FORMS & KS_MOE) : !(FORMS & KS_DENSE)) return hipErrorInvalidValue;
+    if constexpr ((FORMS & KS_MOE) != 0) {
+        if (grouped) {
+            p.row_index = g.row_index; p.tile_tab = g.tile_tab; p.n_tiles_dev = g.n_tiles_dev;
+            p.b_group_stride = g.b_group_stride; p.a_bytes = g.a_bytes;
+            return launch_ks_kind<SHARED, BM, BN, X, NST, KS_GROUPED>(p, KsNoSlices{}, stream);
+        }
     }
-    if (g.n_slices == 0) return launch_ks_kind<SHARED, BM, BN, X, NST, KS_PLAIN>(p, KsNoSlices{}, stream);
-    KsSlices sl{};
-    sl.M = g.M; sl.tiles_n = g.tiles_n; sl.slice_rows = g.slice_rows; sl.slice_chunks = g.slice_chunks;
-    sl.chunk_rows = g.chunk_rows; sl.ldc_slice = (int)g.ldc_slice; sl.slice_mul = div_mul(g.slice_rows);
-    sl.slice_ctr = g.slice_ctr;
-    for (int w = 0; w < g.n_slices; ++w) { sl.slice_dst[w] = g.slice_dst[w]; sl.slice_flag[w] = g.slice_flag[w]; }
-    return launch_ks_kind<SHARED, BM, BN, X, NST, KS_SLICED>(p, sl, stream);
+    if constexpr ((FORMS & KS_DENSE) != 0) {
+        if (g.n_slices == 0) return launch_ks_kind<SHARED, BM, BN, X, NST, KS_PLAIN>(p, KsNoSlices{}, stream);
+        KsSlices sl{};
+        sl.M = g.M; sl.tiles_n = g.tiles_n; sl.slice_rows = g.slice_rows; sl.slice_chunks = g.slice_chunks;
+        sl.chunk_rows = g.chunk_rows; sl.ldc_slice = (int)g.ldc_slice; sl.slice_mul = div_mul(g.slice_rows);
+        sl.slice_ctr = g.slice_ctr;
+        for (int w = 0; w < g.n_slices; ++w) { sl.slice_dst[w] = g.slice_dst[w]; sl.slice_flag[w] = g.slice_flag[w]; }
+        return launch_ks_kind<SHARED, BM, BN, X, NST, KS_SLICED>(p, sl, stream);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace agg
 
 // One launch function per tile shape (gemm_ks_*.hip); gemm_dispatch.hip names them.
-#define AGG_KS_INSTANCE(SHARED, BM, BN, X, NST)                                                             \
+#define AGG_KS_INSTANCE(SHARED, BM, BN, X, NST, FORMS)                                                      \
     namespace agg {                                                                                         \
     hipError_t launch_gemm_ks_##BM##x##BN(const GemmParams& p, bool grouped, int grid, hipStream_t s)       \
     {                                                                                                       \
-        return launch_ks<SHARED, BM, BN, X, NST>(p, grouped, grid, s);                                      \
+        return launch_ks<SHARED, BM, BN, X, NST, FORMS>(p, grouped, grid, s);                               \
     }                                                                                                       \
     }
