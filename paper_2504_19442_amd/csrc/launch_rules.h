@@ -115,21 +115,28 @@ inline double expected_m_tiles(double mean, int bm)
     return n;
 }
 
+// The same for the grouped GEMM, where every tile has a weight matrix of its own to pull.  Fitted to the measured times of every
+// tile for 740 problems drawn from 4 to 8192 tokens, 4 to 64 experts, top-1 to 4, N 96 to 2048, K 64 to 4096 (gathered rows in bf16
+// and fp32, rows in place): the choice costs 0.7 % more than the best tile of each (geometric mean; 0.8 % on 370 other draws) and takes
+// 12 % less time than the choice among 256x224, 256x256 and 128x128 alone, which is faster by more than 5 % on 12 of the 1110, by
+// more than 10 % on two.
 constexpr TileCost kTileCostsGrouped[] = {
-    {KS_16x32, 3.0, 0.09}, {KS_16x64, 3.0, 0.12}, {KS_32x32, 3.0, 0.125}, {KS_64x64, 3.0, 0.24}, {KS_64x128, 3.5, 0.38},
-    {TILE_128x128 | TILE_K32, 4.0, 0.60}, {TILE_128x256 | TILE_K32, 4.0, 0.94}, {TILE_256x224 | TILE_K32, 4.0, 1.50},
+    {KS_16x32, 3.4, 0.113}, {KS_16x64, 3.4, 0.179}, {KS_32x32, 2.6, 0.142}, {KS_64x64, 3.3, 0.267}, {KS_64x128, 3.5, 0.40},
+    {TILE_128x128 | TILE_K32, 3.0, 0.60}, {TILE_128x256 | TILE_K32, 2.9, 0.94}, {TILE_256x224 | TILE_K32, 4.1, 1.50},
     {TILE_256x256 | TILE_K32, 4.0, 1.73},
 };
+constexpr double kGroupedStoreBytesPerUs = 82e3;     // fp32 rows, per compute unit
+constexpr double kGroupedWeightBytesPerUs = 7.2e6;   // weights of the experts that have rows, whole chip
 
 // Tile shape of a grouped GEMM: `rows` rows of A spread over E experts, [N][K] weights per expert.  Rounds of tiles times
-// the cost of a tile, as in best_tile (the large tiles cost a fifth more here, where every tile has a weight matrix of its
-// own to pull from HBM; fp32 rows are stored at about 19 KB/us per compute unit), but not less than the weights of the
-// experts that have rows take from HBM at 5.9 TB/s; where they bound it, a last round that fills only part of the chip
-// costs its share of that time, and the smaller tile wins.  Measured, us per call with routing, bf16 out: 64 tokens of
-// Table 4 (two rows per expert) 128x128 203, 64x64 179, 16x32 164; 512 tokens 128x128 230, 32x32 208.  Rows in place with
-// K = 192 and fp32 out (the GEMM of Table 5, kernel alone): 256x256 70, 128x256 63, 128x128 71.  Gathered rows never take
-// 128x256: the whole call at 8192 tokens is 1 % faster in bf16 (374 against 376) but its first pass on new weights 5 %
-// slower (457 against 435), and in fp32 it is 5 % slower throughout (392 against 371).
+// the cost of a tile, as in best_tile, but not less than the weights of the experts that have rows take from HBM; where they
+// bound it, a last round that fills only part of the chip costs its share of that time, and the smaller tile wins.  Measured,
+// us per call with routing, bf16 out, Table 4: 64 tokens (two rows per expert) 16x64 149, 16x32 154, 64x64 158, 128x128 196; 512
+// tokens 64x64 190, 64x128 197, 32x32 197, 128x128 226; 2048 tokens 128x128 232, 64x128 277.  Rows in place with K = 192 and fp32
+// out (the GEMM of Table 5, kernel alone, cold): 256x256 70, 128x256 63, 128x128 71.  Gathered rows never take 128x256: at 8192
+// tokens of Table 4, the one size where it was looked at closely, the whole call is 1 % faster in bf16 (374 against 376) but its
+// first pass on new weights 5 % slower (457 against 435), and in fp32 it is 5 % slower throughout (392 against 371).  (At other sizes
+// of the draws it would be the best tile, by up to a fifth.)
 // Which K-split tile is taken, or that a numbered one is, follows from the problem alone: the small tiles are left out where their
 // table (P pairs) would have more entries than the static one, whatever table is used.  Among the numbered ones, which all give
 // the same bits, those are left out whose table would have more than `tab_base` entries; -1 if that is all of them.
@@ -137,7 +144,7 @@ inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, b
                              long long tab_base, bool large_only = false)
 {
     const double active = E * (1.0 - std::pow(1.0 - 1.0 / E, (double)rows));       // experts with at least one row
-    const double hbm_us = active * N * K * 2.0 / 5.9e6;
+    const double hbm_us = active * N * K * 2.0 / kGroupedWeightBytesPerUs;
     int best = -1, best_that_fits = -1;
     double best_cost = 1e300, fits_cost = 1e300;
     for (const TileCost& k : kTileCostsGrouped) {
@@ -147,7 +154,7 @@ inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, b
         if ((small && (large_only || entries > kStaticTabEntries)) || (gathered && t.bm == 128 && t.bn == 256)) continue;
         const double tiles = active * expected_m_tiles((double)rows / active, t.bm) * ((N + t.bn - 1) / t.bn);
         const double rounds = std::ceil(tiles / num_cus);
-        const double tile_us = k.fixed_us + k.us_per_k64 * (K / 64) + (f32 ? t.bm * t.bn * 4 / 19e3 : 0.0);
+        const double tile_us = k.fixed_us + k.us_per_k64 * (K / 64) + (f32 ? t.bm * t.bn * 4 / kGroupedStoreBytesPerUs : 0.0);
         const double cost = std::max(rounds * tile_us, hbm_us * rounds * num_cus / std::max(tiles, (double)num_cus));
         if (cost < best_cost) {
             best_cost = cost;

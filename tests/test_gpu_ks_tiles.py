@@ -80,16 +80,16 @@ def test_the_choices_above_reach_every_tile_of_the_dense_table():
 
 # tile, output type, whether its workgroups take a second tile, tokens, top-k, experts, N, K
 MOE_TILES = [
-    ("16x32", agg.BF16, False, 60, 1, 40, 129, 1600),
-    ("16x32", agg.F32, True, 364, 2, 2, 340, 2560),
-    ("16x64", agg.F32, True, 368, 3, 86, 277, 64),
-    ("16x64", agg.BF16, True, 368, 3, 86, 277, 832),
-    ("32x32", agg.F32, True, 4926, 3, 55, 20, 64),
+    ("16x32", agg.BF16, False, 60, 1, 20, 100, 1792),
+    ("16x32", agg.F32, True, 120, 3, 38, 404, 1856),
+    ("16x64", agg.F32, True, 462, 2, 93, 268, 832),
+    ("16x64", agg.BF16, True, 1068, 1, 88, 305, 192),
+    ("32x32", agg.F32, True, 4844, 3, 78, 28, 320),
     ("32x32", agg.BF16, False, 1398, 3, 6, 20, 1088),
-    ("64x64", agg.F32, True, 2806, 3, 5, 150, 192),
-    ("64x64", agg.BF16, False, 1400, 3, 3, 36, 576),
-    ("64x128", agg.F32, True, 4628, 3, 46, 133, 64),
-    ("64x128", agg.BF16, True, 3232, 2, 2, 580, 448),
+    ("64x64", agg.F32, True, 1820, 3, 3, 268, 3392),
+    ("64x64", agg.BF16, True, 1708, 2, 89, 277, 192),
+    ("64x128", agg.F32, True, 1296, 2, 2, 1492, 1600),
+    ("64x128", agg.BF16, True, 2096, 3, 4, 555, 576),
 ]
 
 

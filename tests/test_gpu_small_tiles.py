@@ -119,7 +119,7 @@ def test_b_given_as_k_by_n_any_alignment_exact(K, N, ldb, offset):
     (4, 1, 64, 32, 4, 1),           # one piece of K, a token or none per expert
     (2, 3, 192, 100, 7, 2),         # rows of a tile beyond the segment, ragged columns
     (8, 8, 1024, 130, 16, 2),       # eight rows per expert
-    (2, 96, 320, 66, 6, 2),         # segments of 64 rows: some end inside a fifth tile of 16
+    (2, 96, 320, 66, 6, 2),         # segments of 64 rows: some end inside a third tile of 32
     (3, 111, 128, 1999, 5, 3),      # odd columns, the smallest numbered tile
     (8, 128, 64, 260, 8, 2),        # 256 rows per expert, 64 x 64 tiles
 ])

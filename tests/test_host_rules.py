@@ -6,7 +6,7 @@ import time
 
 import pytest
 
-from host_rules import lib
+from host_rules import lib, tile_name
 
 
 def _play(entries, fails):
@@ -89,3 +89,21 @@ def test_the_order_of_the_sums_does_not_depend_on_what_was_reserved(gathered, f3
             tile = lib().tile_grouped(256, P, E, N, K, gathered, f32, P, room, 0)
             taken.add(tile if tile >= 8 else "numbered")
         assert len(taken) == 1, (P, E, N, K, taken)
+
+
+# Measured, us per call with routing, weights in no cache where they exceed it: the tile that a sum of fixed costs had picked, and the
+# one that was taken before there were K-split tiles (128x128 in all of these).
+@pytest.mark.parametrize("gathered,f32,tokens,topk,E,N,K,slow", [
+    (1, 0, 578, 4, 5, 824, 3392, "64x64"),          # 49.7 against 33.4
+    (1, 1, 752, 2, 60, 805, 3328, "16x64"),         # 107.9 against 78.5 (64x128: 72.7)
+    (1, 1, 40, 2, 33, 681, 640, "16x64"),           # 19.7 against 16.6
+    (1, 1, 5168, 2, 6, 160, 1920, "64x64"),         # 33.7 against 29.1
+    (1, 0, 5056, 4, 6, 182, 2944, "64x64"),         # 79.7 against 66.3 (256x224: 62.3)
+    (1, 1, 848, 2, 16, 900, 256, "64x64"),          # 19.8 against 17.0
+    (0, 1, 40, 2, 62, 1856, 832, "16x64"),          # 55.9 against 49.4
+    (0, 1, 344, 1, 52, 1756, 896, "16x64"),         # 59.2 against 54.2
+    (0, 1, 96, 2, 48, 508, 768, "16x64"),           # 28.3 against 25.9
+])
+def test_moe_calls_do_not_take_a_tile_that_was_measured_slower_than_the_old_choice(gathered, f32, tokens, topk, E, N, K, slow):
+    P = tokens * topk
+    assert tile_name(lib().tile_grouped(256, P, E, N, K, gathered, f32, P, 1 << 28, 0)) != slow
