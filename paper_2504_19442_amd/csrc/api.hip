@@ -31,10 +31,10 @@ inline long long wait_ticks(const agg_ctx* c)
     return (long long)((double)c->wall_khz * (double)c->wait_limit_us / 1000.0);
 }
 
-// large_only: without the K-split tiles.
-int choose_tile(const agg_ctx* c, int M, int N, int K, bool large_only = false)
+// slices: GEMM + ReduceScatter's epilogue; large_only: without the K-split tiles.
+int choose_tile(const agg_ctx* c, int M, int N, int K, bool slices = false, bool large_only = false)
 {
-    return c->tile_config >= 0 ? c->tile_config : best_tile(c->num_cus, M, N, K, large_only);
+    return c->tile_config >= 0 ? c->tile_config : best_tile(c->num_cus, M, N, K, slices, large_only);
 }
 
 // Workgroups of a launch of `tiles` tiles: one per tile up to one per CU (a multiple of 8, so that neighbouring tiles can be
@@ -743,7 +743,7 @@ int gemm_rs_scatter(agg_ctx* c, int M, int N, int Kl, const void* A_local, int l
         p.slice_dst[w] = slice_dst[w];
         p.slice_flag[w] = slice_signal ? slice_signal[w] : nullptr;
     }
-    const int cfg = choose_tile(c, M, N, Kl);
+    const int cfg = choose_tile(c, M, N, Kl, true);
     fill_schedule(c, p, cfg, Ms, first_slice * Ms);
     const long long tiles = (long long)p.tiles_m * p.tiles_n;
     const int grid = gemm_grid(c, cfg, tiles);
@@ -809,8 +809,8 @@ int gemm_rs(agg_ctx* c, int M, int N, int Kl, const void* A_local, int lda, cons
         p.slice_flag[0] = own_flag;
         // the sum over K in the same order as with P_other, so that the slice is the same bit for bit: a K-split tile if
         // the whole product takes one, and then that one
-        int cfg = choose_tile(c, M, N, Kl);
-        if (cfg < TILE_CONFIGS) cfg = choose_tile(c, Ms, N, Kl, true);
+        int cfg = choose_tile(c, M, N, Kl, true);
+        if (cfg < TILE_CONFIGS) cfg = choose_tile(c, Ms, N, Kl, true, true);
         fill_schedule(c, p, cfg, Ms, 0);
         const long long tiles = (long long)p.tiles_m * p.tiles_n;
         const int grid = gemm_grid(c, cfg, tiles);

@@ -50,14 +50,21 @@ constexpr TileCost kTileCosts[] = {
     {KS_64x128, 3.5, 0.37}, {KS_64x64, 3.0, 0.24}, {KS_64x32, 4.0, 0.20}, {KS_32x32, 3.0, 0.125}, {KS_16x32, 3.0, 0.09},
     {KS_16x16, 3.0, 0.07},
 };
+constexpr double kPublishUs = 0.009, kStoreUs256 = 10.0, kStoreUs128x256 = 4.0;     // best_tile, slices
 // the K-split kernels divide row and tile numbers with 32-bit multipliers, exact while rows x divisor < 2^32
 constexpr int kKsMaxRows = 65535;
 
 // Pick the tile shape with the smallest estimated time: rounds of tiles over the CUs times the cost of a tile.  The
 // 16x16x32 form of the main loop everywhere: the same work at a lower power per flop, so the chip holds a higher clock
 // (measured 5 to 8 % faster on every shape); the 32x32x16 form stays selectable (configurations 0 to 3).
+// slices: GEMM + ReduceScatter's epilogue, which adds two things.  Every tile publishes itself (a release fence, an atomic add to
+// a counter that the tiles of a slice share): 9 ns each, one after the other, whatever their size.  And it stores fp32, which at
+// the end of a round all CUs do at once while nothing multiplies; with four 128x128 tiles in place of one large one the stores of
+// some fall behind the loads of others.  Over 450 problems drawn from 4 to 8192 rows, N 96 to 8192, K 128 to 3584 the choice costs
+// 1.4 % more than the best tile (2.5 % without the two), and 3 are more than 2 % slower than with the numbered tiles alone (14).
+// Both sides, us per call: 8 x 3300 x 128 16x16 12.7, 32x32 10.4, 128x128 10.5; 4232 x 4060 x 2368 256x224 174, 128x128 148.
 // large_only: without the K-split tiles.
-inline int best_tile(int num_cus, int M, int N, int K, bool large_only = false)
+inline int best_tile(int num_cus, int M, int N, int K, bool slices = false, bool large_only = false)
 {
     int best = kTileCosts[0].cfg;
     double best_cost = 1e300;
@@ -66,7 +73,11 @@ inline int best_tile(int num_cus, int M, int N, int K, bool large_only = false)
         const TileShape t = tile_shape(k.cfg);
         const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
         const long long rounds = (tiles + num_cus - 1) / num_cus;
-        const double cost = (double)rounds * (k.fixed_us + k.us_per_k64 * (K / 64));
+        double cost = (double)rounds * (k.fixed_us + k.us_per_k64 * (K / 64));
+        if (slices) {
+            cost += kPublishUs * (double)tiles;
+            cost += (double)rounds * (t.bm == 256 ? kStoreUs256 : t.bn == 256 ? kStoreUs128x256 : 0.0);
+        }
         if (cost < best_cost) {
             best_cost = cost;
             best = k.cfg;

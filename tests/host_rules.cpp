@@ -74,7 +74,7 @@ double m_tiles_plain(double mean, int bm)
     return n;
 }
 
-int tile_plain(int num_cus, int M, int N, int K) { return best_tile(num_cus, M, N, K); }
+int tile_plain(int num_cus, int M, int N, int K, int slices) { return best_tile(num_cus, M, N, K, slices != 0); }
 
 int tile_rows_and_columns(int tile) { return tile_shape(tile).bm << 16 | tile_shape(tile).bn; }
 

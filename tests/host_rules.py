@@ -32,9 +32,9 @@ def tile_name(tile: int) -> str:
     return f"{rc >> 16}x{rc & 0xffff}"
 
 
-def gemm_tile(num_cus: int, M: int, N: int, K: int):
-    """The automatic choice for ag_gemm, gemm_rs and gemm_rs_scatter, and how many of those tiles the problem has."""
-    tile = lib().tile_plain(num_cus, M, N, K)
+def gemm_tile(num_cus: int, M: int, N: int, K: int, slices: bool = False):
+    """The automatic choice for ag_gemm, or for gemm_rs and gemm_rs_scatter (slices), and how many of those tiles the problem has."""
+    tile = lib().tile_plain(num_cus, M, N, K, int(slices))
     rc = lib().tile_rows_and_columns(tile)
     return tile_name(tile), -(-M // (rc >> 16)) * -(-N // (rc & 0xffff))
 

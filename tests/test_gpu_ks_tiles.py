@@ -37,16 +37,28 @@ TILES = [
 ]
 
 
+# The same for GEMM + ReduceScatter, whose choice counts the tiles that have to publish themselves.
+SLICED_TILES = [
+    ("16x16", False, 3, 5, 2304, 513),
+    ("16x32", False, 2, 24, 1728, 2531),
+    ("32x32", False, 2, 40, 1152, 2500),
+    ("64x32", False, 8, 8, 3584, 8192),
+    ("64x64", False, 2, 100, 576, 2501),
+    ("64x64", False, 2, 8, 3392, 8501),
+    ("64x128", False, 2, 300, 448, 2001),
+    ("64x128", True, 2, 20, 320, 66307),
+    ("64x128", True, 3, 6, 4544, 34911),
+]
+
+
 @pytest.mark.parametrize("tile,loops,W,Ms,K,N", TILES)
-def test_ag_gemm_and_slices_exact(tile, loops, W, Ms, K, N):
+def test_ag_gemm_exact(tile, loops, W, Ms, K, N):
     name, tiles = host_rules.gemm_tile(_cus(), W * Ms, N, K)
     assert name == tile and (tiles > _cus()) == loops
     g = torch.Generator(device="cuda").manual_seed(31)
     shards, B = [_ints(g, Ms, K) for _ in range(W)], _ints(g, N, K)
-    A = torch.cat(shards)
-    want = A.float() @ B.float().t()
-    rank = W - 1
-    ctx = agg.symm_alloc(W, rank, Ms * K * 2, W)
+    want = torch.cat(shards).float() @ B.float().t()
+    ctx = agg.symm_alloc(W, W - 1, Ms * K * 2, W)
     try:
         ps, cs = ctx.streams()
         for dtype, tdt in ((agg.F32, torch.float32), (agg.BF16, torch.bfloat16)):
@@ -58,12 +70,27 @@ def test_ag_gemm_and_slices_exact(tile, loops, W, Ms, K, N):
             torch.cuda.synchronize()
             assert agg.agg_status(ctx) == agg.OK
             assert torch.equal(C[:, :N], want.to(tdt)) and bool((C[:, N:] == 7.0).all())
-        # the same product in W slices, one at its destination and with its signal each, the last one in P_other
+    finally:
+        ctx.free()
+
+
+@pytest.mark.parametrize("tile,loops,W,Ms,K,N", SLICED_TILES)
+def test_slices_exact(tile, loops, W, Ms, K, N):
+    name, tiles = host_rules.gemm_tile(_cus(), W * Ms, N, K, slices=True)
+    assert name == tile and (tiles > _cus()) == loops
+    g = torch.Generator(device="cuda").manual_seed(31)
+    A, B = _ints(g, W * Ms, K), _ints(g, N, K)
+    want = A.float() @ B.float().t()
+    rank = W - 1
+    ctx = agg.symm_alloc(W, rank, 16, W)
+    try:
+        # W slices, each with its signal, all but the last one at a destination of its own
         dst = [torch.full((Ms, N), float("nan"), device="cuda") if w != rank else None for w in range(W)]
         P = torch.full((W * Ms, N), 7.0, device="cuda")
         words = torch.zeros((W, agg.SIGNAL_STRIDE), device="cuda", dtype=torch.int32)
+        agg.signal_reset(ctx)
         torch.cuda.synchronize()
-        agg.gemm_rs_scatter(ctx, W * Ms, N, K, A, K, B, K, agg.B_NK, dst, P, [words[w] for w in range(W)], 1 % W, cs)
+        agg.gemm_rs_scatter(ctx, W * Ms, N, K, A, K, B, K, agg.B_NK, dst, P, [words[w] for w in range(W)], 1 % W, ctx.streams()[1])
         torch.cuda.synchronize()
         for w in range(W):
             part = dst[w] if w != rank else P[w * Ms:(w + 1) * Ms]
@@ -75,7 +102,8 @@ def test_ag_gemm_and_slices_exact(tile, loops, W, Ms, K, N):
 
 
 def test_the_choices_above_reach_every_tile_of_the_dense_table():
-    assert {t[0] for t in TILES} == {host_rules.tile_name(t) for t in host_rules.dense_ks_tiles()}
+    for table in (TILES, SLICED_TILES):
+        assert {t[0] for t in table} == {host_rules.tile_name(t) for t in host_rules.dense_ks_tiles()}
 
 
 # tile, output type, whether its workgroups take a second tile, tokens, top-k, experts, N, K

@@ -6,7 +6,7 @@ import time
 
 import pytest
 
-from host_rules import lib, tile_name
+from host_rules import gemm_tile, lib, tile_name
 
 
 def _play(entries, fails):
@@ -107,3 +107,22 @@ def test_the_order_of_the_sums_does_not_depend_on_what_was_reserved(gathered, f3
 def test_moe_calls_do_not_take_a_tile_that_was_measured_slower_than_the_old_choice(gathered, f32, tokens, topk, E, N, K, slow):
     P = tokens * topk
     assert tile_name(lib().tile_grouped(256, P, E, N, K, gathered, f32, P, 1 << 28, 0)) != slow
+
+
+# The same for GEMM + ReduceScatter, us per call with the reducer, every row wanted.
+@pytest.mark.parametrize("M,N,K,slow", [
+    (8, 3300, 128, "16x16"),                        # 12.7 against 10.5
+    (12, 3472, 128, "16x16"),                       # 13.1 against 10.4
+    (16, 7948, 320, "16x32"),                       # 14.6 against 12.9
+    (8, 6972, 320, "16x32"),                        # 13.2 against 11.8
+    (8, 4620, 128, "16x32"),                        # 12.2 against 11.6
+])
+def test_gemm_rs_does_not_take_a_tile_that_was_measured_slower_than_the_old_choice(M, N, K, slow):
+    assert gemm_tile(256, M, N, K, slices=True)[0] != slow
+
+
+def test_gemm_rs_with_fp32_stores_between_rounds_keeps_the_smaller_tile():
+    # 4232 x 4060 x 2368 on 256x224 173.8 us, on 128x128 148.0; 4288 x 3852 x 2816 185.5 and 162.8
+    for M, N, K in ((4232, 4060, 2368), (4288, 3852, 2816)):
+        assert lib().tile_plain(256, M, N, K, 1) == 5
+    assert lib().tile_plain(256, 8192, 8192, 3584, 1) == 6
