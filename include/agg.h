@@ -160,7 +160,9 @@ int ag_producer_emulate(agg_ctx* ctx, const void* const* remote_shards, const in
  * C[M, N] = A[M, K] . B with A = T viewed as [M, K] bf16 row-major (lda = K; M = W * Ms, shard r = rows
  * [r*Ms, (r+1)*Ms), so shard_bytes must equal Ms*K*2), B bf16 in the layout b_layout names with leading
  * dimension ldb (elements), C row-major with leading dimension ldc (elements) of type c_dtype.
- * Accumulation is fp32; bf16 output is rounded to nearest even from the fp32 accumulator.
+ * Accumulation is fp32; bf16 output is rounded to nearest even from the fp32 accumulator.  How the sum over K is grouped
+ * depends on the tile, and the automatic choice of the tile on M, N and K: see agg_set_tile_config for results whose bits do
+ * not depend on the batch.
  * Each tile waits (acquire) for every signal covering its rows to reach the current epoch before its
  * first load of A.  Requirements: K % 64 == 0, M % W == 0; for AGG_B_NK ldb % 8 == 0 and B 16-byte aligned;
  * C aligned to its element size; M, N arbitrary (>= 0; 0 is a no-op).
@@ -333,7 +335,8 @@ int agg_set_local_shard(agg_ctx* ctx, const void* local_shard);
  * peers' shards whole, in pull order rank+1, rank+2, ... -- matches a producer that delivers one shard after the
  * other (a switched fabric).  AGG_ORDER_SUBCHUNK: the local shard, then the first chunk of every peer, the second
  * chunk of every peer, ... -- matches AGG_PRODUCER_LINKS (a full mesh, every peer on its own link).  It needs
- * shards and chunks that are whole numbers of tile rows and is otherwise ignored.  The result is the same bit for
+ * shards and chunks that are whole numbers of tile rows, and one of the numbered tile shapes (the small tiles that the
+ * automatic choice takes for small problems go column block by column block); it is otherwise ignored.  The result is the same bit for
  * bit in either order.
  */
 enum { AGG_ORDER_ROTATED = 0, AGG_ORDER_SUBCHUNK = 1 };
@@ -396,7 +399,11 @@ int moe_rs(agg_ctx* ctx, int Ttok, int topk, int E, int N, int Klocal,
  * (the sum over K runs in the same order in all of them); the two forms group the sum over K differently (16 or 32
  * terms per instruction) and may differ in the last bits, both within the tolerance.  The automatic choice also has smaller
  * tiles for problems that would leave most of the chip idle with these; they cannot be selected by number, and they add up
- * K in a few partial sums (fp32, fixed order), so their last bits may differ as well. */
+ * K in a few partial sums (fp32, fixed order), so their last bits may differ as well.  Which tile a call takes follows from
+ * its sizes alone: M, N and K for ag_gemm, gemm_rs and gemm_rs_scatter (the whole product's, also where only the own rows are
+ * computed); tokens, top-k, experts, N, K and the output type for ag_moe_gemm and moe_rs.  Repeated calls give the same bits,
+ * but a row may come out with other last bits in a batch of another size.  Where that matters, set a configuration (4 is the
+ * form of the automatic choice): all shapes of it give a row the same bits whatever M, N or the number of experts. */
 int agg_set_tile_config(agg_ctx* ctx, int tile_config);
 
 /*
