@@ -14,8 +14,9 @@
 // different rows) runs at 16 B/clk per compute unit, whole 128-byte lines at 57.  What a workgroup does before its first
 // load counts as much as the loads (10 % to 30 % of a launch here): the launch's arguments are one compact struct, and no
 // integer is divided on the way (multipliers come from the host): 10.0 -> 8.5 us at 16 x 3584 x 4096.
-// The time left is B from HBM (5.4 TB/s) plus A through the load path (118 KB/us per compute unit): the two add up, the
-// path holds only about 24 KiB of misses and hits queue behind them.
+// The time left is B from HBM (5.4 to 6.4 TB/s) plus A through the load path (118 KB/us per compute unit): the two add up, the
+// path holds only about 24 KiB of misses and hits queue behind them.  What is not near any bound is the start: every instance
+// spills 30 to 110 scalar registers (each slot's stage bound and descriptor are lifted out of the tile loop).
 //
 // Measured against the 128x128 tile of the large kernel (us per GEMM, B not in cache): 16 x 3584 x 4096 24.9 -> 8.5 (16x16
 // tiles), 64 x 8192 x 3584 33.3 -> 18.5 (64x32), 128 x 7168 x 8192 74.6 -> 42 (64x64), 999 x 1999 x 1984 21 -> 15.6 (64x128).

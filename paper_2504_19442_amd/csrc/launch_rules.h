@@ -40,7 +40,8 @@ inline TileShape tile_shape(int cfg)
 // of K.  From sweeps of M, N, K with every shape: what a tile costs follows the bytes it pulls through its compute unit's
 // load path, (BM + BN) x 128 per 64 of K at about 70 KB/us, up to 128 x 128; the large tiles are bound by the matrix pipes
 // at the clock the chip holds with all of them busy.  Over 60 shapes drawn from M 16..8192, N 96..7168, K 256..8192 (over
-// their logarithms) the choice costs 1.7 % more than the best shape of each.  Where the line lies, both sides measured in
+// their logarithms) the choice costs 1.4 % more than the best shape of each, and it is the best or within 2 % of it on 54
+// (profiles/tile_choice.txt).  Where the line lies, both sides measured in
 // us: 16x3584x4096 16x16 8.7, 128x128 24.9; 64x8192x3584 64x32 19.1, 64x64 22, 128x128 33; 128x7168x8192 64x64 42,
 // 128x128 75; 999x1999x1984 64x128 17.2, 128x128 21; 1024x3584x4096 128x128 34, 64x128 51.
 struct TileCost { int cfg; double fixed_us, us_per_k64; };

@@ -5,7 +5,7 @@
 // access; streaming stores.
 // What is left beside the bytes is the start: the signals are looked at by the lanes of one wave side by side (one after
 // the other by one thread, each a trip to memory, cost 4 us per workgroup), and where all slots are there the first
-// block is loaded like every other.  Eight slots of 1024 x 8192 (302 MB, in no cache) 64.7 -> 59.6 us (54.6 with the loads
+// block is loaded like every other.  Eight slots of 1024 x 8192 (268 MB read, 34 written, in no cache) 64.7 -> 59.6 us (54.6 with the loads
 // launch_reduce picks), of 8 x 8192 5.2 -> 3.6;
 // six slots of 512 x 4096 20.6 -> 15.6 and sixteen of 256 x 4096 29.8 -> 18.1 (four slots' loads in flight together
 // where no kernel is unrolled for the world size).
@@ -201,13 +201,17 @@ static void launch_reduce_nt(const ReduceArgs& a, int n_workgroups, hipStream_t 
     }
 }
 
-// Slots that together exceed the memory-side cache (256 MB) come from HBM whatever the loads ask for, and loads with the
-// streaming hint run faster then: eight slots of 1024 x 8192 (268 MB) that were not read before 59.7 us, with the hint 54.6
-// (in a loop over one and the same slots, a part of which the cache then keeps, it is the other way round: 49 and 53).
-// Below, ordinary loads: 67 MB in two slots 25.1 and 24.4, 134 MB in four 34.6 and 34.5, 33 MB in four 12.0 and 12.8.
+// From 256 MB of slots on, the size of the memory-side cache, the loads carry the streaming hint.  Both sides, us, ordinary loads
+// and hint, eight slots of 1024 x 8192 (268 MB): slots not touched lately 59.0 and 54.2, slots that have just been written
+// 53.7 and 54.4; 336 MB: 72.9 and 66.1, just written 81 and 64.  Four slots of 2048 x 8192 64.0 and 61.3, just written 73.5 and
+// 72.2; two 78.2 and 76.5, just written 87.6 and 83.4.  What loses is a loop that reads one and the same slots without anyone
+// writing them in between (part of them then stays in that cache): 47.2 and 52.0, with four slots 49.4 and 59.8; from
+// 336 MB on that, too, is faster with the hint (68.1 and 64.6).  Below the line the hint gains on slots not touched lately (134 MB
+// 34.1 and 30.6, 201 MB 46.2 and 41.8) and loses up to 5 % on ones that the cache holds, which slots of that size usually
+// are: ordinary loads.
 hipError_t launch_reduce(const ReduceArgs& a, int n_workgroups, hipStream_t stream, bool beside_gemm)
 {
-    if (a.n_vec4 * 16 * a.W > (256ll << 20) - 1) launch_reduce_nt<true>(a, n_workgroups, stream, beside_gemm);
+    if (a.n_vec4 * 16 * a.W >= (256ll << 20)) launch_reduce_nt<true>(a, n_workgroups, stream, beside_gemm);
     else launch_reduce_nt<false>(a, n_workgroups, stream, beside_gemm);
     return hipGetLastError();
 }
