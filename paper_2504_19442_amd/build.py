@@ -43,7 +43,7 @@ def check_agprs(asm_path: str) -> None:
 
 
 def _is_gemm_unit(src: str) -> bool:
-    return os.path.basename(src).startswith("gemm_inst_")
+    return os.path.basename(src).startswith(("gemm_inst_", "gemm_pipe_"))
 
 
 def _compile(src: str) -> str:

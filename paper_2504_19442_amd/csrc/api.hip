@@ -318,7 +318,7 @@ int agg_set_link_rate(agg_ctx* c, double gigabytes_per_second)
 
 int agg_set_tile_config(agg_ctx* c, int cfg)
 {
-    if (!c || cfg < -1 || cfg >= TILE_CONFIGS) return AGG_ERR_INVALID_ARG;
+    if (!c || cfg < -1 || cfg >= TILE_NUMBERED) return AGG_ERR_INVALID_ARG;
     c->tile_config = cfg;
     return AGG_OK;
 }

@@ -64,39 +64,17 @@ __device__ __forceinline__ float acc_read()
 
 [[maybe_unused]] constexpr int QS = 4;   // quarter-steps (K = 16 each) per stage
 
+// A tile of BM x BN by four waves, wave w owning rows [w TM, (w + 1) TM), and the schedule of the 16x16x32 form of the main loop.
 template <int BM, int BN>
-struct Cfg {
+struct TileCfg {
     static constexpr int TM = BM / 4;            // rows per wave
-    static constexpr int MB = TM / 32;           // 32x32 blocks per wave, M direction
-    static constexpr int NB = BN / 32;           // and N direction
-    static constexpr int ACC = MB * NB * 16;     // accumulator registers per lane
+    static constexpr int ACC = TM * BN / 64;     // accumulator registers per lane
     static constexpr int A_UNITS = BM / UNIT_ROWS;
     static constexpr int B_UNITS = BN / UNIT_ROWS;
     static constexpr int UNITS = A_UNITS + B_UNITS;
     static constexpr int L = UNITS / 4;          // load instructions per wave per stage
-    static constexpr int STAGE_BYTES = (BM + BN) * ROW_BYTES;
-    // The LDS ring holds RW loads per wave (4 KiB each: the same load of all four waves), a stage is L of them.
-    // RW >= 2 L; RW need not be a multiple of L: the stream of loads simply wraps around the ring, so that the
-    // whole LDS is used as look-ahead even when only 2 1/3 stages fit.
-    static constexpr int RW = (BN == 256) ? 36 : (BM == 256) ? 35 : 32;
-    static constexpr int RING_BYTES = RW * 4096;
-    static constexpr int PERIOD = std::lcm(L, RW) / L;     // stages after which ring positions repeat
-    // epilogue staging: each wave stages 32 rows x BN columns at a time
-    static constexpr int PITCH_BF16 = BN * 2 + 16;
-    static constexpr int PITCH_F32 = BN * 4 + 16;
-    static constexpr int LDS_BYTES = (RING_BYTES > 4 * 32 * PITCH_F32) ? RING_BYTES : 4 * 32 * PITCH_F32;
-    static_assert(BM % 128 == 0 && BN % 32 == 0, "tile shape");
+    static_assert(BM % 64 == 0 && BN % 32 == 0, "tile shape");
     static_assert(A_UNITS % 4 == 0 && B_UNITS % 4 == 0, "units must split evenly over 4 waves");
-    static_assert(RW >= 2 * L && RW <= 63, "ring: at least two stages, and the prologue's loads fit the vmcnt range");
-    static_assert(PERIOD <= 9, "the main loop is unrolled over PERIOD stages");
-    static_assert(ACC == 64 || ACC == 128 || ACC == 224 || ACC == 256, "add a reservation line for this accumulator count");
-    // One quarter-step is SLOTS = MB*NB MFMAs.  Its memory instructions, in order: LQ global->LDS loads
-    // (while a stage's loads are being issued: the three quarter-steps after a barrier), then the F = MB+NB
-    // fragment reads of the next quarter-step.  They are dealt out QUOTA per MFMA slot.
-    static constexpr int SLOTS = MB * NB;
-    static constexpr int F = MB + NB;
-    static constexpr int LQ = (L + 2) / 3;   // loads per quarter-step while a batch is issued
-    static constexpr int QUOTA = (LQ + F + SLOTS - 1) / SLOTS;
 
     // ---- the 16x16x32 form of the main loop (MF = 16).  A stage is two half-steps of K = 32; a half-step is NB16 groups
     // of MB16 MFMAs, group j working on the B fragment of column block j and all MB16 A fragments of the wave.
@@ -112,8 +90,7 @@ struct Cfg {
     static constexpr int LH1_ = (NS - SB + PACE - 1) / PACE;
     static constexpr int LH1 = LH1_ < L ? LH1_ : L;   // loads issued in the rest of the second half-step
     static constexpr int LH0 = L - LH1;          // the others: in the next stage's first half-step
-    static constexpr int P0 = RW - L + LH1;      // loads issued by the prologue
-    static_assert(SB + (L - 1) * PACE < 2 * NS && P0 >= L && P0 <= 63, "load schedule of the 16x16x32 loop");
+    static_assert(SB + (L - 1) * PACE < 2 * NS, "load schedule of the 16x16x32 loop");
     static_assert(DLY + MB16 <= NB16, "the reads of the next A fragments fit between the barrier and the end of the half-step");
     struct Op { int type, idx; };                // 0 none, 1 read B fragment idx, 2 read A fragment idx, 3 global->LDS load idx
     static constexpr int PER_SLOT = 3;
@@ -153,6 +130,38 @@ struct Cfg {
         return S;
     }
     static_assert(make_slots(0).complete && make_slots(1).complete, "every memory operation of a half-step has a slot");
+};
+
+template <int BM, int BN>
+struct Cfg : TileCfg<BM, BN> {
+    using T_ = TileCfg<BM, BN>;
+    static constexpr int L = T_::L, TM = T_::TM, ACC = T_::ACC;
+    static constexpr int MB = TM / 32;           // 32x32 blocks per wave, M direction
+    static constexpr int NB = BN / 32;           // and N direction
+    static constexpr int STAGE_BYTES = (BM + BN) * ROW_BYTES;
+    // The LDS ring holds RW loads per wave (4 KiB each: the same load of all four waves), a stage is L of them.
+    // RW >= 2 L; RW need not be a multiple of L: the stream of loads simply wraps around the ring, so that the
+    // whole LDS is used as look-ahead even when only 2 1/3 stages fit.
+    static constexpr int RW = (BN == 256) ? 36 : (BM == 256) ? 35 : 32;
+    static constexpr int RING_BYTES = RW * 4096;
+    static constexpr int PERIOD = std::lcm(L, RW) / L;     // stages after which ring positions repeat
+    // epilogue staging: each wave stages 32 rows x BN columns at a time
+    static constexpr int PITCH_BF16 = BN * 2 + 16;
+    static constexpr int PITCH_F32 = BN * 4 + 16;
+    static constexpr int LDS_BYTES = (RING_BYTES > 4 * 32 * PITCH_F32) ? RING_BYTES : 4 * 32 * PITCH_F32;
+    static_assert(BM % 128 == 0 && BN % 32 == 0, "tile shape");
+    static_assert(RW >= 2 * L && RW <= 63, "ring: at least two stages, and the prologue's loads fit the vmcnt range");
+    static_assert(PERIOD <= 9, "the main loop is unrolled over PERIOD stages");
+    static_assert(ACC == 64 || ACC == 128 || ACC == 224 || ACC == 256, "add a reservation line for this accumulator count");
+    // One quarter-step is SLOTS = MB*NB MFMAs.  Its memory instructions, in order: LQ global->LDS loads
+    // (while a stage's loads are being issued: the three quarter-steps after a barrier), then the F = MB+NB
+    // fragment reads of the next quarter-step.  They are dealt out QUOTA per MFMA slot.
+    static constexpr int SLOTS = MB * NB;
+    static constexpr int F = MB + NB;
+    static constexpr int LQ = (L + 2) / 3;   // loads per quarter-step while a batch is issued
+    static constexpr int QUOTA = (LQ + F + SLOTS - 1) / SLOTS;
+    static constexpr int P0 = RW - L + T_::LH1;  // loads issued by the prologue of the 16x16x32 form
+    static_assert(P0 >= L && P0 <= 63, "load schedule of the 16x16x32 loop");
 };
 
 // Register budget: 448 of the 512 registers a SIMD has (see the file comment).

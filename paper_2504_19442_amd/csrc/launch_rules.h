@@ -9,16 +9,23 @@ namespace agg {
 
 // A tile configuration = a tile shape (bits 0-1) and the MFMA form of the main loop (bit 2): v_mfma_f32_32x32x16_bf16,
 // or, with TILE_K32, v_mfma_f32_16x16x32_bf16 (half the accumulator traffic per flop: the chip holds a higher clock).
-enum TileConfig { TILE_256x224 = 0, TILE_128x128 = 1, TILE_256x256 = 2, TILE_128x256 = 3, TILE_K32 = 4, TILE_CONFIGS = 8 };
+// Those are what agg_set_tile_config takes.  The tiles of gemm_pipe.h (grouped GEMM, 16x16x32 form: the same bits) belong to the
+// automatic choice alone.
+enum TileConfig { TILE_256x224 = 0, TILE_128x128 = 1, TILE_256x256 = 2, TILE_128x256 = 3, TILE_K32 = 4, TILE_NUMBERED = 8,
+                  PIPE_128x192 = TILE_NUMBERED, PIPE_128x224, PIPE_192x192, PIPE_320x128, TILE_CONFIGS };
 
 // Tile configurations of the K-split kernels (gemm_ks.h): what the automatic choice takes where the tiles above would leave
 // most of the chip idle; not selectable by number.
-enum KsTileConfig { KS_16x16 = 8, KS_16x32, KS_16x64, KS_32x32, KS_64x32, KS_64x64, KS_64x128, KS_CONFIGS_END };
+enum KsTileConfig { KS_16x16 = TILE_CONFIGS, KS_16x32, KS_16x64, KS_32x32, KS_64x32, KS_64x64, KS_64x128, KS_CONFIGS_END };
 
 struct TileShape { int bm, bn; };
 inline TileShape tile_shape(int cfg)
 {
     switch (cfg) {
+        case PIPE_128x192: return {128, 192};
+        case PIPE_128x224: return {128, 224};
+        case PIPE_192x192: return {192, 192};
+        case PIPE_320x128: return {320, 128};
         case KS_16x16: return {16, 16};
         case KS_16x32: return {16, 32};
         case KS_16x64: return {16, 64};
@@ -131,11 +138,14 @@ inline double expected_m_tiles(double mean, int bm)
 // tile for 740 problems drawn from 4 to 8192 tokens, 4 to 64 experts, top-1 to 4, N 96 to 2048, K 64 to 4096 (gathered rows in bf16
 // and fp32, rows in place): the choice costs 0.7 % more than the best tile of each (geometric mean; 0.8 % on 370 other draws) and takes
 // 12 % less time than the choice among 256x224, 256x256 and 128x128 alone, which is faster by more than 5 % on 12 of the 1110, by
-// more than 10 % on two.
+// more than 10 % on two.  The costs of the tiles of gemm_pipe.h are fitted to 800 further draws, half of them with 256 and
+// more tokens per rank: on 800 others the choice with them takes 5.7 % less time for gathered rows and 1 % for rows in place than without
+// them, is slower by more than 5 % on 6 and by more than 10 % on two, and costs 1 % more than the best tile.
 constexpr TileCost kTileCostsGrouped[] = {
     {KS_16x32, 3.4, 0.113}, {KS_16x64, 3.4, 0.179}, {KS_32x32, 2.6, 0.142}, {KS_64x64, 3.3, 0.267}, {KS_64x128, 3.5, 0.40},
     {TILE_128x128 | TILE_K32, 3.0, 0.60}, {TILE_128x256 | TILE_K32, 2.9, 0.94}, {TILE_256x224 | TILE_K32, 4.1, 1.50},
     {TILE_256x256 | TILE_K32, 4.0, 1.73},
+    {PIPE_128x192, 3.7, 0.723}, {PIPE_128x224, 3.3, 0.854}, {PIPE_192x192, 2.7, 1.007}, {PIPE_320x128, 2.9, 1.004},
 };
 constexpr double kGroupedStoreBytesPerUs = 82e3;     // fp32 rows, per compute unit
 constexpr double kGroupedWeightBytesPerUs = 7.2e6;   // weights of the experts that have rows, whole chip
@@ -145,12 +155,13 @@ constexpr double kGroupedWeightBytesPerUs = 7.2e6;   // weights of the experts t
 // bound it, a last round that fills only part of the chip costs its share of that time, and the smaller tile wins.  Measured,
 // us per call with routing, bf16 out, Table 4: 64 tokens (two rows per expert) 16x64 149, 16x32 154, 64x64 158, 128x128 196; 512
 // tokens 64x64 190, 64x128 197, 32x32 197, 128x128 226; 2048 tokens 128x128 232, 64x128 277.  Rows in place with K = 192 and fp32
-// out (the GEMM of Table 5, kernel alone, cold): 256x256 70, 128x256 63, 128x128 71.  Gathered rows never take 128x256: at 8192
-// tokens of Table 4, the one size where it was looked at closely, the whole call is 1 % faster in bf16 (374 against 376) but its
-// first pass on new weights 5 % slower (457 against 435), and in fp32 it is 5 % slower throughout (392 against 371).  (At other sizes
-// of the draws it would be the best tile, by up to a fifth.)
-// Which K-split tile is taken, or that a numbered one is, follows from the problem alone: the small tiles are left out where their
-// table (P pairs) would have more entries than the static one, whatever table is used.  Among the numbered ones, which all give
+// out (the GEMM of Table 5, kernel alone, cold): 256x256 70, 128x256 63, 128x128 71.  Gathered rows never take the 128x256 tile of the large
+// kernel: at 8192 tokens of Table 4 the whole call is 1 % faster in bf16 (374 against 376) but its first pass on new weights 5 % slower
+// (457 against 435), and in fp32 it is 5 % slower throughout (392 against 371); where it would be the best of the numbered tiles, that
+// of gemm_pipe.h is faster.  There, with routing, weights beyond the memory-side cache, us: 8192 tokens 320x128 298, 256x224 383,
+// 256x256 382; 4096 tokens 192x192 236, 320x128 281, 256x256 275.
+// Which K-split tile is taken, or that another one is, follows from the problem alone: the small tiles and those of gemm_pipe.h are left
+// out where their table (P pairs) would have more entries than the static one, whatever table is used.  Among the numbered ones, which all give
 // the same bits, those are left out whose table would have more than `tab_base` entries; -1 if that is all of them.
 inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, bool gathered, bool f32, long long P,
                              long long tab_base, bool large_only = false)
@@ -161,9 +172,12 @@ inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, b
     double best_cost = 1e300, fits_cost = 1e300;
     for (const TileCost& k : kTileCostsGrouped) {
         const TileShape t = tile_shape(k.cfg);
-        const bool small = k.cfg >= TILE_CONFIGS;
+        const bool small = k.cfg >= TILE_CONFIGS, numbered = k.cfg < TILE_NUMBERED;
         const long long entries = moe_table_entries(P, E, N, t);
-        if ((small && (large_only || entries > kStaticTabEntries)) || (gathered && t.bm == 128 && t.bn == 256)) continue;
+        if ((small && large_only) || (!numbered && entries > kStaticTabEntries) || (gathered && numbered && t.bm == 128 && t.bn == 256)) continue;
+        // a tile of gemm_pipe.h that is nearly empty: the weights' bytes are what counts, and the small tiles ask for more of them at a
+        // time (48 tokens, 3 rows per expert, 29 x 1659 x 2304: 128x192 72 us, 16x64 50)
+        if (!numbered && !small && (double)rows < active * t.bm / 8) continue;
         const double tiles = active * expected_m_tiles((double)rows / active, t.bm) * ((N + t.bn - 1) / t.bn);
         const double rounds = std::ceil(tiles / num_cus);
         const double tile_us = k.fixed_us + k.us_per_k64 * (K / 64) + (f32 ? t.bm * t.bn * 4 / kGroupedStoreBytesPerUs : 0.0);
@@ -172,12 +186,12 @@ inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, b
             best_cost = cost;
             best = k.cfg;
         }
-        if (!small && entries <= tab_base && cost < fits_cost) {
+        if (numbered && entries <= tab_base && cost < fits_cost) {
             fits_cost = cost;
             best_that_fits = k.cfg;
         }
     }
-    return best >= TILE_CONFIGS ? best : best_that_fits;
+    return best >= TILE_NUMBERED ? best : best_that_fits;
 }
 
 // Workgroups of a reducer launch over n_vec4 float4 whose caller leaves the size to the library.  Persistent, each walking

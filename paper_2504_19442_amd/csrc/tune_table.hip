@@ -24,7 +24,7 @@ bool valid_key(int W, int M, int N, int K) { return W >= 1 && W <= kMaxWorld && 
 // (the automatic choice, -1, has one order: its small tiles follow none)
 bool valid_entry(const agg_tune_result& r)
 {
-    return r.tile_config >= (r.tile_order == AGG_ORDER_ROTATED ? -1 : 0) && r.tile_config < TILE_CONFIGS &&
+    return r.tile_config >= (r.tile_order == AGG_ORDER_ROTATED ? -1 : 0) && r.tile_config < TILE_NUMBERED &&
            (r.tile_order == AGG_ORDER_ROTATED || r.tile_order == AGG_ORDER_SUBCHUNK) && r.producer_workgroups >= 0 &&
            r.producer_workgroups <= 4096 && r.configs_tried >= 0 && r.best_ms >= 0.f;
 }
