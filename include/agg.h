@@ -47,12 +47,13 @@ enum {
 
 enum { AGG_BF16 = 0, AGG_F32 = 1 };          /* element type of an output matrix */
 enum { AGG_B_NK = 0,                         /* B stored [N][K], K contiguous (weight layout of a linear layer): read in place */
-       AGG_B_KN = 1 };                       /* B stored [K][N], N contiguous: transposed into a buffer of the context
+       AGG_B_KN = 1 };                       /* B stored [K][N], N contiguous; ldb >= N.  With the automatic tile choice, B on
+                                                16 bytes and ldb and N multiples of 8, small and medium problems read
+                                                it in place.  Else it is transposed into a buffer of the context
                                                 on the GEMM's stream before every GEMM (one more pass over B; the
-                                                buffer is sized by agg_reserve_b_kn beforehand; calls with this
-                                                layout on one context share it: a call on another stream than the
-                                                previous one is made to wait, on the device, for that one's GEMM);
-                                                ldb >= N */
+                                                calls that do on one context share it: a call on another stream than the
+                                                previous one is made to wait, on the device, for that one's GEMM).
+                                                The buffer has to be there in both cases: agg_reserve_b_kn */
 enum { AGG_PRODUCER_KERNEL = 0,              /* copy kernel on a few CUs, release-stores the signals */
        AGG_PRODUCER_SDMA = 1,               /* copy engine (no compute units) + one 4-byte copy per signal */
        AGG_PRODUCER_LINKS = 2,              /* full mesh: every peer's shard on a "link" of its own, all at once, chunk by chunk */
@@ -161,8 +162,8 @@ int ag_producer_emulate(agg_ctx* ctx, const void* const* remote_shards, const in
  * [r*Ms, (r+1)*Ms), so shard_bytes must equal Ms*K*2), B bf16 in the layout b_layout names with leading
  * dimension ldb (elements), C row-major with leading dimension ldc (elements) of type c_dtype.
  * Accumulation is fp32; bf16 output is rounded to nearest even from the fp32 accumulator.  How the sum over K is grouped
- * depends on the tile, and the automatic choice of the tile on M, N and K: see agg_set_tile_config for results whose bits do
- * not depend on the batch.
+ * depends on the tile, and the automatic choice of the tile on M, N, K and, for AGG_B_KN, on whether B is read in place (see there):
+ * agg_set_tile_config gives results whose bits depend neither on the batch nor on the layout of B.
  * Each tile waits (acquire) for every signal covering its rows to reach the current epoch before its
  * first load of A.  Requirements: K % 64 == 0, M % W == 0; for AGG_B_NK ldb % 8 == 0 and B 16-byte aligned;
  * C aligned to its element size; M, N arbitrary (>= 0; 0 is a no-op).

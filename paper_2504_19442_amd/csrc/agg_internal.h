@@ -24,6 +24,7 @@ struct GemmParams {
     void* C;              // every row whose slice has no destination of its own
     long long lda, ldb, ldc;
     long long b_total_bytes;   // all of B (all groups' matrices)
+    int b_kn;                  // B is [K][N], ldb elements from one k to the next, and read in place (launch_rules.h: tile_kn)
     int M, N, K;
     int c_is_f32;
     // tile schedule (Section 3.7: rank-rotated order, local shard first)

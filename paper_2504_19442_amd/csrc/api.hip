@@ -77,18 +77,18 @@ int check_gemm_operands(int M, int N, int K, const void* B, int ldb, int b_layou
     return AGG_OK;
 }
 
-// The GEMM kernel reads B as [N][K].  A B given as [K][N] is transposed first, on the GEMM's stream, into a buffer
-// of the context that agg_reserve_b_kn has sized beforehand: the call itself allocates nothing.  Callers whose
-// weights do not change should store them as [N][K] and save the pass (2 x N x K x 2 bytes of traffic per call).
-int resolve_b(agg_ctx* c, const void* B, int ldb, int b_layout, int N, int K, hipStream_t stream, const uint16_t** B_nk,
+// The GEMM kernels read B as [N][K], those of gemm_ks_kn.hip as [K][N].  Where those do not apply, a B given as [K][N] is transposed first, on
+// the GEMM's stream, into a buffer of the context that agg_reserve_b_kn has sized beforehand: the call itself allocates nothing.
+// Callers whose weights do not change should store them as [N][K] and save the pass (2 x N x K x 2 bytes of traffic per call).
+int resolve_b(agg_ctx* c, const void* B, int ldb, int b_layout, int N, int K, hipStream_t stream, bool in_place, const uint16_t** B_nk,
               long long* ld_nk)
 {
-    if (b_layout == AGG_B_NK) {
+    if (b_layout == AGG_B_KN && c->b_nk_elems < (size_t)N * K) return AGG_ERR_NOT_RESERVED;      // (also where it is read in place)
+    if (b_layout == AGG_B_NK || in_place) {
         *B_nk = (const uint16_t*)B;
         *ld_nk = ldb;
         return AGG_OK;
     }
-    if (c->b_nk_elems < (size_t)N * K) return AGG_ERR_NOT_RESERVED;
     // the buffer is one per context: a call on another stream than the last one that used it first waits (on the
     // device) for that one's GEMM, so that two such calls can never read each other's transposed B
     if (c->b_nk_in_use && stream != c->b_nk_stream) HIP_TRY(hipStreamWaitEvent(stream, c->b_nk_free, 0));
@@ -98,10 +98,21 @@ int resolve_b(agg_ctx* c, const void* B, int ldb, int b_layout, int N, int K, hi
     return AGG_OK;
 }
 
-// After the launch of a GEMM that reads the context's transposed copy of B: mark where the buffer becomes free again.
-int b_kn_launched(agg_ctx* c, int b_layout, hipStream_t stream)
+// A B stored [K][N] that the automatic choice reads in place: *cfg becomes the tile for it.  False: it is to be transposed.  The loads are 16
+// bytes at multiples of 16, of columns that all exist; their offsets, to the stages past the end of K, stay below 2^31.
+bool kn_in_place(const agg_ctx* c, const void* B, int ldb, int b_layout, int M, int N, int K, bool slices, int* cfg)
 {
-    if (b_layout != AGG_B_KN) return AGG_OK;
+    if (b_layout != AGG_B_KN || !aligned16(B) || ldb % 8 != 0 || N % 8 != 0 || (long long)(K + 1024) * ldb * 2 >= (1ll << 31)) return false;
+    if (c->tile_config >= 0) return false;      // a tile asked for by number: the transposed copy, and its bits
+    const int t = tile_kn(c->num_cus, *cfg, M, N, K, slices);
+    if (t >= 0) *cfg = t;
+    return t >= 0;
+}
+
+// After the launch of a GEMM that reads the context's transposed copy of B: mark where the buffer becomes free again.
+int b_kn_launched(agg_ctx* c, int b_layout, bool in_place, hipStream_t stream)
+{
+    if (b_layout != AGG_B_KN || in_place) return AGG_OK;
     HIP_TRY(hipEventRecord(c->b_nk_free, stream));
     c->b_nk_stream = stream;
     c->b_nk_in_use = 1;
@@ -503,8 +514,10 @@ int ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb, int b_layou
     p.A_local = (const uint16_t*)c->local_shard;
     p.local_lo = c->rank * Ms;
     p.local_hi = p.local_lo + Ms;
-    if ((rc = resolve_b(c, B, ldb, b_layout, N, K, (hipStream_t)consumer_stream, &p.B, &p.ldb)) != AGG_OK) return rc;
-    p.b_total_bytes = p.ldb * N * 2;
+    int cfg = choose_tile(c, M, N, K);
+    p.b_kn = kn_in_place(c, B, ldb, b_layout, M, N, K, false, &cfg);
+    if ((rc = resolve_b(c, B, ldb, b_layout, N, K, (hipStream_t)consumer_stream, p.b_kn, &p.B, &p.ldb)) != AGG_OK) return rc;
+    p.b_total_bytes = p.b_kn ? 2 * p.ldb * K : 2 * p.ldb * N;
     p.C = C;
     p.lda = K;
     p.ldc = ldc;
@@ -512,7 +525,6 @@ int ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb, int b_layou
     p.N = N;
     p.K = K;
     p.c_is_f32 = c_dtype == AGG_F32;
-    const int cfg = choose_tile(c, M, N, K);
     fill_schedule(c, p, cfg, Ms, c->rank * Ms);
     {
         // sub-chunk order (Section 3.7, full mesh): possible when shards and chunks are whole numbers of tiles
@@ -536,7 +548,7 @@ int ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb, int b_layou
     const long long tiles = (long long)p.tiles_m * p.tiles_n;
     const int grid = gemm_grid(c, cfg, tiles);
     if ((rc = hip_fail(launch_gemm(p, cfg, grid, (hipStream_t)consumer_stream))) != AGG_OK) return rc;
-    return b_kn_launched(c, b_layout, (hipStream_t)consumer_stream);
+    return b_kn_launched(c, b_layout, p.b_kn, (hipStream_t)consumer_stream);
 }
 
 static int reduce_impl(agg_ctx* c, int Ms, int N, const float* const* slots, void* R, int ldr, int r_dtype, int n_workgroups,
@@ -720,8 +732,10 @@ int gemm_rs_scatter(agg_ctx* c, int M, int N, int Kl, const void* A_local, int l
 
     GemmParams p{};
     p.A = (const uint16_t*)A_local;
-    if ((rc = resolve_b(c, B_local, ldb, b_layout, N, Kl, (hipStream_t)gemm_stream, &p.B, &p.ldb)) != AGG_OK) return rc;
-    p.b_total_bytes = p.ldb * N * 2;
+    int cfg = choose_tile(c, M, N, Kl, true);
+    p.b_kn = kn_in_place(c, B_local, ldb, b_layout, M, N, Kl, true, &cfg);
+    if ((rc = resolve_b(c, B_local, ldb, b_layout, N, Kl, (hipStream_t)gemm_stream, p.b_kn, &p.B, &p.ldb)) != AGG_OK) return rc;
+    p.b_total_bytes = p.b_kn ? 2 * p.ldb * Kl : 2 * p.ldb * N;
     p.C = P_other;
     p.lda = lda;
     p.ldc = N;
@@ -743,12 +757,11 @@ int gemm_rs_scatter(agg_ctx* c, int M, int N, int Kl, const void* A_local, int l
         p.slice_dst[w] = slice_dst[w];
         p.slice_flag[w] = slice_signal ? slice_signal[w] : nullptr;
     }
-    const int cfg = choose_tile(c, M, N, Kl, true);
     fill_schedule(c, p, cfg, Ms, first_slice * Ms);
     const long long tiles = (long long)p.tiles_m * p.tiles_n;
     const int grid = gemm_grid(c, cfg, tiles);
     if ((rc = hip_fail(launch_gemm(p, cfg, grid, (hipStream_t)gemm_stream))) != AGG_OK) return rc;
-    return b_kn_launched(c, b_layout, (hipStream_t)gemm_stream);
+    return b_kn_launched(c, b_layout, p.b_kn, (hipStream_t)gemm_stream);
 }
 
 int gemm_rs(agg_ctx* c, int M, int N, int Kl, const void* A_local, int lda, const void* B_local, int ldb, int b_layout,
@@ -787,8 +800,14 @@ int gemm_rs(agg_ctx* c, int M, int N, int Kl, const void* A_local, int lda, cons
         if (lda % 8 != 0 || !aligned16(A_local)) return AGG_ERR_MISALIGNED;
         GemmParams p{};
         p.A = (const uint16_t*)A_local + (long long)c->rank * Ms * lda;
-        if ((rc = resolve_b(c, B_local, ldb, b_layout, N, Kl, (hipStream_t)gemm_stream, &p.B, &p.ldb)) != AGG_OK) return rc;
-        p.b_total_bytes = p.ldb * N * 2;
+        // the sum over K in the same order as with P_other, so that the slice is the same bit for bit: a K-split tile if
+        // the whole product takes one, and then that one; B read in place if it is for the whole product
+        int cfg = choose_tile(c, M, N, Kl, true);
+        p.b_kn = kn_in_place(c, B_local, ldb, b_layout, M, N, Kl, true, &cfg);
+        if (p.b_kn) cfg = tile_kn(c->num_cus, -1, Ms, N, Kl, true);
+        else if (cfg < TILE_CONFIGS) cfg = choose_tile(c, Ms, N, Kl, true, true);
+        if ((rc = resolve_b(c, B_local, ldb, b_layout, N, Kl, (hipStream_t)gemm_stream, p.b_kn, &p.B, &p.ldb)) != AGG_OK) return rc;
+        p.b_total_bytes = p.b_kn ? 2 * p.ldb * Kl : 2 * p.ldb * N;
         p.C = (void*)slots[c->rank];
         p.lda = lda;
         p.ldc = N;
@@ -807,15 +826,11 @@ int gemm_rs(agg_ctx* c, int M, int N, int Kl, const void* A_local, int lda, cons
         p.ldc_slice = N;
         p.slice_ctr = c->counters + c->n_signals;
         p.slice_flag[0] = own_flag;
-        // the sum over K in the same order as with P_other, so that the slice is the same bit for bit: a K-split tile if
-        // the whole product takes one, and then that one
-        int cfg = choose_tile(c, M, N, Kl, true);
-        if (cfg < TILE_CONFIGS) cfg = choose_tile(c, Ms, N, Kl, true, true);
         fill_schedule(c, p, cfg, Ms, 0);
         const long long tiles = (long long)p.tiles_m * p.tiles_n;
         const int grid = gemm_grid(c, cfg, tiles);
         rc = hip_fail(launch_gemm(p, cfg, grid, (hipStream_t)gemm_stream));
-        if (rc == AGG_OK) rc = b_kn_launched(c, b_layout, (hipStream_t)gemm_stream);
+        if (rc == AGG_OK) rc = b_kn_launched(c, b_layout, p.b_kn, (hipStream_t)gemm_stream);
     }
     if (rc != AGG_OK) return rc;
     // The reducer waits for this rank's own slot, which the GEMM above produces.  A reducer that spun for that

@@ -40,8 +40,20 @@ static hipError_t launch_any(const GemmParams& p, bool grouped, int cfg, int gri
     }
 }
 
+hipError_t launch_gemm_kn_64x64(const GemmParams& p, int grid, hipStream_t s);
+hipError_t launch_gemm_kn_64x128(const GemmParams& p, int grid, hipStream_t s);
+hipError_t launch_gemm_kn_128x128(const GemmParams& p, int grid, hipStream_t s);
+
 hipError_t launch_gemm(const GemmParams& p, int cfg, int grid, hipStream_t stream)
 {
+    if (p.b_kn) {
+        switch (cfg) {
+            case KN_64x64: return launch_gemm_kn_64x64(p, grid, stream);
+            case KN_64x128: return launch_gemm_kn_64x128(p, grid, stream);
+            case KN_128x128: return launch_gemm_kn_128x128(p, grid, stream);
+            default: return hipErrorInvalidValue;
+        }
+    }
     return launch_any(p, false, cfg, grid, stream);
 }
 

@@ -20,6 +20,9 @@
 //
 // Measured against the 128x128 tile of the large kernel (us per GEMM, B not in cache): 16 x 3584 x 4096 24.9 -> 8.5 (16x16
 // tiles), 64 x 8192 x 3584 33.3 -> 18.5 (64x32), 128 x 7168 x 8192 74.6 -> 42 (64x64), 999 x 1999 x 1984 21 -> 15.6 (64x128).
+// KN: a B stored [K][N], read in place by gemm_km_kernel (64x64, 64x128, 128x128): no transposed copy, which costs a kernel, its bytes twice and
+// an event.  Transposing and GEMM, and in place, us: 1024 x 3584 x 4096 49.6 -> 40.2 (128x128), 376 x 5160 x 1984 29.7 -> 17.8 (64x128),
+// 84 x 240 x 704 12.2 -> 7.6 (64x64).
 #pragma once
 #include "gemm_tile.h"
 #include "ks_stage.h"
@@ -350,7 +353,7 @@ struct KmCfg {
     static_assert(A_UNITS % S == 0 && B_UNITS % S == 0 && NST % 2 == 0 && NST >= 4 && LDS_BYTES <= 159 * 1024, "tile");
 };
 
-template <int BM, int BN, int NW, int NST, KsKind KIND>
+template <int BM, int BN, int NW, int NST, KsKind KIND, bool KN = false>
 __global__ __launch_bounds__(128 * NW)
 void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED, KsSlices, KsNoSlices> sl)
 {
@@ -371,6 +374,16 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
     const unsigned lds_ld = lds_u + wave * 1024;
     const unsigned fr = lds_u + (lane & 15) * ROW_BYTES + (((4 * kh + (lane >> 4)) ^ ((lane >> 1) & 7)) << 4);
     const unsigned fr_b = fr + (RB + nw * CB) * 2048;
+    // KN: B is [K][N].  A stage of it is 64 rows of one k each, BN columns (whole lines), 16-byte chunk c of row k in slot c ^ kn_swizzle(k).
+    // Lane l of a wave takes columns 2 (l % 16) and 2 (l % 16) + 1 of the wave's 32, of the eight k that its fragments hold: eight
+    // 4-byte reads, and a byte permute per pair of k puts them into the fragments of the even and of the odd columns.  (The
+    // hardware's transposing LDS read would do without the permutes, but the compiler waits for all loads in flight in front of it: five
+    // times slower.)  The swizzle puts the rows that a read's 16-lane groups take into different banks.
+    static_assert(!KN || (CB == 2 && KIND != KS_GROUPED && (BN == 64 || BN == 128)), "[K][N] operand");
+    constexpr int KN_ROW = BN * 2;
+    auto kn_swizzle = [](int k) { return ((k >> 3) & (BN / 32 - 1)) << 2; };
+    const int kn_k = 32 * kh + 8 * (lane >> 4), kn_n = lane & 15;
+    const unsigned fr_kn = lds_u + BM * ROW_BYTES + kn_k * KN_ROW + (((nw * 4 + (kn_n >> 2)) ^ kn_swizzle(kn_k)) << 4) + (kn_n & 3) * 4;
 
     const int KC = p.KC;
     const int total_tiles = GROUPED ? *p.n_tiles_dev : p.total_tiles;
@@ -385,9 +398,9 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
         const bool gated = p.flags && w.f_hi >= w.f_lo;
         const uint16_t* a_base = GROUPED ? p.A
                                : w.from_local ? p.A_local + (long long)(m0 - p.local_lo) * p.lda : p.A + (long long)m0 * p.lda;
-        const uint16_t* b_base = p.B + (GROUPED ? (long long)w.expert * p.b_group_stride : 0ll) + (long long)n0 * p.ldb;
+        const uint16_t* b_base = KN ? p.B + n0 : p.B + (GROUPED ? (long long)w.expert * p.b_group_stride : 0ll) + (long long)n0 * p.ldb;
         const unsigned a_bytes = GROUPED ? p.a_bytes : (unsigned)min(BM, p.M - m0) * lda2;
-        const unsigned b_bytes = (unsigned)min(BN, p.N - n0) * ldb2;
+        const unsigned b_bytes = KN ? (unsigned)(KC * BK - 1) * ldb2 + (unsigned)(p.N - n0) * 2u : (unsigned)min(BN, p.N - n0) * ldb2;
         unsigned off_a[LA], off_b[LB];
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
@@ -397,10 +410,17 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
         }
         if constexpr (GROUPED) asm volatile("" ::: "memory");
 #pragma unroll
-        for (int i = 0; i < LB; ++i) off_b[i] = (unsigned)((wave + S * i) * UNIT_ROWS + ld_row) * ldb2 + (unsigned)(ld_chunk * 16);
+        for (int i = 0; i < LB; ++i) {
+            if constexpr (KN) {
+                const int q = (wave + S * i) * 64 + lane, k = q / (BN / 8), c = (q % (BN / 8)) ^ kn_swizzle(k);
+                off_b[i] = n0 + c * 8 < p.N ? (unsigned)k * ldb2 + (unsigned)(c * 16) : 0x80000000u;      // columns past the edge load as zero
+            } else {
+                off_b[i] = (unsigned)((wave + S * i) * UNIT_ROWS + ld_row) * ldb2 + (unsigned)(ld_chunk * 16);
+            }
+        }
         auto issue_b = [&](int s, auto slot_c) {
             constexpr int slot = decltype(slot_c)::value;
-            const KsStage st = ks_stage(s, KC, ROW_BYTES, b_bytes);
+            const KsStage st = ks_stage(s, KC, KN ? BK * (int)ldb2 : ROW_BYTES, b_bytes);
             const __amdgpu_buffer_rsrc_t rs = make_rsrc(b_base, st.bytes);
             auto load = [&](auto aux_c) {
                 static_for<LB>([&](auto i_c) {
@@ -441,8 +461,15 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
 #pragma unroll
             for (int j = 0; j < CB; ++j) acc[i][j] = f32x4_{0.f, 0.f, 0.f, 0.f};
         bf16x8 fa[2][RB], fb[2][CB];
+        typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
+        unsigned kn[2][KN ? 8 : 1];            // the column pairs of KN's next fragments
         auto read_frags = [&](auto slot_c, auto set_c) {
             constexpr int slot = decltype(slot_c)::value, set = decltype(set_c)::value;
+            if constexpr (KN) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    kn[set][k] = *(__attribute__((address_space(3))) const unsigned*)(unsigned long)(fr_kn + slot * C_::STAGE + k * KN_ROW);
+            } else
 #pragma unroll
             for (int j = 0; j < CB; ++j) fb[set][j] = *(lds_frag*)(unsigned long)(fr_b + slot * C_::STAGE + j * 2048);
 #pragma unroll
@@ -470,6 +497,16 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
                 issue_b(s + NST - 1, std::integral_constant<int, (slot + NST - 1) % NST>{});
                 issue_a(s + NST - 1, std::integral_constant<int, (slot + NST - 1) % NST>{});
                 read_frags(std::integral_constant<int, (slot + 1) % NST>{}, std::integral_constant<int, (slot + 1) & 1>{});
+                if constexpr (KN) {
+                    u32x4 even, odd;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        even[k] = __builtin_amdgcn_perm(kn[slot & 1][2 * k + 1], kn[slot & 1][2 * k], 0x05040100u);
+                        odd[k] = __builtin_amdgcn_perm(kn[slot & 1][2 * k + 1], kn[slot & 1][2 * k], 0x07060302u);
+                    }
+                    fb[slot & 1][0] = __builtin_bit_cast(bf16x8, even);
+                    fb[slot & 1][CB - 1] = __builtin_bit_cast(bf16x8, odd);
+                }
 #pragma unroll
                 for (int j = 0; j < CB; ++j)
 #pragma unroll
@@ -484,10 +521,17 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
         __syncthreads();
         float* const red = (float*)lds;
 #pragma unroll
-        for (int i = 0; i < RB; ++i)
+        for (int i = 0; i < RB; ++i) {
+            float* const to = red + (kh * BM + i * 16 + (lane & 15)) * PITCH + nw * CB * 16;
+            if constexpr (KN) {                // the lane's eight columns, the even ones in one block, the odd ones in the other
+                const f32x4_ e = acc[i][0], o = acc[i][CB - 1];
+                *(f32x4_*)(to + 8 * (lane >> 4)) = f32x4_{e[0], o[0], e[1], o[1]};
+                *(f32x4_*)(to + 8 * (lane >> 4) + 4) = f32x4_{e[2], o[2], e[3], o[3]};
+            } else {
 #pragma unroll
-            for (int j = 0; j < CB; ++j)
-                *(f32x4_*)(red + (kh * BM + i * 16 + (lane & 15)) * PITCH + (nw * CB + j) * 16 + 4 * (lane >> 4)) = acc[i][j];
+                for (int j = 0; j < CB; ++j) *(f32x4_*)(to + j * 16 + 4 * (lane >> 4)) = acc[i][j];
+            }
+        }
         __syncthreads();
         ks_store<BM, BN, 2, S * 64, KIND>(p, sl, w, red, tid);
         if constexpr (KIND == KS_SLICED) {
@@ -502,13 +546,13 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
 }
 
 // SHARED: gemm_km_kernel with X = NW, else gemm_ks_kernel with X = S.
-template <bool SHARED, int BM, int BN, int X, int NST, KsKind KIND>
+template <bool SHARED, int BM, int BN, int X, int NST, KsKind KIND, bool KN = false>
 static hipError_t launch_ks_kind(const KsParams& p, const std::conditional_t<KIND == KS_SLICED, KsSlices, KsNoSlices>& sl,
                                  hipStream_t stream)
 {
     using C_ = std::conditional_t<SHARED, KmCfg<BM, BN, X, NST>, KsCfg<BM, BN, X, NST>>;
     void (*kernel)(const KsParams, const std::conditional_t<KIND == KS_SLICED, KsSlices, KsNoSlices>);
-    if constexpr (SHARED) kernel = gemm_km_kernel<BM, BN, X, NST, KIND>;
+    if constexpr (SHARED) kernel = gemm_km_kernel<BM, BN, X, NST, KIND, KN>;
     else kernel = gemm_ks_kernel<BM, BN, X, NST, KIND>;
     constexpr int threads = SHARED ? 128 * X : 64 * X;
     static bool attr_set = false;
@@ -525,7 +569,7 @@ static hipError_t launch_ks_kind(const KsParams& p, const std::conditional_t<KIN
 enum KsForms { KS_DENSE = 1, KS_MOE = 2 };
 
 // The launch of `g` (a GemmParams whose tile fields are those of this tile shape) on this kernel.
-template <bool SHARED, int BM, int BN, int X, int NST, int FORMS>
+template <bool SHARED, int BM, int BN, int X, int NST, int FORMS, bool KN = false>
 static hipError_t launch_ks(const GemmParams& g, bool grouped, int grid, hipStream_t stream)
 {
     KsParams p{};
@@ -554,13 +598,13 @@ static hipError_t launch_ks(const GemmParams& g, bool grouped, int grid, hipStre
         }
     }
     if constexpr ((FORMS & KS_DENSE) != 0) {
-        if (g.n_slices == 0) return launch_ks_kind<SHARED, BM, BN, X, NST, KS_PLAIN>(p, KsNoSlices{}, stream);
+        if (g.n_slices == 0) return launch_ks_kind<SHARED, BM, BN, X, NST, KS_PLAIN, KN>(p, KsNoSlices{}, stream);
         KsSlices sl{};
         sl.M = g.M; sl.tiles_n = g.tiles_n; sl.slice_rows = g.slice_rows; sl.slice_chunks = g.slice_chunks;
         sl.chunk_rows = g.chunk_rows; sl.ldc_slice = (int)g.ldc_slice; sl.slice_mul = div_mul(g.slice_rows);
         sl.slice_ctr = g.slice_ctr;
         for (int w = 0; w < g.n_slices; ++w) { sl.slice_dst[w] = g.slice_dst[w]; sl.slice_flag[w] = g.slice_flag[w]; }
-        return launch_ks_kind<SHARED, BM, BN, X, NST, KS_SLICED>(p, sl, stream);
+        return launch_ks_kind<SHARED, BM, BN, X, NST, KS_SLICED, KN>(p, sl, stream);
     }
     return hipErrorInvalidValue;
 }
@@ -573,5 +617,13 @@ static hipError_t launch_ks(const GemmParams& g, bool grouped, int grid, hipStre
     hipError_t launch_gemm_ks_##BM##x##BN(const GemmParams& p, bool grouped, int grid, hipStream_t s)       \
     {                                                                                                       \
         return launch_ks<SHARED, BM, BN, X, NST, FORMS>(p, grouped, grid, s);                               \
+    }                                                                                                       \
+    }
+// ... for a B stored [K][N] and read in place
+#define AGG_KN_INSTANCE(BM, BN, NW, NST)                                                                    \
+    namespace agg {                                                                                         \
+    hipError_t launch_gemm_kn_##BM##x##BN(const GemmParams& p, int grid, hipStream_t s)                     \
+    {                                                                                                       \
+        return launch_ks<true, BM, BN, NW, NST, KS_DENSE, true>(p, false, grid, s);                         \
     }                                                                                                       \
     }

@@ -15,8 +15,8 @@ enum TileConfig { TILE_256x224 = 0, TILE_128x128 = 1, TILE_256x256 = 2, TILE_128
                   PIPE_128x192 = TILE_NUMBERED, PIPE_128x224, PIPE_192x192, PIPE_320x128, TILE_CONFIGS };
 
 // Tile configurations of the K-split kernels (gemm_ks.h): what the automatic choice takes where the tiles above would leave
-// most of the chip idle; not selectable by number.
-enum KsTileConfig { KS_16x16 = TILE_CONFIGS, KS_16x32, KS_16x64, KS_32x32, KS_64x32, KS_64x64, KS_64x128, KS_CONFIGS_END };
+// most of the chip idle; not selectable by number.  KN_: the same for a B stored [K][N] and read in place.
+enum KsTileConfig { KS_16x16 = TILE_CONFIGS, KS_16x32, KS_16x64, KS_32x32, KS_64x32, KS_64x64, KS_64x128, KN_64x64, KN_64x128, KN_128x128, KS_CONFIGS_END };
 
 struct TileShape { int bm, bn; };
 inline TileShape tile_shape(int cfg)
@@ -31,8 +31,9 @@ inline TileShape tile_shape(int cfg)
         case KS_16x64: return {16, 64};
         case KS_32x32: return {32, 32};
         case KS_64x32: return {64, 32};
-        case KS_64x64: return {64, 64};
-        case KS_64x128: return {64, 128};
+        case KS_64x64: case KN_64x64: return {64, 64};
+        case KS_64x128: case KN_64x128: return {64, 128};
+        case KN_128x128: return {128, 128};
         default: break;
     }
     switch (cfg & 3) {
@@ -58,9 +59,24 @@ constexpr TileCost kTileCosts[] = {
     {KS_64x128, 3.5, 0.37}, {KS_64x64, 3.0, 0.24}, {KS_64x32, 4.0, 0.20}, {KS_32x32, 3.0, 0.125}, {KS_16x32, 3.0, 0.09},
     {KS_16x16, 3.0, 0.07},
 };
+constexpr TileCost kTileCostsKn[] = {{KN_64x64, 3.9, 0.299}, {KN_64x128, 4.0, 0.38}, {KN_128x128, 4.6, 0.556}};
+constexpr double kTransposeUs = 7.6, kTransposeBytesPerUs = 5.6e6;        // tile_kn
 constexpr double kPublishUs = 0.009, kStoreUs256 = 10.0, kStoreUs128x256 = 4.0;     // best_tile, slices
 // the K-split kernels divide row and tile numbers with 32-bit multipliers, exact while rows x divisor < 2^32
 constexpr int kKsMaxRows = 65535;
+
+inline double tile_cost(int num_cus, const TileCost& k, int M, int N, int K, bool slices)
+{
+    const TileShape t = tile_shape(k.cfg);
+    const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+    const long long rounds = (tiles + num_cus - 1) / num_cus;
+    double cost = (double)rounds * (k.fixed_us + k.us_per_k64 * (K / 64));
+    if (slices) {
+        cost += kPublishUs * (double)tiles;
+        cost += (double)rounds * (t.bm == 256 ? kStoreUs256 : t.bn == 256 ? kStoreUs128x256 : 0.0);
+    }
+    return cost;
+}
 
 // Pick the tile shape with the smallest estimated time: rounds of tiles over the CUs times the cost of a tile.  The
 // 16x16x32 form of the main loop everywhere: the same work at a lower power per flop, so the chip holds a higher clock
@@ -78,14 +94,30 @@ inline int best_tile(int num_cus, int M, int N, int K, bool slices = false, bool
     double best_cost = 1e300;
     for (const TileCost& k : kTileCosts) {
         if (k.cfg >= TILE_CONFIGS && (large_only || M > kKsMaxRows)) continue;
-        const TileShape t = tile_shape(k.cfg);
-        const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-        const long long rounds = (tiles + num_cus - 1) / num_cus;
-        double cost = (double)rounds * (k.fixed_us + k.us_per_k64 * (K / 64));
-        if (slices) {
-            cost += kPublishUs * (double)tiles;
-            cost += (double)rounds * (t.bm == 256 ? kStoreUs256 : t.bn == 256 ? kStoreUs128x256 : 0.0);
+        const double cost = tile_cost(num_cus, k, M, N, K, slices);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = k.cfg;
         }
+    }
+    return best;
+}
+
+// Tile for a B stored [K][N] that can be read in place (its rows on 16 bytes, whole 16-byte chunks of columns), or -1: it is transposed first
+// and `cfg`, best_tile's choice for the transposed one, is taken.  Transposing costs its bytes, read and written, and 7.6 us: a kernel more and the
+// event behind the GEMM.  Over 166 problems drawn from M 16..8192, N 96..7168, K 256..8192 the choice takes 28 % less time than transposing
+// always, is never slower, and costs 0.3 % more than the better of both.  Both sides, us: 1024 x 3584 x 4096 128x128 in place 40.2,
+// transposed 49.6; 57 x 96 x 320 5.8 and 11.2; 30 x 336 x 2624 15.0 and 13.3; 2048 x 3584 x 4096 80.2 and 69.8.
+// cfg = -1: the best of the tiles that read in place (they all give the same bits).
+inline int tile_kn(int num_cus, int cfg, int M, int N, int K, bool slices = false)
+{
+    int best = -1;
+    double best_cost = 1e300;
+    for (const TileCost& k : kTileCosts)
+        if (k.cfg == cfg) best_cost = tile_cost(num_cus, k, M, N, K, slices) + kTransposeUs + 4.0 * N * K / kTransposeBytesPerUs;
+    if (M > kKsMaxRows) return -1;
+    for (const TileCost& k : kTileCostsKn) {
+        const double cost = tile_cost(num_cus, k, M, N, K, slices);
         if (cost < best_cost) {
             best_cost = cost;
             best = k.cfg;

@@ -76,6 +76,9 @@ double m_tiles_plain(double mean, int bm)
 
 int tile_plain(int num_cus, int M, int N, int K, int slices) { return best_tile(num_cus, M, N, K, slices != 0); }
 
+// The tile of a [K][N] operand that can be read in place, -1 = transposed first.
+int tile_of_kn(int num_cus, int M, int N, int K, int slices) { return tile_kn(num_cus, best_tile(num_cus, M, N, K, slices != 0), M, N, K, slices != 0); }
+
 int tile_rows_and_columns(int tile) { return tile_shape(tile).bm << 16 | tile_shape(tile).bn; }
 
 // The K-split tiles that the automatic choice can take; returns how many.

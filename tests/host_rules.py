@@ -39,6 +39,12 @@ def gemm_tile(num_cus: int, M: int, N: int, K: int, slices: bool = False):
     return tile_name(tile), -(-M // (rc >> 16)) * -(-N // (rc & 0xffff))
 
 
+def kn_tile(num_cus: int, M: int, N: int, K: int, slices: bool = False):
+    """The tile that reads a [K][N] operand in place, or None where it is transposed."""
+    tile = lib().tile_of_kn(num_cus, M, N, K, int(slices))
+    return None if tile < 0 else tile_name(tile)
+
+
 def moe_tile(num_cus: int, tokens: int, topk: int, E: int, N: int, K: int, gathered: bool, f32: bool) -> str:
     """The automatic choice for ag_moe_gemm (gathered) and moe_rs on a context reserved for the problem."""
     return tile_name(lib().tile_grouped(num_cus, tokens * topk, E, N, K, int(gathered), int(f32), tokens * topk, 1 << 28, 0))

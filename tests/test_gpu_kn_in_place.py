@@ -1,0 +1,135 @@
+"""A B stored [K][N] that the GEMMs read in place: every tile that does, at the edges of tiles, rings and 16-byte chunks, rows longer than N
+whose rest is NaN, nothing behind the last row's N, more tiles than workgroups, several signals; the same bits with and without the other
+ranks' rows; and operands that do not qualify, which are transposed.  Integer inputs: sums of at most 4 x 6464 are exact in fp32 in any order."""
+import numpy as np
+import pytest
+import torch
+
+import host_rules
+import paper_2504_19442_amd as agg
+
+pytestmark = pytest.mark.gpu
+
+
+def _cus():
+    return agg.agg_device_info()[0]
+
+
+def _ints(g, *shape):
+    return torch.randint(-2, 3, shape, device="cuda", generator=g, dtype=torch.int8).to(torch.bfloat16)
+
+
+def _kn(g, K, N, ldb, offset=0):
+    """B [K, N] and the buffer that holds it: rows of ldb elements from `offset` on, NaN everywhere else, no element behind the last one."""
+    B = _ints(g, K, N)
+    flat = torch.full((offset + (K - 1) * ldb + N,), float("nan"), device="cuda", dtype=torch.bfloat16)
+    flat[offset:].as_strided((K, N), (ldb, 1)).copy_(B)
+    return B, flat
+
+
+# tile (None: transposed), W, rows per rank, K, N, ldb, offset
+CASES = [
+    ("64x64", 2, 6, 64, 8, 8, 0),                # one chunk of a row, one stage
+    ("64x64", 3, 21, 192, 72, 80, 0),            # one row less than a tile, a second column tile of one chunk, padded rows
+    ("64x64", 2, 65, 704, 752, 752, 8),
+    ("64x64", 2, 32, 2112, 1200, 1208, 0),
+    ("64x128", 2, 469, 704, 1336, 1344, 0),
+    ("64x128", 2, 669, 64, 1088, 1088, 16),
+    ("64x128", 2, 422, 2112, 1160, 1160, 0),
+        ("128x128", 2, 689, 704, 1496, 1496, 0),
+    ("128x128", 2, 626, 64, 1568, 1576, 0),
+    ("128x128", 2, 624, 2112, 1584, 1584, 0),
+    ("128x128", 2, 1435, 192, 1832, 1840, 0),    # more tiles than workgroups
+    (None, 2, 6, 64, 12, 16, 0),                 # columns that are no whole chunks
+    (None, 2, 6, 64, 16, 20, 0),                 # rows that do not start on 16 bytes
+    (None, 2, 6, 64, 16, 16, 1),                 # nor does the first one
+    (None, 2, 9, 6464, 24, 24, 0),               # a long K on few tiles: transposing is faster
+]
+
+
+@pytest.mark.parametrize("tile,W,Ms,K,N,ldb,offset", CASES)
+def test_ag_gemm_exact(tile, W, Ms, K, N, ldb, offset):
+    M = W * Ms
+    if tile or (N % 8 == 0 and ldb % 8 == 0 and offset % 8 == 0):
+        assert host_rules.kn_tile(_cus(), M, N, K) == tile
+    g = torch.Generator(device="cuda").manual_seed(51)
+    cps = 3 if Ms % 3 == 0 else 1
+    shards, (B, flat) = [_ints(g, Ms, K) for _ in range(W)], _kn(g, K, N, ldb, offset)
+    want = torch.cat(shards).float() @ B.float()
+    ctx = agg.symm_alloc(W, W - 1, Ms * K * 2, W * cps)
+    try:
+        ps, cs = ctx.streams()
+        C = torch.empty((M, N), device="cuda")
+        agg.signal_reset(ctx)
+        with pytest.raises(agg.AggError) as e:   # the buffer of a transposed copy has to be there either way
+            agg.ag_gemm(ctx, M, N, K, flat.data_ptr() + 2 * offset, ldb, agg.B_KN, C, N, agg.F32, cs)
+        assert e.value.code == agg.ERR_NOT_RESERVED
+        agg.agg_reserve_b_kn(ctx, N, K)
+        for dtype, tdt in ((agg.F32, torch.float32), (agg.BF16, torch.bfloat16)):
+            C = torch.full((M, N + 3), 7.0, device="cuda", dtype=tdt)
+            agg.signal_reset(ctx)
+            torch.cuda.synchronize()
+            agg.ag_producer_emulate(ctx, shards, None, agg.PRODUCER_KERNEL, 0, ps)
+            agg.ag_gemm(ctx, M, N, K, flat.data_ptr() + 2 * offset, ldb, agg.B_KN, C, N + 3, dtype, cs)
+            torch.cuda.synchronize()
+            assert agg.agg_status(ctx) == agg.OK
+            assert torch.equal(C[:, :N], want.to(tdt)) and bool((C[:, N:] == 7.0).all())
+    finally:
+        ctx.free()
+
+
+@pytest.mark.parametrize("tile,W,Ms,K,N", [("64x64", 4, 25, 576, 200), ("64x128", 2, 342, 192, 624), ("128x128", 2, 689, 704, 1496)])
+def test_gemm_rs_same_bits_with_and_without_the_other_rows(tile, W, Ms, K, N):
+    M, rank = W * Ms, 1
+    assert host_rules.kn_tile(_cus(), M, N, K, slices=True) == tile
+    g = torch.Generator(device="cuda").manual_seed(52)
+    A = torch.empty((M, K), device="cuda", dtype=torch.bfloat16).uniform_(-1, 1, generator=g)
+    B = torch.empty((K, N), device="cuda", dtype=torch.bfloat16).normal_(0, 0.02, generator=g)
+    want = (A.double().cpu() @ B.double().cpu()).cuda()
+    ctx = agg.symm_alloc(W, rank, 16, W)
+    try:
+        agg.agg_reserve_b_kn(ctx, N, K)
+        cs = ctx.streams()[1]
+        own = {}
+        for P in (torch.full((M, N), 7.0, device="cuda"), None):
+            slots = [torch.zeros((Ms, N), device="cuda") for _ in range(W)]
+            slots[rank].fill_(float("nan"))
+            R = torch.full((Ms, N), float("nan"), device="cuda")
+            agg.signal_reset(ctx)
+            torch.cuda.synchronize()
+            for w in range(W):
+                if w != rank:
+                    agg.signal_set(ctx, w, cs)
+            agg.gemm_rs(ctx, M, N, K, A, K, B, N, agg.B_KN, slots, P, R, N, agg.F32, cs, cs)
+            torch.cuda.synchronize()
+            assert agg.agg_status(ctx) == agg.OK
+            assert torch.equal(R, slots[rank])
+            own[P is None] = R
+            if P is not None:
+                P[rank * Ms:(rank + 1) * Ms] = R
+                assert float((P - want).norm() / want.norm()) < 1e-6          # fp32 sums of K <= 576 products
+        assert torch.equal(own[True], own[False])
+    finally:
+        ctx.free()
+
+
+def test_weights_beyond_the_memory_side_cache():
+    W, Ms, K, N = 2, 50, 4096, 33280             # 273 MB: the streaming hint
+    tile = host_rules.kn_tile(_cus(), W * Ms, N, K)
+    assert tile in ("64x128", "128x128")
+    g = torch.Generator(device="cuda").manual_seed(53)
+    shards, B = [_ints(g, Ms, K) for _ in range(W)], _ints(g, K, N)
+    ctx = agg.symm_alloc(W, 0, Ms * K * 2, W)
+    try:
+        agg.agg_reserve_b_kn(ctx, N, K)
+        ps, cs = ctx.streams()
+        C = torch.full((W * Ms, N), float("nan"), device="cuda")
+        agg.signal_reset(ctx)
+        torch.cuda.synchronize()
+        agg.ag_producer_emulate(ctx, shards, None, agg.PRODUCER_KERNEL, 0, ps)
+        agg.ag_gemm(ctx, W * Ms, N, K, B, N, agg.B_KN, C, N, agg.F32, cs)
+        torch.cuda.synchronize()
+        assert agg.agg_status(ctx) == agg.OK
+        assert torch.equal(C, torch.cat(shards).float() @ B.float())
+    finally:
+        ctx.free()
