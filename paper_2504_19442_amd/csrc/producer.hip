@@ -4,6 +4,8 @@
 // registers, so its waves fit beside the consumer's on any CU (Section 3.8, resource partition).
 #include "agg_internal.h"
 
+#include <type_traits>
+
 // Cache policy bits of the buffer instructions below, in the gfx940 / gfx950 encoding of the `aux` operand:
 // 2 = nt (streaming) on the loads, 16 = sc1 (agent scope: written through this XCD's L2) on the stores.  The
 // publication of a chunk rests on three properties of this hardware, not on the language's memory model:
@@ -57,18 +59,22 @@ __global__ __launch_bounds__(256) void producer_kernel(const ProducerArgs a)
         const unsigned bytes = hi > lo ? (unsigned)((hi - lo) * 16) : 0u;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(s), 0, bytes, 0x00020000);
         const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(d, 0, bytes, 0x00020000);
-        // four independent 16-byte loads in flight per lane; out-of-range lanes of the last round load zero
-        // and store nothing (the descriptors bound both)
-        for (unsigned off = tid * 16u; off < bytes; off += 4u * span) {
-            u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, NT);
-            u32x4 v1 = __builtin_amdgcn_raw_buffer_load_b128(rs, off + span, 0, NT);
-            u32x4 v2 = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 2u * span, 0, NT);
-            u32x4 v3 = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 3u * span, 0, NT);
-            __builtin_amdgcn_raw_buffer_store_b128(v0, rd, off, 0, WT);
-            __builtin_amdgcn_raw_buffer_store_b128(v1, rd, off + span, 0, WT);
-            __builtin_amdgcn_raw_buffer_store_b128(v2, rd, off + 2u * span, 0, WT);
-            __builtin_amdgcn_raw_buffer_store_b128(v3, rd, off + 3u * span, 0, WT);
-        }
+        // U independent 16-byte loads in flight per lane; out-of-range lanes of the last round load zero and store nothing (the
+        // descriptors bound both).  Eight where a slice is more than four cover: 43 registers, so that a copy wave still fits beside a
+        // GEMM's on a SIMD (64 are left).  Four and eight, us alone: 8 x 16 MiB 43.0 and 42.6, by one-wave workgroups 90.9 and 61.5,
+        // 4 x 2 MiB 6.9 and 6.5, slices of 16 KiB 3.30 and 3.44.
+        auto copy = [&](auto u_c) {
+            constexpr unsigned U = decltype(u_c)::value;
+            for (unsigned off = tid * 16u; off < bytes; off += U * span) {
+                u32x4 v[U];
+#pragma unroll
+                for (unsigned k = 0; k < U; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, off + k * span, 0, NT);
+#pragma unroll
+                for (unsigned k = 0; k < U; ++k) __builtin_amdgcn_raw_buffer_store_b128(v[k], rd, off + k * span, 0, WT);
+            }
+        };
+        if (bytes <= 4u * span) copy(std::integral_constant<unsigned, 4>{});
+        else copy(std::integral_constant<unsigned, 8>{});
         // signal: the last workgroup of the team to finish the chunk sets it (set_signal after the copy, Algorithm 2)
         __builtin_amdgcn_s_waitcnt(0);              // every store of this lane has completed
         __syncthreads();                            // ... of this workgroup
@@ -163,8 +169,12 @@ __global__ void epoch_advance_kernel(int* epoch_word)
 hipError_t launch_producer(const ProducerArgs& a_in, int n_workgroups, int threads, hipStream_t stream)
 {
     ProducerArgs a = a_in;
-    // team size: slices of at least 64 KiB, at most the whole grid on one chunk
-    long long team = a.chunk_bytes / 65536;
+    // team size: slices of at least 64 KiB, at most the whole grid on one chunk.  Where slices of 32 KiB leave three eighths of the grid
+    // without one, those: they are copied in one trip, and the teams, each of whose workgroups counts itself done at one
+    // address, stay small enough.  Slices of 64 and 32 KiB, us, 256 workgroups: 8 x 256 KiB 4.4 and 3.9, 3 x 1.3 MB 6.1 and 5.0, 2 x 2 MiB 5.4 and
+    // 5.0, 4 x 1.5 MiB 6.1 and 6.1, 4 x 2 MiB 6.5 and 7.3 (16 KiB: 4.5, 6.0, 6.2, 8.0, 9.9).
+    const long long total = a.chunk_bytes * a.chunks_per_shard * a.n_jobs;
+    long long team = a.chunk_bytes / (total / 32768 <= n_workgroups * 5ll / 8 ? 32768 : 65536);
     if (team < 1) team = 1;
     if (team > n_workgroups) team = n_workgroups;
     a.team = (int)team;
