@@ -171,13 +171,14 @@ inline double expected_m_tiles(double mean, int bm)
 // and fp32, rows in place): the choice costs 0.7 % more than the best tile of each (geometric mean; 0.8 % on 370 other draws) and takes
 // 12 % less time than the choice among 256x224, 256x256 and 128x128 alone, which is faster by more than 5 % on 12 of the 1110, by
 // more than 10 % on two.  The costs of the tiles of gemm_pipe.h are fitted to 800 further draws, half of them with 256 and
-// more tokens per rank: on 800 others the choice with them takes 5.7 % less time for gathered rows and 1 % for rows in place than without
-// them, is slower by more than 5 % on 6 and by more than 10 % on two, and costs 1 % more than the best tile.
+// more tokens per rank: on 800 others the choice with them takes 4.3 % less time for gathered rows and 0.8 % for rows in place than without
+// them, is slower by more than 5 % on 4 and by more than 10 % on one, and costs 1.9 % more than the best tile (1 % if those tiles were to
+// take the place of K-split ones as well, which would change bits).
 constexpr TileCost kTileCostsGrouped[] = {
     {KS_16x32, 3.4, 0.113}, {KS_16x64, 3.4, 0.179}, {KS_32x32, 2.6, 0.142}, {KS_64x64, 3.3, 0.267}, {KS_64x128, 3.5, 0.40},
     {TILE_128x128 | TILE_K32, 3.0, 0.60}, {TILE_128x256 | TILE_K32, 2.9, 0.94}, {TILE_256x224 | TILE_K32, 4.1, 1.50},
     {TILE_256x256 | TILE_K32, 4.0, 1.73},
-    {PIPE_128x192, 3.7, 0.723}, {PIPE_128x224, 3.3, 0.854}, {PIPE_192x192, 2.7, 1.007}, {PIPE_320x128, 2.9, 1.004},
+    {PIPE_128x192, 3.7, 0.742}, {PIPE_128x224, 3.2, 0.894}, {PIPE_192x192, 2.7, 1.013}, {PIPE_320x128, 3.5, 0.997},
 };
 constexpr double kGroupedStoreBytesPerUs = 82e3;     // fp32 rows, per compute unit
 constexpr double kGroupedWeightBytesPerUs = 7.2e6;   // weights of the experts that have rows, whole chip
@@ -192,6 +193,7 @@ constexpr double kGroupedWeightBytesPerUs = 7.2e6;   // weights of the experts t
 // (457 against 435), and in fp32 it is 5 % slower throughout (392 against 371); where it would be the best of the numbered tiles, that
 // of gemm_pipe.h is faster.  There, with routing, weights beyond the memory-side cache, us: 8192 tokens 320x128 298, 256x224 383,
 // 256x256 382; 4096 tokens 192x192 236, 320x128 281, 256x256 275.
+// A tile of gemm_pipe.h takes the place of a numbered one, whose bits it gives, never of a K-split one.
 // Which K-split tile is taken, or that another one is, follows from the problem alone: the small tiles and those of gemm_pipe.h are left
 // out where their table (P pairs) would have more entries than the static one, whatever table is used.  Among the numbered ones, which all give
 // the same bits, those are left out whose table would have more than `tab_base` entries; -1 if that is all of them.
@@ -200,30 +202,35 @@ inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, b
 {
     const double active = E * (1.0 - std::pow(1.0 - 1.0 / E, (double)rows));       // experts with at least one row
     const double hbm_us = active * N * K * 2.0 / kGroupedWeightBytesPerUs;
-    int best = -1, best_that_fits = -1;
-    double best_cost = 1e300, fits_cost = 1e300;
+    int best = -1, best_that_fits = -1, best_pipe = -1;
+    double best_cost = 1e300, fits_cost = 1e300, pipe_cost = 1e300;
     for (const TileCost& k : kTileCostsGrouped) {
         const TileShape t = tile_shape(k.cfg);
-        const bool small = k.cfg >= TILE_CONFIGS, numbered = k.cfg < TILE_NUMBERED;
+        const bool small = k.cfg >= TILE_CONFIGS, numbered = k.cfg < TILE_NUMBERED, pipe = !small && !numbered;
         const long long entries = moe_table_entries(P, E, N, t);
         if ((small && large_only) || (!numbered && entries > kStaticTabEntries) || (gathered && numbered && t.bm == 128 && t.bn == 256)) continue;
         // a tile of gemm_pipe.h that is nearly empty: the weights' bytes are what counts, and the small tiles ask for more of them at a
         // time (48 tokens, 3 rows per expert, 29 x 1659 x 2304: 128x192 72 us, 16x64 50)
-        if (!numbered && !small && (double)rows < active * t.bm / 8) continue;
+        if (pipe && (double)rows < active * t.bm / 8) continue;
         const double tiles = active * expected_m_tiles((double)rows / active, t.bm) * ((N + t.bn - 1) / t.bn);
         const double rounds = std::ceil(tiles / num_cus);
         const double tile_us = k.fixed_us + k.us_per_k64 * (K / 64) + (f32 ? t.bm * t.bn * 4 / kGroupedStoreBytesPerUs : 0.0);
         const double cost = std::max(rounds * tile_us, hbm_us * rounds * num_cus / std::max(tiles, (double)num_cus));
-        if (cost < best_cost) {
+        if (!pipe && cost < best_cost) {
             best_cost = cost;
             best = k.cfg;
+        }
+        if (pipe && cost < pipe_cost) {
+            pipe_cost = cost;
+            best_pipe = k.cfg;
         }
         if (numbered && entries <= tab_base && cost < fits_cost) {
             fits_cost = cost;
             best_that_fits = k.cfg;
         }
     }
-    return best >= TILE_NUMBERED ? best : best_that_fits;
+    if (best >= TILE_CONFIGS) return best;
+    return pipe_cost < best_cost ? best_pipe : best_that_fits;
 }
 
 // Workgroups of a reducer launch over n_vec4 float4 whose caller leaves the size to the library.  Persistent, each walking
