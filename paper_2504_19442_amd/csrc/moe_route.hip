@@ -231,6 +231,119 @@ __global__ __launch_bounds__(kRouteThreads) void moe_route_kernel(const MoeRoute
     }
 }
 
+// The same for up to THREADS x kSmallIds pairs: every workgroup counts all experts' pairs itself (a histogram in LDS), so that nothing is
+// exchanged between workgroups and the control block's counters are left alone.  What the kernel above waits for at such sizes is the ticket
+// and the other workgroups' counts, two trips to memory in a row; this one makes one trip (the ids), then stores.  A lane holds
+// kSmallIds consecutive pairs.  Kernel, 128 pairs of 64 experts: 7.4 -> 4.9 us; with a GEMM of 64 x 64 behind it, us, the kernel above and
+// this one: 128 pairs 12.2 and 9.1, 1024 pairs 12.6 and 9.9, 2048 pairs 13.0 and 10.2 (8 experts: 11.9 and 9.7, 256: 16.3 and 10.2), 4096 pairs, 512
+// threads, 12.3 and 10.0 (8: 11.6 and 10.0, 256: 16.4 and 10.7).  What grows with the number of pairs is the histogram, an LDS atomic per
+// pair: 8192 pairs 12.9 and 12.6 (8: 12.2 and 12.9), so 4096 is where the line lies.
+constexpr int kSmallIds = 8;
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void moe_route_small_kernel(const MoeRouteArgs a)
+{
+    constexpr int WAVES = THREADS / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, e = blockIdx.x;
+    __shared__ int hist[kMoeMaxExperts], hist_kept[kMoeMaxExperts];       // pairs per expert, and those whose rows get tiles
+    __shared__ int seg_tok[THREADS * kSmallIds];                         // this expert's tokens in sorted order
+    __shared__ int s_off[WAVES], s_tiles[WAVES], s_cnt[WAVES], s_below[WAVES];
+    const bool keep = a.keep_lo < a.keep_hi;
+    const int x_lo = keep ? a.keep_lo * a.topk : 0, x_hi = keep ? a.keep_hi * a.topk : 0;
+    const int i0 = tid * kSmallIds;
+    int v[kSmallIds];
+    if (i0 + kSmallIds <= a.P) {                     // (the ids are aligned to 16 bytes, i0 is a multiple of 8)
+        const int4 q0 = ((const int4*)a.topk_ids)[2 * tid], q1 = ((const int4*)a.topk_ids)[2 * tid + 1];
+        v[0] = q0.x; v[1] = q0.y; v[2] = q0.z; v[3] = q0.w;
+        v[4] = q1.x; v[5] = q1.y; v[6] = q1.z; v[7] = q1.w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < kSmallIds; ++k) v[k] = i0 + k < a.P ? a.topk_ids[i0 + k] : -1;
+    }
+    for (int i = tid; i < a.E; i += THREADS) {
+        hist[i] = 0;
+        if (keep) hist_kept[i] = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSmallIds; ++k)
+        if ((unsigned)v[k] < (unsigned)a.E) {
+            atomicAdd(&hist[v[k]], 1);
+            if (keep && i0 + k >= x_lo && i0 + k < x_hi) atomicAdd(&hist_kept[v[k]], 1);
+        }
+    // matches of this wave in front of this lane's, and below x_lo
+    int before = 0, wtot = 0, below = 0;
+#pragma unroll
+    for (int k = 0; k < kSmallIds; ++k) {
+        const bool hit = v[k] == e;
+        const unsigned long long m = __ballot(hit);
+        before += __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+        wtot += __popcll(m);
+        below += __popcll(__ballot(hit && i0 + k < x_lo));
+    }
+    if (lane == 0) { s_cnt[wave] = wtot; s_below[wave] = below; }
+    __syncthreads();
+    // the experts before e: segment offset and first tile index
+    const int* const tiled_of = keep ? hist_kept : hist;
+    int off = 0, tiles = 0;
+    for (int i = tid; i < e; i += THREADS) {
+        off += hist[i];
+        tiles += ((tiled_of[i] + a.bm - 1) / a.bm) * a.tiles_n;
+    }
+    for (int sft = 32; sft > 0; sft >>= 1) {
+        off += __shfl_down(off, sft);
+        tiles += __shfl_down(tiles, sft);
+    }
+    if (lane == 0) { s_off[wave] = off; s_tiles[wave] = tiles; }
+    __syncthreads();
+    int seg_lo = 0, first = 0, wbase = 0, lo_cnt = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        seg_lo += s_off[w];
+        first += s_tiles[w];
+        if (w < wave) wbase += s_cnt[w];
+        lo_cnt += s_below[w];
+    }
+    const int cnt = hist[e], tiled = tiled_of[e];
+    int at = wbase + before;
+#pragma unroll
+    for (int k = 0; k < kSmallIds; ++k) {
+        const int i = i0 + k;
+        if (v[k] == e) {
+            const int tk = i / a.topk;
+            seg_tok[at] = tk;
+            a.sorted_token[seg_lo + at] = tk;
+            if (a.pair_pos) a.pair_pos[i] = seg_lo + at;
+            ++at;
+        } else if (e == 0 && a.pair_pos && i < a.P && (unsigned)v[k] >= (unsigned)a.E) {
+            a.pair_pos[i] = -1;                      // an id outside [0, E): the pair is nowhere in the sorted order
+        }
+    }
+    const int mt = (tiled + a.bm - 1) / a.bm;
+    if (tid == 0) {
+        a.seg_off[e] = seg_lo;
+        if (e == a.E - 1) {
+            a.seg_off[a.E] = seg_lo + cnt;
+            const int total = first + mt * a.tiles_n;
+            *a.n_tiles_dev = total <= a.tab_capacity ? total : 0;         // the capacity is an upper bound by construction
+        }
+    }
+    __syncthreads();
+    if (first + mt * a.tiles_n > a.tab_capacity) return;
+    const int row_lo = keep ? lo_cnt : 0;            // inside the segment
+    for (int k = tid; k < mt * a.tiles_n; k += THREADS) {
+        const int n = k / mt, m = k - n * mt;
+        const int r0 = row_lo + m * a.bm, r1 = min(r0 + a.bm, row_lo + tiled);
+        MoeTile t;
+        t.expert = e;
+        t.m0 = t.st_lo = seg_lo + r0;
+        t.m_end = t.st_hi = seg_lo + r1;
+        t.n_tile = n;
+        t.f_lo = min(seg_tok[r0] / a.rows_per_flag, a.n_flags - 1);
+        t.f_hi = min(seg_tok[r1 - 1] / a.rows_per_flag, a.n_flags - 1);
+        a.tile_tab[first + k] = t;
+    }
+}
+
 // Top-k reduction (Section 4.1, "MoE ReduceScatter", the step between the grouped GEMM and the reduce scatter):
 // every token's `topk` rows of Y are weighted with its gate values and summed in slot order, fp32, starting from the
 // first product.  Streaming, one float4 column chunk per lane, tokens of this rank first (their slice is what the
@@ -297,7 +410,9 @@ hipError_t launch_topk_reduce(const TopkReduceArgs& a, int n_workgroups, hipStre
 hipError_t launch_moe_route(const MoeRouteArgs& a, hipStream_t stream)
 {
     if (a.E > kMoeMaxExperts || !a.ctrl || !a.err) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(moe_route_kernel, dim3(a.E), dim3(kRouteThreads), 0, stream, a);
+    if (a.P <= 256 * kSmallIds) hipLaunchKernelGGL(moe_route_small_kernel<256>, dim3(a.E), dim3(256), 0, stream, a);
+    else if (a.P <= 512 * kSmallIds) hipLaunchKernelGGL(moe_route_small_kernel<512>, dim3(a.E), dim3(512), 0, stream, a);
+    else hipLaunchKernelGGL(moe_route_kernel, dim3(a.E), dim3(kRouteThreads), 0, stream, a);
     return hipGetLastError();
 }
 
