@@ -21,9 +21,12 @@
 //   MF = 32: v_mfma_f32_32x32x16_bf16.  A stage is four quarter-steps of K = 16, fragments double-buffered.
 // One workgroup barrier per stage; memory instructions are dealt out between the MFMAs (a wave issues in
 // order, and bunches of memory instructions between two MFMAs starve the matrix pipe).
-// The MFMA computes the transposed block (B fragment as first operand), so that a lane ends up holding
-// four consecutive columns of one output row; the epilogue stages each wave's rows through LDS and
-// stores them to C as whole 16-byte row chunks.
+// The columns are dealt to the 16x16 blocks so that a lane ends up holding 4 (fp32) or 8 (bf16) consecutive columns of an output row and
+// 16 lanes a whole run of them (out_cols).  fp32 rows go from the registers to C, 256 bytes of a row by 16 lanes; bf16 ones through LDS,
+// so that a store covers whole rows of the tile.  (MF = 32 computes the transposed block, B fragment as first operand: four consecutive
+// columns of a row per lane; it stages both.)  fp32, 16 rows by 64 bytes per store before and 4 rows by 256 now, us: GEMM half of
+// gemm_rs_full 374 -> 352 (256x256; 409 -> 378 on 256x224 tiles, 530 -> 499 on 128x128).  bf16 straight from the registers, 256x224: 70B
+// shape 685 -> 694, 8B 119.1 -> 120.6.
 //
 // Registers: the fp32 accumulators live in accumulator registers a0..a(ACC-1) that only the inline
 // asm of this file touches (MFMA, zeroing, read-out); the compiler allocates the ordinary registers and is
@@ -60,6 +63,74 @@ __device__ __forceinline__ float acc_read()
     float x;
     asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(x) : "n"(R));
     return x;
+}
+
+// ---- how the columns of a tile are dealt to its 16-column blocks (16x16x32 form).  A lane of a block holds, of four rows, the block's column
+// l % 16.  Block j of a group of g blocks therefore takes the columns j, j + g, j + 2 g, ... of the group: a lane then holds g
+// consecutive columns of a row and 16 lanes 16 g of them, so that rows go from the registers to memory in whole lines, consecutive lanes
+// side by side.  Where g is 8 (bf16) or 4 (fp32) a lane stores 16 bytes and 16 lanes 256.  What it costs is nothing: the rows of B
+// are put into LDS in that order.  (With consecutive columns in a block and rows across the lanes, a store touches 16 rows in
+// pieces of 64 bytes: 32 KB/us per compute unit, against 79 for lanes side by side, and with the streaming hint 2.6 TB/s for all of them, against
+// 5.5; bf16 then had to go through LDS.)
+struct OutCols { int n, start[4], size[4]; };      // groups: first block, number of blocks
+template <int BN, int ESZ>
+__host__ __device__ constexpr OutCols out_cols()
+{
+    OutCols c{};
+    for (int at = 0; at < BN / 16;) {
+        int g = 16 / ESZ;
+        while (g > BN / 16 - at) g /= 2;
+        c.start[c.n] = at;
+        c.size[c.n++] = g;
+        at += g;
+    }
+    return c;
+}
+// The column of the tile that row l of B's tile in LDS holds.
+template <int BN, int ESZ>
+__device__ __forceinline__ int out_col(int l)
+{
+    constexpr OutCols c = out_cols<BN, ESZ>();
+    int col = 0;
+#pragma unroll
+    for (int k = 0; k < c.n; ++k) {
+        const int m = l - 16 * c.start[k];
+        if (m >= 0) col = 16 * c.start[k] + c.size[k] * (m & 15) + (m >> 4);
+    }
+    return col;
+}
+// The G values that a lane holds of a row: accumulators R, R + 4, ..
+template <class T, int G, int R>
+__device__ __forceinline__ auto acc_row()
+{
+    typedef __attribute__((__vector_size__(G * sizeof(T)))) T V;
+    V x;
+    static_for<G>([&](auto k_c) { x[decltype(k_c)::value] = (T)acc_read<R + 4 * decltype(k_c)::value>(); });
+    return x;
+}
+template <int AUX, class V>
+__device__ __forceinline__ void buffer_store(const V& x, __amdgpu_buffer_rsrc_t rs, unsigned off)
+{
+    typedef __attribute__((__vector_size__(16))) unsigned u32x4;
+    typedef __attribute__((__vector_size__(8))) unsigned u32x2;
+    if constexpr (sizeof(V) == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rs, off, 0, AUX);
+    else if constexpr (sizeof(V) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), rs, off, 0, AUX);
+    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), rs, off, 0, AUX);
+}
+// x to q[0], q[1], .., of which `left` are inside the matrix.
+template <bool NT, class T, class V>
+__device__ __forceinline__ void store_cols(T* q, const V& x, int left)
+{
+    constexpr int G = sizeof(V) / sizeof(T);
+    if (left >= G) {
+        if constexpr (NT) __builtin_nontemporal_store(x, (unaligned_t<V>*)q);
+        else *(unaligned_t<V>*)q = x;
+    } else {
+        static_for<G - 1>([&](auto k_c) {
+            constexpr int k = decltype(k_c)::value;
+            if (k < left) q[k] = x[k];
+        });
+    }
 }
 
 [[maybe_unused]] constexpr int QS = 4;   // quarter-steps (K = 16 each) per stage
@@ -263,8 +334,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
                 } else {
                     ld_off[i] = (unsigned)((u * UNIT_ROWS + ld_row) * (int)p.lda * 2 + chunk * 16);
                 }
-            } else
-                ld_off[i] = (unsigned)(((u - C_::A_UNITS) * UNIT_ROWS + ld_row) * (int)p.ldb * 2 + chunk * 16);
+            } else {
+                int col = (u - C_::A_UNITS) * UNIT_ROWS + ld_row;
+                if constexpr (MF == 16) col = p.c_is_f32 ? out_col<BN, 4>(col) : out_col<BN, 2>(col);
+                ld_off[i] = (unsigned)(col * (int)p.ldb * 2 + chunk * 16);
+            }
         }
 
         // one global->LDS load: the i-th load of stage ks of this wave, into ring position pos (compile-time)
@@ -321,8 +395,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
             });
 
             // ---- main loop, PERIOD stages per pass so that ring positions are constants.  The MFMAs are volatile asm,
-            // so memory operations keep their place between them: the order below is the schedule.  The B fragment
-            // is the first MFMA operand, so accumulator block (i, j) holds the transposed 16x16 block.
+            // so memory operations keep their place between them: the order below is the schedule.
             //
             // Stage ks: during half-step 0 every fragment of half-step 1 is read.  In half-step 1, after DLY groups (by
             // then the wave's last reads of stage ks are long back), the wave waits until its own loads of stage ks+1
@@ -352,7 +425,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
                         static_for<C_::NS>([&](auto s_c) {
                             constexpr int sl = decltype(s_c)::value;
                             constexpr int j = sl / MB16, i = sl % MB16;
-                            mfma_acc16<i * NB16 + j>(fb[j], fa[h][i]);
+                            mfma_acc16<i * NB16 + j>(fa[h][i], fb[j]);
                             if constexpr (h == 1 && sl == C_::SB) {
                                 // stage ks+1 has landed for this wave (all but the RW - 2L youngest loads are back) and
                                 // its own fragment reads of stage ks are back; after the barrier that holds for all waves
@@ -487,7 +560,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
             }
         }
 
-        // ---- epilogue.  Accumulator block (i, j) is the transposed block: lane l holds output row
+        // ---- epilogue.  MF = 16: lane l holds of accumulator block (i, j), in register v, row i*16 + 4*(l/16) + v of a column that
+        // out_cols names.  MF = 32: accumulator block (i, j) is the transposed block: lane l holds output row
         // i*32 + l%32 and, in register v, column j*32 + 8*(v/4) + 4*(l/32) + v%4 -- four consecutive columns per
         // group of four registers.
         asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7");     // the last MFMAs retire before the read-out
@@ -508,58 +582,59 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
                 const int cpr_valid = n_valid * esz / 16;                  // whole 16-byte chunks of a row, and what is left
                 const int tail = n_valid - cpr_valid * (16 / esz);
                 if constexpr (MF == 16 && esz == 4) {
-                    // fp32 output from 16x16 blocks: the four values a lane holds of a block are 16 consecutive
-                    // bytes of an output row, and the four lanes that share a row cover 64 consecutive bytes --
-                    // whole 64-byte sectors per store, so the values go from the registers straight to memory
-                    // (neighbouring column blocks, stored back to back, complete the 128-byte lines in L2)
-                    const int colq = 4 * (lane_e >> 4);
-                    static_for<C_::MB16>([&](auto i_c) {
-                        constexpr int i = decltype(i_c)::value;
-                        char* dst = row_ptr(row_w + i * 16 + (lane_e & 15), esz);
-                        if (dst) {
-                            T* q = (T*)dst + colq;
-                            auto store_row = [&](auto put) {
-                                static_for<C_::NB16>([&](auto j_c) {
-                                    constexpr int j = decltype(j_c)::value;
-                                    constexpr int r0 = (i * C_::NB16 + j) * 4;
-                                    const float x0 = acc_read<r0>(), x1 = acc_read<r0 + 1>(), x2 = acc_read<r0 + 2>(),
-                                                x3 = acc_read<r0 + 3>();
-                                    if (n_valid == BN || colq + j * 16 + 4 <= n_valid) {
-                                        put(Tx4{(T)x0, (T)x1, (T)x2, (T)x3}, (unaligned_t<Tx4>*)(q + j * 16));
-                                    } else {                       // the ragged end of the row
-                                        if (colq + j * 16 < n_valid) q[j * 16] = (T)x0;
-                                        if (colq + j * 16 + 1 < n_valid) q[j * 16 + 1] = (T)x1;
-                                        if (colq + j * 16 + 2 < n_valid) q[j * 16 + 2] = (T)x2;
-                                    }
-                                });
-                            };
-                            // rows in place (MoE + ReduceScatter): the next kernel reads them, they may stay in the caches
-                            // (256x256 tiles at K = 192: 80 us with streaming stores, 70 without)
-                            if (GROUPED && !p.row_index) store_row([](Tx4 v, unaligned_t<Tx4>* at) { *at = v; });
-                            else store_row([](Tx4 v, unaligned_t<Tx4>* at) { __builtin_nontemporal_store(v, at); });
+                    // fp32: 16 lanes hold consecutive columns of a row (out_cols): straight from the registers to memory, rows
+                    // 4 (l / 16) + 0..3 of every 16.  They go to C, or (GEMM-RS) to the destination of their slice; a tile that touches
+                    // two slices looks the destination up row by row.  C is not read again by this kernel: streaming stores keep it from
+                    // displacing the A and B lines that are.
+                    constexpr OutCols cols = out_cols<BN, esz>();
+                    char* base = p.C ? (char*)p.C + ((long long)row_w * p.ldc + n0) * esz : nullptr;
+                    long long ld = p.ldc * esz;
+                    bool one_dst = true;
+                    if (!GROUPED && p.n_slices) {
+                        const int w0 = m0 / p.slice_rows;
+                        one_dst = (min(m0 + BM, p.M) - 1) / p.slice_rows == w0;
+                        if (one_dst && p.slice_dst[w0]) {
+                            base = (char*)p.slice_dst[w0] + ((long long)(row_w - w0 * p.slice_rows) * p.ldc_slice + n0) * esz;
+                            ld = p.ldc_slice * esz;
                         }
-                    });
+                    }
+                    auto store_rows = [&](auto nt_c) {
+                        static_for<C_::MB16 * 4>([&](auto iv_c) {
+                            constexpr int i = decltype(iv_c)::value / 4, v = decltype(iv_c)::value % 4;
+                            const int r = i * 16 + 4 * (lane_e >> 4) + v, row = row_w + r;
+                            char* dst = one_dst ? (base && row >= st_lo && row < st_hi ? base + r * ld : nullptr) : row_ptr(row, esz);
+                            if (dst)
+                                static_for<cols.n>([&](auto g_c) {
+                                    constexpr int s = cols.start[decltype(g_c)::value], g = cols.size[decltype(g_c)::value];
+                                    const int col = 16 * s + g * (lane_e & 15);
+                                    store_cols<decltype(nt_c)::value>((T*)dst + col, acc_row<T, g, (i * C_::NB16 + s) * 4 + v>(), n_valid - col);
+                                });
+                        });
+                    };
+                    // rows in place (MoE + ReduceScatter): the next kernel reads them, they may stay in the caches
+                    // (256x256 tiles at K = 192: 80 us with streaming stores, 70 without)
+                    if (GROUPED && esz == 4 && !p.row_index) store_rows(std::false_type{});
+                    else store_rows(std::true_type{});
                     return;
-                }
+                } else {
                 // stage 32 rows x BN columns per pass in this wave's own part of LDS, then move whole
                 // 16-byte chunks of rows to C: full cache lines per store instruction
                 constexpr int pitch = BN * esz + 16;
                 constexpr int cpr = BN * esz / 16;                // 16-byte chunks per row
                 constexpr int iters = (32 * cpr + 63) / 64;       // chunk c = lane + 64*it: row c / cpr, chunk c % cpr
                 unsigned char* stage = lds + wave * 32 * pitch;
-                unsigned char* wr = MF == 16 ? stage + (lane_e & 15) * pitch + 4 * (lane_e >> 4) * esz
-                                             : stage + (lane_e & 31) * pitch + 4 * (lane_e >> 5) * esz;
+                unsigned char* wr = MF == 16 ? stage + 4 * (lane_e >> 4) * pitch : stage + (lane_e & 31) * pitch + 4 * (lane_e >> 5) * esz;
                 const int r_lane = lane_e / cpr, cc_lane = lane_e - r_lane * cpr;
                 static_for<MB>([&](auto i_c) {
                     constexpr int i = decltype(i_c)::value;
                     if constexpr (MF == 16) {
-                        // 16x16 block (ib, j) of the pass: lane l holds row 16 ib + l%16, columns 16 j + 4 (l/16) + 0..3
-                        static_for<2 * C_::NB16>([&](auto bj_c) {
-                            constexpr int ib = decltype(bj_c)::value / C_::NB16, j = decltype(bj_c)::value % C_::NB16;
-                            constexpr int r0 = ((2 * i + ib) * C_::NB16 + j) * 4;
-                            const float x0 = acc_read<r0>(), x1 = acc_read<r0 + 1>(), x2 = acc_read<r0 + 2>(),
-                                        x3 = acc_read<r0 + 3>();
-                            *(Tx4*)(wr + ib * 16 * pitch + j * 16 * esz) = Tx4{(T)x0, (T)x1, (T)x2, (T)x3};
+                        // 16-row block ib of the pass: lane l holds columns of rows 16 ib + 4 (l / 16) + 0..3
+                        constexpr OutCols cols = out_cols<BN, esz>();
+                        static_for<8 * cols.n>([&](auto c_) {
+                            constexpr int gi = decltype(c_)::value % cols.n, v = decltype(c_)::value / cols.n % 4, ib = decltype(c_)::value / cols.n / 4;
+                            constexpr int s = cols.start[gi], g = cols.size[gi];
+                            const auto x = acc_row<T, g, ((2 * i + ib) * C_::NB16 + s) * 4 + v>();
+                            *(decltype(acc_row<T, g, 0>())*)(wr + (ib * 16 + v) * pitch + (16 * s + g * (lane_e & 15)) * esz) = x;
                         });
                     } else {
                         static_for<NB * 4>([&](auto jq_c) {
@@ -653,6 +728,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
                         if (dst) ((T*)dst)[e] = *(const T*)(stage + tr * pitch + e * esz);
                     }
                 });
+                }
             };
             if (p.c_is_f32) epilogue(float{}); else epilogue(__bf16{});
         }

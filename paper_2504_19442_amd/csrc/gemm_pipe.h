@@ -6,9 +6,9 @@
 //    the one after that; loads return in order, so the wait for A leaves B in flight, and B, which comes from HBM, has two stages to
 //    arrive, A, which mostly hits the L2, one.
 //  * The stream does not end with a tile: the last stages of a tile ask for the first ones of the next, whose list entry, token rows
-//    and signals are looked at meanwhile, and the tile's rows are stored while those are on their way.  The staging area of the
-//    stores is therefore apart from the rings, and every store is counted (buffer stores whose descriptor holds back the
-//    rows that are not wanted), so that the first wait of the next tile can leave them outstanding.
+//    and signals are looked at meanwhile, and the tile's rows are stored while those are on their way: from the registers (the rings are
+//    in use), and counted (buffer stores whose descriptor holds back the rows that are not wanted), so that the first wait of the
+//    next tile can leave them outstanding.
 //  * The entries of the tile list and the token rows come through LDS as well: a load into registers would be waited for together with
 //    every load in front of it.
 // Shapes: 320x128 and 192x192 are there for segments that fill one tile but not two of a power of two (each weight then crosses the load
@@ -17,7 +17,8 @@
 // Measured, Table 4 (8192 tokens, 222 to 298 rows per expert, 1 GB of weights), routing and GEMM, us: 256x256 of gemm_kernel 382; 320x128
 // in that kernel 340, with the streaming hint on B 313; here 298 (kernel 280 to 300: 3.6 to 4 TB/s, 0.9 to 1 PFLOP/s; 59 % of the cycles
 // are MFMAs, at 1.9 GHz).  What is left: the load path, 56 KiB per 1280 MFMA cycles (the loop of gemm_kernel without any loads takes 208 us,
-// without those of A 268, without those of B 245), and power.  Table 5 (K = 192, rows in place, fp32), kernel: 54 -> 47.6, 3.9 TB/s.
+// without those of A 268, without those of B 245), and power.  Table 5 (K = 192, rows in place, fp32), kernel: 54 -> 47.6, 3.9 TB/s;
+// with whole lines per store (out_cols) the call is 108.6 -> 102.3, Table 4 in fp32 341 -> 334.
 #pragma once
 #include "gemm_kernel.h"
 #include "ks_stage.h"
@@ -31,18 +32,15 @@ struct PipeCfg : TileCfg<BM, BN> {
     static constexpr int LA = BM / 32, LB = BN / 32;         // loads of a stage, per wave
     static constexpr int A_STAGE = BM * ROW_BYTES, B_STAGE = BN * ROW_BYTES;
     static constexpr int B_AT = RA * A_STAGE;                // where B's ring starts
-    static constexpr int ER = 16;                            // rows a wave stages at a time for its stores
-    static constexpr int PITCH = BN * 2 + 16;
-    static constexpr int STAGING_AT = B_AT + RB * B_STAGE;
-    static constexpr int ROWS_AT = STAGING_AT + 4 * ER * PITCH;          // rows of A of the next tile
+    static constexpr int ROWS_AT = B_AT + RB * B_STAGE;      // rows of A of the next tile
     static constexpr int ROW_LOADS = (BM + 255) / 256;                   // a wave's loads of them
     static constexpr int ENTRY_AT = ROWS_AT + ROW_LOADS * 1024;          // an entry of the tile list, a copy per wave
     static constexpr int WORD_AT = ENTRY_AT + 1024;
     static constexpr int LDS_BYTES = WORD_AT + 16;
     static constexpr int MIN_STAGES = RB;                    // a tile has at least this many stages (empty ones, where K is shorter)
-    static constexpr int N_ST_BF16 = Base::MB16 * (ER * BN * 2 / 16 / 64), N_ST_F32 = Base::MB16 * Base::NB16;
+    static constexpr int N_ST_BF16 = Base::MB16 * 4 * out_cols<BN, 2>().n, N_ST_F32 = Base::MB16 * 4 * out_cols<BN, 4>().n;     // stores of a wave
     static_assert(RB == RA + 1, "what a stage's barrier waits for: all but the last stage of B");
-    static_assert(Base::L == LA + LB && LDS_BYTES <= 159 * 1024 && (ER * BN * 2 / 16) % 64 == 0, "tile");
+    static_assert(Base::L == LA + LB && LDS_BYTES <= 159 * 1024, "tile");
 };
 
 // first MFMA of a tile's accumulator block: C = 0
@@ -140,7 +138,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
         for (int i = 0; i < LA; ++i) off_a[i] = w.m0 + ld_row + i * 32 < w.m_lim ? row[i] * lda2 + ld_chunk : 0x80000000u;
     };
 #pragma unroll
-    for (int i = 0; i < LB; ++i) off_b[i] = (unsigned)(ld_row + i * 32) * ldb2 + ld_chunk;
+    for (int i = 0; i < LB; ++i) off_b[i] = (unsigned)(p.c_is_f32 ? out_col<BN, 4>(ld_row + i * 32) : out_col<BN, 2>(ld_row + i * 32)) * ldb2 + ld_chunk;
 
     // ---- the stream of loads.  The stages of a tile are followed by those of the next one; a stage past the end of K, or of the list,
     // loads nothing.
@@ -274,8 +272,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
             static_for<C_::NS>([&](auto s_c) {
                 constexpr int sl = decltype(s_c)::value;
                 constexpr int j = sl / MB16, i = sl % MB16;
-                if constexpr (first && h == 0) mfma_acc16_first<i * NB16 + j>(fb[j], fa[h][i]);
-                else mfma_acc16<i * NB16 + j>(fb[j], fa[h][i]);
+                if constexpr (first && h == 0) mfma_acc16_first<i * NB16 + j>(fa[h][i], fb[j]);
+                else mfma_acc16<i * NB16 + j>(fa[h][i], fb[j]);
                 if constexpr (h == 1 && sl == C_::SB) {
                     // The running stage's fragments are all in registers, and the next stage has landed: of the loads behind it, those
                     // of B alone may be outstanding (and, in a tile's first stage, the stores of the tile before it).
@@ -342,87 +340,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
             auto stores = [&](auto tag) {
                 using T = decltype(tag);
                 constexpr int esz = sizeof(T);
-                typedef __attribute__((__vector_size__(4 * sizeof(T)))) T Tx4;
-                typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
+                constexpr OutCols cols = out_cols<BN, esz>();
                 char* const c_row0 = (char*)p.C + ((long long)row_w * p.ldc + cur.n0) * esz;
                 const unsigned ldc_b = (unsigned)p.ldc * esz;
                 // whole columns, rows that start on 16 bytes: a fixed number of stores, rows outside [st_lo, st_hi) held back by the
                 // descriptor
                 const bool whole = n_valid == BN && ((reinterpret_cast<uintptr_t>(p.C) | ((unsigned long long)p.ldc * esz)) & 15) == 0 && p.ldc < (1 << 22);
                 first_wait = !whole ? WAIT_ALL : esz == 2 ? WAIT_BF16 : WAIT_F32;
-                if constexpr (esz == 4) {
-                    const int colq = 4 * (lane_e >> 4);
-                    auto store_rows = [&](auto nt_c) {
-                        const __amdgpu_buffer_rsrc_t rs = make_rsrc(c_row0, (unsigned)TM * ldc_b);
-                        static_for<MB16>([&](auto i_c) {
-                            constexpr int i = decltype(i_c)::value;
-                            const int r = i * 16 + (lane_e & 15);
-                            const bool in = row_w + r >= cur.st_lo && row_w + r < cur.st_hi;
-                            const unsigned off = in ? (unsigned)r * ldc_b + (unsigned)colq * 4u : 0x80000000u;
-                            static_for<NB16>([&](auto j_c) {
-                                constexpr int j = decltype(j_c)::value;
-                                constexpr int r0 = (i * NB16 + j) * 4;
-                                const float x0 = acc_read<r0>(), x1 = acc_read<r0 + 1>(), x2 = acc_read<r0 + 2>(), x3 = acc_read<r0 + 3>();
-                                const Tx4 v{x0, x1, x2, x3};
-                                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, off + j * 64, 0, decltype(nt_c)::value);
-                            });
-                        });
-                    };
-                    if (whole) {
-                        // rows in place (MoE + ReduceScatter): the next kernel reads them, they may stay in the caches
-                        if (p.row_index) store_rows(std::integral_constant<int, 2>{});
-                        else store_rows(std::integral_constant<int, 0>{});
-                    } else {
-                        static_for<MB16>([&](auto i_c) {
-                            constexpr int i = decltype(i_c)::value;
-                            const int r = i * 16 + (lane_e & 15);
-                            const bool in = row_w + r >= cur.st_lo && row_w + r < cur.st_hi;
-                            T* q = (T*)(c_row0 + (long long)r * p.ldc * esz) + colq;
-                            static_for<NB16>([&](auto j_c) {
-                                constexpr int j = decltype(j_c)::value;
-                                constexpr int r0 = (i * NB16 + j) * 4;
-                                const float x[4] = {acc_read<r0>(), acc_read<r0 + 1>(), acc_read<r0 + 2>(), acc_read<r0 + 3>()};
-                                if (in && colq + j * 16 + 4 <= n_valid) *(unaligned_t<Tx4>*)(q + j * 16) = Tx4{x[0], x[1], x[2], x[3]};
-                                else if (in) {
-                                    if (colq + j * 16 < n_valid) q[j * 16] = x[0];
-                                    if (colq + j * 16 + 1 < n_valid) q[j * 16 + 1] = x[1];
-                                    if (colq + j * 16 + 2 < n_valid) q[j * 16 + 2] = x[2];
-                                }
-                            });
-                        });
-                    }
-                } else {
-                    // ER rows x BN columns at a time through this wave's part of the staging area, then whole 16-byte chunks of rows
-                    constexpr int ER = C_::ER, PITCH = C_::PITCH, CPR = BN * 2 / 16, ITERS = ER * CPR / 64;
-                    unsigned char* const st = lds + C_::STAGING_AT + wave * (ER * PITCH);
-                    unsigned char* const wr = st + (lane_e & 15) * PITCH + 8 * (lane_e >> 4);
-                    const __amdgpu_buffer_rsrc_t rs = make_rsrc(c_row0, (unsigned)TM * ldc_b);
-                    static_for<MB16>([&](auto i_c) {
-                        constexpr int i = decltype(i_c)::value;
-                        static_for<NB16>([&](auto j_c) {
-                            constexpr int j = decltype(j_c)::value;
-                            constexpr int r0 = (i * NB16 + j) * 4;
-                            const float x0 = acc_read<r0>(), x1 = acc_read<r0 + 1>(), x2 = acc_read<r0 + 2>(), x3 = acc_read<r0 + 3>();
-                            *(Tx4*)(wr + j * 32) = Tx4{(T)x0, (T)x1, (T)x2, (T)x3};
-                        });
-                        // (the wave reads what it wrote itself: LDS keeps a wave's operations in order)
-                        static_for<ITERS>([&](auto k_c) {
-                            constexpr int k = decltype(k_c)::value;
-                            const int c = lane_e + 64 * k, r = c / CPR, cc = c % CPR;
-                            const int row = row_w + i * 16 + r;
-                            const bool in = row >= cur.st_lo && row < cur.st_hi;
-                            const u32x4 v = *(const u32x4*)(st + r * PITCH + cc * 16);
-                            if (whole) {
-                                __builtin_amdgcn_raw_buffer_store_b128(v, rs, in ? (unsigned)(i * 16 + r) * ldc_b + cc * 16u : 0x80000000u, 0, 2);
-                            } else if (in) {
-                                T* q = (T*)(c_row0 + (long long)(i * 16 + r) * p.ldc * esz) + cc * 8;
-                                if (cc * 8 + 8 <= n_valid) *(unaligned_t<u32x4>*)q = v;
-                                else
-                                    for (int e = 0; cc * 8 + e < n_valid; ++e) q[e] = *(const T*)(st + r * PITCH + cc * 16 + e * 2);
-                            }
-                        });
+                // rows in place (MoE + ReduceScatter): the next kernel reads them, they may stay in the caches
+                const bool stream_out = esz == 2 || p.row_index;
+                const __amdgpu_buffer_rsrc_t rs = make_rsrc(c_row0, (unsigned)TM * ldc_b);
+                static_for<MB16 * 4>([&](auto iv_c) {
+                    constexpr int i = decltype(iv_c)::value / 4, v = decltype(iv_c)::value % 4;
+                    const int r = i * 16 + 4 * (lane_e >> 4) + v;
+                    const bool in = row_w + r >= cur.st_lo && row_w + r < cur.st_hi;
+                    const unsigned off = in ? (unsigned)r * ldc_b : 0x80000000u;
+                    static_for<cols.n>([&](auto g_c) {
+                        constexpr int s = cols.start[decltype(g_c)::value], g = cols.size[decltype(g_c)::value];
+                        const auto x = acc_row<T, g, (i * NB16 + s) * 4 + v>();
+                        const int col = 16 * s + g * (lane_e & 15);
+                        if (whole) {
+                            if (stream_out) buffer_store<2>(x, rs, off + col * esz);
+                            else buffer_store<0>(x, rs, off + col * esz);
+                        } else if (in) {
+                            store_cols<false>((T*)(c_row0 + (long long)r * p.ldc * esz) + col, x, n_valid - col);
+                        }
                     });
-                }
+                });
             };
             if (p.c_is_f32) stores(float{}); else stores(__bf16{});
         }
