@@ -21,7 +21,7 @@
 // Measured against the 128x128 tile of the large kernel (us per GEMM, B not in cache): 16 x 3584 x 4096 24.9 -> 8.5 (16x16
 // tiles), 64 x 8192 x 3584 33.3 -> 18.5 (64x32), 128 x 7168 x 8192 74.6 -> 42 (64x64), 999 x 1999 x 1984 21 -> 15.6 (64x128).
 // KN: a B stored [K][N], read in place by gemm_km_kernel (64x64, 64x128, 128x128): no transposed copy, which costs a kernel, its bytes twice and
-// an event.  Transposing and GEMM, and in place, us: 1024 x 3584 x 4096 49.6 -> 40.2 (128x128), 376 x 5160 x 1984 29.7 -> 17.8 (64x128),
+// an event.  Transposing and GEMM, and in place, us: 1024 x 3584 x 4096 49.6 -> 38.6 (128x128), 376 x 5160 x 1984 29.7 -> 17.8 (64x128),
 // 84 x 240 x 704 12.2 -> 7.6 (64x64).
 #pragma once
 #include "gemm_tile.h"
@@ -460,6 +460,7 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
         for (int i = 0; i < RB; ++i)
 #pragma unroll
             for (int j = 0; j < CB; ++j) acc[i][j] = f32x4_{0.f, 0.f, 0.f, 0.f};
+        constexpr int NM1 = RB * CB / 2;
         bf16x8 fa[2][RB], fb[2][CB];
         typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
         unsigned kn[2][KN ? 8 : 1];            // the column pairs of KN's next fragments
@@ -494,8 +495,6 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_sched_barrier(0);
-                issue_b(s + NST - 1, std::integral_constant<int, (slot + NST - 1) % NST>{});
-                issue_a(s + NST - 1, std::integral_constant<int, (slot + NST - 1) % NST>{});
                 read_frags(std::integral_constant<int, (slot + 1) % NST>{}, std::integral_constant<int, (slot + 1) & 1>{});
                 if constexpr (KN) {
                     u32x4 even, odd;
@@ -507,11 +506,27 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
                     fb[slot & 1][0] = __builtin_bit_cast(bf16x8, even);
                     fb[slot & 1][CB - 1] = __builtin_bit_cast(bf16x8, odd);
                 }
-#pragma unroll
-                for (int j = 0; j < CB; ++j)
-#pragma unroll
-                    for (int i = 0; i < RB; ++i)
+                auto multiply = [&](auto from_c, auto to_c) {
+                    static_for<decltype(to_c)::value - decltype(from_c)::value>([&](auto n_c) {
+                        constexpr int n = decltype(from_c)::value + decltype(n_c)::value, j = n / RB, i = n % RB;
                         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[slot & 1][j], fa[slot & 1][i], acc[i][j], 0, 0, 0);
+                    });
+                };
+                // One LDS read behind each MFMA, and the loads in the middle: all eight waves come from the barrier at once, and reads (or
+                // loads) ahead of the first MFMA hold each of them at the same queue while the matrix cores have nothing to do.  Reads
+                // and loads first, reads between MFMAs, and this, us: [K][N] 1024 x 3584 x 4096 (128x128) 40.2, 39.2, 38.6;
+                // 512 x 3584 x 4096 (64x128) 29.4, 28.6, 25.5; [N][K] 256 x 4096 x 4096 (64x64) 23.5, 22.7, 22.5; 512 x 3584 x 4096
+                // (64x128) 23.3, 22.6, 22.0.
+                multiply(std::integral_constant<int, 0>{}, std::integral_constant<int, NM1>{});
+                static_for<NM1>([&](auto) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);     // LDS read
+                });
+                __builtin_amdgcn_sched_barrier(0);
+                issue_b(s + NST - 1, std::integral_constant<int, (slot + NST - 1) % NST>{});
+                issue_a(s + NST - 1, std::integral_constant<int, (slot + NST - 1) % NST>{});
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(std::integral_constant<int, NM1>{}, std::integral_constant<int, RB * CB>{});
                 __builtin_amdgcn_sched_barrier(0);
             });
         }

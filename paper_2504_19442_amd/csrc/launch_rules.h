@@ -106,8 +106,9 @@ inline int best_tile(int num_cus, int M, int N, int K, bool slices = false, bool
 // Tile for a B stored [K][N] that can be read in place (its rows on 16 bytes, whole 16-byte chunks of columns), or -1: it is transposed first
 // and `cfg`, best_tile's choice for the transposed one, is taken.  Transposing costs its bytes, read and written, and 7.6 us: a kernel more and the
 // event behind the GEMM.  Over 166 problems drawn from M 16..8192, N 96..7168, K 256..8192 the choice takes 28 % less time than transposing
-// always, is never slower, and costs 0.3 % more than the better of both.  Both sides, us: 1024 x 3584 x 4096 128x128 in place 40.2,
-// transposed 49.6; 57 x 96 x 320 5.8 and 11.2; 30 x 336 x 2624 15.0 and 13.3; 2048 x 3584 x 4096 80.2 and 69.8.
+// always, is never slower, and costs 0.3 % more than the better of both (drawn before the in-place tiles got another 4 to 10 % faster).  Both sides,
+// us: 1024 x 3584 x 4096 128x128 in place 38.6, transposed 49.6; 57 x 96 x 320 5.8 and 11.2; 30 x 336 x 2624 15.0 and 13.3; 2048 x 3584 x 4096
+// 76 and 69.8.
 // cfg = -1: the best of the tiles that read in place (they all give the same bits).
 inline int tile_kn(int num_cus, int cfg, int M, int N, int K, bool slices = false)
 {
