@@ -4,8 +4,6 @@
 // registers, so its waves fit beside the consumer's on any CU (Section 3.8, resource partition).
 #include "agg_internal.h"
 
-#include <type_traits>
-
 // Cache policy bits of the buffer instructions below, in the gfx940 / gfx950 encoding of the `aux` operand:
 // 2 = nt (streaming) on the loads, 16 = sc1 (agent scope: written through this XCD's L2) on the stores.  The
 // publication of a chunk rests on three properties of this hardware, not on the language's memory model:
@@ -33,6 +31,12 @@ typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 // signal -- a wait for the stores to complete is the release.  (An agent-scope release fence would write
 // back the whole L2, once per workgroup and chunk, and that cost more than the copy itself.)  The consumer's
 // acquire invalidates its own L2 lines, so its loads fetch the data from memory.
+//
+// U independent 16-byte loads are in flight per lane.  Eight take 43 registers, so that a copy wave still fits beside a GEMM's on a SIMD
+// (64 are left), four 23.  Four and eight, us alone: 8 x 16 MiB 43.0 and 42.6, by one-wave workgroups 90.9 and 61.5, 4 x 2 MiB 6.9 and
+// 6.5, slices of 16 KiB, which four cover, 3.30 and 3.44.  Launches back to back, both in one kernel that looks at the slice, and this: 8 x
+// 16 KiB 3.05 and 2.96, 8 x 256 KiB 3.87 and 3.79, 3 x 1.3 MB 4.76 and 4.70.
+template <unsigned U>
 __global__ __launch_bounds__(256) void producer_kernel(const ProducerArgs a)
 {
     const int tid = threadIdx.x;
@@ -59,22 +63,14 @@ __global__ __launch_bounds__(256) void producer_kernel(const ProducerArgs a)
         const unsigned bytes = hi > lo ? (unsigned)((hi - lo) * 16) : 0u;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(s), 0, bytes, 0x00020000);
         const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(d, 0, bytes, 0x00020000);
-        // U independent 16-byte loads in flight per lane; out-of-range lanes of the last round load zero and store nothing (the
-        // descriptors bound both).  Eight where a slice is more than four cover: 43 registers, so that a copy wave still fits beside a
-        // GEMM's on a SIMD (64 are left).  Four and eight, us alone: 8 x 16 MiB 43.0 and 42.6, by one-wave workgroups 90.9 and 61.5,
-        // 4 x 2 MiB 6.9 and 6.5, slices of 16 KiB 3.30 and 3.44.
-        auto copy = [&](auto u_c) {
-            constexpr unsigned U = decltype(u_c)::value;
-            for (unsigned off = tid * 16u; off < bytes; off += U * span) {
-                u32x4 v[U];
+        // out-of-range lanes of the last round load zero and store nothing (the descriptors bound both)
+        for (unsigned off = tid * 16u; off < bytes; off += U * span) {
+            u32x4 v[U];
 #pragma unroll
-                for (unsigned k = 0; k < U; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, off + k * span, 0, NT);
+            for (unsigned k = 0; k < U; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, off + k * span, 0, NT);
 #pragma unroll
-                for (unsigned k = 0; k < U; ++k) __builtin_amdgcn_raw_buffer_store_b128(v[k], rd, off + k * span, 0, WT);
-            }
-        };
-        if (bytes <= 4u * span) copy(std::integral_constant<unsigned, 4>{});
-        else copy(std::integral_constant<unsigned, 8>{});
+            for (unsigned k = 0; k < U; ++k) __builtin_amdgcn_raw_buffer_store_b128(v[k], rd, off + k * span, 0, WT);
+        }
         // signal: the last workgroup of the team to finish the chunk sets it (set_signal after the copy, Algorithm 2)
         __builtin_amdgcn_s_waitcnt(0);              // every store of this lane has completed
         __syncthreads();                            // ... of this workgroup
@@ -169,16 +165,20 @@ __global__ void epoch_advance_kernel(int* epoch_word)
 hipError_t launch_producer(const ProducerArgs& a_in, int n_workgroups, int threads, hipStream_t stream)
 {
     ProducerArgs a = a_in;
-    // team size: slices of at least 64 KiB, at most the whole grid on one chunk.  Where slices of 32 KiB leave three eighths of the grid
-    // without one, those: they are copied in one trip, and the teams, each of whose workgroups counts itself done at one
-    // address, stay small enough.  Slices of 64 and 32 KiB, us, 256 workgroups: 8 x 256 KiB 4.4 and 3.9, 3 x 1.3 MB 6.1 and 5.0, 2 x 2 MiB 5.4 and
-    // 5.0, 4 x 1.5 MiB 6.1 and 6.1, 4 x 2 MiB 6.5 and 7.3 (16 KiB: 4.5, 6.0, 6.2, 8.0, 9.9).
+    // team size: slices of at least 64 KiB, at most the whole grid on one chunk.  Where slices of 32 KiB and a little more leave three eighths
+    // of the grid without one, those: a workgroup of four waves copies 32 KiB in one trip (a rest of a few hundred bytes in a second
+    // one, where the chunk is no multiple of 32 KiB), and the teams, each of whose workgroups counts itself done at one address, stay
+    // small enough.  Slices of 64 and 32 KiB, us, 256 workgroups: 8 x 256 KiB 4.4 and 3.9, 3 x 1.3 MB 6.1 and 5.0, 2 x 2 MiB 5.4 and 5.0,
+    // 4 x 1.5 MiB 6.1 and 6.1, 4 x 2 MiB 6.5 and 7.3 (16 KiB: 4.5, 6.0, 6.2, 8.0, 9.9).
     const long long total = a.chunk_bytes * a.chunks_per_shard * a.n_jobs;
     long long team = a.chunk_bytes / (total / 32768 <= n_workgroups * 5ll / 8 ? 32768 : 65536);
     if (team < 1) team = 1;
     if (team > n_workgroups) team = n_workgroups;
     a.team = (int)team;
-    hipLaunchKernelGGL(producer_kernel, dim3(n_workgroups), dim3(threads), 0, stream, a);
+    // a slice that four loads per lane cover gains nothing from eight
+    const long long slice = (a.chunk_bytes / 16 + team - 1) / team * 16;
+    if (slice <= 4ll * 16 * threads) hipLaunchKernelGGL(producer_kernel<4>, dim3(n_workgroups), dim3(threads), 0, stream, a);
+    else hipLaunchKernelGGL(producer_kernel<8>, dim3(n_workgroups), dim3(threads), 0, stream, a);
     return hipGetLastError();
 }
 
