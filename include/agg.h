@@ -215,7 +215,8 @@ int gemm_rs(agg_ctx* ctx, int M, int N, int Klocal,
  * tile shapes x both tile orders x three producer sizes (half, one and two workgroups per compute unit; one candidate
  * when the copy engines are used).  Each candidate runs once to warm up (before the very first one there are twenty-nine runs
  * more, so that the chip's clocks have settled) and runs_per_config more times; the median run counts.  For problems on which
- * the automatic choice takes one of its small tiles (see agg_set_tile_config) those first runs use that choice and the last
+ * the automatic choice takes one of its small tiles (see agg_set_tile_config) or reads a [K][N] operand in place (see AGG_B_KN; the
+ * candidates transpose it) those first runs use that choice and the last
  * fifteen are timed: where no candidate comes within a microsecond of it the result is tile_config = -1 (automatic) in the
  * rotated order.  The GPU is held back for 0.1 ms before every run, so that the time is the GPU's and not that of the host's
  * calls.  The best configuration is stored in the context (tile shape, tile order, producer

@@ -644,10 +644,12 @@ int agg_autotune_ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb
     };
     // Untimed runs first: one per candidate, and a longer series before the very first candidate, so that the chip's clocks
     // have settled under load before anything is compared.  Where the automatic choice takes a tile that is not among the
-    // candidates, that series runs with it, and its second half is timed: the time a candidate has to come near to.
+    // candidates (a small one, or one that reads a [K][N] operand in place), that series runs with it, and its second half is timed:
+    // the time a candidate has to come near to.
     constexpr int kWarm = 30, kSettled = 15;
     c->tile_config = -1;
-    const bool automatic = choose_tile(c, M, N, K) >= TILE_CONFIGS;
+    int auto_tile = choose_tile(c, M, N, K);
+    const bool automatic = kn_in_place(c, B, ldb, b_layout, M, N, K, false, &auto_tile) || auto_tile >= TILE_CONFIGS;
     std::vector<float> auto_times;
     for (int it = 0; it < kWarm - 1 && rc == AGG_OK; ++it) {
         c->tile_config = automatic ? -1 : tiles[0];

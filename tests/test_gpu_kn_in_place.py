@@ -133,3 +133,69 @@ def test_weights_beyond_the_memory_side_cache():
         assert torch.equal(C, torch.cat(shards).float() @ B.float())
     finally:
         ctx.free()
+
+
+def _call(ctx, shards, M, N, K, B, ldb, layout):
+    ps, cs = ctx.streams()
+    C = torch.full((M, N), float("nan"), device="cuda")
+    agg.signal_reset(ctx)
+    torch.cuda.synchronize()
+    agg.ag_producer_emulate(ctx, shards, None, agg.PRODUCER_KERNEL, 0, ps)
+    agg.ag_gemm(ctx, M, N, K, B, ldb, layout, C, N, agg.F32, cs)
+    torch.cuda.synchronize()
+    assert agg.agg_status(ctx) == agg.OK
+    return C
+
+
+class _Problem:
+    """Random inputs: read in place K is added up in two halves, by the numbered tiles in one run, so that the bits tell which it was."""
+
+    def __init__(self, seed, Ms, K, N, cps=1):
+        self.W, self.Ms, self.K, self.N = 4, Ms, K, N
+        self.M = self.W * Ms
+        assert host_rules.kn_tile(_cus(), self.M, self.N, self.K) == "128x128"
+        assert host_rules.gemm_tile(_cus(), self.M, self.N, self.K)[0] == "numbered"
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        self.shards = [torch.empty((Ms, self.K), device="cuda", dtype=torch.bfloat16).uniform_(-1, 1, generator=g) for _ in range(self.W)]
+        self.kn = torch.empty((self.K, self.N), device="cuda", dtype=torch.bfloat16).normal_(0, 0.02, generator=g)
+        self.nk = self.kn.t().contiguous()
+        self.cps, self.open = cps, []
+        self.in_place = self.by_kn(self.context())
+        numbered = self.context()
+        numbered.set_tile_config(5)
+        self.copied = self.by_kn(numbered)
+        assert not torch.equal(self.in_place, self.copied) and torch.equal(self.copied, self.by_nk(numbered))
+
+    def context(self):
+        ctx = agg.symm_alloc(self.W, 0, self.Ms * self.K * 2, self.W * self.cps)
+        self.open.append(ctx)
+        agg.agg_reserve_b_kn(ctx, self.N, self.K)
+        return ctx
+
+    def by_kn(self, ctx):
+        return _call(ctx, self.shards, self.M, self.N, self.K, self.kn, self.N, agg.B_KN)
+
+    def by_nk(self, ctx):
+        return _call(ctx, self.shards, self.M, self.N, self.K, self.nk, self.K, agg.B_NK)
+
+    def close(self):
+        for ctx in self.open:
+            ctx.free()
+        agg.agg_tune_table_clear()
+
+
+def test_tuning_times_the_tiles_that_read_in_place():
+    # beside the copy the call takes 82 us, with the best of the numbered tiles and its transposed copy 105
+    p = _Problem(61, 128, 8192, 7168)
+    try:
+        agg.agg_tune_table_clear()
+        tuned, other = p.context(), p.context()
+        C = torch.empty((p.M, p.N), device="cuda")
+        res = agg.agg_autotune_ag_gemm(tuned, p.M, p.N, p.K, p.kn, p.N, agg.B_KN, C, p.N, agg.F32, p.shards, agg.PRODUCER_KERNEL, 3)
+        assert res.configs_tried == 24 and (res.tile_config, res.tile_order) == (-1, agg.ORDER_ROTATED)
+        assert agg.agg_tune_table_get(p.W, p.M, p.N, p.K).tile_config == -1
+        assert agg.agg_tune_table_apply(other, p.M, p.N, p.K)
+        for ctx in (tuned, other):
+            assert torch.equal(p.by_kn(ctx), p.in_place)
+    finally:
+        p.close()
