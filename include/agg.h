@@ -338,8 +338,8 @@ int agg_set_local_shard(agg_ctx* ctx, const void* local_shard);
  * other (a switched fabric).  AGG_ORDER_SUBCHUNK: the local shard, then the first chunk of every peer, the second
  * chunk of every peer, ... -- matches AGG_PRODUCER_LINKS (a full mesh, every peer on its own link).  It needs
  * shards and chunks that are whole numbers of tile rows, and one of the numbered tile shapes (the small tiles that the
- * automatic choice takes for small problems go column block by column block); it is otherwise ignored.  The result is the same bit for
- * bit in either order.
+ * automatic choice takes for small problems, and for AGG_B_KN operands where a single round of a numbered shape is the
+ * alternative, go column block by column block); it is otherwise ignored.  The result is the same bit for bit in either order.
  */
 enum { AGG_ORDER_ROTATED = 0, AGG_ORDER_SUBCHUNK = 1 };
 int agg_set_tile_order(agg_ctx* ctx, int order);

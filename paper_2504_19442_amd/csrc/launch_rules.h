@@ -65,10 +65,12 @@ constexpr double kPublishUs = 0.009, kStoreUs256 = 10.0, kStoreUs128x256 = 4.0; 
 // the K-split kernels divide row and tile numbers with 32-bit multipliers, exact while rows x divisor < 2^32
 constexpr int kKsMaxRows = 65535;
 
+inline long long tile_count(TileShape t, int M, int N) { return (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
+
 inline double tile_cost(int num_cus, const TileCost& k, int M, int N, int K, bool slices)
 {
     const TileShape t = tile_shape(k.cfg);
-    const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+    const long long tiles = tile_count(t, M, N);
     const long long rounds = (tiles + num_cus - 1) / num_cus;
     double cost = (double)rounds * (k.fixed_us + k.us_per_k64 * (K / 64));
     if (slices) {
@@ -109,6 +111,9 @@ inline int best_tile(int num_cus, int M, int N, int K, bool slices = false, bool
 // always, is never slower, and costs 0.3 % more than the better of both (drawn before the in-place tiles got another 4 to 10 % faster).  Both sides,
 // us: 1024 x 3584 x 4096 128x128 in place 38.6, transposed 49.6; 57 x 96 x 320 5.8 and 11.2; 30 x 336 x 2624 15.0 and 13.3; 2048 x 3584 x 4096
 // 76 and 69.8.
+// Where `cfg` is a numbered tile and the problem has more than one round of them, it is taken: those follow the order that the rows arrive in or
+// that the slices are wanted in (agg_set_tile_order, first_slice), the small tiles do not, and the bits must not depend on the order.  In a
+// single round all tiles start at once.  (One in a thousand problems of those ranges, by the costs 10 % slower than in place.)
 // cfg = -1: the best of the tiles that read in place (they all give the same bits).
 inline int tile_kn(int num_cus, int cfg, int M, int N, int K, bool slices = false)
 {
@@ -116,7 +121,7 @@ inline int tile_kn(int num_cus, int cfg, int M, int N, int K, bool slices = fals
     double best_cost = 1e300;
     for (const TileCost& k : kTileCosts)
         if (k.cfg == cfg) best_cost = tile_cost(num_cus, k, M, N, K, slices) + kTransposeUs + 4.0 * N * K / kTransposeBytesPerUs;
-    if (M > kKsMaxRows) return -1;
+    if (M > kKsMaxRows || (cfg >= 0 && cfg < TILE_CONFIGS && tile_count(tile_shape(cfg), M, N) > num_cus)) return -1;
     for (const TileCost& k : kTileCostsKn) {
         const double cost = tile_cost(num_cus, k, M, N, K, slices);
         if (cost < best_cost) {

@@ -150,10 +150,10 @@ def _call(ctx, shards, M, N, K, B, ldb, layout):
 class _Problem:
     """Random inputs: read in place K is added up in two halves, by the numbered tiles in one run, so that the bits tell which it was."""
 
-    def __init__(self, seed, Ms, K, N, cps=1):
+    def __init__(self, seed, Ms, K, N, cps=1, in_place=True):
         self.W, self.Ms, self.K, self.N = 4, Ms, K, N
         self.M = self.W * Ms
-        assert host_rules.kn_tile(_cus(), self.M, self.N, self.K) == "128x128"
+        assert host_rules.kn_tile(_cus(), self.M, self.N, self.K) == ("128x128" if in_place else None)
         assert host_rules.gemm_tile(_cus(), self.M, self.N, self.K)[0] == "numbered"
         g = torch.Generator(device="cuda").manual_seed(seed)
         self.shards = [torch.empty((Ms, self.K), device="cuda", dtype=torch.bfloat16).uniform_(-1, 1, generator=g) for _ in range(self.W)]
@@ -164,7 +164,7 @@ class _Problem:
         numbered = self.context()
         numbered.set_tile_config(5)
         self.copied = self.by_kn(numbered)
-        assert not torch.equal(self.in_place, self.copied) and torch.equal(self.copied, self.by_nk(numbered))
+        assert torch.equal(self.in_place, self.copied) != in_place and torch.equal(self.copied, self.by_nk(numbered))
 
     def context(self):
         ctx = agg.symm_alloc(self.W, 0, self.Ms * self.K * 2, self.W * self.cps)
@@ -199,3 +199,16 @@ def test_tuning_times_the_tiles_that_read_in_place():
             assert torch.equal(p.by_kn(ctx), p.in_place)
     finally:
         p.close()
+
+
+def test_the_order_of_the_tiles_is_kept_where_it_counts_and_changes_no_bits():
+    # one round of the numbered tile: all start at once, B may be read in place; two rounds: they follow the order that is asked for
+    for Ms, K, N, cps, in_place in ((256, 4096, 3584, 2, True), (768, 2048, 2592, 6, False)):
+        p = _Problem(63, Ms, K, N, cps, in_place)
+        try:
+            for order in (agg.ORDER_SUBCHUNK, agg.ORDER_ROTATED):
+                ctx = p.context()
+                ctx.set_tile_order(order)
+                assert torch.equal(p.by_kn(ctx), p.in_place if in_place else p.copied), (Ms, order)
+        finally:
+            p.close()

@@ -6,7 +6,7 @@ import time
 
 import pytest
 
-from host_rules import gemm_tile, lib, tile_name
+from host_rules import gemm_tile, kn_tile, lib, tile_name
 
 
 def _play(entries, fails):
@@ -126,3 +126,16 @@ def test_gemm_rs_with_fp32_stores_between_rounds_keeps_the_smaller_tile():
     for M, N, K in ((4232, 4060, 2368), (4288, 3852, 2816)):
         assert lib().tile_plain(256, M, N, K, 1) == 5
     assert lib().tile_plain(256, 8192, 8192, 3584, 1) == 6
+
+
+def test_an_operand_is_read_in_place_only_where_the_order_of_the_numbered_tiles_does_not_count():
+    rng = random.Random(65)
+    several = 0
+    for _ in range(20000):
+        M, N, K = rng.randint(1, 8192), 8 * rng.randint(1, 896), 64 * rng.randint(1, 128)
+        for slices in (False, True):
+            tile, tiles = gemm_tile(256, M, N, K, slices)
+            if tile == "numbered" and tiles > 256:
+                several += 1
+                assert kn_tile(256, M, N, K, slices) is None
+    assert several > 1000
