@@ -219,8 +219,9 @@ int gemm_rs(agg_ctx* ctx, int M, int N, int Klocal,
  * candidates transpose it) those first runs use that choice and the last
  * fifteen are timed: where no candidate comes within a microsecond of it the result is tile_config = -1 (automatic) in the
  * rotated order.  The GPU is held back for 0.1 ms before every run, so that the time is the GPU's and not that of the host's
- * calls.  The best configuration is stored in the context (tile shape, tile order, producer
- * size used when ag_producer_emulate is called with n_workgroups = 0) and returned.  Synchronous.  On one GPU
+ * calls.  The best configuration is stored in the context (tile shape for calls with this b_layout, tile order, producer
+ * size used when ag_producer_emulate is called with n_workgroups = 0) and returned.  A tile shape found for AGG_B_NK also holds
+ * for AGG_B_KN where B is transposed: with agg_set_tile_config it always is, here where the automatic choice does not read it in place.  Synchronous.  On one GPU
  * there is no agreement between ranks to reach; on a node the ranks would exchange *out and take the slowest
  * rank's best.  C is overwritten.  Any error leaves the context's settings as they were.
  */
@@ -234,11 +235,14 @@ int agg_autotune_ag_gemm(agg_ctx* ctx, int M, int N, int K, const void* B, int l
 
 /*
  * Table of tuned configurations (Section 3.8: tuning results are kept and reused).  Process-wide and thread-safe; the
- * key is (world size, M, N, K).  agg_autotune_ag_gemm enters every result it returns.  agg_tune_table_apply copies the
- * entry for (ctx's world size, M, N, K) into the context (tile shape, tile order, producer size), as the tuner itself
+ * key is (world size, M, N, K) and the layout of B.  agg_autotune_ag_gemm enters every result it returns.  agg_tune_table_put
+ * enters one for AGG_B_NK; agg_tune_table_get returns that one, or, where there is none, the one for AGG_B_KN.
+ * agg_tune_table_apply copies the
+ * entries for (ctx's world size, M, N, K) into the context (tile shape for calls with their layout; tile order and producer
+ * size of the AGG_B_NK one, if there is one), as the tuner itself
  * does at its end, or returns AGG_ERR_NOT_FOUND and leaves the context alone.  save writes the table as text (one
- * header line, then "W M N K tile_config tile_order producer_workgroups configs_tried best_ms" per entry; lines
- * starting with # are comments); load merges such a file into the table (entries of the file win) and returns the
+ * header line, then "W M N K tile_config tile_order producer_workgroups configs_tried best_ms" per entry, followed by "KN"
+ * for AGG_B_KN; lines starting with # are comments); load merges such a file into the table (entries of the file win) and returns the
  * number of entries read, AGG_ERR_IO if the file cannot be read, or AGG_ERR_INVALID_ARG for a file with a wrong
  * header, a malformed line or a value out of range -- the table is then left exactly as it was.  tile_config = -1 (automatic) is
  * in range with the rotated order only.  None of these calls

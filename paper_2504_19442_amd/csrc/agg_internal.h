@@ -143,7 +143,11 @@ struct ReduceArgs {
     long long wait_ticks;
     int* err;
 };
-void tune_table_put(int W, int M, int N, int K, const agg_tune_result& r);   // the process-wide table of tuned configurations
+// The process-wide table of tuned configurations: the entry of a problem whose B has layout b_layout; and the context's settings from what
+// it holds for a problem, the order and the producer's size from the entry of `layout` where there are two.
+void tune_table_put(int b_layout, int W, int M, int N, int K, const agg_tune_result& r);
+int tune_table_apply(agg_ctx* c, int M, int N, int K, int layout);
+constexpr int kKnAsNk = -2;                 // agg_ctx::kn_config
 hipError_t launch_reduce(const ReduceArgs& a, int n_workgroups, hipStream_t stream, bool beside_gemm);
 
 }  // namespace agg
@@ -164,6 +168,7 @@ struct agg_ctx {
     int device_epoch;    // 1: launches read the epoch from epoch_word when they start (HIP graph replay)
     int device;
     int tile_config;     // -1 = automatic
+    int kn_config;       // the same for a B stored [K][N]; kKnAsNk: read in place where the automatic choice does so, else tile_config
     int tile_order;      // AGG_ORDER_*
     int rs_own_last;     // gemm_rs computes the own slice last (1) or first (0)
     int rs_chunks;       // row chunks per GEMM-RS slice and reducer slot, each with a signal of its own (>= 1)

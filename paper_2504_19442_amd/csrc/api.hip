@@ -32,9 +32,10 @@ inline long long wait_ticks(const agg_ctx* c)
 }
 
 // slices: GEMM + ReduceScatter's epilogue; large_only: without the K-split tiles.
-int choose_tile(const agg_ctx* c, int M, int N, int K, bool slices = false, bool large_only = false)
+int choose_tile(const agg_ctx* c, int b_layout, int M, int N, int K, bool slices = false, bool large_only = false)
 {
-    return c->tile_config >= 0 ? c->tile_config : best_tile(c->num_cus, M, N, K, slices, large_only);
+    const int asked = b_layout == AGG_B_KN && c->kn_config != kKnAsNk ? c->kn_config : c->tile_config;
+    return asked >= 0 ? asked : best_tile(c->num_cus, M, N, K, slices, large_only);
 }
 
 // Workgroups of a launch of `tiles` tiles: one per tile up to one per CU (a multiple of 8, so that neighbouring tiles can be
@@ -103,8 +104,8 @@ int resolve_b(agg_ctx* c, const void* B, int ldb, int b_layout, int N, int K, hi
 bool kn_in_place(const agg_ctx* c, const void* B, int ldb, int b_layout, int M, int N, int K, bool slices, int* cfg)
 {
     if (b_layout != AGG_B_KN || !aligned16(B) || ldb % 8 != 0 || N % 8 != 0 || (long long)(K + 1024) * ldb * 2 >= (1ll << 31)) return false;
-    if (c->tile_config >= 0) return false;      // a tile asked for by number: the transposed copy, and its bits
-    const int t = tile_kn(c->num_cus, *cfg, M, N, K, slices);
+    if (c->kn_config >= 0) return false;        // a tile asked for by number: the transposed copy, and its bits
+    const int t = tile_kn(c->num_cus, best_tile(c->num_cus, M, N, K, slices), M, N, K, slices);
     if (t >= 0) *cfg = t;
     return t >= 0;
 }
@@ -174,7 +175,7 @@ int symm_alloc(agg_ctx** out, int world_size, int rank, size_t shard_bytes, int 
     c->n_signals = n_signals;
     c->epoch = 1;
     c->wait_limit_us = 2000000;
-    c->tile_config = -1;
+    c->tile_config = c->kn_config = -1;
     c->rs_chunks = 1;
     c->rs_own_last = 1;
     int rc = AGG_OK;
@@ -330,7 +331,7 @@ int agg_set_link_rate(agg_ctx* c, double gigabytes_per_second)
 int agg_set_tile_config(agg_ctx* c, int cfg)
 {
     if (!c || cfg < -1 || cfg >= TILE_NUMBERED) return AGG_ERR_INVALID_ARG;
-    c->tile_config = cfg;
+    c->tile_config = c->kn_config = cfg;
     return AGG_OK;
 }
 
@@ -514,7 +515,7 @@ int ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb, int b_layou
     p.A_local = (const uint16_t*)c->local_shard;
     p.local_lo = c->rank * Ms;
     p.local_hi = p.local_lo + Ms;
-    int cfg = choose_tile(c, M, N, K);
+    int cfg = choose_tile(c, b_layout, M, N, K);
     p.b_kn = kn_in_place(c, B, ldb, b_layout, M, N, K, false, &cfg);
     if ((rc = resolve_b(c, B, ldb, b_layout, N, K, (hipStream_t)consumer_stream, p.b_kn, &p.B, &p.ldb)) != AGG_OK) return rc;
     p.b_total_bytes = p.b_kn ? 2 * p.ldb * K : 2 * p.ldb * N;
@@ -605,7 +606,8 @@ int agg_autotune_ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb
                          agg_tune_result* out)
 {
     if (!c || !out || runs_per_config < 1 || runs_per_config > 1000) return AGG_ERR_INVALID_ARG;
-    const int saved_tile = c->tile_config, saved_order = c->tile_order, saved_wgs = c->producer_wgs;
+    const int saved_tile = c->tile_config, saved_kn = c->kn_config, saved_order = c->tile_order, saved_wgs = c->producer_wgs;
+    int& config = b_layout == AGG_B_KN ? c->kn_config : c->tile_config;
     const int tiles[4] = {TILE_256x224 | TILE_K32, TILE_256x256 | TILE_K32, TILE_128x256 | TILE_K32, TILE_128x128 | TILE_K32};
     const int orders[2] = {AGG_ORDER_ROTATED, AGG_ORDER_SUBCHUNK};
     const int wgs[3] = {c->num_cus / 2 > 0 ? c->num_cus / 2 : 1, c->num_cus, 2 * c->num_cus};
@@ -647,12 +649,12 @@ int agg_autotune_ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb
     // candidates (a small one, or one that reads a [K][N] operand in place), that series runs with it, and its second half is timed:
     // the time a candidate has to come near to.
     constexpr int kWarm = 30, kSettled = 15;
-    c->tile_config = -1;
-    int auto_tile = choose_tile(c, M, N, K);
+    config = -1;
+    int auto_tile = choose_tile(c, b_layout, M, N, K);
     const bool automatic = kn_in_place(c, B, ldb, b_layout, M, N, K, false, &auto_tile) || auto_tile >= TILE_CONFIGS;
     std::vector<float> auto_times;
     for (int it = 0; it < kWarm - 1 && rc == AGG_OK; ++it) {
-        c->tile_config = automatic ? -1 : tiles[0];
+        config = automatic ? -1 : tiles[0];
         c->tile_order = orders[0];
         c->producer_wgs = wgs[1];
         float ms = 0.f;
@@ -661,7 +663,7 @@ int agg_autotune_ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb
     for (int ti = 0; ti < 4 && rc == AGG_OK; ++ti)
         for (int oi = 0; oi < 2 && rc == AGG_OK; ++oi)
             for (int wi = 0; wi < (sdma ? 1 : 3) && rc == AGG_OK; ++wi) {
-                c->tile_config = tiles[ti];
+                config = tiles[ti];
                 c->tile_order = orders[oi];
                 c->producer_wgs = wgs[wi];
                 std::vector<float> times;
@@ -694,16 +696,15 @@ int agg_autotune_ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     (void)hipEventDestroy(join);
+    c->tile_config = saved_tile;
+    c->kn_config = saved_kn;
     if (rc != AGG_OK) {
-        c->tile_config = saved_tile;
         c->tile_order = saved_order;
         c->producer_wgs = saved_wgs;
         return rc;
     }
-    c->tile_config = res.tile_config;
-    c->tile_order = res.tile_order;
-    c->producer_wgs = res.producer_workgroups;
-    tune_table_put(c->W, M, N, K, res);
+    tune_table_put(b_layout, c->W, M, N, K, res);
+    (void)tune_table_apply(c, M, N, K, b_layout);
     *out = res;
     return AGG_OK;
 }
@@ -734,7 +735,7 @@ int gemm_rs_scatter(agg_ctx* c, int M, int N, int Kl, const void* A_local, int l
 
     GemmParams p{};
     p.A = (const uint16_t*)A_local;
-    int cfg = choose_tile(c, M, N, Kl, true);
+    int cfg = choose_tile(c, b_layout, M, N, Kl, true);
     p.b_kn = kn_in_place(c, B_local, ldb, b_layout, M, N, Kl, true, &cfg);
     if ((rc = resolve_b(c, B_local, ldb, b_layout, N, Kl, (hipStream_t)gemm_stream, p.b_kn, &p.B, &p.ldb)) != AGG_OK) return rc;
     p.b_total_bytes = p.b_kn ? 2 * p.ldb * Kl : 2 * p.ldb * N;
@@ -804,10 +805,10 @@ int gemm_rs(agg_ctx* c, int M, int N, int Kl, const void* A_local, int lda, cons
         p.A = (const uint16_t*)A_local + (long long)c->rank * Ms * lda;
         // the sum over K in the same order as with P_other, so that the slice is the same bit for bit: a K-split tile if
         // the whole product takes one, and then that one; B read in place if it is for the whole product
-        int cfg = choose_tile(c, M, N, Kl, true);
+        int cfg = choose_tile(c, b_layout, M, N, Kl, true);
         p.b_kn = kn_in_place(c, B_local, ldb, b_layout, M, N, Kl, true, &cfg);
         if (p.b_kn) cfg = tile_kn(c->num_cus, -1, Ms, N, Kl, true);
-        else if (cfg < TILE_CONFIGS) cfg = choose_tile(c, Ms, N, Kl, true, true);
+        else if (cfg < TILE_CONFIGS) cfg = choose_tile(c, b_layout, Ms, N, Kl, true, true);
         if ((rc = resolve_b(c, B_local, ldb, b_layout, N, Kl, (hipStream_t)gemm_stream, p.b_kn, &p.B, &p.ldb)) != AGG_OK) return rc;
         p.b_total_bytes = p.b_kn ? 2 * p.ldb * Kl : 2 * p.ldb * N;
         p.C = (void*)slots[c->rank];

@@ -201,6 +201,41 @@ def test_tuning_times_the_tiles_that_read_in_place():
         p.close()
 
 
+def _entry(tile, order):
+    r = agg.TuneResult()
+    r.tile_config, r.tile_order, r.producer_workgroups, r.configs_tried, r.best_ms = tile, order, 0, 24, 0.05
+    return r
+
+
+def test_what_is_tuned_for_one_layout_leaves_the_other_alone(tmp_path):
+    p = _Problem(62, 128, 8192, 7168)
+    try:
+        agg.agg_tune_table_clear()
+        for order in (agg.ORDER_ROTATED, agg.ORDER_SUBCHUNK):
+            agg.agg_tune_table_put(p.W, p.M, p.N, p.K, _entry(5, order))
+            ctx = p.context()
+            assert agg.agg_tune_table_apply(ctx, p.M, p.N, p.K)
+            assert torch.equal(p.by_nk(ctx), p.copied) and torch.equal(p.by_kn(ctx), p.in_place)
+            ctx.set_tile_config(5)                              # by number: the transposed copy, and its bits
+            assert torch.equal(p.by_kn(ctx), p.copied)
+        # tuning the [K][N] operand keeps the entry of the other one, in memory and in a file
+        tuned = p.context()
+        C = torch.empty((p.M, p.N), device="cuda")
+        res = agg.agg_autotune_ag_gemm(tuned, p.M, p.N, p.K, p.kn, p.N, agg.B_KN, C, p.N, agg.F32, p.shards, agg.PRODUCER_KERNEL, 3)
+        assert res.tile_config == -1
+        for _ in range(2):
+            assert agg.agg_tune_table_size() == 2
+            assert agg.agg_tune_table_get(p.W, p.M, p.N, p.K).tile_config == 5
+            ctx = p.context()
+            assert agg.agg_tune_table_apply(ctx, p.M, p.N, p.K)
+            assert torch.equal(p.by_nk(ctx), p.copied) and torch.equal(p.by_kn(ctx), p.in_place)
+            agg.agg_tune_table_save(str(tmp_path / "t.txt"))
+            agg.agg_tune_table_clear()
+            assert agg.agg_tune_table_load(str(tmp_path / "t.txt")) == 2
+    finally:
+        p.close()
+
+
 def test_the_order_of_the_tiles_is_kept_where_it_counts_and_changes_no_bits():
     # one round of the numbered tile: all start at once, B may be read in place; two rounds: they follow the order that is asked for
     for Ms, K, N, cps, in_place in ((256, 4096, 3584, 2, True), (768, 2048, 2592, 6, False)):

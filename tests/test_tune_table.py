@@ -112,3 +112,25 @@ def test_the_automatic_choice_can_be_kept_in_the_rotated_order_only(tmp_path):
             agg.agg_tune_table_load(p)
         assert e.value.code == agg.ERR_INVALID_ARG
     assert agg.agg_tune_table_size() == 1
+
+
+def test_entries_of_a_kn_operand_stand_beside_the_others(tmp_path):
+    p = str(tmp_path / "both.txt")
+    open(p, "w").write("agg-tune-table 1\n4 512 7168 8192 -1 0 256 24 0.082 KN\n4 512 7168 8192 5 1 128 24 0.075\r\n2 64 64 64 6 0 32 24 0.1\tKN \r\n")
+    assert agg.agg_tune_table_load(p) == 3 and agg.agg_tune_table_size() == 3
+    assert agg.agg_tune_table_get(4, 512, 7168, 8192).tile_config == 5      # get names no layout: [N][K] where there is one
+    assert agg.agg_tune_table_get(2, 64, 64, 64).tile_config == 6
+    agg.agg_tune_table_put(4, 512, 7168, 8192, _entry(tile=4, order=0))
+    assert agg.agg_tune_table_size() == 3
+    agg.agg_tune_table_save(p)
+    text = open(p).read().splitlines()
+    assert {"4 512 7168 8192 -1 0 256 24 0.082 KN", "4 512 7168 8192 4 0 256 18 0.7125", "2 64 64 64 6 0 32 24 0.1 KN"} == set(text[2:])
+    for bad in ("KN 1", "KNK", "kn", "NK", "KN KN"):
+        open(p, "w").write(f"agg-tune-table 1\n8 64 64 64 0 0 0 1 0.5 {bad}\n")
+        with pytest.raises(agg.AggError) as e:
+            agg.agg_tune_table_load(p)
+        assert e.value.code == agg.ERR_INVALID_ARG
+    open(p, "w").write("agg-tune-table 1\n8 64 64 64 0 0 0 1 0.5KN\n")
+    with pytest.raises(agg.AggError):
+        agg.agg_tune_table_load(p)
+    assert agg.agg_tune_table_size() == 3
