@@ -8,7 +8,8 @@
 //  * The stream does not end with a tile: the last stages of a tile ask for the first ones of the next, whose list entry, token rows
 //    and signals are looked at meanwhile, and the tile's rows are stored while those are on their way: from the registers (the rings are
 //    in use), and counted (buffer stores whose descriptor holds back the rows that are not wanted), so that the first wait of the
-//    next tile can leave them outstanding.
+//    next tile can leave them outstanding.  Signals that are not there yet hold nothing back but the next tile's rows of A: those are asked
+//    for when the tile's rows have been stored and the signals waited for.
 //  * The entries of the tile list and the token rows come through LDS as well: a load into registers would be waited for together with
 //    every load in front of it.
 // Shapes: 320x128 and 192x192 are there for segments that fill one tile but not two of a power of two (each weight then crosses the load
@@ -57,13 +58,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
     using C_ = PipeCfg<BM, BN>;
     constexpr int LA = C_::LA, LB = C_::LB, TM = C_::TM, MB16 = C_::MB16, NB16 = C_::NB16, RA = C_::RA, RB = C_::RB;
     // naming the last accumulator register makes the compiler reserve a0..a(ACC-1) for this kernel
+    static_assert(C_::ACC == 160 || C_::ACC == 144 || C_::ACC == 112 || C_::ACC == 96, "add a reservation line for this accumulator count");
     if constexpr (C_::ACC == 160) asm volatile("; accumulators a0..a159" ::: "a159");
     else if constexpr (C_::ACC == 144) asm volatile("; accumulators a0..a143" ::: "a143");
-    else if constexpr (C_::ACC == 128) asm volatile("; accumulators a0..a127" ::: "a127");
     else if constexpr (C_::ACC == 112) asm volatile("; accumulators a0..a111" ::: "a111");
-    else if constexpr (C_::ACC == 96) asm volatile("; accumulators a0..a95" ::: "a95");
-    else if constexpr (C_::ACC == 64) asm volatile("; accumulators a0..a63" ::: "a63");
-    else static_assert(C_::ACC == 0, "add a reservation line for this accumulator count");
+    else asm volatile("; accumulators a0..a95" ::: "a95");
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -74,7 +73,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
     const unsigned lds_u = (unsigned)(unsigned long)(lds_byte*)LDS_PTR(lds);
     const unsigned lds_wave = lds_u + wave * 1024;
     typedef __attribute__((address_space(3))) volatile int lds_int;
-    lds_int* const s_gave_up = (lds_int*)(unsigned long)(lds_u + C_::WORD_AT);
+    lds_int* const s_word = (lds_int*)(unsigned long)(lds_u + C_::WORD_AT);
     unsigned fr_a[2], fr_b[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -184,14 +183,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
     // ---- signals: seen are those of [seen_lo, seen_hi]
     int seen_lo = 0x7FFFFFFF, seen_hi = -1;
     auto must_wait = [&](const Tile& w) { return p.flags && w.valid && w.f_hi >= w.f_lo && (w.f_lo < seen_lo || w.f_hi > seen_hi); };
-    auto poll = [&](const Tile& w) {          // wave 0, in front of a barrier
+    // wave 0, in front of a barrier: a look at the signals, or the wait for them
+    auto look = [&](const Tile& w, auto wait_c) {
         if (wave == 0) {
-            const bool any = __ballot(poll_signals(p, w.f_lo, w.f_hi, epoch, lane)) != 0;
-            if (lane == 0) *s_gave_up = any;
+            bool any;
+            if constexpr (decltype(wait_c)::value) any = __ballot(poll_signals(p, w.f_lo, w.f_hi, epoch, lane)) != 0;
+            else any = signals_missing(p, w.f_lo, w.f_hi, epoch, lane);
+            if (lane == 0) *s_word = any;
         }
         asm volatile("" ::: "memory");
     };
-    auto polled = [&](const Tile& w) {        // all waves, behind it; false: the wait was given up
+    auto seen = [&](const Tile& w) {          // all waves, behind it; false: not all are there
+        if (__builtin_amdgcn_readfirstlane(*s_word) != 0) return false;
         if (w.f_lo <= seen_hi + 1 && w.f_hi >= seen_lo - 1 && seen_hi >= 0) {
             seen_lo = min(seen_lo, w.f_lo);
             seen_hi = max(seen_hi, w.f_hi);
@@ -199,7 +202,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
             seen_lo = w.f_lo;
             seen_hi = w.f_hi;
         }
-        return __builtin_amdgcn_readfirstlane(*s_gave_up) == 0;
+        return true;
     };
 
     // ---- start: the first tile's B is asked for before its signals are looked at
@@ -224,9 +227,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
         static_for<LB>([&](auto i_c) { load_b(i_c); });
     });
     if (must_wait(cur)) {
-        poll(cur);
+        look(cur, std::true_type{});
         __syncthreads();
-        if (!polled(cur)) { __builtin_amdgcn_s_waitcnt(vmcnt_imm(0)); return; }
+        if (!seen(cur)) { __builtin_amdgcn_s_waitcnt(vmcnt_imm(0)); return; }
         __syncthreads();
     }
     arrived(std::integral_constant<int, RB * LB>{});
@@ -257,10 +260,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
     enum { WAIT_ALL, WAIT_BF16, WAIT_F32 };
     int first_wait = WAIT_ALL;               // what the first stage's barrier of a tile may leave outstanding
 
-    // Stage ks of the running tile.  false: a wait for signals was given up.
+    // Stage ks of the running tile.  The next tile's signals are looked at two stages before its end.  Where some are still to come, its
+    // rows of A are not asked for (`late`): they are waited for when this tile's rows have been stored.
+    static_assert(C_::MIN_STAGES > RA, "the look at the signals is not in a tile's first stage");
+    bool late = false;
     auto stage = [&](int ks, auto first_c) {
         constexpr bool first = decltype(first_c)::value;
-        bool ok = true;
         static_for<2>([&](auto h_c) {
             constexpr int h = decltype(h_c)::value;
             constexpr auto slots = C_::make_slots(h);
@@ -277,9 +282,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
                 if constexpr (h == 1 && sl == C_::SB) {
                     // The running stage's fragments are all in registers, and the next stage has landed: of the loads behind it, those
                     // of B alone may be outstanding (and, in a tile's first stage, the stores of the tile before it).
-                    const bool to_next_a = ks == KE - RA;
+                    const bool to_next_a = !first && ks == KE - RA;
                     const bool gate = to_next_a && must_wait(nxt);
-                    if (gate) poll(nxt);
+                    if (gate) look(nxt, std::false_type{});
                     if constexpr (first) {
                         if (first_wait == WAIT_BF16) __builtin_amdgcn_s_waitcnt(vmcnt_imm(LB + C_::N_ST_BF16 < 63 ? LB + C_::N_ST_BF16 : 63) & ~(0xF << 8));
                         else if (first_wait == WAIT_F32) __builtin_amdgcn_s_waitcnt(vmcnt_imm(LB + C_::N_ST_F32 < 63 ? LB + C_::N_ST_F32 : 63) & ~(0xF << 8));
@@ -289,11 +294,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
                     }
                     __builtin_amdgcn_s_barrier();
                     asm volatile("" ::: "memory");
-                    if (gate && !polled(nxt)) ok = false;
                     if (to_next_a) {
+                        late = gate && !seen(nxt);
                         rows_to_offsets(nxt);
                         ka = 0;
-                        kc_a = nxt.valid ? KS : 0;
+                        kc_a = nxt.valid && !late ? KS : 0;
                     }
                     if (ks == KE - RB) point_b(nxt);
                     dst_a = at_a;
@@ -314,13 +319,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
                 });
             });
         });
-        return ok;
     };
 
     for (;;) {
-        if (!stage(0, std::true_type{})) { __builtin_amdgcn_s_waitcnt(vmcnt_imm(0)); return; }
-        for (int ks = 1; ks < KE; ++ks)
-            if (!stage(ks, std::false_type{})) { __builtin_amdgcn_s_waitcnt(vmcnt_imm(0)); return; }
+        stage(0, std::true_type{});
+        for (int ks = 1; ks < KE; ++ks) stage(ks, std::false_type{});
 
         // ---- between two tiles.  What is asked for first: the list's entry after the next tile's, the rest of the batch of loads that
         // the last barrier released (all that the first stage of the next tile waits for), and then the stores.
@@ -372,6 +375,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(192))) void gem
         }
         asm volatile("" ::: "memory");
         if (!nxt.valid) break;
+        if (late) {
+            // The next tile's first stages of A, into the places that nothing was loaded into; its first fragments of A again
+            look(nxt, std::true_type{});
+            __syncthreads();
+            if (!seen(nxt)) break;
+            ka = 0;
+            kc_a = KS;
+            static_for<RA>([&](auto s_c) {
+                dst_a = at_a + decltype(s_c)::value * C_::A_STAGE;
+                if (dst_a >= RA * C_::A_STAGE) dst_a -= RA * C_::A_STAGE;
+                batch_a();
+                static_for<LA>([&](auto i_c) { load_a(i_c); });
+            });
+            arrived(std::integral_constant<int, 0>{});
+            static_for<MB16>([&](auto i_c) { read_a(i_c, 0); });
+            late = false;
+        }
         cur = nxt;
         nxt = after;
         t += G;

@@ -143,7 +143,19 @@ __device__ __forceinline__ int poll_signals(const Params& p, int f_lo, int f_hi,
     return gave_up;
 }
 
-// The same for a whole workgroup; true: a wait was given up, and the launch drains (agg_status reports the time-out).
+// One look at them, by one wave: whether any is still to come.  If none is, the acquire is done as well.
+template <class Params>
+__device__ __forceinline__ bool signals_missing(const Params& p, int f_lo, int f_hi, int epoch, int lane)
+{
+    bool missing = false;
+    for (int f = f_lo + lane; f <= f_hi; f += 64)
+        missing |= __hip_atomic_load(p.flags + (long long)f * kSignalStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch;
+    const bool any = __ballot(missing) != 0;
+    if (!any) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    return any;
+}
+
+// The wait for a whole workgroup; true: a wait was given up, and the launch drains (agg_status reports the time-out).
 __device__ __forceinline__ bool tile_wait_gave_up(const GemmParams& p, int f_lo, int f_hi, int epoch, int wave, int lane)
 {
     int gave_up = 0;

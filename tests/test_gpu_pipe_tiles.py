@@ -172,3 +172,51 @@ def test_a_signal_that_never_comes_ends_the_launch():
         assert torch.equal(Y, _expected(lambda o: torch.cat(shards)[o], B, ids)[1])
     finally:
         ctx.free()
+
+
+@pytest.mark.parametrize("T,E", [(5904, 3), (6400, 4)])
+def test_a_tile_that_is_done_is_stored_before_the_next_ones_signals_are_waited_for(T, E):
+    # experts of some 1600 to 2000 rows, the other rank's shard never arrives: what a workgroup has computed before it comes to a tile with
+    # rows of that shard is in Y, and nothing else is
+    topk, N, K, W, cps = 1, 3000, 192, 2, 4
+    cus = agg.agg_device_info()[0]
+    tile = host_rules.moe_tile(cus, T, topk, E, N, K, True, True)
+    assert tile in ("128x192", "128x224", "192x192", "320x128")
+    bm, bn = map(int, tile.split("x"))
+    g = torch.Generator(device="cuda").manual_seed(44)
+    shards, B = [_ints(g, T // W, K) for _ in range(W)], _ints(g, E, N, K)
+    ids = torch.randint(0, E, (T, 1), device="cuda", generator=g).to(torch.int32)
+    order, want = _expected(lambda o: torch.cat(shards)[o], B, ids)
+    own = (order < T // W).cpu().numpy()
+    ends = np.cumsum(torch.bincount(ids.reshape(-1).long(), minlength=E).cpu().numpy())
+    tiles = []                                                  # the list: an expert's columns one after the other, rows fastest
+    for e, hi in enumerate(ends):
+        lo = hi - (ends[e] - (ends[e - 1] if e else 0))
+        tiles += [(m, min(m + bm, hi), n) for n in range(0, N, bn) for m in range(lo, hi, bm)]
+    done = []
+    for t, (lo, hi, n) in enumerate(tiles):                     # tile t is walked by the workgroup that has had tile t - cus
+        done.append(bool(own[lo:hi].all()) and (t < cus or done[t - cus]))
+    assert any(d and not done[t + cus] for t, d in enumerate(done[:-cus]))
+    Y_want = torch.full((T, N), 7.0, device="cuda")
+    for d, (lo, hi, n) in zip(done, tiles):
+        if d:
+            Y_want[lo:hi, n:n + bn] = want[lo:hi, n:n + bn]
+    tok, seg = torch.empty(T, device="cuda", dtype=torch.int32), torch.empty(E + 1, device="cuda", dtype=torch.int32)
+    ctx = agg.symm_alloc(W, 0, T // W * K * 2, W * cps)
+    try:
+        agg.agg_reserve_moe(ctx, T, topk, E, N)
+        ps, cs = ctx.streams()
+        ctx.set_wait_limit_us(2000)
+        for config in (5, -1):                                  # a numbered tile (128x128: another list) and the automatic choice
+            Y = torch.full((T, N), 7.0, device="cuda")
+            ctx.set_tile_config(config)
+            agg.signal_reset(ctx)
+            agg.ag_producer_emulate(ctx, shards, [], agg.PRODUCER_KERNEL, 0, ps)
+            torch.cuda.synchronize()
+            agg.ag_moe_gemm(ctx, T, topk, E, N, K, ids, B, tok, seg, Y, N, agg.F32, cs)
+            torch.cuda.synchronize()
+            assert agg.agg_status(ctx) == agg.ERR_TIMEOUT
+            assert bool(((Y == want) | (Y == 7.0)).all())
+        assert torch.equal(Y, Y_want)
+    finally:
+        ctx.free()
