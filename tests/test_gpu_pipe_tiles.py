@@ -220,3 +220,44 @@ def test_a_tile_that_is_done_is_stored_before_the_next_ones_signals_are_waited_f
         assert torch.equal(Y, Y_want)
     finally:
         ctx.free()
+
+
+# tile, output type, tokens, top-k, experts, N, K
+SAME_BITS = [
+    ("128x192", agg.BF16, 4908, 3, 30, 1152, 320),
+    ("128x224", agg.F32, 6360, 2, 30, 1188, 192),
+    ("192x192", agg.F32, 6502, 3, 36, 1064, 832),
+    ("320x128", agg.BF16, 5270, 1, 23, 1168, 832),
+    ("320x128", agg.F32, 3634, 3, 24, 616, 64),
+]
+
+
+@pytest.mark.parametrize("tile,dtype,T,topk,E,N,K", SAME_BITS)
+def test_the_same_bits_as_the_numbered_tiles(tile, dtype, T, topk, E, N, K):
+    # random inputs: a sum over K in another order would show
+    assert host_rules.moe_tile(agg.agg_device_info()[0], T, topk, E, N, K, True, dtype == agg.F32) == tile
+    g = torch.Generator(device="cuda").manual_seed(45)
+    W = 2
+    shards = [torch.empty((T // W, K), device="cuda", dtype=torch.bfloat16).uniform_(-1, 1, generator=g) for _ in range(W)]
+    B = torch.empty((E, N, K), device="cuda", dtype=torch.bfloat16).normal_(0, 0.02, generator=g)
+    ids = _routing(g, T, topk, E, int(tile.split("x")[0]))
+    tdt = torch.float32 if dtype == agg.F32 else torch.bfloat16
+    tok, seg = torch.empty(T * topk, device="cuda", dtype=torch.int32), torch.empty(E + 1, device="cuda", dtype=torch.int32)
+    ctx = agg.symm_alloc(W, 1, T // W * K * 2, W)
+    try:
+        agg.agg_reserve_moe(ctx, T, topk, E, N)
+        ps, cs = ctx.streams()
+        Y = {}
+        for config in (-1, 4, 5, 6):                            # 16x16x32 MFMAs: 256x224, 128x128, 256x256
+            Y[config] = torch.full((T * topk, N), float("nan"), device="cuda", dtype=tdt)
+            ctx.set_tile_config(config)
+            agg.signal_reset(ctx)
+            torch.cuda.synchronize()
+            agg.ag_producer_emulate(ctx, shards, None, agg.PRODUCER_KERNEL, 0, ps)
+            agg.ag_moe_gemm(ctx, T, topk, E, N, K, ids, B, tok, seg, Y[config], N, dtype, cs)
+            torch.cuda.synchronize()
+            assert agg.agg_status(ctx) == agg.OK
+        for config in (4, 5, 6):
+            assert torch.equal(Y[-1].view(torch.uint8), Y[config].view(torch.uint8)), config
+    finally:
+        ctx.free()
