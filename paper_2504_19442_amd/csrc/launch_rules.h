@@ -176,10 +176,11 @@ inline double expected_m_tiles(double mean, int bm)
 // tile for 740 problems drawn from 4 to 8192 tokens, 4 to 64 experts, top-1 to 4, N 96 to 2048, K 64 to 4096 (gathered rows in bf16
 // and fp32, rows in place): the choice costs 0.7 % more than the best tile of each (geometric mean; 0.8 % on 370 other draws) and takes
 // 12 % less time than the choice among 256x224, 256x256 and 128x128 alone, which is faster by more than 5 % on 12 of the 1110, by
-// more than 10 % on two.  The costs of the tiles of gemm_pipe.h are fitted to 800 further draws, half of them with 256 and
-// more tokens per rank: on 800 others the choice with them takes 4.3 % less time for gathered rows and 0.8 % for rows in place than without
-// them, is slower by more than 5 % on 4 and by more than 10 % on one, and costs 1.9 % more than the best tile (1 % if those tiles were to
-// take the place of K-split ones as well, which would change bits).
+// more than 10 % on two.  The costs of the tiles of gemm_pipe.h are fitted to 800 further draws.  On 1226 others, all such that the choice
+// without them is a numbered tile, they take the place of one in 333 of 766 for gathered rows, which then take 6.3 % less time (all: 2.8 %), and
+// in 31 of 460 for rows in place (3.8 % less); 37 of the 333 are slower by more than 5 %, 20 by more than 10 % (1168 tokens x 4,
+// 6 x 1695 x 384: 32.9 and 24.8): mostly those whose tiles are estimated to just fill their last round and do not quite fit into it, which
+// depends on the routing.  (An estimate with the spread of the number of tiles does no better on average.)
 constexpr TileCost kTileCostsGrouped[] = {
     {KS_16x32, 3.4, 0.113}, {KS_16x64, 3.4, 0.179}, {KS_32x32, 2.6, 0.142}, {KS_64x64, 3.3, 0.267}, {KS_64x128, 3.5, 0.40},
     {TILE_128x128 | TILE_K32, 3.0, 0.60}, {TILE_128x256 | TILE_K32, 2.9, 0.94}, {TILE_256x224 | TILE_K32, 4.1, 1.50},
@@ -220,6 +221,10 @@ inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, b
         if (pipe && (double)rows < active * t.bm / 8) continue;
         const double tiles = active * expected_m_tiles((double)rows / active, t.bm) * ((N + t.bn - 1) / t.bn);
         const double rounds = std::ceil(tiles / num_cus);
+        // ... or, rows in place (short K, fp32 out), a single round of them: there is no next tile whose loads could be under way beside the
+        // stores, and the numbered tiles start and end sooner.  Over 460 draws the call with them takes, in one round, 3.5 % longer than with
+        // the numbered choice (1064 tokens x 2, 25 x 1308 x 192: 32.6 and 29.2), in more 4 % less (7896 x 4, 9 x 576 x 512: 71.4 and 84.5)
+        if (pipe && !gathered && rounds < 2.0) continue;
         const double tile_us = k.fixed_us + k.us_per_k64 * (K / 64) + (f32 ? t.bm * t.bn * 4 / kGroupedStoreBytesPerUs : 0.0);
         const double cost = std::max(rounds * tile_us, hbm_us * rounds * num_cus / std::max(tiles, (double)num_cus));
         if (!pipe && cost < best_cost) {

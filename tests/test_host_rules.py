@@ -139,3 +139,17 @@ def test_an_operand_is_read_in_place_only_where_the_order_of_the_numbered_tiles_
                 several += 1
                 assert kn_tile(256, M, N, K, slices) is None
     assert several > 1000
+
+
+# Rows in place, us per call with the top-k reduction and the reducer: the tile of gemm_pipe.h that the costs name, and the numbered one.
+@pytest.mark.parametrize("tokens,topk,E,N,K,tile", [
+    (1064, 2, 25, 1308, 192, "numbered"),           # one round: 32.6 and 29.2
+    (1552, 2, 62, 776, 256, "numbered"),            # 35.0 and 31.9
+    (548, 4, 18, 1588, 256, "numbered"),            # 36.2 and 33.1
+    (714, 1, 33, 1560, 576, "numbered"),            # 35.2 and 32.5
+    (7896, 4, 9, 576, 512, "192x192"),              # several: 71.4 and 84.5
+    (4392, 4, 28, 868, 256, "320x128"),             # 64.0 and 71.4
+])
+def test_rows_in_place_take_a_streaming_tile_for_several_rounds_only(tokens, topk, E, N, K, tile):
+    P = tokens * topk
+    assert tile_name(lib().tile_grouped(256, P, E, N, K, 0, 1, P, 1 << 28, 0)) == tile
