@@ -304,9 +304,9 @@ int ag_moe_gemm(agg_ctx* ctx, int Ttok, int topk, int E, int N, int K,
  *   agg_reserve_moe : the routing's counters (66 KB, zeroed once) and the tile table of the grouped GEMM (ag_moe_gemm,
  *                     moe_rs) for problems of up to Ttok * topk pairs, E experts and N columns, whatever tile
  *                     configuration is chosen later: 1088 KiB together, and a second allocation where the problem's table
- *                     needs more than 32760 entries.  The routing kernel's workgroups read one another's counts through
- *                     those counters and wait for them (bounded by the limit of agg_set_wait_limit_us, like every wait): a MoE
- *                     call is one launch of E workgroups of 1024 threads that all have to become resident in turn.
+ *                     needs more than 32760 entries.  For more than 4096 pairs the routing kernel's workgroups read one another's
+ *                     counts through those counters and wait for them (bounded by the limit of agg_set_wait_limit_us, like every
+ *                     wait): such a call is one launch of E workgroups of 1024 threads that all have to become resident in turn.
  */
 int agg_reserve_b_kn(agg_ctx* ctx, int N, int K);
 int agg_reserve_moe(agg_ctx* ctx, int Ttok, int topk, int E, int N);

@@ -15,11 +15,11 @@
 // Shapes: 320x128 and 192x192 are there for segments that fill one tile but not two of a power of two (each weight then crosses the load
 // path once, and no second tile is nearly empty), 128x192 and 128x224 for shorter and for much longer ones.  192x128, 256x160, 128x128 and
 // 256x128 would add 0.3 % or less each over the ranges of launch_rules.h.
-// Measured, Table 4 (8192 tokens, 222 to 298 rows per expert, 1 GB of weights), routing and GEMM, us: 256x256 of gemm_kernel 382; 320x128
-// in that kernel 340, with the streaming hint on B 313; here 298 (kernel 280 to 300: 3.6 to 4 TB/s, 0.9 to 1 PFLOP/s; 59 % of the cycles
-// are MFMAs, at 1.9 GHz).  What is left: the load path, 56 KiB per 1280 MFMA cycles (the loop of gemm_kernel without any loads takes 208 us,
+// Measured, Table 4 (8192 tokens, 222 to 298 rows per expert, 1 GB of weights), all shards there, routing and GEMM, us: 256x256 of gemm_kernel
+// 382; 320x128 in that kernel 340, with the streaming hint on B 313; here 298 (another box: 335 and 291; kernel 280 to 300: 3.6 to 4 TB/s, 0.9
+// to 1 PFLOP/s; 59 % of the cycles are MFMAs, at 1.9 GHz).  With the gather beside it the call takes 340.  What is left: the load path, 56 KiB per 1280 MFMA cycles (the loop of gemm_kernel without any loads takes 208 us,
 // without those of A 268, without those of B 245), and power.  Table 5 (K = 192, rows in place, fp32), kernel: 54 -> 47.6, 3.9 TB/s;
-// with whole lines per store (out_cols) the call is 108.6 -> 102.3, Table 4 in fp32 341 -> 334.
+// with whole lines per store (out_cols) the call is 108.6 -> 102.3 on one stream, Table 4 in fp32 341 -> 334 (routing and GEMM: 301).
 #pragma once
 #include "gemm_kernel.h"
 #include "ks_stage.h"

@@ -107,9 +107,9 @@ inline int best_tile(int num_cus, int M, int N, int K, bool slices = false, bool
 
 // Tile for a B stored [K][N] that can be read in place (its rows on 16 bytes, whole 16-byte chunks of columns), or -1: it is transposed first
 // and `cfg`, best_tile's choice for the transposed one, is taken.  Transposing costs its bytes, read and written, and 7.6 us: a kernel more and the
-// event behind the GEMM.  Over 166 problems drawn from M 16..8192, N 96..7168, K 256..8192 the choice takes 28 % less time than transposing
-// always, is never slower, and costs 0.3 % more than the better of both (drawn before the in-place tiles got another 4 to 10 % faster).  Both sides,
-// us: 1024 x 3584 x 4096 128x128 in place 38.6, transposed 49.6; 57 x 96 x 320 5.8 and 11.2; 30 x 336 x 2624 15.0 and 13.3; 2048 x 3584 x 4096
+// event behind the GEMM.  Over 200 problems drawn from M 4..8192, N 96..7168, K 256..8192 the choice takes 30 % less time than transposing
+// always, is slower by more than 2 % on none, and costs 0.8 % more than the better of both (by more than 5 % on 12, all transposed: the costs
+// are those of in-place tiles 4 to 10 % slower than they are now).  Both sides, us: 1024 x 3584 x 4096 128x128 in place 38.6, transposed 49.6; 57 x 96 x 320 5.8 and 11.2; 30 x 336 x 2624 15.0 and 13.3; 2048 x 3584 x 4096
 // 76 and 69.8.
 // Where `cfg` is a numbered tile and the problem has more than one round of them, it is taken: those follow the order that the rows arrive in or
 // that the slices are wanted in (agg_set_tile_order, first_slice), the small tiles do not, and the bits must not depend on the order.  In a
@@ -198,8 +198,8 @@ constexpr double kGroupedWeightBytesPerUs = 7.2e6;   // weights of the experts t
 // out (the GEMM of Table 5, kernel alone, cold): 256x256 70, 128x256 63, 128x128 71.  Gathered rows never take the 128x256 tile of the large
 // kernel: at 8192 tokens of Table 4 the whole call is 1 % faster in bf16 (374 against 376) but its first pass on new weights 5 % slower
 // (457 against 435), and in fp32 it is 5 % slower throughout (392 against 371); where it would be the best of the numbered tiles, that
-// of gemm_pipe.h is faster.  There, with routing, weights beyond the memory-side cache, us: 8192 tokens 320x128 298, 256x224 383,
-// 256x256 382; 4096 tokens 192x192 236, 320x128 281, 256x256 275.
+// of gemm_pipe.h is faster.  There, with routing, weights beyond the memory-side cache, us: 8192 tokens 320x128 291, 128x256 330, 256x256 335,
+// 256x224 368; 4096 tokens 192x192 232, 320x128 254, 256x256 267.
 // A tile of gemm_pipe.h takes the place of a numbered one, whose bits it gives, never of a K-split one.
 // Which K-split tile is taken, or that another one is, follows from the problem alone: the small tiles and those of gemm_pipe.h are left
 // out where their table (P pairs) would have more entries than the static one, whatever table is used.  Among the numbered ones, which all give

@@ -169,7 +169,8 @@ hipError_t launch_producer(const ProducerArgs& a_in, int n_workgroups, int threa
     // of the grid without one, those: a workgroup of four waves copies 32 KiB in one trip (a rest of a few hundred bytes in a second
     // one, where the chunk is no multiple of 32 KiB), and the teams, each of whose workgroups counts itself done at one address, stay
     // small enough.  Slices of 64 and 32 KiB, us, 256 workgroups: 8 x 256 KiB 4.4 and 3.9, 3 x 1.3 MB 6.1 and 5.0, 2 x 2 MiB 5.4 and 5.0,
-    // 4 x 1.5 MiB 6.1 and 6.1, 4 x 2 MiB 6.5 and 7.3 (16 KiB: 4.5, 6.0, 6.2, 8.0, 9.9).
+    // 4 x 1.5 MiB 6.1 and 6.1, 4 x 2 MiB 6.5 and 7.3 (16 KiB: 4.5, 6.0, 6.2, 8.0, 9.9).  Back to back in a graph the two cross a little
+    // lower: 8 x 128 KiB 4.2 and 3.6, 3 x 1.3 MB 5.1 and 4.9, 4 x 1 MiB 4.6 and 4.7, 4 x 1.5 MiB 5.1 and 5.6.
     const long long total = a.chunk_bytes * a.chunks_per_shard * a.n_jobs;
     long long team = a.chunk_bytes / (total / 32768 <= n_workgroups * 5ll / 8 ? 32768 : 65536);
     if (team < 1) team = 1;
