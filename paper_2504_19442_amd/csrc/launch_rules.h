@@ -179,8 +179,8 @@ inline double expected_m_tiles(double mean, int bm)
 // more than 10 % on two.  The costs of the tiles of gemm_pipe.h are fitted to 800 further draws.  On 1226 others, all such that the choice
 // without them is a numbered tile, they take the place of one in 333 of 766 for gathered rows, which then take 6.3 % less time (all: 2.8 %), and
 // in 31 of 460 for rows in place (3.8 % less); 37 of the 333 are slower by more than 5 %, 20 by more than 10 % (1168 tokens x 4,
-// 6 x 1695 x 384: 32.9 and 24.8): mostly those whose tiles are estimated to just fill their last round and do not quite fit into it, which
-// depends on the routing.  (An estimate with the spread of the number of tiles does no better on average.)
+// 6 x 1695 x 384: 32.9 and 24.8): of those about half have tiles that are estimated to just fill their last round and do not quite fit into
+// it, which depends on the routing.  (An estimate with the spread of the number of tiles does no better on average.)
 constexpr TileCost kTileCostsGrouped[] = {
     {KS_16x32, 3.4, 0.113}, {KS_16x64, 3.4, 0.179}, {KS_32x32, 2.6, 0.142}, {KS_64x64, 3.3, 0.267}, {KS_64x128, 3.5, 0.40},
     {TILE_128x128 | TILE_K32, 3.0, 0.60}, {TILE_128x256 | TILE_K32, 2.9, 0.94}, {TILE_256x224 | TILE_K32, 4.1, 1.50},
