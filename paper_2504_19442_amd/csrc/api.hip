@@ -651,7 +651,7 @@ int agg_autotune_ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb
     constexpr int kWarm = 30, kSettled = 15;
     config = -1;
     int auto_tile = choose_tile(c, b_layout, M, N, K);
-    const bool automatic = kn_in_place(c, B, ldb, b_layout, M, N, K, false, &auto_tile) || auto_tile >= TILE_CONFIGS;
+    const bool in_place = kn_in_place(c, B, ldb, b_layout, M, N, K, false, &auto_tile), automatic = in_place || auto_tile >= TILE_CONFIGS;
     std::vector<float> auto_times;
     for (int it = 0; it < kWarm - 1 && rc == AGG_OK; ++it) {
         config = automatic ? -1 : tiles[0];
@@ -685,9 +685,11 @@ int agg_autotune_ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb
     // A candidate is the result (they all add up K in one order) unless the automatic choice is faster by more than the
     // medians of repeated tunings differ.  Measured, ms, automatic choice and best candidate: 16 x 3584 x 4096 0.0226 and 0.038,
     // 128 x 7168 x 8192 0.0475 and 0.0617, 999 x 1999 x 1984 0.0351 and 0.037, 1024 x 256 x 128 0.023 and 0.0213.
+    // The other way round where the automatic choice reads B in place: the candidates transpose it, which the copy of the shards hides here
+    // but nothing does where T is there already (1024 x 3584 x 4096: 0.056 and 0.057 beside the copy, 0.042 and 0.052 behind it).
     constexpr float kResolutionMs = 0.001f;
     const float auto_ms = median(auto_times);
-    if (rc == AGG_OK && auto_ms + kResolutionMs < best) {
+    if (rc == AGG_OK && auto_ms < best + (in_place ? kResolutionMs : -kResolutionMs)) {
         res.tile_config = -1;
         res.tile_order = orders[0];
         res.producer_workgroups = sdma ? 0 : wgs[1];

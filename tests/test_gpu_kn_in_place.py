@@ -184,9 +184,11 @@ class _Problem:
         agg.agg_tune_table_clear()
 
 
-def test_tuning_times_the_tiles_that_read_in_place():
-    # beside the copy the call takes 82 us, with the best of the numbered tiles and its transposed copy 105
-    p = _Problem(61, 128, 8192, 7168)
+@pytest.mark.parametrize("Ms,K,N", [(128, 8192, 7168), (256, 4096, 3584)])
+def test_tuning_times_the_tiles_that_read_in_place(Ms, K, N):
+    # beside the copy the call takes 82 us, with the best of the numbered tiles and its transposed copy 105; and 55 and 57, where a candidate
+    # would have to be faster by 1
+    p = _Problem(61, Ms, K, N)
     try:
         agg.agg_tune_table_clear()
         tuned, other = p.context(), p.context()
