@@ -22,7 +22,8 @@
 // tiles), 64 x 8192 x 3584 33.3 -> 18.5 (64x32), 128 x 7168 x 8192 74.6 -> 42 (64x64), 999 x 1999 x 1984 21 -> 15.6 (64x128).
 // KN: a B stored [K][N], read in place by gemm_km_kernel (64x64, 64x128, 128x128): no transposed copy, which costs a kernel, its bytes twice and
 // an event.  Transposing and GEMM, and in place, us: 1024 x 3584 x 4096 49.6 -> 38.6 (128x128), 376 x 5160 x 1984 29.7 -> 17.8 (64x128),
-// 84 x 240 x 704 12.2 -> 7.6 (64x64).
+// 84 x 240 x 704 12.2 -> 7.6 (64x64).  Since then (an instance per cache policy; 128x128: parts of 64x64 per wave, a look-ahead of four stages), us per call with
+// the copy: 1024 x 3584 x 4096 41.5 -> 40.3, 256 x 4096 x 4096 24.4 -> 23.2 (64x64), 512 x 3584 x 4096 30.0 -> 29.7 (64x128).
 #pragma once
 #include "gemm_tile.h"
 #include "ks_stage.h"
@@ -339,9 +340,11 @@ void gemm_ks_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
 }
 
 // One ring, shared: stages of 64 x (BM + BN), the waves split a stage's K in two and the columns in NW.
-template <int BM, int BN, int NW, int NST>
+// WM: the NW parts are WM parts of the rows times NW / WM of the columns.
+template <int BM, int BN, int NW, int NST, int WM = 1>
 struct KmCfg {
-    static constexpr int S = 2 * NW;                         // waves: two halves of a stage's K times NW parts of the columns
+    static constexpr int S = 2 * NW;                         // waves: two halves of a stage's K times NW parts of the tile
+    static constexpr int WN = NW / WM;
     static constexpr int A_UNITS = BM / UNIT_ROWS, B_UNITS = BN / UNIT_ROWS;
     static constexpr int LA = A_UNITS / S, LB = B_UNITS / S, L = LA + LB;     // loads of a stage, per wave
     static constexpr int STAGE = (BM + BN) * ROW_BYTES;
@@ -349,16 +352,22 @@ struct KmCfg {
     static constexpr int PITCH = BN + 4;
     static constexpr int RED = 2 * BM * PITCH * 4;
     static constexpr int LDS_BYTES = RING > RED ? RING : RED;
-    static constexpr int RB = BM / 16, CB = BN / NW / 16;
-    static_assert(A_UNITS % S == 0 && B_UNITS % S == 0 && NST % 2 == 0 && NST >= 4 && LDS_BYTES <= 159 * 1024, "tile");
+    static constexpr int RB = BM / WM / 16, CB = BN / WN / 16;
+    // Stages on their way ahead of the one whose fragments are multiplied.  With a short ring the slot of that stage is filled again at
+    // once, for which its reads must be back at the barrier; with a longer one the slot of the stage before, and no read is waited for.
+    // NST - 1 and NST, us per call: [K][N] 1024 x 3584 x 4096 (128x128, four slots) 42.7 and 41.7; 999 x 1999 x 1984 (64x128, six) 20.6 and 20.7.
+    static constexpr int AHEAD = NST <= 4 ? NST : NST - 1;
+    static_assert(NW % WM == 0 && A_UNITS % S == 0 && B_UNITS % S == 0 && NST % 2 == 0 && NST >= 4 && LDS_BYTES <= 159 * 1024, "tile");
 };
 
-template <int BM, int BN, int NW, int NST, KsKind KIND, bool KN = false>
+// STREAM ([K][N] only): B's loads carry the streaming hint.
+template <int BM, int BN, int NW, int NST, KsKind KIND, bool KN = false, int WM = 1, bool STREAM = false>
 __global__ __launch_bounds__(128 * NW)
 void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED, KsSlices, KsNoSlices> sl)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    using C_ = KmCfg<BM, BN, NW, NST>;
+    using C_ = KmCfg<BM, BN, NW, NST, WM>;
+    constexpr int AHEAD = C_::AHEAD;
     constexpr int S = C_::S, LA = C_::LA, LB = C_::LB, L = C_::L, RB = C_::RB, CB = C_::CB, PITCH = C_::PITCH;
     constexpr bool GROUPED = KIND == KS_GROUPED;
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -366,24 +375,25 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
     ks_fetch_params(p);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kh = wave & 1, nw = wave >> 1;
+    const int kh = wave & 1, nw = WM > 1 ? (wave >> 1) % C_::WN : wave >> 1, mw = WM > 1 ? (wave >> 1) / C_::WN : 0;
     const int ld_row = lane >> 3;
     // unit u = wave + S * i: S is even, so a wave's units are all even or all odd
     const int ld_chunk = (lane & 7) ^ (((wave & 1) * 4 + (lane >> 4)) & 7);
     const unsigned lds_u = (unsigned)(unsigned long)(lds_byte*)LDS_PTR(lds);
     const unsigned lds_ld = lds_u + wave * 1024;
-    const unsigned fr = lds_u + (lane & 15) * ROW_BYTES + (((4 * kh + (lane >> 4)) ^ ((lane >> 1) & 7)) << 4);
-    const unsigned fr_b = fr + (RB + nw * CB) * 2048;
+    const unsigned fr_0 = lds_u + (lane & 15) * ROW_BYTES + (((4 * kh + (lane >> 4)) ^ ((lane >> 1) & 7)) << 4);
+    const unsigned fr = fr_0 + mw * RB * 2048, fr_b = fr_0 + (BM / 16 + nw * CB) * 2048;
     // KN: B is [K][N].  A stage of it is 64 rows of one k each, BN columns (whole lines), 16-byte chunk c of row k in slot c ^ kn_swizzle(k).
-    // Lane l of a wave takes columns 2 (l % 16) and 2 (l % 16) + 1 of the wave's 32, of the eight k that its fragments hold: eight
-    // 4-byte reads, and a byte permute per pair of k puts them into the fragments of the even and of the odd columns.  (The
-    // hardware's transposing LDS read would do without the permutes, but the compiler waits for all loads in flight in front of it: five
-    // times slower.)  The swizzle puts the rows that a read's 16-lane groups take into different banks.
-    static_assert(!KN || (CB == 2 && KIND != KS_GROUPED && (BN == 64 || BN == 128)), "[K][N] operand");
+    // Lane l of a wave takes the CB columns from CB (l % 16) on of the wave's 16 CB, of the eight k that its fragments hold: eight
+    // reads of 2 CB bytes, and a byte permute per column and pair of k puts them into CB fragments, number j that of the columns
+    // CB n + j.  (The hardware's transposing LDS read would do without the permutes, but the compiler waits for all loads in flight in front of
+    // it: five times slower.)  The swizzle puts the rows that a read's 16-lane groups take into different banks.
+    static_assert(!KN || ((CB == 2 || (CB == 4 && BN == 128)) && KIND != KS_GROUPED && (BN == 64 || BN == 128)), "[K][N] operand");
     constexpr int KN_ROW = BN * 2;
-    auto kn_swizzle = [](int k) { return ((k >> 3) & (BN / 32 - 1)) << 2; };
+    auto kn_swizzle = [](int k) { return CB == 4 ? ((k >> 3) & 1) << 3 | ((k >> 4) & 1) << 2 : ((k >> 3) & (BN / 32 - 1)) << 2; };
     const int kn_k = 32 * kh + 8 * (lane >> 4), kn_n = lane & 15;
-    const unsigned fr_kn = lds_u + BM * ROW_BYTES + kn_k * KN_ROW + (((nw * 4 + (kn_n >> 2)) ^ kn_swizzle(kn_k)) << 4) + (kn_n & 3) * 4;
+    const unsigned fr_kn = lds_u + BM * ROW_BYTES + kn_k * KN_ROW
+                         + (((nw * CB * 2 + kn_n * CB / 8) ^ kn_swizzle(kn_k)) << 4) + kn_n * CB * 2 % 16;
 
     const int KC = p.KC;
     const int total_tiles = GROUPED ? *p.n_tiles_dev : p.total_tiles;
@@ -429,7 +439,9 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
                                                              16, off_b[i], st.k_off, 0, decltype(aux_c)::value);
                 });
             };
-            if (p.b_streams) load(std::integral_constant<int, 2>{});               // 2 = nt
+            // 2 = nt; [K][N]: an instance each (choosing in every stage: 1024 x 3584 x 4096 40.4 -> 38.8 us per call)
+            if constexpr (KN) load(std::integral_constant<int, STREAM ? 2 : 0>{});
+            else if (p.b_streams) load(std::integral_constant<int, 2>{});
             else load(std::integral_constant<int, 0>{});
         };
         auto issue_a = [&](int s, auto slot_c) {
@@ -442,7 +454,7 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
                                                          off_a[i], st.k_off, 0, 0);
             });
         };
-        auto issue_all_b = [&] { static_for<NST - 1>([&](auto j_c) { issue_b(decltype(j_c)::value, j_c); }); };
+        auto issue_all_b = [&] { static_for<AHEAD>([&](auto j_c) { issue_b(decltype(j_c)::value, j_c); }); };
         if (wave != 0 || !gated) issue_all_b();
         if (gated && ks_wait(p, w, &s_gave_up, wave, lane, issue_all_b)) {
             __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // the launch drains; agg_status reports the time-out
@@ -453,7 +465,7 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
             for (int i = 0; i < LA; ++i)
                 off_a[i] = off_a[i] != 0xFFFFFFFFu ? off_a[i] * lda2 + (unsigned)(ld_chunk * 16) : 0xFFFFFF00u;
         }
-        static_for<NST - 1>([&](auto j_c) { issue_a(decltype(j_c)::value, j_c); });
+        static_for<AHEAD>([&](auto j_c) { issue_a(decltype(j_c)::value, j_c); });
 
         f32x4_ acc[RB][CB];
 #pragma unroll
@@ -463,13 +475,14 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
         constexpr int NM1 = RB * CB / 2;
         bf16x8 fa[2][RB], fb[2][CB];
         typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
-        unsigned kn[2][KN ? 8 : 1];            // the column pairs of KN's next fragments
+        typedef std::conditional_t<CB == 4, __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned, unsigned> kn_cols;
+        kn_cols kn[2][KN ? 8 : 1];             // CB columns of each k of KN's next fragments
         auto read_frags = [&](auto slot_c, auto set_c) {
             constexpr int slot = decltype(slot_c)::value, set = decltype(set_c)::value;
             if constexpr (KN) {
 #pragma unroll
                 for (int k = 0; k < 8; ++k)
-                    kn[set][k] = *(__attribute__((address_space(3))) const unsigned*)(unsigned long)(fr_kn + slot * C_::STAGE + k * KN_ROW);
+                    kn[set][k] = *(__attribute__((address_space(3))) const kn_cols*)(unsigned long)(fr_kn + slot * C_::STAGE + k * KN_ROW);
             } else
 #pragma unroll
             for (int j = 0; j < CB; ++j) fb[set][j] = *(lds_frag*)(unsigned long)(fr_b + slot * C_::STAGE + j * 2048);
@@ -477,7 +490,7 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
             for (int i = 0; i < RB; ++i) fa[set][i] = *(lds_frag*)(unsigned long)(fr + slot * C_::STAGE + i * 2048);
         };
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * LA));     // stage 0 has landed
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((AHEAD - 1) * LA));   // stage 0 has landed
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         read_frags(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
@@ -490,21 +503,27 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
                 if (s >= KC) return;
                 asm volatile("" ::: "memory");
                 // stage s + 1 has landed; behind the barrier that holds for all waves, and nobody needs stage s - 1 any more
-                if (s0 == 0 && slot <= NST - 3) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 3 - slot > 0 ? NST - 3 - slot : 0) * LA + slot * L));
-                else __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 3) * L));
+                // (AHEAD = NST: nor stage s, this wave's reads of it are back)
+                constexpr int reads_back = AHEAD == NST ? ~(0xF << 8) : ~0;
+                if (s0 == 0 && slot <= AHEAD - 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm((AHEAD - 2 - slot) * LA + slot * L) & reads_back);
+                else __builtin_amdgcn_s_waitcnt(vmcnt_imm((AHEAD - 2) * L) & reads_back);
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_sched_barrier(0);
                 read_frags(std::integral_constant<int, (slot + 1) % NST>{}, std::integral_constant<int, (slot + 1) & 1>{});
                 if constexpr (KN) {
-                    u32x4 even, odd;
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        even[k] = __builtin_amdgcn_perm(kn[slot & 1][2 * k + 1], kn[slot & 1][2 * k], 0x05040100u);
-                        odd[k] = __builtin_amdgcn_perm(kn[slot & 1][2 * k + 1], kn[slot & 1][2 * k], 0x07060302u);
+                    for (int j = 0; j < CB; ++j) {
+                        u32x4 f;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const kn_cols lo = kn[slot & 1][2 * k], hi = kn[slot & 1][2 * k + 1];
+                            const unsigned sel = j & 1 ? 0x07060302u : 0x05040100u;
+                            if constexpr (CB == 4) f[k] = __builtin_amdgcn_perm(hi[j / 2], lo[j / 2], sel);
+                            else f[k] = __builtin_amdgcn_perm(hi, lo, sel);
+                        }
+                        fb[slot & 1][j] = __builtin_bit_cast(bf16x8, f);
                     }
-                    fb[slot & 1][0] = __builtin_bit_cast(bf16x8, even);
-                    fb[slot & 1][CB - 1] = __builtin_bit_cast(bf16x8, odd);
                 }
                 auto multiply = [&](auto from_c, auto to_c) {
                     static_for<decltype(to_c)::value - decltype(from_c)::value>([&](auto n_c) {
@@ -523,8 +542,8 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
                     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);     // LDS read
                 });
                 __builtin_amdgcn_sched_barrier(0);
-                issue_b(s + NST - 1, std::integral_constant<int, (slot + NST - 1) % NST>{});
-                issue_a(s + NST - 1, std::integral_constant<int, (slot + NST - 1) % NST>{});
+                issue_b(s + AHEAD, std::integral_constant<int, (slot + AHEAD) % NST>{});
+                issue_a(s + AHEAD, std::integral_constant<int, (slot + AHEAD) % NST>{});
                 __builtin_amdgcn_sched_barrier(0);
                 multiply(std::integral_constant<int, NM1>{}, std::integral_constant<int, RB * CB>{});
                 __builtin_amdgcn_sched_barrier(0);
@@ -537,11 +556,13 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
         float* const red = (float*)lds;
 #pragma unroll
         for (int i = 0; i < RB; ++i) {
-            float* const to = red + (kh * BM + i * 16 + (lane & 15)) * PITCH + nw * CB * 16;
-            if constexpr (KN) {                // the lane's eight columns, the even ones in one block, the odd ones in the other
-                const f32x4_ e = acc[i][0], o = acc[i][CB - 1];
-                *(f32x4_*)(to + 8 * (lane >> 4)) = f32x4_{e[0], o[0], e[1], o[1]};
-                *(f32x4_*)(to + 8 * (lane >> 4) + 4) = f32x4_{e[2], o[2], e[3], o[3]};
+            float* const to = red + (kh * BM + (mw * RB + i) * 16 + (lane & 15)) * PITCH + nw * CB * 16;
+            if constexpr (KN) {                // block j holds columns CB n + j: a lane's 4 CB columns are consecutive
+                float c[4 * CB];
+#pragma unroll
+                for (int v = 0; v < 4 * CB; ++v) c[v] = acc[i][v % CB][v / CB];
+#pragma unroll
+                for (int q = 0; q < CB; ++q) *(f32x4_*)(to + 4 * CB * (lane >> 4) + 4 * q) = f32x4_{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
             } else {
 #pragma unroll
                 for (int j = 0; j < CB; ++j) *(f32x4_*)(to + j * 16 + 4 * (lane >> 4)) = acc[i][j];
@@ -561,20 +582,23 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
 }
 
 // SHARED: gemm_km_kernel with X = NW, else gemm_ks_kernel with X = S.
-template <bool SHARED, int BM, int BN, int X, int NST, KsKind KIND, bool KN = false>
+template <bool SHARED, int BM, int BN, int X, int NST, KsKind KIND, bool KN = false, int WM = 1>
 static hipError_t launch_ks_kind(const KsParams& p, const std::conditional_t<KIND == KS_SLICED, KsSlices, KsNoSlices>& sl,
                                  hipStream_t stream)
 {
-    using C_ = std::conditional_t<SHARED, KmCfg<BM, BN, X, NST>, KsCfg<BM, BN, X, NST>>;
+    using C_ = std::conditional_t<SHARED, KmCfg<BM, BN, X, NST, WM>, KsCfg<BM, BN, X, NST>>;
     void (*kernel)(const KsParams, const std::conditional_t<KIND == KS_SLICED, KsSlices, KsNoSlices>);
-    if constexpr (SHARED) kernel = gemm_km_kernel<BM, BN, X, NST, KIND, KN>;
+    constexpr bool BY_HINT = SHARED && KN;             // an instance without the streaming hint and one with it
+    if constexpr (BY_HINT) kernel = p.b_streams ? gemm_km_kernel<BM, BN, X, NST, KIND, KN, WM, true> : gemm_km_kernel<BM, BN, X, NST, KIND, KN, WM, false>;
+    else if constexpr (SHARED) kernel = gemm_km_kernel<BM, BN, X, NST, KIND, KN, WM>;
     else kernel = gemm_ks_kernel<BM, BN, X, NST, KIND>;
     constexpr int threads = SHARED ? 128 * X : 64 * X;
-    static bool attr_set = false;
-    if (!attr_set) {
+    static bool attr_set[2] = {false, false};
+    bool& set = attr_set[BY_HINT && p.b_streams];
+    if (!set) {
         hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, C_::LDS_BYTES);
         if (e != hipSuccess) return e;
-        attr_set = true;
+        set = true;
     }
     hipLaunchKernelGGL(kernel, dim3(p.grid), dim3(threads), C_::LDS_BYTES, stream, p, sl);
     return hipGetLastError();
@@ -584,7 +608,7 @@ static hipError_t launch_ks_kind(const KsParams& p, const std::conditional_t<KIN
 enum KsForms { KS_DENSE = 1, KS_MOE = 2 };
 
 // The launch of `g` (a GemmParams whose tile fields are those of this tile shape) on this kernel.
-template <bool SHARED, int BM, int BN, int X, int NST, int FORMS, bool KN = false>
+template <bool SHARED, int BM, int BN, int X, int NST, int FORMS, bool KN = false, int WM = 1>
 static hipError_t launch_ks(const GemmParams& g, bool grouped, int grid, hipStream_t stream)
 {
     KsParams p{};
@@ -613,13 +637,13 @@ static hipError_t launch_ks(const GemmParams& g, bool grouped, int grid, hipStre
         }
     }
     if constexpr ((FORMS & KS_DENSE) != 0) {
-        if (g.n_slices == 0) return launch_ks_kind<SHARED, BM, BN, X, NST, KS_PLAIN, KN>(p, KsNoSlices{}, stream);
+        if (g.n_slices == 0) return launch_ks_kind<SHARED, BM, BN, X, NST, KS_PLAIN, KN, WM>(p, KsNoSlices{}, stream);
         KsSlices sl{};
         sl.M = g.M; sl.tiles_n = g.tiles_n; sl.slice_rows = g.slice_rows; sl.slice_chunks = g.slice_chunks;
         sl.chunk_rows = g.chunk_rows; sl.ldc_slice = (int)g.ldc_slice; sl.slice_mul = div_mul(g.slice_rows);
         sl.slice_ctr = g.slice_ctr;
         for (int w = 0; w < g.n_slices; ++w) { sl.slice_dst[w] = g.slice_dst[w]; sl.slice_flag[w] = g.slice_flag[w]; }
-        return launch_ks_kind<SHARED, BM, BN, X, NST, KS_SLICED, KN>(p, sl, stream);
+        return launch_ks_kind<SHARED, BM, BN, X, NST, KS_SLICED, KN, WM>(p, sl, stream);
     }
     return hipErrorInvalidValue;
 }
@@ -635,10 +659,10 @@ static hipError_t launch_ks(const GemmParams& g, bool grouped, int grid, hipStre
     }                                                                                                       \
     }
 // ... for a B stored [K][N] and read in place
-#define AGG_KN_INSTANCE(BM, BN, NW, NST)                                                                    \
+#define AGG_KN_INSTANCE(BM, BN, NW, NST, WM)                                                                \
     namespace agg {                                                                                         \
     hipError_t launch_gemm_kn_##BM##x##BN(const GemmParams& p, int grid, hipStream_t s)                     \
     {                                                                                                       \
-        return launch_ks<true, BM, BN, NW, NST, KS_DENSE, true>(p, false, grid, s);                         \
+        return launch_ks<true, BM, BN, NW, NST, KS_DENSE, true, WM>(p, false, grid, s);                     \
     }                                                                                                       \
     }

@@ -135,6 +135,22 @@ def test_weights_beyond_the_memory_side_cache():
         ctx.free()
 
 
+# tile, rows per rank (of two), K, N: stages fewer than, as many as and one and two laps more than the slots of the 128x128 tile's ring of four,
+# and the instances with the streaming hint (256 MB of weights and more)
+@pytest.mark.parametrize("tile,Ms,K,N", [("128x128", 626, k, 1568) for k in (128, 256, 320, 512, 576)]
+                         + [("64x64", 8, 8192, 16384), ("64x128", 64, 8192, 16384), ("128x128", 100, 8192, 16384)])
+def test_every_length_of_the_short_ring_and_the_streaming_instances(tile, Ms, K, N):
+    assert host_rules.kn_tile(_cus(), 2 * Ms, N, K) == tile
+    g = torch.Generator(device="cuda").manual_seed(K)
+    shards, B = [_ints(g, Ms, K) for _ in range(2)], _ints(g, K, N)
+    ctx = agg.symm_alloc(2, 0, Ms * K * 2, 2)
+    try:
+        agg.agg_reserve_b_kn(ctx, N, K)
+        assert torch.equal(_call(ctx, shards, 2 * Ms, N, K, B, N, agg.B_KN), torch.cat(shards).float() @ B.float())
+    finally:
+        ctx.free()
+
+
 def _call(ctx, shards, M, N, K, B, ldb, layout):
     ps, cs = ctx.streams()
     C = torch.full((M, N), float("nan"), device="cuda")
