@@ -148,7 +148,7 @@ struct ReduceArgs {
 void tune_table_put(int b_layout, int W, int M, int N, int K, const agg_tune_result& r);
 int tune_table_apply(agg_ctx* c, int M, int N, int K, int layout);
 constexpr int kKnAsNk = -2;                 // agg_ctx::kn_config
-hipError_t launch_reduce(const ReduceArgs& a, int n_workgroups, hipStream_t stream, bool beside_gemm);
+hipError_t launch_reduce(const ReduceArgs& a, int n_workgroups, hipStream_t stream);
 
 }  // namespace agg
 

@@ -589,7 +589,7 @@ static int reduce_impl(agg_ctx* c, int Ms, int N, const float* const* slots, voi
     a.wait_ticks = wait_ticks(c);
     a.err = c->err;
     const int nwg = n_workgroups > 0 ? n_workgroups : reduce_workgroups(c->W, c->num_cus, a.n_vec4, beside_gemm);
-    return hip_fail(launch_reduce(a, nwg, (hipStream_t)stream, beside_gemm));
+    return hip_fail(launch_reduce(a, nwg, (hipStream_t)stream));
 }
 
 int rs_reduce(agg_ctx* c, int Ms, int N, const float* const* slots, void* R, int ldr, int r_dtype, int n_workgroups,

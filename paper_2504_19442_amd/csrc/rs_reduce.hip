@@ -5,10 +5,13 @@
 // access; streaming stores.
 // What is left beside the bytes is the start: the signals are looked at by the lanes of one wave side by side (one after
 // the other by one thread, each a trip to memory, cost 4 us per workgroup), and where all slots are there the first
-// block is loaded like every other.  Eight slots of 1024 x 8192 (268 MB read, 34 written, in no cache) 64.7 -> 59.6 us (54.6 with the loads
-// launch_reduce picks), of 8 x 8192 5.2 -> 3.6;
-// six slots of 512 x 4096 20.6 -> 15.6 and sixteen of 256 x 4096 29.8 -> 18.1 (four slots' loads in flight together
-// where no kernel is unrolled for the world size).
+// block is loaded like every other.
+// Once all slots are there, loads never stop: the register of a slot's value is loaded again, for the next block, as soon as the value
+// has been added, so that W x RU loads per lane are in flight throughout, where a block that is loaded whole, added and stored drains them in
+// between.  Few workgroups then do better than many (reduce_workgroups), and 64 registers are enough for every world size: a
+// reducer fits beside any GEMM of this library.  Blocks loaded whole, and this, us per call with the kernel that raises the signals, slots not
+// touched lately: eight slots of 1024 x 8192 55.5 and 52.6, of 1000 x 8000 58.8 and 54.7, four 41.6 and 33.9, three 38.1 and 26.6,
+// two 21.7 and 19.4; behind the GEMM of gemm_rs (256 workgroups) 450 and 443.
 #include "agg_internal.h"
 
 namespace agg {
@@ -39,14 +42,15 @@ __device__ inline bool wait_signals(const ReduceArgs& a, int n, int epoch, int l
     return ok;
 }
 
-__device__ inline void store_out(const ReduceArgs& a, long long i, f32x4 v)
+template <class I>      // I: an integer type that holds the number of float4
+__device__ inline void store_out(const ReduceArgs& a, I i, f32x4 v)
 {
     long long off;
     if (a.row_vec4) {
-        const long long row = i / a.row_vec4;
-        off = row * a.ldr + (i - row * a.row_vec4) * 4;
+        const I row = i / (I)a.row_vec4;
+        off = row * a.ldr + (long long)(i - row * (I)a.row_vec4) * 4;
     } else {
-        off = i * 4;
+        off = (long long)i * 4;
     }
     if (a.r_is_f32) {
         __builtin_nontemporal_store(v, (f32x4*)((float*)a.R + off));
@@ -62,7 +66,7 @@ __device__ inline void store_out(const ReduceArgs& a, long long i, f32x4 v)
 // flight together); WT == 0: any world size.
 // NT: the slots are read past the caches (launch_reduce).
 template <int WT, int RU, bool NT>   // RU = float4 per lane per slot and block
-__global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a)
+__global__ __launch_bounds__(256, 8) void reduce_kernel(const ReduceArgs a)
 {
     const int tid = threadIdx.x;
     const int W = WT > 0 ? WT : a.W;
@@ -124,6 +128,38 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a)
         } else if (seen < W) {
             look(0);                   // when all have arrived, the block is loaded whole below
         }
+        if constexpr (WT > 0) {
+            // 32-bit offsets (the number of workgroups is at most 2^16); loads past the end return zero
+            if (a.chunks <= 1 && seen == W && a.n_vec4 < (1ll << 27)) {
+                const unsigned bytes = (unsigned)a.n_vec4 * 16u, step = (unsigned)stride * 16u;
+                unsigned at = (unsigned)base * 16u;
+                f32x4 v[RU][WT];
+                auto fetch = [&](int u, int w, unsigned off) {
+                    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.slot[w]), 0, bytes, 0x00020000);
+                    v[u][w] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, NT ? 2 : 0));
+                };
+#pragma unroll
+                for (int u = 0; u < RU; ++u)
+#pragma unroll
+                    for (int w = 0; w < WT; ++w) fetch(u, w, at + u * step);
+                for (;;) {
+#pragma unroll
+                    for (int u = 0; u < RU; ++u) {
+                        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int w = 0; w < WT; ++w) {
+                            sum = sum + v[u][w];
+                            asm volatile("" : "+v"(sum));        // added before its register is loaded again
+                            fetch(u, w, at + RU * step);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        if (at < bytes) store_out(a, at / 16u, sum);
+                        at += step;
+                        if (at - tid * 16u >= bytes) return;
+                    }
+                }
+            }
+        }
         if (a.chunks <= 1 && seen < W) {
             // slots still to arrive: take them one by one in the order of Algorithm 3
             for (int w = 0; w < W; ++w) {
@@ -182,20 +218,16 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a)
     }
 }
 
-// beside_gemm: the launch is meant to run on the same compute units as the GEMM kernel, whose waves leave 64 vector
-// registers per SIMD lane free: only kernels of at most 64 registers per lane fit there (a bigger one starts only where
-// a GEMM workgroup has finished).  All variants but <8, 2, ..> are that small.
+// RU: about eight loads in flight per lane.  At most 64 registers each (50 to 58; the second launch bound): the GEMM's waves leave 64 per
+// SIMD lane, so a reducer runs on the same compute units.
 template <bool NT>
-static void launch_reduce_nt(const ReduceArgs& a, int n_workgroups, hipStream_t stream, bool beside_gemm)
+static void launch_reduce_nt(const ReduceArgs& a, int n_workgroups, hipStream_t stream)
 {
     const dim3 grid(n_workgroups), wg(256);
     switch (a.W) {
-        case 8:
-            if (beside_gemm) hipLaunchKernelGGL((reduce_kernel<8, 1, NT>), grid, wg, 0, stream, a);
-            else hipLaunchKernelGGL((reduce_kernel<8, 2, NT>), grid, wg, 0, stream, a);
-            break;
+        case 8: hipLaunchKernelGGL((reduce_kernel<8, 1, NT>), grid, wg, 0, stream, a); break;
         case 4: hipLaunchKernelGGL((reduce_kernel<4, 2, NT>), grid, wg, 0, stream, a); break;
-        case 3: hipLaunchKernelGGL((reduce_kernel<3, 2, NT>), grid, wg, 0, stream, a); break;
+        case 3: hipLaunchKernelGGL((reduce_kernel<3, 3, NT>), grid, wg, 0, stream, a); break;
         case 2: hipLaunchKernelGGL((reduce_kernel<2, 4, NT>), grid, wg, 0, stream, a); break;
         default: hipLaunchKernelGGL((reduce_kernel<0, 2, NT>), grid, wg, 0, stream, a); break;
     }
@@ -209,10 +241,10 @@ static void launch_reduce_nt(const ReduceArgs& a, int n_workgroups, hipStream_t 
 // 336 MB on that, too, is faster with the hint (68.1 and 64.6).  Below the line the hint gains on slots not touched lately (134 MB
 // 34.1 and 30.6, 201 MB 46.2 and 41.8) and loses up to 5 % on ones that the cache holds, which slots of that size usually
 // are: ordinary loads.
-hipError_t launch_reduce(const ReduceArgs& a, int n_workgroups, hipStream_t stream, bool beside_gemm)
+hipError_t launch_reduce(const ReduceArgs& a, int n_workgroups, hipStream_t stream)
 {
-    if (a.n_vec4 * 16 * a.W >= (256ll << 20)) launch_reduce_nt<true>(a, n_workgroups, stream, beside_gemm);
-    else launch_reduce_nt<false>(a, n_workgroups, stream, beside_gemm);
+    if (a.n_vec4 * 16 * a.W >= (256ll << 20)) launch_reduce_nt<true>(a, n_workgroups, stream);
+    else launch_reduce_nt<false>(a, n_workgroups, stream);
     return hipGetLastError();
 }
 

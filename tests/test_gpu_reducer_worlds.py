@@ -45,6 +45,33 @@ def test_reducer_world_sizes_bit_exact(W, Ms, N):
         ctx.free()
 
 
+# blocks of 256 float4 per workgroup: fewer than the unrolled loop holds, as many, one more, several laps; whole and partial last blocks
+@pytest.mark.parametrize("W", [2, 3, 4, 8])
+@pytest.mark.parametrize("n_vec4,workgroups", [(1, 0), (255, 1), (256, 3), (257, 1), (513, 2), (256 * 4, 1), (256 * 5 - 3, 1), (256 * 23 + 1, 5), (256 * 1100 + 77, 0)])
+def test_reducer_loop_lengths_bit_exact(W, n_vec4, workgroups):
+    g = torch.Generator(device="cuda").manual_seed(7500 + W)
+    slots = [torch.randn((n_vec4, 4), device="cuda", generator=g) * 10.0 ** w for w in range(W)]
+    want = torch.zeros((n_vec4, 4), device="cuda")
+    for s in slots:
+        want = want + s
+    ctx = agg.symm_alloc(W, 0, 16, W)
+    try:
+        _, cs = ctx.streams()
+        agg.signal_reset(ctx)
+        for w in range(W):
+            agg.signal_set(ctx, w, cs)
+        for ldr, dtype in ((4, torch.float32), (8, torch.float32), (12, torch.bfloat16)):
+            R = torch.full((n_vec4 + 1, ldr), 3.0, device="cuda", dtype=dtype)
+            torch.cuda.synchronize()
+            agg.rs_reduce(ctx, n_vec4, 4, slots, R, ldr, agg.F32 if dtype == torch.float32 else agg.BF16, workgroups, cs)
+            torch.cuda.synchronize()
+            assert agg.agg_status(ctx) == agg.OK
+            assert torch.equal(R[:-1, :4], want.to(dtype))
+            assert bool((R[:, 4:] == 3.0).all()) and bool((R[-1] == 3.0).all())
+    finally:
+        ctx.free()
+
+
 @pytest.mark.parametrize("W,Ms,N,ldr", [(8, 1024, 8192, 8192), (16, 1024, 4100, 4104), (3, 2048, 11000, 11000), (2, 4096, 8188, 8188)])
 def test_reducer_slots_beyond_the_memory_side_cache_bit_exact(W, Ms, N, ldr):
     # 256 MB of slots and more (the last: just below); the reference adds the slots in order, one fp32 rounding each
