@@ -200,7 +200,8 @@ int rs_reduce(agg_ctx* ctx, int Ms, int N, const float* const* slots,
  * The other rows go to P_other (fp32 [M, N], leading dimension N; rows of the own slice are not written;
  * may be NULL to skip computing them).  Enqueues on reduce_stream a stream-level wait for the own slot's
  * signal (it holds no compute unit, so the GEMM can always become resident) and then the reduction of
- * rs_reduce, which waits for every slot's signal and runs beside the rest of the GEMM.  Peers' slots "arrive" when the caller sets their signals
+ * rs_reduce, which waits for every slot's signal and runs beside the rest of the GEMM.  (With gemm_stream == reduce_stream the
+ * reducer follows the GEMM, does not wait for the own slot and raises its signals when it starts.)  Peers' slots "arrive" when the caller sets their signals
  * (signal_set, or a producer of the caller's own).
  */
 int gemm_rs(agg_ctx* ctx, int M, int N, int Klocal,
@@ -392,7 +393,8 @@ int agg_set_link_rate(agg_ctx* ctx, double gigabytes_per_second);
  * sorted_token [Ttok*topk], sorted_expert_offsets [E+1], pair_pos [Ttok*topk]: DEVICE int32 outputs the call fills and
  * uses (pair_pos[t*topk+s] = row of pair (t, s) in the sorted order).  Requirements: Klocal % 64 == 0, N % 4 == 0,
  * Ttok % W == 0, 16-byte aligned H, weights2, topk_ids, gate, Y, slots, Z_other.  GEMM, top-k reduction and the own
- * signal run on gemm_stream, the reducer on reduce_stream behind a stream-level wait for that signal.
+ * signal run on gemm_stream, the reducer on reduce_stream behind a stream-level wait for that signal.  With one stream for both the
+ * reducer follows the reduction and raises the own slot's signals when it starts.
  */
 int moe_rs(agg_ctx* ctx, int Ttok, int topk, int E, int N, int Klocal,
            const void* H, const void* weights2, const int32_t* topk_ids, const float* gate,

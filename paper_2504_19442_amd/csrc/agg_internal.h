@@ -134,8 +134,9 @@ struct ReduceArgs {
     long long ldr;
     int r_is_f32;
     int N;
-    const int* flags;
+    int* flags;
     int flag_step;                // signal index of slot w = w * flag_step
+    int own;                      // slot that an earlier kernel of the same stream has completed: its signals are raised, not waited for; -1 = none
     int chunks;                   // > 1: slot w arrives in this many row chunks, chunk c on signal w * flag_step + c
     long long chunk_vec4;         // float4 elements per chunk
     int epoch;

@@ -12,6 +12,8 @@
 // reducer fits beside any GEMM of this library.  Blocks loaded whole, and this, us per call with the kernel that raises the signals, slots not
 // touched lately: eight slots of 1024 x 8192 55.5 and 52.6, of 1000 x 8000 58.8 and 54.7, four 41.6 and 33.9, three 38.1 and 26.6,
 // two 21.7 and 19.4; behind the GEMM of gemm_rs (256 workgroups) 450 and 443.
+// ReduceArgs::own: behind the GEMM on its own stream there is nothing to wait for in the own slot, and its signals are raised here, by one
+// workgroup, instead of by every tile or by a kernel of its own (api.hip: gemm_rs, moe_rs).
 #include "agg_internal.h"
 
 namespace agg {
@@ -22,13 +24,15 @@ typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 
 
 // Wave 0 of a workgroup waits for the n signals f(0) .. f(n - 1), one lane each (64 at a time): they are looked at side by
-// side, each look is a trip to memory.  False in the lanes that gave up.
+// side, each look is a trip to memory.  f < 0: nothing to wait for.  False in the lanes that gave up.
 template <class F>
 __device__ inline bool wait_signals(const ReduceArgs& a, int n, int epoch, int lane, F&& f)
 {
     bool ok = true;
     for (int k = lane; k < n; k += 64) {
-        const int* fp = a.flags + f(k) * kSignalStride;
+        const long long at = f(k);
+        if (at < 0) continue;
+        const int* fp = a.flags + at * kSignalStride;
         const long long t0 = wall_clock64();
         while (__hip_atomic_load(fp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch) {
             if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || wall_clock64() - t0 > a.wait_ticks) {
@@ -72,6 +76,9 @@ __global__ __launch_bounds__(256, 8) void reduce_kernel(const ReduceArgs a)
     const int W = WT > 0 ? WT : a.W;
     const int epoch = a.epoch_ptr ? __hip_atomic_load(a.epoch_ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : a.epoch;
     const long long stride = (long long)gridDim.x * 256;
+    // (what its signals stand for was complete when this kernel started)
+    if (a.own >= 0 && blockIdx.x == 0 && tid < a.chunks)
+        __hip_atomic_store(a.flags + ((long long)a.own * a.flag_step + tid) * kSignalStride, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     auto load = [](const f32x4* p) { return NT ? __builtin_nontemporal_load(p) : *p; };
     __shared__ int s_upto;
     int seen = 0;                      // slots 0..seen-1 are known to have arrived (uniform over the workgroup)
@@ -84,7 +91,7 @@ __global__ __launch_bounds__(256, 8) void reduce_kernel(const ReduceArgs a)
             const long long t0 = wall_clock64();
             int upto;
             for (;;) {
-                const bool here = tid >= W || __hip_atomic_load(fp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= epoch;
+                const bool here = tid >= W || tid == a.own || __hip_atomic_load(fp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= epoch;
                 const unsigned long long missing = ~__ballot(here);
                 upto = missing ? (int)__builtin_ctzll(missing) : W;
                 if (upto >= want) break;
@@ -119,7 +126,9 @@ __global__ __launch_bounds__(256, 8) void reduce_kernel(const ReduceArgs a)
                 bool ok = true;
                 if (tid < 64) {
                     const int c0 = chunks_seen;
-                    ok = wait_signals(a, (need - c0 + 1) * W, epoch, tid, [&](int k) { return (long long)(k % W) * a.flag_step + c0 + k / W; });
+                    ok = wait_signals(a, (need - c0 + 1) * W, epoch, tid, [&](int k) {
+                        return k % W == a.own ? -1ll : (long long)(k % W) * a.flag_step + c0 + k / W;
+                    });
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 }
                 if (__syncthreads_or(!ok)) return;
