@@ -165,7 +165,8 @@ int ag_producer_emulate(agg_ctx* ctx, const void* const* remote_shards, const in
  * depends on the tile, and the automatic choice of the tile on M, N, K and, for AGG_B_KN, on whether B is read in place (see there):
  * agg_set_tile_config gives results whose bits depend neither on the batch nor on the layout of B.
  * Each tile waits (acquire) for every signal covering its rows to reach the current epoch before its
- * first load of A.  Requirements: K % 64 == 0, M % W == 0; for AGG_B_NK ldb % 8 == 0 and B 16-byte aligned;
+ * first load of A -- but where ag_producer_emulate (AGG_PRODUCER_KERNEL) has enqueued the copies of all shards for this epoch on
+ * consumer_stream itself, the default stream or one of symm_streams, the order of the stream takes the place of the signals.  Requirements: K % 64 == 0, M % W == 0; for AGG_B_NK ldb % 8 == 0 and B 16-byte aligned;
  * C aligned to its element size; M, N arbitrary (>= 0; 0 is a no-op).
  */
 int ag_gemm(agg_ctx* ctx, int M, int N, int K,
