@@ -96,6 +96,10 @@ struct TopkReduceArgs {
     int own_lo, own_hi;           // tokens of this rank: their rows go to Z_own (row t - own_lo) ...
     float* Z_own;
     float* Z_other;               // ... all other tokens to row t of Z_other (nullptr: not computed)
+    int* flag;                    // not null: the last workgroup with own tokens raises these n_flags signals (Z_own then below 2 GiB)
+    int n_flags, epoch;
+    const int* epoch_ptr;         // not null: the epoch is read from this device word
+    int* counter;                 // workgroups that have stored theirs; zero between launches
 };
 hipError_t launch_topk_reduce(const TopkReduceArgs& a, int n_workgroups, hipStream_t stream);
 hipError_t launch_gemm_grouped(const GemmParams& p, int cfg, int grid, hipStream_t stream);

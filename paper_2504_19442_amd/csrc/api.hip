@@ -1082,12 +1082,22 @@ int moe_rs(agg_ctx* c, int Ttok, int topk, int E, int N, int Kl, const void* H, 
     t.own_hi = t.own_lo + Tr;
     t.Z_own = const_cast<float*>(slots[c->rank]);
     t.Z_other = Z_other;
-    if ((rc = hip_fail(launch_topk_reduce(t, c->num_cus * 4, (hipStream_t)gemm_stream))) != AGG_OK) return rc;
-    // 3. notify: the own slot is complete; then the reducer, which waits for the peers' signals itself.  On one stream the reducer does both:
-    // a kernel less (us per call, small problems: 28.2 and 25.2).
-    if (gemm_stream == reduce_stream) return reduce_impl(c, Tr, N, slots, R, ldr, r_dtype, 0, reduce_stream, false, true);
+    // 3. notify: the own slot is complete; then the reducer, which waits for the peers' signals itself.  On two streams the top-k reduction
+    // raises the own slot's signals as soon as its rows are stored; on one the reducer does, a kernel less in both (us per call, small problems on
+    // one stream: 28.2 and 25.2).
+    const bool one_stream = gemm_stream == reduce_stream;
     int32_t* own_flag = c->signals + (size_t)c->rank * (c->n_signals / W) * kSignalStride;
-    for (int ch = 0; ch < c->rs_chunks; ++ch)   // the reduction above completes all row chunks of the slot at once
+    const bool raises = !one_stream && (long long)Tr * N * 4 < (1ll << 31);
+    if (raises) {
+        t.flag = own_flag;
+        t.n_flags = c->rs_chunks;
+        t.epoch = c->epoch;
+        t.epoch_ptr = c->device_epoch ? c->epoch_word : nullptr;
+        t.counter = c->counters + c->n_signals;
+    }
+    if ((rc = hip_fail(launch_topk_reduce(t, c->num_cus * 4, (hipStream_t)gemm_stream))) != AGG_OK) return rc;
+    if (one_stream) return reduce_impl(c, Tr, N, slots, R, ldr, r_dtype, 0, reduce_stream, false, true);
+    for (int ch = 0; !raises && ch < c->rs_chunks; ++ch)
         if ((rc = hip_fail(launch_signal_set(own_flag + ch * kSignalStride, c->epoch, c->device_epoch ? c->epoch_word : nullptr,
                                              (hipStream_t)gemm_stream))) != AGG_OK)
             return rc;

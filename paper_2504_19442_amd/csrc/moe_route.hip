@@ -350,6 +350,10 @@ __global__ __launch_bounds__(THREADS) void moe_route_small_kernel(const MoeRoute
 // reducer waits for).  A lane works on U tokens at a time: the row of a pair is found through pair_pos, so every
 // product is two loads in a row (index, then data); with U tokens in hand the U indices are in flight together and
 // then the U rows, instead of one such chain after the other.
+// The own tokens' signals are raised as soon as those are stored, by the last workgroup that holds any, so that the reducer runs beside the
+// rest; their rows are stored through the L2 (sc1), as the copy kernel's are, so that a wait for the stores is all that publishing takes.
+// A kernel of its own for the signals behind the whole reduction, and this, us per call: 8192 tokens of Table 5 135.7 and 133.5, 1096 x 2
+// 34 x 300 x 64 73.2 and 70.3.
 __global__ __launch_bounds__(256) void topk_reduce_kernel(const TopkReduceArgs a)
 {
     typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
@@ -358,7 +362,10 @@ __global__ __launch_bounds__(256) void topk_reduce_kernel(const TopkReduceArgs a
     const int own_n = a.own_hi - a.own_lo;
     const int n_tok = a.Z_other ? a.T : own_n;                 // tokens that are reduced: own first, then the others
     const long long total = (long long)((n_tok + U - 1) / U) * n4;
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
+    const long long stride = (long long)gridDim.x * 256, own_total = (long long)((own_n + U - 1) / U) * n4;
+    const __amdgpu_buffer_rsrc_t own_rs = __builtin_amdgcn_make_buffer_rsrc(a.Z_own, 0, a.flag ? (unsigned)own_n * (unsigned)n4 * 16u : 0u, 0x00020000);
+    for (long long base = (long long)blockIdx.x * 256; base < total; base += stride) {
+        const long long i = base + threadIdx.x < total ? base + threadIdx.x : total - 1;      // (the last lane's work twice: the same values)
         const int grp = (int)(i / n4);
         const int j = (int)(i - (long long)grp * n4);
         int tk[U];
@@ -395,8 +402,29 @@ __global__ __launch_bounds__(256) void topk_reduce_kernel(const TopkReduceArgs a
             const int t = tk[u];
             if (t < 0) continue;
             const bool own = t >= a.own_lo && t < a.own_hi;
-            f32x4* dst = own ? (f32x4*)(a.Z_own + (long long)(t - a.own_lo) * a.N) + j : (f32x4*)(a.Z_other + (long long)t * a.N) + j;
-            *dst = z[u];
+            if (own && a.flag) {
+                typedef __attribute__((__vector_size__(16))) unsigned u32x4;
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, z[u]), own_rs, ((unsigned)(t - a.own_lo) * (unsigned)n4 + (unsigned)j) * 16u, 0, 16);
+            } else {
+                f32x4* dst = own ? (f32x4*)(a.Z_own + (long long)(t - a.own_lo) * a.N) + j : (f32x4*)(a.Z_other + (long long)t * a.N) + j;
+                *dst = z[u];
+            }
+        }
+        if (a.flag && base < own_total && base + stride >= own_total) {      // this workgroup's last own tokens
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0);
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (threadIdx.x == 0) {
+                const long long holders = (own_total + 255) / 256;
+                const int prev = __hip_atomic_fetch_add(a.counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (prev == (int)(holders < (long long)gridDim.x ? holders : (long long)gridDim.x) - 1) {
+                    const int epoch = a.epoch_ptr ? __hip_atomic_load(a.epoch_ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : a.epoch;
+                    __hip_atomic_store(a.counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    for (int k = 0; k < a.n_flags; ++k)
+                        __hip_atomic_store(a.flag + k * kSignalStride, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
         }
     }
 }

@@ -1,5 +1,5 @@
-"""GEMM + ReduceScatter and MoE + ReduceScatter on one stream, where the reducer raises the own slot's signals: the same bits as on two
-streams, and every one of the signals raised."""
+"""GEMM + ReduceScatter and MoE + ReduceScatter on one stream, where the reducer raises the own slot's signals, and on two, where the GEMM or
+the top-k reduction does: the same bits, and every one of the signals raised."""
 import numpy as np
 import pytest
 import torch
@@ -29,7 +29,7 @@ def _both(W, rank, chunks, Ms, N, call, reserve=lambda ctx: None):
         ctx.set_rs_chunks(chunks)
         reserve(ctx)
         ps, cs = ctx.streams()
-        for a, b in ((ps, cs), (cs, cs), (cs, cs)):
+        for a, b in ((ps, cs), (ps, cs), (cs, cs), (cs, cs)):
             slots = [torch.full((Ms, N), float("nan"), device="cuda") if w == rank else peers[w] for w in range(W)]
             R = torch.full((Ms, N), float("nan"), device="cuda")
             agg.signal_reset(ctx)
@@ -66,7 +66,8 @@ def test_gemm_rs(W, rank, chunks, Ms, N, K, other):
     _both(W, rank, chunks, Ms, N, lambda ctx, slots, R, a, b: agg.gemm_rs(ctx, W * Ms, N, K, A, K, B, K, agg.B_NK, slots, P, R, N, agg.F32, a, b))
 
 
-@pytest.mark.parametrize("W,rank,chunks,Ms,N,K,E,topk", [(2, 1, 1, 3, 100, 64, 4, 2), (4, 0, 2, 16, 128, 192, 8, 1), (8, 3, 1, 300, 512, 64, 16, 3)])
+@pytest.mark.parametrize("W,rank,chunks,Ms,N,K,E,topk", [(2, 1, 1, 3, 100, 64, 4, 2), (4, 0, 2, 16, 128, 192, 8, 1), (8, 3, 1, 300, 512, 64, 16, 3),
+                                                       (2, 0, 4, 5000, 1024, 64, 4, 1)])       # the last: several own blocks per workgroup of the reduction
 @pytest.mark.parametrize("other", [False, True])
 def test_moe_rs(W, rank, chunks, Ms, N, K, E, topk, other):
     g = torch.Generator(device="cuda").manual_seed(4)
