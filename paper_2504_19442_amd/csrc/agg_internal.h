@@ -106,9 +106,7 @@ hipError_t launch_gemm_grouped(const GemmParams& p, int cfg, int grid, hipStream
 
 hipError_t launch_gemm(const GemmParams& p, int cfg, int grid, hipStream_t stream);
 
-struct ProducerArgs {
-    const void* src[kMaxWorld];   // src[j] = local buffer of the j-th shard to arrive
-    int rank_of[kMaxWorld];       // its rank (destination slot in T)
+struct ProducerCommon {
     int n_jobs;
     char* T;
     long long shard_bytes;
@@ -122,6 +120,12 @@ struct ProducerArgs {
     int link_wgs;                 // full-mesh mode: workgroups per link (set by launch_producer_links)
     double ticks_per_byte;        // full-mesh mode: wall-clock ticks a link takes per byte (0 = not paced)
 };
+template <int JOBS>
+struct ProducerJobs : ProducerCommon {
+    const void* src[JOBS];        // src[j] = local buffer of the j-th shard to arrive
+    int rank_of[JOBS];            // its rank (destination slot in T)
+};
+using ProducerArgs = ProducerJobs<kMaxWorld>;
 hipError_t launch_producer(const ProducerArgs& a, int n_workgroups, int threads, hipStream_t stream);
 hipError_t launch_producer_links(const ProducerArgs& a, int n_workgroups, hipStream_t stream);
 hipError_t launch_signal_set(int* flag, int value, const int* value_ptr, hipStream_t stream);

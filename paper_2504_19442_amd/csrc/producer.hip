@@ -4,6 +4,8 @@
 // registers, so its waves fit beside the consumer's on any CU (Section 3.8, resource partition).
 #include "agg_internal.h"
 
+#include <type_traits>
+
 // Cache policy bits of the buffer instructions below, in the gfx940 / gfx950 encoding of the `aux` operand:
 // 2 = nt (streaming) on the loads, 16 = sc1 (agent scope: written through this XCD's L2) on the stores.  The
 // publication of a chunk rests on three properties of this hardware, not on the language's memory model:
@@ -36,8 +38,9 @@ typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 // (64 are left), four 23.  Four and eight, us alone: 8 x 16 MiB 43.0 and 42.6, by one-wave workgroups 90.9 and 61.5, 4 x 2 MiB 6.9 and
 // 6.5, slices of 16 KiB, which four cover, 3.30 and 3.44.  Launches back to back, both in one kernel that looks at the slice, and this: 8 x
 // 16 KiB 3.05 and 2.96, 8 x 256 KiB 3.87 and 3.79, 3 x 1.3 MB 4.76 and 4.70.
-template <unsigned U>
-__global__ __launch_bounds__(256) void producer_kernel(const ProducerArgs a)
+// JOBS: what the launch's arguments have room for (launch_producer).
+template <unsigned U, int JOBS>
+__global__ __launch_bounds__(256) void producer_kernel(const ProducerJobs<JOBS> a)
 {
     const int tid = threadIdx.x;
     const unsigned span = blockDim.x * 16u;         // bytes one load instruction of the workgroup covers
@@ -178,9 +181,22 @@ hipError_t launch_producer(const ProducerArgs& a_in, int n_workgroups, int threa
     a.team = (int)team;
     // a slice that four loads per lane cover gains nothing from eight
     const long long slice = (a.chunk_bytes / 16 + team - 1) / team * 16;
-    if (slice <= 4ll * 16 * threads) hipLaunchKernelGGL(producer_kernel<4>, dim3(n_workgroups), dim3(threads), 0, stream, a);
-    else hipLaunchKernelGGL(producer_kernel<8>, dim3(n_workgroups), dim3(threads), 0, stream, a);
-    return hipGetLastError();
+    const bool four = slice <= 4ll * 16 * threads;
+    auto launch = [&](auto jobs_c) {
+        constexpr int JOBS = decltype(jobs_c)::value;
+        ProducerJobs<JOBS> j;
+        static_cast<ProducerCommon&>(j) = a;
+        for (int k = 0; k < JOBS; ++k) {
+            j.src[k] = a.src[k];
+            j.rank_of[k] = a.rank_of[k];
+        }
+        if (four) hipLaunchKernelGGL((producer_kernel<4, JOBS>), dim3(n_workgroups), dim3(threads), 0, stream, j);
+        else hipLaunchKernelGGL((producer_kernel<8, JOBS>), dim3(n_workgroups), dim3(threads), 0, stream, j);
+        return hipGetLastError();
+    };
+    // The arguments travel with every launch; those for eight shards are a fifth of those for any world.  Always the
+    // latter, and this, us per call that the host's launches bound: 16 x 3584 x 4096 13.0 and 12.5, 48 x 1768 x 1920 13.0 and 12.6.
+    return a.n_jobs <= 8 ? launch(std::integral_constant<int, 8>{}) : launch(std::integral_constant<int, kMaxWorld>{});
 }
 
 // All jobs of `a` are links that run side by side; the grid is shared out evenly among them.
