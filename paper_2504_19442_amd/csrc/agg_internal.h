@@ -135,8 +135,7 @@ hipError_t launch_signal_probe(const int* flag, int value, long long ticks, int*
 hipError_t launch_transpose_kn(const uint16_t* B_kn, long long ldb, int K, int N, uint16_t* B_nk, hipStream_t stream);
 hipError_t launch_mfma_ceiling(float* sink, int grid, int iters, int constant_operands, hipStream_t stream);
 
-struct ReduceArgs {
-    const float* slot[kMaxWorld];
+struct ReduceCommon {
     int W;
     long long n_vec4;             // number of float4 elements
     long long row_vec4;           // float4 per row (N / 4) when ldr != N, else 0
@@ -154,6 +153,11 @@ struct ReduceArgs {
     long long wait_ticks;
     int* err;
 };
+template <int SLOTS>
+struct ReduceSlots : ReduceCommon {
+    const float* slot[SLOTS];
+};
+using ReduceArgs = ReduceSlots<kMaxWorld>;
 // The process-wide table of tuned configurations: the entry of a problem whose B has layout b_layout; and the context's settings from what
 // it holds for a problem, the order and the producer's size from the entry of `layout` where there are two.
 void tune_table_put(int b_layout, int W, int M, int N, int K, const agg_tune_result& r);

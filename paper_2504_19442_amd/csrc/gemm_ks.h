@@ -61,13 +61,14 @@ struct KsParams {
     unsigned a_bytes;
 };
 
-// KS_SLICED: as in GemmParams
+// KS_SLICED: as in GemmParams, for up to WORLD slices (every launch carries them)
+template <int WORLD>
 struct KsSlices {
     int M, tiles_n, slice_rows, slice_chunks, chunk_rows, ldc_slice;
     unsigned slice_mul;
     int* slice_ctr;
-    void* slice_dst[kMaxWorld];
-    int* slice_flag[kMaxWorld];
+    void* slice_dst[WORLD];
+    int* slice_flag[WORLD];
 };
 struct KsNoSlices {};
 
@@ -183,9 +184,9 @@ __device__ __forceinline__ void ks_fetch_params(const KsParams& p)
 }
 
 // Private rings.
-template <int BM, int BN, int S, int NST, KsKind KIND>
+template <int BM, int BN, int S, int NST, KsKind KIND, class SL>
 __global__ __launch_bounds__(S * 64)
-void gemm_ks_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED, KsSlices, KsNoSlices> sl)
+void gemm_ks_kernel(const KsParams p, const SL sl)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using C_ = KsCfg<BM, BN, S, NST>;
@@ -361,9 +362,9 @@ struct KmCfg {
 };
 
 // STREAM ([K][N] only): B's loads carry the streaming hint.
-template <int BM, int BN, int NW, int NST, KsKind KIND, bool KN = false, int WM = 1, bool STREAM = false>
+template <int BM, int BN, int NW, int NST, KsKind KIND, class SL, bool KN = false, int WM = 1, bool STREAM = false>
 __global__ __launch_bounds__(128 * NW)
-void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED, KsSlices, KsNoSlices> sl)
+void gemm_km_kernel(const KsParams p, const SL sl)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using C_ = KmCfg<BM, BN, NW, NST, WM>;
@@ -582,16 +583,15 @@ void gemm_km_kernel(const KsParams p, const std::conditional_t<KIND == KS_SLICED
 }
 
 // SHARED: gemm_km_kernel with X = NW, else gemm_ks_kernel with X = S.
-template <bool SHARED, int BM, int BN, int X, int NST, KsKind KIND, bool KN = false, int WM = 1>
-static hipError_t launch_ks_kind(const KsParams& p, const std::conditional_t<KIND == KS_SLICED, KsSlices, KsNoSlices>& sl,
-                                 hipStream_t stream)
+template <bool SHARED, int BM, int BN, int X, int NST, KsKind KIND, bool KN = false, int WM = 1, class SL>
+static hipError_t launch_ks_kind(const KsParams& p, const SL& sl, hipStream_t stream)
 {
     using C_ = std::conditional_t<SHARED, KmCfg<BM, BN, X, NST, WM>, KsCfg<BM, BN, X, NST>>;
-    void (*kernel)(const KsParams, const std::conditional_t<KIND == KS_SLICED, KsSlices, KsNoSlices>);
+    void (*kernel)(const KsParams, const SL);
     constexpr bool BY_HINT = SHARED && KN;             // an instance without the streaming hint and one with it
-    if constexpr (BY_HINT) kernel = p.b_streams ? gemm_km_kernel<BM, BN, X, NST, KIND, KN, WM, true> : gemm_km_kernel<BM, BN, X, NST, KIND, KN, WM, false>;
-    else if constexpr (SHARED) kernel = gemm_km_kernel<BM, BN, X, NST, KIND, KN, WM>;
-    else kernel = gemm_ks_kernel<BM, BN, X, NST, KIND>;
+    if constexpr (BY_HINT) kernel = p.b_streams ? gemm_km_kernel<BM, BN, X, NST, KIND, SL, KN, WM, true> : gemm_km_kernel<BM, BN, X, NST, KIND, SL, KN, WM, false>;
+    else if constexpr (SHARED) kernel = gemm_km_kernel<BM, BN, X, NST, KIND, SL, KN, WM>;
+    else kernel = gemm_ks_kernel<BM, BN, X, NST, KIND, SL>;
     constexpr int threads = SHARED ? 128 * X : 64 * X;
     static bool attr_set[2] = {false, false};
     bool& set = attr_set[BY_HINT && p.b_streams];
@@ -638,12 +638,14 @@ static hipError_t launch_ks(const GemmParams& g, bool grouped, int grid, hipStre
     }
     if constexpr ((FORMS & KS_DENSE) != 0) {
         if (g.n_slices == 0) return launch_ks_kind<SHARED, BM, BN, X, NST, KS_PLAIN, KN, WM>(p, KsNoSlices{}, stream);
-        KsSlices sl{};
-        sl.M = g.M; sl.tiles_n = g.tiles_n; sl.slice_rows = g.slice_rows; sl.slice_chunks = g.slice_chunks;
-        sl.chunk_rows = g.chunk_rows; sl.ldc_slice = (int)g.ldc_slice; sl.slice_mul = div_mul(g.slice_rows);
-        sl.slice_ctr = g.slice_ctr;
-        for (int w = 0; w < g.n_slices; ++w) { sl.slice_dst[w] = g.slice_dst[w]; sl.slice_flag[w] = g.slice_flag[w]; }
-        return launch_ks_kind<SHARED, BM, BN, X, NST, KS_SLICED, KN, WM>(p, sl, stream);
+        auto launch = [&](auto sl) {
+            sl.M = g.M; sl.tiles_n = g.tiles_n; sl.slice_rows = g.slice_rows; sl.slice_chunks = g.slice_chunks;
+            sl.chunk_rows = g.chunk_rows; sl.ldc_slice = (int)g.ldc_slice; sl.slice_mul = div_mul(g.slice_rows);
+            sl.slice_ctr = g.slice_ctr;
+            for (int w = 0; w < g.n_slices; ++w) { sl.slice_dst[w] = g.slice_dst[w]; sl.slice_flag[w] = g.slice_flag[w]; }
+            return launch_ks_kind<SHARED, BM, BN, X, NST, KS_SLICED, KN, WM>(p, sl, stream);
+        };
+        return g.n_slices <= 8 ? launch(KsSlices<8>{}) : launch(KsSlices<kMaxWorld>{});
     }
     return hipErrorInvalidValue;
 }

@@ -26,7 +26,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 // Wave 0 of a workgroup waits for the n signals f(0) .. f(n - 1), one lane each (64 at a time): they are looked at side by
 // side, each look is a trip to memory.  f < 0: nothing to wait for.  False in the lanes that gave up.
 template <class F>
-__device__ inline bool wait_signals(const ReduceArgs& a, int n, int epoch, int lane, F&& f)
+__device__ inline bool wait_signals(const ReduceCommon& a, int n, int epoch, int lane, F&& f)
 {
     bool ok = true;
     for (int k = lane; k < n; k += 64) {
@@ -47,7 +47,7 @@ __device__ inline bool wait_signals(const ReduceArgs& a, int n, int epoch, int l
 }
 
 template <class I>      // I: an integer type that holds the number of float4
-__device__ inline void store_out(const ReduceArgs& a, I i, f32x4 v)
+__device__ inline void store_out(const ReduceCommon& a, I i, f32x4 v)
 {
     long long off;
     if (a.row_vec4) {
@@ -70,7 +70,7 @@ __device__ inline void store_out(const ReduceArgs& a, I i, f32x4 v)
 // flight together); WT == 0: any world size.
 // NT: the slots are read past the caches (launch_reduce).
 template <int WT, int RU, bool NT>   // RU = float4 per lane per slot and block
-__global__ __launch_bounds__(256, 8) void reduce_kernel(const ReduceArgs a)
+__global__ __launch_bounds__(256, 8) void reduce_kernel(const ReduceSlots<WT ? 8 : kMaxWorld> a)
 {
     const int tid = threadIdx.x;
     const int W = WT > 0 ? WT : a.W;
@@ -233,11 +233,16 @@ template <bool NT>
 static void launch_reduce_nt(const ReduceArgs& a, int n_workgroups, hipStream_t stream)
 {
     const dim3 grid(n_workgroups), wg(256);
+    // (arguments for eight slots where there are no more: every launch carries them.  Always for 64, here and in gemm_ks.h, and this, us per
+    // call that the host's launches bound: 17.3 and 16.5, 64 x 8192 x 3584 on one stream 20.6 and 20.5)
+    ReduceSlots<8> e;
+    static_cast<ReduceCommon&>(e) = a;
+    for (int w = 0; w < 8; ++w) e.slot[w] = a.slot[w];
     switch (a.W) {
-        case 8: hipLaunchKernelGGL((reduce_kernel<8, 1, NT>), grid, wg, 0, stream, a); break;
-        case 4: hipLaunchKernelGGL((reduce_kernel<4, 2, NT>), grid, wg, 0, stream, a); break;
-        case 3: hipLaunchKernelGGL((reduce_kernel<3, 3, NT>), grid, wg, 0, stream, a); break;
-        case 2: hipLaunchKernelGGL((reduce_kernel<2, 4, NT>), grid, wg, 0, stream, a); break;
+        case 8: hipLaunchKernelGGL((reduce_kernel<8, 1, NT>), grid, wg, 0, stream, e); break;
+        case 4: hipLaunchKernelGGL((reduce_kernel<4, 2, NT>), grid, wg, 0, stream, e); break;
+        case 3: hipLaunchKernelGGL((reduce_kernel<3, 3, NT>), grid, wg, 0, stream, e); break;
+        case 2: hipLaunchKernelGGL((reduce_kernel<2, 4, NT>), grid, wg, 0, stream, e); break;
         default: hipLaunchKernelGGL((reduce_kernel<0, 2, NT>), grid, wg, 0, stream, a); break;
     }
 }
