@@ -21,3 +21,15 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode != 0
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_no_compiler_is_started_once_tests_run():
+    """A GPU test must not start a process: what the tests load is compiled when the session begins."""
+    code = ("import subprocess, conftest\n"
+            "conftest.pytest_configure(type('Config', (), {'addinivalue_line': lambda *a: None})())\n"
+            "def refuse(*a, **k): raise AssertionError('a process was started')\n"
+            "subprocess.Popen = subprocess.run = refuse\n"
+            "import host_rules, oracle\n"
+            "host_rules.kn_tile(256, 1024, 3584, 4096), host_rules.dense_ks_tiles(), oracle.lib()\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=os.path.join(ROOT, "tests"), capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
