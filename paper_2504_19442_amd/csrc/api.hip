@@ -182,7 +182,8 @@ int symm_alloc(agg_ctx** out, int world_size, int rank, size_t shard_bytes, int 
     hipDeviceProp_t prop;
     int khz = 0;
     const size_t sig_bytes = (size_t)n_signals * kSignalStride * sizeof(int);
-    const size_t ctr_bytes = ((size_t)n_signals + kMaxWorld * kMaxRsChunks + 32) * sizeof(int);   // producer counters, then one per chunk of a GEMM-RS slice
+    // producer counters, then one per chunk of a GEMM-RS slice, then the top-k reduction's
+    const size_t ctr_bytes = ((size_t)n_signals + kMaxWorld * kMaxRsChunks + 32) * sizeof(int);
     if ((rc = hip_fail(hipGetDevice(&c->device))) != AGG_OK) goto fail;
     if ((rc = hip_fail(hipGetDeviceProperties(&prop, c->device))) != AGG_OK) goto fail;
     if ((rc = hip_fail(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, c->device))) != AGG_OK) goto fail;
@@ -1093,7 +1094,7 @@ int moe_rs(agg_ctx* c, int Ttok, int topk, int E, int N, int Kl, const void* H, 
         t.n_flags = c->rs_chunks;
         t.epoch = c->epoch;
         t.epoch_ptr = c->device_epoch ? c->epoch_word : nullptr;
-        t.counter = c->counters + c->n_signals;
+        t.counter = c->counters + c->n_signals + kMaxWorld * kMaxRsChunks;      // (a gemm_rs_scatter may run beside this call)
     }
     if ((rc = hip_fail(launch_topk_reduce(t, c->num_cus * 4, (hipStream_t)gemm_stream))) != AGG_OK) return rc;
     if (one_stream) return reduce_impl(c, Tr, N, slots, R, ldr, r_dtype, 0, reduce_stream, false, true);

@@ -81,3 +81,54 @@ def test_moe_rs(W, rank, chunks, Ms, N, K, E, topk, other):
     seg = torch.empty(E + 1, device="cuda", dtype=torch.int32)
     _both(W, rank, chunks, Ms, N, lambda ctx, slots, R, a, b: agg.moe_rs(ctx, T, topk, E, N, K, H, B, ids, gate, Y, tok, seg, pos, slots, Z, R, N,
                                                                          agg.F32, a, b), lambda ctx: agg.agg_reserve_moe(ctx, T, topk, E, N))
+
+
+def test_gemm_rs_scatter_beside_moe_rs():
+    """Both count what has been stored before they raise a signal: on one context at the same time, each counts its own."""
+    W, Ms, N, K, E, topk = 2, 512, 1024, 64, 4, 2
+    T = W * Ms
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def ints(*shape):
+        return torch.randint(-2, 3, shape, device="cuda", generator=g, dtype=torch.int8).to(torch.bfloat16)
+
+    A, B, H, B2 = ints(T, K), ints(N, K), ints(T * topk, K), ints(E, N, K)
+    ids = torch.rand((T, E), device="cuda", generator=g).argsort(dim=1)[:, :topk].to(torch.int32).contiguous()
+    gate = torch.ones((T, topk), device="cuda")
+    flat = ids.reshape(-1).long()
+    order = torch.argsort(flat, stable=True)
+    rows = torch.empty((T * topk, N), device="cuda")
+    for e in range(E):
+        at = flat[order] == e
+        rows[at] = H[at].float() @ B2[e].float().t()
+    where = torch.empty_like(order)
+    where[order] = torch.arange(T * topk, device="cuda")
+    peer = torch.randint(-8, 9, (Ms, N), device="cuda", generator=g).float()
+    want_own, want_P = rows[where].view(T, topk, N).sum(dim=1)[:Ms], A.float() @ B.float().t()
+    ctx = agg.symm_alloc(W, 0, 16, W * 4)
+    try:
+        agg.agg_reserve_moe(ctx, T, topk, E, N)
+        ps, cs = ctx.streams()
+        third = torch.cuda.Stream()
+        Y, Z, R = (torch.empty((n, N), device="cuda") for n in (T * topk, T, Ms))
+        tok, pos = (torch.empty(T * topk, device="cuda", dtype=torch.int32) for _ in range(2))
+        seg = torch.empty(E + 1, device="cuda", dtype=torch.int32)
+        own = torch.empty((Ms, N), device="cuda")
+        for chunks in (1, 4) * 4:
+            ctx.set_rs_chunks(chunks)
+            P = [torch.full((Ms, N), float("nan"), device="cuda") for _ in range(W)]
+            raised = torch.zeros((W, chunks, agg.SIGNAL_STRIDE), device="cuda", dtype=torch.int32)
+            own.fill_(float("nan"))
+            agg.signal_reset(ctx)
+            torch.cuda.synchronize()
+            for c in range(chunks):
+                agg.signal_set(ctx, 4 + c, cs)
+            agg.gemm_rs_scatter(ctx, T, N, K, A, K, B, K, agg.B_NK, P, None, [raised[w].data_ptr() for w in range(W)], 0, third)
+            agg.moe_rs(ctx, T, topk, E, N, K, H, B2, ids, gate, Y, tok, seg, pos, [own, peer], Z, R, N, agg.F32, ps, cs)
+            agg.gemm_rs_scatter(ctx, T, N, K, A, K, B, K, agg.B_NK, P, None, [raised[w].data_ptr() for w in range(W)], 0, third)
+            torch.cuda.synchronize()
+            assert agg.agg_status(ctx) == agg.OK
+            assert torch.equal(own, want_own) and torch.equal(R, want_own + peer) and torch.equal(torch.cat(P), want_P)
+            assert bool((raised[:, :, 0] == ctx.epoch).all())
+    finally:
+        ctx.free()
