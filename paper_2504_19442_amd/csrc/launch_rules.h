@@ -244,16 +244,20 @@ inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, b
     return pipe_cost < best_cost ? best_pipe : best_that_fits;
 }
 
+// Worlds and slots (below 2 GiB, for 32-bit offsets) of reduce_flow_kernel, whose loads never stop.  Above, two slots of 2 GiB take 1157 us
+// with the kernel for any world, eight 3790.
+inline bool reduce_flows(int W, long long n_vec4) { return (W == 8 || (W >= 2 && W <= 4)) && n_vec4 < (1ll << 27); }
+
 // Workgroups of a reducer launch over n_vec4 float4 whose caller leaves the size to the library.  Persistent, each walking
 // many blocks of 256 (one acquire per workgroup, not per block).
-//   W = 2, 3, 4, 8 (kernels whose loads never stop, 50 to 58 registers): what counts is that few streams are in flight, seven workgroups
+//   Loads that never stop (58 to 64 registers): what counts is that few streams are in flight, seven workgroups
 //     per eight CUs, three per four with eight slots.  That leaves room for any GEMM of this library: one wave of at most
 //     64 registers per SIMD beside 448 of 512.  Eight slots and at most four blocks per CU: too little to walk, two per CU (one beside a GEMM)
 //     end sooner (200 x 4000, the same slots again and again: 12.0 us with one per CU, 11.8 with two).
 //     128 / 192 / 208 / 224 / 240 / 256 / 512 workgroups, us per call, slots not touched lately: eight slots of 1024 x 8192
 //     60.7 / 52.9 / 52.9 / 53.4 / 54.9 / 58.6 / 59.0, of 500 x 4096 15.0 / 16.0 / . / . / . / 16.9 / 18.2; four of 1000 x 8000 . / 33.2 / 32.5 /
 //     32.5 / 32.8 / 34.4 / 37.3; three of 1024 x 8192 34.0 / 27.8 / . / 26.6 / . / 25.9 / .; two of 1000 x 8000 . / 19.0 / 18.7 / 18.7 / 18.7 / . / 20.4.
-//   Other worlds (58 registers): three per two CUs, beside a GEMM one per CU.  The reducer may have to wait for a GEMM that is
+//   Other worlds, larger slots (57 registers): three per two CUs, beside a GEMM one per CU.  The reducer may have to wait for a GEMM that is
 //     launched after it: half of the CUs keep room for any GEMM workgroup of this library, and three such reducers leave all CUs
 //     room for the K-split ones.  At 1 / 1.25 / 1.5 / 2 per CU six slots of 1024 x 8192 take 46.2 / 48.4 / 46.4 / 46.3, sixteen
 //     95.5 / 109 / 104 / 99.1.
@@ -261,8 +265,10 @@ inline int reduce_workgroups(int W, int num_cus, long long n_vec4, bool beside_g
 {
     const long long need = (n_vec4 + 255) / 256;
     long long want = beside_gemm ? num_cus : num_cus * 3ll / 2;
-    if (W == 8) want = need > 4ll * num_cus ? num_cus * 3ll / 4 : beside_gemm ? num_cus : num_cus * 2ll;
-    else if (W >= 2 && W <= 4) want = num_cus * 7ll / 8;
+    if (reduce_flows(W, n_vec4)) {
+        if (W == 8) want = need > 4ll * num_cus ? num_cus * 3ll / 4 : beside_gemm ? num_cus : num_cus * 2ll;
+        else want = num_cus * 7ll / 8;
+    }
     const long long n = need < want ? need : want;
     return n < 1 ? 1 : (int)n;
 }

@@ -72,6 +72,101 @@ def test_reducer_loop_lengths_bit_exact(W, n_vec4, workgroups):
         ctx.free()
 
 
+# Row chunks: shorter than a block, not whole blocks, several laps long; the last chunks' signals raised while the reducer waits for them
+@pytest.mark.parametrize("W", [2, 3, 4, 8])
+@pytest.mark.parametrize("rows,chunks,workgroups", [(16, 16, 1), (300, 3, 1), (256 * 9, 4, 2), (256 * 41 - 5, 7, 3), (256 * 300, 16, 0)])
+def test_reducer_chunk_lengths_bit_exact(W, rows, chunks, workgroups):
+    rows = rows // chunks * chunks
+    g = torch.Generator(device="cuda").manual_seed(7600 + W)
+    data = [torch.randn((rows, 4), device="cuda", generator=g) * 10.0 ** w for w in range(W)]
+    want = torch.zeros((rows, 4), device="cuda")
+    for x in data:
+        want = want + x
+    ctx = agg.symm_alloc(W, 0, 16, W * 16)
+    try:
+        ctx.set_rs_chunks(chunks)
+        ps, cs = ctx.streams()
+        prod = torch.cuda.ExternalStream(ps)
+        for late in range(min(chunks, 3)):               # chunks that arrive behind the launch
+            slots = [torch.full((rows, 4), float("nan"), device="cuda") for _ in range(W)]
+            R = torch.full((rows, 8), 3.0, device="cuda")
+            agg.signal_reset(ctx)
+            torch.cuda.synchronize()
+
+            def deliver(c):
+                part = slice(c * (rows // chunks), (c + 1) * (rows // chunks))
+                for w in range(W):
+                    with torch.cuda.stream(prod):
+                        slots[w][part].copy_(data[w][part])
+                    agg.signal_set(ctx, w * 16 + c, prod)
+
+            for c in range(chunks - late):
+                deliver(c)
+            prod.synchronize()
+            agg.rs_reduce(ctx, rows, 4, slots, R, 8, agg.F32, workgroups, cs)
+            for c in range(chunks - late, chunks):
+                deliver(c)
+            torch.cuda.synchronize()
+            assert agg.agg_status(ctx) == agg.OK
+            assert torch.equal(R[:, :4].contiguous().view(torch.int32), want.view(torch.int32)) and bool((R[:, 4:] == 3.0).all())
+    finally:
+        ctx.free()
+
+
+@pytest.mark.parametrize("W", [2, 8])
+def test_reducer_of_chunked_slots_takes_the_time_of_whole_ones(W):
+    # 1024 x 8192, us with one signal per slot and with four: 21.5 and 21.5, 51.7 and 52.5 (with a loop that drains at every block 41.5, 84.4)
+    Ms, N = 1024, 8192
+    slots = [[torch.zeros((Ms, N), device="cuda") for _ in range(W)] for _ in range(8 // W + 1)]
+    R = torch.empty((Ms, N), device="cuda")
+    ctx = agg.symm_alloc(W, 0, 16, W * 4)
+    try:
+        agg.signal_reset(ctx)
+        for k in range(W * 4):
+            agg.signal_set(ctx, k, None)
+
+        def median_us(chunks):
+            ctx.set_rs_chunks(chunks)
+            times = []
+            for _ in range(9):
+                a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                a.record()
+                for k in range(20):
+                    agg.rs_reduce(ctx, Ms, N, slots[k % len(slots)], R, N, agg.F32, 0, None)
+                b.record()
+                b.synchronize()
+                times.append(a.elapsed_time(b) * 50.0)
+            return sorted(times)[4]
+
+        median_us(1)
+        whole, four = median_us(1), median_us(4)
+        assert agg.agg_status(ctx) == agg.OK
+        assert four <= 1.3 * whole, (whole, four)
+    finally:
+        ctx.free()
+
+
+@pytest.mark.parametrize("W,n_vec4", [(2, (1 << 27) - 1), (2, 1 << 27), (3, (1 << 27) + 300)])
+def test_reducer_on_both_sides_of_slots_of_2_gib_bit_exact(W, n_vec4):
+    slots = [torch.empty((n_vec4, 4), device="cuda") for _ in range(W)]
+    for w, x in enumerate(slots):
+        x.view(-1).copy_(torch.arange(n_vec4 * 4, device="cuda", dtype=torch.int32).mul_(w + 1).bitwise_and_(0xffff))       # whole numbers: exact
+    R = torch.full((n_vec4, 4), float("nan"), device="cuda")
+    ctx = agg.symm_alloc(W, 0, 16, W)
+    try:
+        agg.signal_reset(ctx)
+        for w in range(W):
+            agg.signal_set(ctx, w, None)
+        agg.rs_reduce(ctx, n_vec4, 4, slots, R, 4, agg.F32, 0, None)
+        torch.cuda.synchronize()
+        assert agg.agg_status(ctx) == agg.OK
+        for x in slots:
+            R -= x
+        assert bool((R == 0.0).all())
+    finally:
+        ctx.free()
+
+
 @pytest.mark.parametrize("W,Ms,N,ldr", [(8, 1024, 8192, 8192), (16, 1024, 4100, 4104), (3, 2048, 11000, 11000), (2, 4096, 8188, 8188)])
 def test_reducer_slots_beyond_the_memory_side_cache_bit_exact(W, Ms, N, ldr):
     # 256 MB of slots and more (the last: just below); the reference adds the slots in order, one fp32 rounding each
