@@ -180,13 +180,12 @@ int ag_gemm(agg_ctx* ctx, int M, int N, int K,
  * A waiting reducer occupies compute units: whatever raises the signals must be able to run beside it
  * (copies, signal_set and this library's producer can; a kernel that needs every register of a CU cannot).  This library's
  * GEMMs that are launched after a waiting reducer, on another stream, find room as follows.  The small tiles of the automatic
- * choice: on every CU.  The tile shapes of agg_set_tile_config: with n_workgroups = 0 on half of the CUs, with n_workgroups of at
- * most the number of CUs on all of them -- but in a world of eight, whose reducer takes more registers, on none: launch the GEMM
- * first there.
+ * choice: on every CU.  The tile shapes of agg_set_tile_config: with n_workgroups of at most the number of CUs on all of them, also with
+ * n_workgroups = 0 in worlds of two, three, four and eight with slots below 2 GiB; with n_workgroups = 0 in other cases on half of the CUs.
  * slots: HOST array of W device pointers to fp32 [Ms, N] row-major (leading dimension N).
  * R: [Ms, N] of r_dtype, leading dimension ldr.  Ms * N must be a multiple of 4; slots 16-byte aligned.
- * n_workgroups: size of the (persistent) grid, 0 = the library's choice (three workgroups per two compute units; two per compute
- * unit in a world of eight).
+ * n_workgroups: size of the (persistent) grid, 0 = the library's choice (at most one workgroup per compute unit in worlds of two, three,
+ * four and eight with slots below 2 GiB, else three per two).
  * With agg_set_rs_chunks(k > 1) the wait is per row chunk of a slot instead (see there).
  */
 int rs_reduce(agg_ctx* ctx, int Ms, int N, const float* const* slots,

@@ -249,26 +249,23 @@ inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, b
 inline bool reduce_flows(int W, long long n_vec4) { return (W == 8 || (W >= 2 && W <= 4)) && n_vec4 < (1ll << 27); }
 
 // Workgroups of a reducer launch over n_vec4 float4 whose caller leaves the size to the library.  Persistent, each walking
-// many blocks of 256 (one acquire per workgroup, not per block).
-//   Loads that never stop (58 to 64 registers): what counts is that few streams are in flight, seven workgroups
-//     per eight CUs, three per four with eight slots.  That leaves room for any GEMM of this library: one wave of at most
-//     64 registers per SIMD beside 448 of 512.  Eight slots and at most four blocks per CU: too little to walk, two per CU (one beside a GEMM)
-//     end sooner (200 x 4000, the same slots again and again: 12.0 us with one per CU, 11.8 with two).
+// many blocks of 256 (one acquire per workgroup, not per block).  A reducer may have to wait for a GEMM that is launched after it, which
+// has to find room: of 512 registers per SIMD lane a workgroup of any of the reducers takes 64, a large GEMM tile 448, a K-split tile up
+// to 384 (128x128 with a [K][N] operand; 288 and less the others).  A GEMM that finds none runs into the time limit of the reducer's wait.
+//   Loads that never stop: what counts is that few streams are in flight, seven workgroups per eight CUs, three per four with eight
+//     slots.  Room for any GEMM on every CU.
 //     128 / 192 / 208 / 224 / 240 / 256 / 512 workgroups, us per call, slots not touched lately: eight slots of 1024 x 8192
-//     60.7 / 52.9 / 52.9 / 53.4 / 54.9 / 58.6 / 59.0, of 500 x 4096 15.0 / 16.0 / . / . / . / 16.9 / 18.2; four of 1000 x 8000 . / 33.2 / 32.5 /
-//     32.5 / 32.8 / 34.4 / 37.3; three of 1024 x 8192 34.0 / 27.8 / . / 26.6 / . / 25.9 / .; two of 1000 x 8000 . / 19.0 / 18.7 / 18.7 / 18.7 / . / 20.4.
-//   Other worlds, larger slots (57 registers): three per two CUs, beside a GEMM one per CU.  The reducer may have to wait for a GEMM that is
-//     launched after it: half of the CUs keep room for any GEMM workgroup of this library, and three such reducers leave all CUs
-//     room for the K-split ones.  At 1 / 1.25 / 1.5 / 2 per CU six slots of 1024 x 8192 take 46.2 / 48.4 / 46.4 / 46.3, sixteen
-//     95.5 / 109 / 104 / 99.1.
+//     60.7 / 52.9 / 52.9 / 53.4 / 54.9 / 58.6 / 59.0, of 500 x 4096 15.0 / 16.0 / . / . / . / 16.9 / 18.2, of 200 x 4000 9.4 / 9.2 / . / . / . / 9.5 /
+//     11.3; four of 1000 x 8000 . / 33.2 / 32.5 / 32.5 / 32.8 / 34.4 / 37.3; three of 1024 x 8192 34.0 / 27.8 / . / 26.6 / . / 25.9 / .; two of
+//     1000 x 8000 . / 19.0 / 18.7 / 18.7 / 18.7 / . / 20.4.
+//   Any world: three per two CUs, room for a K-split tile on every CU and for a large one on half of them; beside a GEMM one per CU.  At 1 /
+//     1.25 / 1.5 / 2 per CU six slots of 1024 x 8192 take 46.2 / 48.4 / 46.4 / 46.3, sixteen 95.5 / 109 / 104 / 99.1; at 1 and 1.5 nine of 300 x 2000
+//     10.9 and 9.8, six of 1024 x 8192 in sixteen chunks 64.9 and 56.4, two of 2 GiB 1302 and 1157.
 inline int reduce_workgroups(int W, int num_cus, long long n_vec4, bool beside_gemm)
 {
     const long long need = (n_vec4 + 255) / 256;
     long long want = beside_gemm ? num_cus : num_cus * 3ll / 2;
-    if (reduce_flows(W, n_vec4)) {
-        if (W == 8) want = need > 4ll * num_cus ? num_cus * 3ll / 4 : beside_gemm ? num_cus : num_cus * 2ll;
-        else want = num_cus * 7ll / 8;
-    }
+    if (reduce_flows(W, n_vec4)) want = W == 8 ? num_cus * 3ll / 4 : num_cus * 7ll / 8;
     const long long n = need < want ? need : want;
     return n < 1 ? 1 : (int)n;
 }

@@ -192,11 +192,11 @@ def test_reducer_slots_beyond_the_memory_side_cache_bit_exact(W, Ms, N, ldr):
         ctx.free()
 
 
-@pytest.mark.parametrize("tile,W", [(6, 2), (6, 3), (6, 4), (4, 6)])
+@pytest.mark.parametrize("tile,W", [(6, 2), (6, 3), (6, 4), (4, 6), (6, 8)])
 def test_a_gemm_launched_behind_a_waiting_reducer_feeds_it(tile, W):
     """The reducer is launched first, with the library's own grid, and waits for all slots; the GEMM that produces them comes
     afterwards on another stream, on large tiles, and has to find room."""
-    Ms, N, K = 64 * (12 // W), 8192, 64              # 3072 to 1024 blocks of the reducer: more than two for every CU
+    Ms, N, K = 64 * (12 // W), 8192, 64              # 3072 to 512 blocks of the reducer: two and more for every CU
     g = torch.Generator(device="cuda").manual_seed(7500 + W)
     A = torch.randint(-2, 3, (W * Ms, K), device="cuda", generator=g).to(torch.bfloat16)
     B = torch.randint(-2, 3, (N, K), device="cuda", generator=g).to(torch.bfloat16)

@@ -48,19 +48,21 @@ def test_stages_past_the_end_of_k_load_nothing(KC, rows, tile_rows, ld):
     assert lib().ks_stage_bad_accesses(KC, 64, rows, tile_rows, C.c_uint(ld)) == 0
 
 
-@pytest.mark.parametrize("W", [1, 2, 3, 4, 5, 6, 7, 9, 16, 64])
+@pytest.mark.parametrize("W", [1, 2, 3, 4, 5, 6, 7, 8, 9, 16, 64])
 def test_a_waiting_reducer_leaves_room_for_a_gemm_that_comes_later(W):
-    """Registers of a SIMD lane: 512.  A reducer workgroup takes 64 at most (all worlds but 8), a large GEMM tile's 448, a K-split
-    tile's up to 208.  However many blocks there are, half of the CUs have to keep room for a large tile; three reducers at once (three
-    ranks of four on one GPU) have to leave every CU room for a K-split tile, beside what an even spread puts on it."""
+    """Registers of a SIMD lane: 512.  A reducer workgroup takes 64 at most, a large GEMM tile's 448, a K-split tile's up to 384 (two waves of 192;
+    all but the 128x128 tile of a [K][N] operand up to 288).  However many blocks there are, half of the CUs have to keep room for a large
+    tile and all for a K-split one.  Three reducers at once (three ranks of four on one GPU) have to leave every CU room for a K-split tile of 288, beside
+    what an even spread puts on it; in worlds without an unrolled kernel for one of 192."""
     cus = 256
-    for n_vec4 in (1, 1000, 256 * 256, 131072, 1 << 21, 1 << 25):
+    for n_vec4 in (1, 1000, 256 * 256, 256 * 512, 1 << 18, 1 << 21, 1 << 25, 1 << 27):
         grid = lib().reduce_grid(W, cus, C.c_longlong(n_vec4), 0)
         assert 1 <= grid <= (n_vec4 + 255) // 256
         per_cu = [grid // cus + (i < grid % cus) for i in range(cus)]
         assert sum(512 - 64 * k >= 448 for k in per_cu) >= cus // 2, (W, n_vec4, grid)
+        assert all(512 - 64 * k >= 384 for k in per_cu), (W, n_vec4, grid)
         spread = [3 * grid // cus + (i < 3 * grid % cus) for i in range(cus)]
-        assert all(512 - 56 * k >= 208 for k in spread), (W, n_vec4, grid)
+        assert all(512 - 64 * k >= (288 if W in (2, 3, 4, 8) and n_vec4 < 1 << 27 else 192) for k in spread), (W, n_vec4, grid)
         assert lib().reduce_grid(W, cus, C.c_longlong(n_vec4), 1) <= cus
 
 
