@@ -163,7 +163,7 @@ using ReduceArgs = ReduceSlots<kMaxWorld>;
 void tune_table_put(int b_layout, int W, int M, int N, int K, const agg_tune_result& r);
 int tune_table_apply(agg_ctx* c, int M, int N, int K, int layout);
 constexpr int kKnAsNk = -2;                 // agg_ctx::kn_config
-hipError_t launch_reduce(const ReduceArgs& a, int n_workgroups, hipStream_t stream);
+hipError_t launch_reduce(const ReduceArgs& a, ReduceShape shape, hipStream_t stream);
 
 }  // namespace agg
 

@@ -631,8 +631,9 @@ static int reduce_impl(agg_ctx* c, int Ms, int N, const float* const* slots, voi
     a.epoch_ptr = c->device_epoch ? c->epoch_word : nullptr;
     a.wait_ticks = wait_ticks(c);
     a.err = c->err;
-    const int nwg = n_workgroups > 0 ? n_workgroups : reduce_workgroups(c->W, c->num_cus, a.n_vec4, beside_gemm);
-    return hip_fail(launch_reduce(a, nwg, (hipStream_t)stream));
+    ReduceShape shape = reduce_shape(c->W, c->num_cus, a.n_vec4, beside_gemm);
+    if (n_workgroups > 0) shape.workgroups = n_workgroups;
+    return hip_fail(launch_reduce(a, shape, (hipStream_t)stream));
 }
 
 int rs_reduce(agg_ctx* c, int Ms, int N, const float* const* slots, void* R, int ldr, int r_dtype, int n_workgroups,

@@ -248,26 +248,33 @@ inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, b
 // with the kernel for any world, eight 3790.
 inline bool reduce_flows(int W, long long n_vec4) { return (W == 8 || (W >= 2 && W <= 4)) && n_vec4 < (1ll << 27); }
 
-// Workgroups of a reducer launch over n_vec4 float4 whose caller leaves the size to the library.  Persistent, each walking
-// many blocks of 256 (one acquire per workgroup, not per block).  A reducer may have to wait for a GEMM that is launched after it, which
-// has to find room: of 512 registers per SIMD lane a workgroup of any of the reducers takes 64, a large GEMM tile 448, a K-split tile up
+// Workgroups, and threads of one, of a reducer launch over n_vec4 float4 whose caller leaves the size to the library.  Persistent, each walking
+// many blocks of a float4 per thread (one acquire per workgroup, not per block).  A reducer may have to wait for a GEMM that is launched after it,
+// which has to find room: of 512 registers per SIMD lane a workgroup of any of the reducers takes 64, a large GEMM tile 448, a K-split tile up
 // to 384 (128x128 with a [K][N] operand; 288 and less the others).  A GEMM that finds none runs into the time limit of the reducer's wait.
-//   Loads that never stop: what counts is that few streams are in flight, seven workgroups per eight CUs, three per four with eight
-//     slots.  Room for any GEMM on every CU.
-//     128 / 192 / 208 / 224 / 240 / 256 / 512 workgroups, us per call, slots not touched lately: eight slots of 1024 x 8192
-//     60.7 / 52.9 / 52.9 / 53.4 / 54.9 / 58.6 / 59.0, of 500 x 4096 15.0 / 16.0 / . / . / . / 16.9 / 18.2, of 200 x 4000 9.4 / 9.2 / . / . / . / 9.5 /
-//     11.3; four of 1000 x 8000 . / 33.2 / 32.5 / 32.5 / 32.8 / 34.4 / 37.3; three of 1024 x 8192 34.0 / 27.8 / . / 26.6 / . / 25.9 / .; two of
-//     1000 x 8000 . / 19.0 / 18.7 / 18.7 / 18.7 / . / 20.4.
+//   Loads that never stop: what counts is that few streams are in flight, and beside a GEMM that every CU has the same share of them (the
+//     GEMM's tiles wait for the slowest CU).  One workgroup of three waves per CU; two to four slots with nothing beside them take seven
+//     of four waves per eight CUs.  Room for any GEMM on every CU.
+//     Eight slots of 1024 x 8192, us per call, slots not touched lately, by workgroups of four waves, 128 / 192 / 224 / 256 / 512 of them, and 256 of
+//     three: 60.7 / 52.9 / 53.4 / 58.6 / 59.0 and 50.8; 200 x 4000 9.4 / 9.2 / . / 9.5 / 11.3 and 9.1.  224 of four waves and 256 of three: four of
+//     1024 x 8192 32.1 and 32.4, three 26.9 and 27.5, two 22.1 and 22.8.
+//     Beside the next call's GEMM (8192 x 8192 x 3584 on 8 ranks, calls that do not wait for the one before), us per call: 192 of four waves 388,
+//     256 of three 380, a loop that drains at every block, 256 of four waves, 375; own slice first 391, 380 and 375; in four chunks 393, 387 and 383.
+//     Behind its own GEMM, calls that wait: 421, 417 and 430; 8192 x 8192 x 1024 222, 218 and 233.
 //   Any world: three per two CUs, room for a K-split tile on every CU and for a large one on half of them; beside a GEMM one per CU.  At 1 /
 //     1.25 / 1.5 / 2 per CU six slots of 1024 x 8192 take 46.2 / 48.4 / 46.4 / 46.3, sixteen 95.5 / 109 / 104 / 99.1; at 1 and 1.5 nine of 300 x 2000
 //     10.9 and 9.8, six of 1024 x 8192 in sixteen chunks 64.9 and 56.4, two of 2 GiB 1302 and 1157.
-inline int reduce_workgroups(int W, int num_cus, long long n_vec4, bool beside_gemm)
+struct ReduceShape {
+    int workgroups, threads;
+};
+inline ReduceShape reduce_shape(int W, int num_cus, long long n_vec4, bool beside_gemm)
 {
-    const long long need = (n_vec4 + 255) / 256;
-    long long want = beside_gemm ? num_cus : num_cus * 3ll / 2;
-    if (reduce_flows(W, n_vec4)) want = W == 8 ? num_cus * 3ll / 4 : num_cus * 7ll / 8;
+    const bool flows = reduce_flows(W, n_vec4), three_waves = flows && (W == 8 || beside_gemm);
+    const int threads = three_waves ? 192 : 256;
+    const long long need = (n_vec4 + threads - 1) / threads;
+    const long long want = three_waves || beside_gemm ? num_cus : flows ? num_cus * 7ll / 8 : num_cus * 3ll / 2;
     const long long n = need < want ? need : want;
-    return n < 1 ? 1 : (int)n;
+    return {n < 1 ? 1 : (int)n, threads};
 }
 
 }  // namespace agg

@@ -77,17 +77,17 @@ __device__ inline void raise_own(const ReduceCommon& a, int epoch, int tid)
 template <bool NT>      // NT: the slots are read past the caches (launch_reduce)
 __device__ inline f32x4 load_in(const f32x4* p) { return NT ? __builtin_nontemporal_load(p) : *p; }
 
-// WT slots below 2 GiB, loads never stop.  RU: float4 per lane in flight per slot.
+// WT slots below 2 GiB, loads never stop.  RU: float4 per lane in flight per slot.  THREADS: reduce_shape.
 // A slot that arrives in row chunks: a workgroup walks the rows upwards and looks at the signals again before the first load of a chunk that
 // had not arrived when it last looked, while its loads of the chunk before are still on their way; the reduction of the first
 // chunks runs while the later ones are still being produced.
 // (64 registers, asked for as such: asked for as eight waves per SIMD, the scalars would have to fit too, and spill.)
-template <int WT, int RU, bool NT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(64))) void reduce_flow_kernel(const ReduceSlots<8> a)
+template <int WT, int RU, bool NT, int THREADS>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_num_vgpr(64))) void reduce_flow_kernel(const ReduceSlots<8> a)
 {
     const int tid = threadIdx.x;
     const int epoch = a.epoch_ptr ? __hip_atomic_load(a.epoch_ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : a.epoch;
-    const unsigned stride = gridDim.x * 256u;     // (32-bit offsets: at most 2^16 workgroups)
+    const unsigned stride = gridDim.x * THREADS;     // (32-bit offsets: at most 2^16 workgroups)
     const unsigned count = (unsigned)a.n_vec4;
     const bool chunked = a.chunks > 1;
     raise_own(a, epoch, tid);
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(64))) void redu
         __syncthreads();
         return true;
     };
-    unsigned pos = blockIdx.x * 256u;             // this workgroup's next block
+    unsigned pos = blockIdx.x * THREADS;             // this workgroup's next block
     if (pos >= count) return;
     look(0);
     if (!chunked && seen < WT) {
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(64))) void redu
 #pragma unroll
         for (int u = 1; u < RU; ++u)
             if (p + stride < count) p += stride;
-        const unsigned end = p + 256u < count ? p + 256u : count;
+        const unsigned end = p + THREADS < count ? p + THREADS : count;
         if (end <= ready) return true;
         if (!look((int)((end - 1) / (unsigned)a.chunk_vec4) + 1)) return false;
         arrived();
@@ -305,9 +305,9 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs a)
 // RU: about eight loads in flight per lane.  At most 64 registers each (the second launch bound; 59 in any world): the GEMM's waves leave 64
 // per SIMD lane, so a reducer runs on the same compute units.
 template <bool NT>
-static void launch_reduce_nt(const ReduceArgs& a, int n_workgroups, hipStream_t stream)
+static void launch_reduce_nt(const ReduceArgs& a, ReduceShape shape, hipStream_t stream)
 {
-    const dim3 grid(n_workgroups), wg(256);
+    const dim3 grid(shape.workgroups), wg(shape.threads);
     if (!reduce_flows(a.W, a.n_vec4)) {
         hipLaunchKernelGGL((reduce_kernel<2, NT>), grid, wg, 0, stream, a);
         return;
@@ -317,12 +317,17 @@ static void launch_reduce_nt(const ReduceArgs& a, int n_workgroups, hipStream_t 
     ReduceSlots<8> e;
     static_cast<ReduceCommon&>(e) = a;
     for (int w = 0; w < 8; ++w) e.slot[w] = a.slot[w];
-    switch (a.W) {
-        case 8: hipLaunchKernelGGL((reduce_flow_kernel<8, 1, NT>), grid, wg, 0, stream, e); break;
-        case 4: hipLaunchKernelGGL((reduce_flow_kernel<4, 2, NT>), grid, wg, 0, stream, e); break;
-        case 3: hipLaunchKernelGGL((reduce_flow_kernel<3, 3, NT>), grid, wg, 0, stream, e); break;
-        default: hipLaunchKernelGGL((reduce_flow_kernel<2, 4, NT>), grid, wg, 0, stream, e); break;
-    }
+    auto flow = [&](auto threads_c) {
+        constexpr int T = decltype(threads_c)::value;
+        switch (a.W) {
+            case 8: hipLaunchKernelGGL((reduce_flow_kernel<8, 1, NT, 192>), grid, wg, 0, stream, e); break;
+            case 4: hipLaunchKernelGGL((reduce_flow_kernel<4, 2, NT, T>), grid, wg, 0, stream, e); break;
+            case 3: hipLaunchKernelGGL((reduce_flow_kernel<3, 3, NT, T>), grid, wg, 0, stream, e); break;
+            default: hipLaunchKernelGGL((reduce_flow_kernel<2, 4, NT, T>), grid, wg, 0, stream, e); break;
+        }
+    };
+    if (shape.threads == 192) flow(std::integral_constant<int, 192>{});
+    else flow(std::integral_constant<int, 256>{});
 }
 
 // From 256 MB of slots on, the size of the memory-side cache, the loads carry the streaming hint.  Both sides, us, ordinary loads
@@ -333,10 +338,10 @@ static void launch_reduce_nt(const ReduceArgs& a, int n_workgroups, hipStream_t 
 // 336 MB on that, too, is faster with the hint (68.1 and 64.6).  Below the line the hint gains on slots not touched lately (134 MB
 // 34.1 and 30.6, 201 MB 46.2 and 41.8) and loses up to 5 % on ones that the cache holds, which slots of that size usually
 // are: ordinary loads.
-hipError_t launch_reduce(const ReduceArgs& a, int n_workgroups, hipStream_t stream)
+hipError_t launch_reduce(const ReduceArgs& a, ReduceShape shape, hipStream_t stream)
 {
-    if (a.n_vec4 * 16 * a.W >= (256ll << 20)) launch_reduce_nt<true>(a, n_workgroups, stream);
-    else launch_reduce_nt<false>(a, n_workgroups, stream);
+    if (a.n_vec4 * 16 * a.W >= (256ll << 20)) launch_reduce_nt<true>(a, shape, stream);
+    else launch_reduce_nt<false>(a, shape, stream);
     return hipGetLastError();
 }
 

@@ -61,7 +61,9 @@ int ks_stage_bad_accesses(int KC, int past, int rows, int tile_rows, unsigned ld
     return bad;
 }
 
-int reduce_grid(int W, int num_cus, long long n_vec4, int beside_gemm) { return reduce_workgroups(W, num_cus, n_vec4, beside_gemm != 0); }
+int reduce_grid(int W, int num_cus, long long n_vec4, int beside_gemm) { return reduce_shape(W, num_cus, n_vec4, beside_gemm != 0).workgroups; }
+
+int reduce_threads(int W, int num_cus, long long n_vec4, int beside_gemm) { return reduce_shape(W, num_cus, n_vec4, beside_gemm != 0).threads; }
 
 double m_tiles(double mean, int bm) { return expected_m_tiles(mean, bm); }
 

@@ -45,9 +45,10 @@ def test_reducer_world_sizes_bit_exact(W, Ms, N):
         ctx.free()
 
 
-# blocks of 256 float4 per workgroup: fewer than the unrolled loop holds, as many, one more, several laps; whole and partial last blocks
+# blocks of 256 or 192 float4 per workgroup: fewer than the unrolled loop holds, as many, one more, several laps; whole and partial last blocks
 @pytest.mark.parametrize("W", [2, 3, 4, 8])
-@pytest.mark.parametrize("n_vec4,workgroups", [(1, 0), (255, 1), (256, 3), (257, 1), (513, 2), (256 * 4, 1), (256 * 5 - 3, 1), (256 * 23 + 1, 5), (256 * 1100 + 77, 0)])
+@pytest.mark.parametrize("n_vec4,workgroups", [(1, 0), (255, 1), (256, 3), (257, 1), (513, 2), (256 * 4, 1), (256 * 5 - 3, 1), (256 * 23 + 1, 5), (256 * 1100 + 77, 0),
+                                                (191, 0), (193, 1), (192 * 2, 3), (192 * 7 + 5, 2), (192 * 256 * 3 + 11, 0)])
 def test_reducer_loop_lengths_bit_exact(W, n_vec4, workgroups):
     g = torch.Generator(device="cuda").manual_seed(7500 + W)
     slots = [torch.randn((n_vec4, 4), device="cuda", generator=g) * 10.0 ** w for w in range(W)]

@@ -57,13 +57,20 @@ def test_a_waiting_reducer_leaves_room_for_a_gemm_that_comes_later(W):
     cus = 256
     for n_vec4 in (1, 1000, 256 * 256, 256 * 512, 1 << 18, 1 << 21, 1 << 25, 1 << 27):
         grid = lib().reduce_grid(W, cus, C.c_longlong(n_vec4), 0)
-        assert 1 <= grid <= (n_vec4 + 255) // 256
+        assert 1 <= grid <= -(-n_vec4 // lib().reduce_threads(W, cus, C.c_longlong(n_vec4), 0))
         per_cu = [grid // cus + (i < grid % cus) for i in range(cus)]
         assert sum(512 - 64 * k >= 448 for k in per_cu) >= cus // 2, (W, n_vec4, grid)
         assert all(512 - 64 * k >= 384 for k in per_cu), (W, n_vec4, grid)
         spread = [3 * grid // cus + (i < 3 * grid % cus) for i in range(cus)]
         assert all(512 - 64 * k >= (288 if W in (2, 3, 4, 8) and n_vec4 < 1 << 27 else 192) for k in spread), (W, n_vec4, grid)
         assert lib().reduce_grid(W, cus, C.c_longlong(n_vec4), 1) <= cus
+
+
+@pytest.mark.parametrize("W", [2, 3, 4, 5, 8, 64])
+def test_a_reducer_beside_a_gemm_takes_the_same_share_of_every_cu(W):
+    # a persistent GEMM ends with its slowest CU
+    for n_vec4 in (256 * 1024, 1 << 21, 1 << 27):
+        assert lib().reduce_grid(W, 256, C.c_longlong(n_vec4), 1) == 256
 
 
 def test_expected_number_of_tiles_is_the_sum_and_costs_no_more_for_long_segments():
