@@ -4,9 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <mutex>
-
 #include "../../include/agg.h"
+#include "delivered.h"
 #include "launch_rules.h"
 #include "moe_table.h"
 
@@ -189,11 +188,7 @@ struct agg_ctx {
     int rs_chunks;       // row chunks per GEMM-RS slice and reducer slot, each with a signal of its own (>= 1)
     int producer_wgs;    // workgroups of the producer kernel when the caller passes 0 (0 = one per CU)
     const void* local_shard;  // see agg_set_local_shard
-    // The shards that copy kernels on one stream have been enqueued for, in one epoch (api.hip: all_behind).
-    std::mutex delivered_mutex;
-    uint64_t delivered;  // a bit per rank
-    int delivered_epoch;
-    hipStream_t delivered_on;
+    agg::Delivered delivered;  // api.hip: all_behind
     double link_GBps;    // pace of a link of the full-mesh producer (0 = not paced)
     hipStream_t producer_stream, consumer_stream;
     // grouped GEMM workspace (sized by agg_reserve_moe; no other call allocates it)

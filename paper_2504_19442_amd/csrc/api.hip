@@ -409,20 +409,12 @@ static bool keeps_order(agg_ctx* c, hipStream_t st)
 // Copies of the jobs' shards have been enqueued on st.
 static void note_delivery(agg_ctx* c, const ProducerArgs& a, hipStream_t st)
 {
-    const bool kept = keeps_order(c, st);
-    std::lock_guard<std::mutex> lock(c->delivered_mutex);
-    if (!kept || c->delivered_epoch != c->epoch || c->delivered_on != st) c->delivered = 0;
-    c->delivered_epoch = c->epoch;
-    c->delivered_on = st;
-    for (int j = 0; kept && j < a.n_jobs; ++j) c->delivered |= 1ull << a.rank_of[j];
+    uint64_t ranks = 0;
+    for (int j = 0; j < a.n_jobs; ++j) ranks |= 1ull << a.rank_of[j];
+    c->delivered.note(ranks, a.epoch, st, [&] { return keeps_order(c, st); });
 }
 
-static bool all_behind(agg_ctx* c, hipStream_t st)
-{
-    if (!keeps_order(c, st)) return false;
-    std::lock_guard<std::mutex> lock(c->delivered_mutex);
-    return c->delivered == ~0ull >> (64 - c->W) && c->delivered_epoch == c->epoch && c->delivered_on == st;
-}
+static bool all_behind(agg_ctx* c, hipStream_t st) { return c->delivered.all(c->W, c->epoch, st, [&] { return keeps_order(c, st); }); }
 
 int ag_producer_emulate(agg_ctx* c, const void* const* remote_shards, const int* arrival_order, int n_arrivals,
                         int mode, int n_workgroups, void* producer_stream)

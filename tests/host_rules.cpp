@@ -1,4 +1,5 @@
 // The host-side rules of the library behind plain C functions, for the tests that check them without a GPU.
+#include "delivered.h"
 #include "ks_stage.h"
 #include "launch_rules.h"
 #include "moe_table.h"
@@ -64,6 +65,21 @@ int ks_stage_bad_accesses(int KC, int past, int rows, int tile_rows, unsigned ld
 int reduce_grid(int W, int num_cus, long long n_vec4, int beside_gemm) { return reduce_shape(W, num_cus, n_vec4, beside_gemm != 0).workgroups; }
 
 int reduce_threads(int W, int num_cus, long long n_vec4, int beside_gemm) { return reduce_shape(W, num_cus, n_vec4, beside_gemm != 0).threads; }
+
+// n calls on one context: kind[i] 0 = a copy of the shards ranks[i] launched with epoch[i] on stream[i], 1 = a GEMM.  kept[i]: that stream keeps
+// order.  answer[i]: the GEMM is behind all of them; asked[i]: how often the runtime was asked about the stream.
+void delivered_play(int W, int n, const int* kind, const unsigned long long* ranks, const int* epoch, const long long* stream, const int* kept,
+                    int* answer, int* asked)
+{
+    Delivered d;
+    for (int i = 0; i < n; ++i) {
+        asked[i] = 0;
+        auto ask = [&] { ++asked[i]; return kept[i] != 0; };
+        answer[i] = 0;
+        if (kind[i] == 0) d.note(ranks[i], epoch[i], (const void*)stream[i], ask);
+        else answer[i] = d.all(W, epoch[i], (const void*)stream[i], ask);
+    }
+}
 
 double m_tiles(double mean, int bm) { return expected_m_tiles(mean, bm); }
 

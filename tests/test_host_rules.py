@@ -73,6 +73,29 @@ def test_a_reducer_beside_a_gemm_takes_the_same_share_of_every_cu(W):
         assert lib().reduce_grid(W, 256, C.c_longlong(n_vec4), 1) == 256
 
 
+# (call, shards, epoch, stream, the stream keeps order) in turn; of every GEMM, what it is told and how often the runtime is asked
+@pytest.mark.parametrize("W,calls,want", [
+    (4, [("copy", 0b1111, 5, 1, 1), ("gemm", 0, 5, 1, 1)], [(1, 1)]),
+    (4, [("copy", 0b0101, 5, 0, 1), ("copy", 0b1010, 5, 0, 1), ("gemm", 0, 5, 0, 1), ("gemm", 0, 5, 0, 1)], [(1, 1), (1, 1)]),
+    (64, [("copy", (1 << 64) - 1, 5, 1, 1), ("gemm", 0, 5, 1, 1)], [(1, 1)]),
+    (4, [("copy", 0b1111, 5, 1, 1), ("gemm", 0, 5, 2, 1)], [(0, 0)]),                                                  # copy and GEMM beside each other
+    (4, [("copy", 0b0111, 5, 1, 1), ("gemm", 0, 5, 1, 1)], [(0, 0)]),                                                  # a shard is missing
+    (4, [("copy", 0b0011, 5, 2, 1), ("copy", 0b1100, 5, 1, 1), ("gemm", 0, 5, 1, 1), ("gemm", 0, 5, 2, 1)], [(0, 0), (0, 0)]),
+    (4, [("copy", 0b1111, 5, 1, 1), ("gemm", 0, 6, 1, 1)], [(0, 0)]),                                                  # of the epoch before
+    (4, [("copy", 0b0011, 5, 1, 1), ("copy", 0b1100, 6, 1, 1), ("gemm", 0, 6, 1, 1)], [(0, 0)]),
+    (4, [("copy", 0b1111, 5, 1, 0), ("gemm", 0, 5, 1, 1)], [(0, 0)]),                                                  # the copy was captured, ...
+    (4, [("copy", 0b0011, 5, 1, 1), ("copy", 0b1100, 5, 1, 0), ("gemm", 0, 5, 1, 1)], [(0, 0)]),                       # ... a part of it, ...
+    (4, [("copy", 0b1111, 5, 1, 1), ("gemm", 0, 5, 1, 0)], [(0, 1)]),                                                  # ... the GEMM is
+])
+def test_a_gemm_is_behind_the_copies_of_its_own_epoch_and_stream_only(W, calls, want):
+    n = len(calls)
+    ints = lambda k: (C.c_int * n)(*[c[k] for c in calls])
+    answer, asked = (C.c_int * n)(), (C.c_int * n)()
+    lib().delivered_play(W, n, (C.c_int * n)(*[int(c[0] == "gemm") for c in calls]), (C.c_ulonglong * n)(*[c[1] for c in calls]), ints(2),
+                         (C.c_longlong * n)(*[c[3] for c in calls]), ints(4), answer, asked)
+    assert [(answer[i], asked[i]) for i in range(n) if calls[i][0] == "gemm"] == want
+
+
 def test_expected_number_of_tiles_is_the_sum_and_costs_no_more_for_long_segments():
     rng = random.Random(31)
     for bm in (16, 32, 64, 128, 256):
