@@ -71,7 +71,10 @@ def test_one_shard_from_another_stream():
     p = Problem(250, 1500, agg.B_NK)
     try:
         ps, cs = p.ctx.streams()
-        for first, last in ((cs, ps), (ps, cs)):
+        for first, last in ((cs, ps), (ps, cs), (cs, ps)):
+            for x in p.shards:
+                x.neg_()                                   # other rows each time: a GEMM that does not wait finds those of the time before
+            p.want.neg_()
             p.C.fill_(float("nan"))
             torch.cuda.synchronize()
             agg.signal_reset(p.ctx)
@@ -101,14 +104,69 @@ def test_what_was_not_delivered_is_waited_for(what):
         p.ctx.free()
 
 
-def test_epoch_on_the_device():
-    p = Problem(250, 1500, agg.B_NK)
+def _captured(stream, what):
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=torch.cuda.ExternalStream(stream), capture_error_mode="thread_local"):
+        what()
+    torch.cuda.synchronize()
+    return g
+
+
+@pytest.mark.parametrize("rows,N", [(3, 200), (250, 1500)])
+def test_epoch_on_the_device(rows, N):
+    p = Problem(rows, N, agg.B_NK)
     try:
+        ps, cs = p.ctx.streams()
+        p.ctx.set_wait_limit_us(2000)
         p.ctx.set_device_epoch(True)
         p.C.fill_(float("nan"))
+        agg.signal_reset(p.ctx, cs)
+        p.deliver(cs)
+        p.gemm(cs)
+        assert p.right()
+        # a replay moves the epoch on behind the host's back: the copies are of the epoch before
+        reset = _captured(cs, lambda: agg.signal_reset(p.ctx, cs))
+        agg.signal_reset(p.ctx, cs)
+        p.deliver(cs)
+        reset.replay()
+        torch.cuda.synchronize()
+        p.gemm(cs)
+        torch.cuda.synchronize()
+        assert agg.agg_status(p.ctx) == agg.ERR_TIMEOUT
+        # a replay brings the GEMM without the copy
+        agg.signal_reset(p.ctx, cs)
+        p.deliver(cs)
+        gemm = _captured(cs, lambda: p.gemm(cs))
+        p.C.fill_(float("nan"))
+        gemm.replay()
+        assert p.right()
+        agg.signal_reset(p.ctx, cs)
+        gemm.replay()
+        torch.cuda.synchronize()
+        assert agg.agg_status(p.ctx) == agg.ERR_TIMEOUT
+    finally:
+        p.ctx.free()
+
+
+def test_copies_that_were_only_recorded_are_waited_for():
+    p = Problem(250, 1500, agg.B_NK)
+    try:
+        ps, cs = p.ctx.streams()
+        p.deliver(cs)                                      # (what is set up on first use)
+        p.gemm(cs)
+        assert p.right()
+        p.ctx.set_wait_limit_us(2000)
         agg.signal_reset(p.ctx)
-        p.deliver(None)
-        p.gemm(None)
+        copy = _captured(cs, lambda: p.deliver(cs))
+        p.gemm(cs)
+        torch.cuda.synchronize()
+        assert agg.agg_status(p.ctx) == agg.ERR_TIMEOUT
+        copy.replay()
+        torch.cuda.synchronize()
+        p.C.fill_(float("nan"))
+        torch.cuda.synchronize()
+        p.gemm(cs)
         assert p.right()
     finally:
         p.ctx.free()
