@@ -22,8 +22,10 @@
 // tiles), 64 x 8192 x 3584 33.3 -> 18.5 (64x32), 128 x 7168 x 8192 74.6 -> 42 (64x64), 999 x 1999 x 1984 21 -> 15.6 (64x128).
 // KN: a B stored [K][N], read in place by gemm_km_kernel (64x64, 64x128, 128x128): no transposed copy, which costs a kernel, its bytes twice and
 // an event.  Transposing and GEMM, and in place, us: 1024 x 3584 x 4096 49.6 -> 38.6 (128x128), 376 x 5160 x 1984 29.7 -> 17.8 (64x128),
-// 84 x 240 x 704 12.2 -> 7.6 (64x64).  Since then (an instance per cache policy; 128x128: parts of 64x64 per wave, a look-ahead of four stages), us per call with
-// the copy: 1024 x 3584 x 4096 41.5 -> 40.3, 256 x 4096 x 4096 24.4 -> 23.2 (64x64), 512 x 3584 x 4096 30.0 -> 29.7 (64x128).
+// 84 x 240 x 704 12.2 -> 7.6 (64x64).  Of these, us per call with the copy, the same weights again and again, without and with: an instance per cache
+// policy of B's loads 1024 x 3584 x 4096 40.7 and 39.1, x 1024 18.9 and 18.2, 256 x 4096 x 4096 (64x64) 25.1 and 23.2, 512 x 3584 x 4096 (64x128)
+// 30.1 and 29.5; in the 128x128 tile parts of 64x64 per wave instead of 128x32 (x 4096) 40.1 and 39.1, and four stages ahead instead
+// of three 40.0 and 39.1.
 #pragma once
 #include "gemm_tile.h"
 #include "ks_stage.h"
@@ -356,7 +358,8 @@ struct KmCfg {
     static constexpr int RB = BM / WM / 16, CB = BN / WN / 16;
     // Stages on their way ahead of the one whose fragments are multiplied.  With a short ring the slot of that stage is filled again at
     // once, for which its reads must be back at the barrier; with a longer one the slot of the stage before, and no read is waited for.
-    // NST - 1 and NST, us per call: [K][N] 1024 x 3584 x 4096 (128x128, four slots) 42.7 and 41.7; 999 x 1999 x 1984 (64x128, six) 20.6 and 20.7.
+    // NST - 1 and NST, us per call: [K][N] 1024 x 3584 x 4096 (128x128, four slots) 40.0 and 39.1, 200 x 16384 x 8192 85.0 and 84.1;
+    // 999 x 1999 x 1984 (64x128, six) 20.6 and 20.7.
     static constexpr int AHEAD = NST <= 4 ? NST : NST - 1;
     static_assert(NW % WM == 0 && A_UNITS % S == 0 && B_UNITS % S == 0 && NST % 2 == 0 && NST >= 4 && LDS_BYTES <= 159 * 1024, "tile");
 };
@@ -440,7 +443,7 @@ void gemm_km_kernel(const KsParams p, const SL sl)
                                                              16, off_b[i], st.k_off, 0, decltype(aux_c)::value);
                 });
             };
-            // 2 = nt; [K][N]: an instance each (choosing in every stage: 1024 x 3584 x 4096 40.4 -> 38.8 us per call)
+            // 2 = nt; [K][N]: an instance each
             if constexpr (KN) load(std::integral_constant<int, STREAM ? 2 : 0>{});
             else if (p.b_streams) load(std::integral_constant<int, 2>{});
             else load(std::integral_constant<int, 0>{});

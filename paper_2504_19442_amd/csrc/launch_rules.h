@@ -88,6 +88,8 @@ inline double tile_cost(int num_cus, const TileCost& k, int M, int N, int K, boo
 // the end of a round all CUs do at once while nothing multiplies; with four 128x128 tiles in place of one large one the stores of
 // some fall behind the loads of others.  Over 450 problems drawn from 4 to 8192 rows, N 96 to 8192, K 128 to 3584 the choice costs
 // 1.4 % more than the best tile (2.5 % without the two), and 3 are more than 2 % slower than with the numbered tiles alone (14).
+// On one stream nothing is published (gemm_rs), and it is counted all the same: the tile, and with it the order of the sums, follows from the
+// sizes alone.
 // Both sides, us per call: 8 x 3300 x 128 16x16 12.7, 32x32 10.4, 128x128 10.5; 4232 x 4060 x 2368 256x224 174, 128x128 148.
 // large_only: without the K-split tiles.
 inline int best_tile(int num_cus, int M, int N, int K, bool slices = false, bool large_only = false)
@@ -109,8 +111,9 @@ inline int best_tile(int num_cus, int M, int N, int K, bool slices = false, bool
 // and `cfg`, best_tile's choice for the transposed one, is taken.  Transposing costs its bytes, read and written, and 7.6 us: a kernel more and the
 // event behind the GEMM.  Over 200 problems drawn from M 4..8192, N 96..7168, K 256..8192 the choice takes 30 % less time than transposing
 // always, is slower by more than 2 % on none, and costs 0.8 % more than the better of both (by more than 5 % on 12, all transposed: the costs
-// are those of in-place tiles 4 to 10 % slower than they are now).  Both sides, us: 1024 x 3584 x 4096 128x128 in place 38.6, transposed 49.6; 57 x 96 x 320 5.8 and 11.2; 30 x 336 x 2624 15.0 and 13.3; 2048 x 3584 x 4096
-// 76 and 69.8.
+// are those of in-place tiles 4 to 10 % slower than they were then, and they have become faster since).  Both sides, us: 1024 x 3584 x 4096
+// 128x128 in place 38.6, transposed 49.6; 57 x 96 x 320 5.8 and 11.2; 30 x 336 x 2624 15.0 and 13.3; two rounds, weights in no cache: 2048 x 3584 x
+// 4096 103 and 77, x 1024 33.0 and 33.1.
 // Where `cfg` is a numbered tile and the problem has more than one round of them, it is taken: those follow the order that the rows arrive in or
 // that the slices are wanted in (agg_set_tile_order, first_slice), the small tiles do not, and the bits must not depend on the order.  In a
 // single round all tiles start at once.  (One in a thousand problems of those ranges, by the costs 10 % slower than in place.)
