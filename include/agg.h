@@ -217,9 +217,8 @@ int gemm_rs(agg_ctx* ctx, int M, int N, int Klocal,
  * when the copy engines are used).  Each candidate runs once to warm up (before the very first one there are twenty-nine runs
  * more, so that the chip's clocks have settled) and runs_per_config more times; the median run counts.  For problems on which
  * the automatic choice takes one of its small tiles (see agg_set_tile_config) or reads a [K][N] operand in place (see AGG_B_KN; the
- * candidates transpose it) those first runs use that choice and the last
- * fifteen are timed: where no candidate comes within a microsecond of it (for an operand read in place: is faster by more than
- * one; a candidate that does, or is, is timed again in turn with it) the result is tile_config = -1 (automatic) in the
+ * candidates transpose it) those runs use that choice, and fifteen of them follow the candidates and are timed: where no candidate
+ * comes within a microsecond of it (for an operand read in place: is faster by more than one) the result is tile_config = -1 (automatic) in the
  * rotated order.  The GPU is held back for 0.1 ms before every run, so that the time is the GPU's and not that of the host's
  * calls.  The best configuration is stored in the context (tile shape for calls with this b_layout, tile order, producer
  * size used when ag_producer_emulate is called with n_workgroups = 0) and returned.  A tile shape found for AGG_B_NK also holds

@@ -682,20 +682,24 @@ int agg_autotune_ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb
     };
     // Untimed runs first: one per candidate, and a longer series before the very first candidate, so that the chip's clocks
     // have settled under load before anything is compared.  Where the automatic choice takes a tile that is not among the
-    // candidates (a small one, or one that reads a [K][N] operand in place), that series runs with it, and its second half is timed:
-    // the time a candidate has to come near to.
+    // candidates (a small one, or one that reads a [K][N] operand in place), that series runs with it, its second half behind the
+    // candidates, and timed: the time a candidate has to come near to.  (Timed ahead of them, 1024 x 3584 x 4096 with a [K][N] operand took
+    // 52.5 us in a process's first tuning and 50.5 in later ones.)
     constexpr int kWarm = 30, kSettled = 15;
     config = -1;
     int auto_tile = choose_tile(c, b_layout, M, N, K);
     const bool in_place = kn_in_place(c, B, ldb, b_layout, M, N, K, false, &auto_tile), automatic = in_place || auto_tile >= TILE_CONFIGS;
     std::vector<float> auto_times;
-    for (int it = 0; it < kWarm - 1 && rc == AGG_OK; ++it) {
-        config = automatic ? -1 : tiles[0];
-        c->tile_order = orders[0];
-        c->producer_wgs = wgs[1];
-        float ms = 0.f;
-        if ((rc = run(&ms)) == AGG_OK && automatic && it >= kWarm - 1 - kSettled) auto_times.push_back(ms);
-    }
+    auto series = [&](int runs, bool time) {
+        for (int it = 0; it < runs && rc == AGG_OK; ++it) {
+            config = automatic ? -1 : tiles[0];
+            c->tile_order = orders[0];
+            c->producer_wgs = wgs[1];
+            float ms = 0.f;
+            if ((rc = run(&ms)) == AGG_OK && time) auto_times.push_back(ms);
+        }
+    };
+    series(automatic ? kWarm - 1 - kSettled : kWarm - 1, false);
     for (int ti = 0; ti < 4 && rc == AGG_OK; ++ti)
         for (int oi = 0; oi < 2 && rc == AGG_OK; ++oi)
             for (int wi = 0; wi < (sdma ? 1 : 3) && rc == AGG_OK; ++wi) {
@@ -718,31 +722,16 @@ int agg_autotune_ag_gemm(agg_ctx* c, int M, int N, int K, const void* B, int ldb
                     res.best_ms = best_here;
                 }
             }
+    if (automatic) series(kSettled, true);
+    if (automatic && rc == AGG_OK) rc = agg_status(c);
     // A candidate is the result (they all add up K in one order) unless the automatic choice is faster by more than the
     // medians of repeated tunings differ.  Measured, ms, automatic choice and best candidate: 16 x 3584 x 4096 0.0226 and 0.038,
     // 128 x 7168 x 8192 0.0475 and 0.0617, 999 x 1999 x 1984 0.0351 and 0.037, 1024 x 256 x 128 0.023 and 0.0213.
     // The other way round where the automatic choice reads B in place: the candidates transpose it, which the copy of the shards hides here
     // but nothing does where T is there already (1024 x 3584 x 4096: 0.056 and 0.057 beside the copy, 0.042 and 0.052 behind it).
     constexpr float kResolutionMs = 0.001f;
-    float auto_ms = median(auto_times);
-    auto automatic_wins = [&] { return auto_ms < best + (in_place ? kResolutionMs : -kResolutionMs); };
-    if (rc == AGG_OK && automatic && !automatic_wins()) {
-        // The automatic choice was timed ahead of the candidates, and the least of two dozen medians is a lucky one: both again, in turn.
-        // (1024 x 3584 x 4096, [K][N]: the automatic choice 52.5 us in a process's first tuning and 50.5 in the ones after it.)
-        std::vector<float> again[2];
-        for (int it = 0; it < 2 * kSettled && rc == AGG_OK; ++it) {
-            const bool candidate = it % 2 != 0;
-            config = candidate ? res.tile_config : -1;
-            c->tile_order = candidate ? res.tile_order : orders[0];
-            c->producer_wgs = candidate && !sdma ? res.producer_workgroups : wgs[1];
-            float ms = 0.f;
-            if ((rc = run(&ms)) == AGG_OK) again[candidate].push_back(ms);
-        }
-        if (rc == AGG_OK) rc = agg_status(c);
-        auto_ms = median(again[0]);
-        res.best_ms = best = median(again[1]);
-    }
-    if (rc == AGG_OK && automatic_wins()) {
+    const float auto_ms = median(auto_times);
+    if (rc == AGG_OK && auto_ms < best + (in_place ? kResolutionMs : -kResolutionMs)) {
         res.tile_config = -1;
         res.tile_order = orders[0];
         res.producer_workgroups = sdma ? 0 : wgs[1];
