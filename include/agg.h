@@ -284,7 +284,7 @@ int gemm_rs_scatter(agg_ctx* ctx, int M, int N, int Klocal,
  * weights: bf16 [E][N][K] (K contiguous per expert).  sorted_token / sorted_expert_offsets are DEVICE
  * outputs the call fills (int32 [Ttok*topk] and int32 [E+1]) and then uses; the caller may read them.
  * A tile lies inside one expert's segment and waits for the signals of the rows of T between its first and its
- * last token (tokens rise inside a segment, so that range holds every token of the tile)  Behind copies of all shards on the
+ * last token (tokens rise inside a segment, so that range holds every token of the tile).  Behind copies of all shards on the
  * same stream there is no wait, as for ag_gemm.
  * Requirements: K % 64 == 0, Ttok % W == 0, shard_bytes == (Ttok / W) * K * 2, Ttok * K * 2 < 2 GiB, E <= 4096,
  * weights and topk_ids 16-byte aligned, ldy >= N.  Ids outside [0, E) are skipped: their pairs appear nowhere and

@@ -10,8 +10,8 @@
 // has been added, so that W x RU loads per lane are in flight throughout, where a block that is loaded whole, added and stored drains them in
 // between.  Few workgroups then do better than many (reduce_workgroups), and 64 registers are enough for every world size: a
 // workgroup fits beside any GEMM of this library.  Blocks loaded whole, and this, us per call with the kernel that raises the signals, slots not
-// touched lately: eight slots of 1024 x 8192 55.5 and 52.6, of 1000 x 8000 58.8 and 54.7, four 41.6 and 33.9, three 38.1 and 26.6,
-// two 21.7 and 19.4; behind the GEMM of gemm_rs (256 workgroups) 450 and 443.  In row chunks, with 4 / 16 chunks of 1024 x 8192: eight slots
+// touched lately: eight slots of 1024 x 8192 55.0 and 50.8, of 1000 x 8000 57.5 and 52.7, four 39.7 and 32.2, three 37.3 and 26.8, two 27.6 and 21.7;
+// behind the GEMM of gemm_rs, 8192 x 8192 x 3584, 430 and 417.  In row chunks, with 4 / 16 chunks of 1024 x 8192: eight slots
 // 56.1 / 60.4 and 52.5 / 52.7, four 42.8 / 50.6 and 32.1 / 32.3, two 32.2 / 34.4 and 21.5 / 21.6.
 // ReduceArgs::own: behind the GEMM on its own stream there is nothing to wait for in the own slot, and its signals are raised here, by one
 // workgroup, instead of by every tile or by a kernel of its own (api.hip: gemm_rs, moe_rs).
@@ -331,12 +331,12 @@ static void launch_reduce_nt(const ReduceArgs& a, ReduceShape shape, hipStream_t
 }
 
 // From 256 MB of slots on, the size of the memory-side cache, the loads carry the streaming hint.  Both sides, us, ordinary loads
-// and hint, eight slots of 1024 x 8192 (268 MB): slots not touched lately 59.0 and 54.2, slots that have just been written
-// 53.7 and 54.4; 336 MB: 72.9 and 66.1, just written 81 and 64.  Four slots of 2048 x 8192 64.0 and 61.3, just written 73.5 and
-// 72.2; two 78.2 and 76.5, just written 87.6 and 83.4.  What loses is a loop that reads one and the same slots without anyone
-// writing them in between (part of them then stays in that cache): 47.2 and 52.0, with four slots 49.4 and 59.8; from
-// 336 MB on that, too, is faster with the hint (68.1 and 64.6).  Below the line the hint gains on slots not touched lately (134 MB
-// 34.1 and 30.6, 201 MB 46.2 and 41.8) and loses up to 5 % on ones that the cache holds, which slots of that size usually
+// and hint, eight slots of 1024 x 8192 (268 MB): slots not touched lately 54.6 and 50.4, slots that have just been written
+// 47.7 and 47.7; 336 MB: 68.3 and 62.1, just written 65.0 and 64.0.  Four slots of 2048 x 8192 59.3 and 55.6, just written 49.0 and
+// 47.5; two 70.5 and 68.3, just written 60.0 and 57.6.  What loses is a loop that reads one and the same slots without anyone
+// writing them in between (part of them then stays in that cache): 45.2 and 48.1, with four slots 46.9 and 53.3; from
+// 336 MB on that, too, is faster with the hint (64.6 and 60.0).  Below the line the hint gains on slots not touched lately (134 MB
+// 31.1 and 28.1, 201 MB 42.2 and 39.2) and loses up to 5 % on ones that the cache holds, which slots of that size usually
 // are: ordinary loads.
 hipError_t launch_reduce(const ReduceArgs& a, ReduceShape shape, hipStream_t stream)
 {
