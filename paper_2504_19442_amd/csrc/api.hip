@@ -624,7 +624,7 @@ static int reduce_impl(agg_ctx* c, int Ms, int N, const float* const* slots, voi
     a.wait_ticks = wait_ticks(c);
     a.err = c->err;
     ReduceShape shape = reduce_shape(c->W, c->num_cus, a.n_vec4, beside_gemm);
-    if (n_workgroups > 0) shape.workgroups = n_workgroups;
+    if (n_workgroups > 0) shape = {n_workgroups, 256};
     return hip_fail(launch_reduce(a, shape, (hipStream_t)stream));
 }
 

@@ -252,7 +252,7 @@ inline int best_tile_grouped(int num_cus, long long rows, int E, int N, int K, b
 inline bool reduce_flows(int W, long long n_vec4) { return (W == 8 || (W >= 2 && W <= 4)) && n_vec4 < (1ll << 27); }
 
 // Workgroups, and threads of one, of a reducer launch over n_vec4 float4 whose caller leaves the size to the library.  Persistent, each walking
-// many blocks of a float4 per thread (one acquire per workgroup, not per block).  A reducer may have to wait for a GEMM that is launched after it,
+// many blocks of a float4 per thread (one acquire per workgroup, not per block).  (Of a size that the caller names: 256 threads.)  A reducer may have to wait for a GEMM that is launched after it,
 // which has to find room: of 512 registers per SIMD lane a workgroup of any of the reducers takes 64, a large GEMM tile 448, a K-split tile up
 // to 384 (128x128 with a [K][N] operand; 288 and less the others).  A GEMM that finds none runs into the time limit of the reducer's wait.
 //   Loads that never stop: what counts is that few streams are in flight, and beside a GEMM that every CU has the same share of them (the

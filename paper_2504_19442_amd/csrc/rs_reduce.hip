@@ -320,7 +320,7 @@ static void launch_reduce_nt(const ReduceArgs& a, ReduceShape shape, hipStream_t
     auto flow = [&](auto threads_c) {
         constexpr int T = decltype(threads_c)::value;
         switch (a.W) {
-            case 8: hipLaunchKernelGGL((reduce_flow_kernel<8, 1, NT, 192>), grid, wg, 0, stream, e); break;
+            case 8: hipLaunchKernelGGL((reduce_flow_kernel<8, 1, NT, T>), grid, wg, 0, stream, e); break;
             case 4: hipLaunchKernelGGL((reduce_flow_kernel<4, 2, NT, T>), grid, wg, 0, stream, e); break;
             case 3: hipLaunchKernelGGL((reduce_flow_kernel<3, 3, NT, T>), grid, wg, 0, stream, e); break;
             default: hipLaunchKernelGGL((reduce_flow_kernel<2, 4, NT, T>), grid, wg, 0, stream, e); break;
